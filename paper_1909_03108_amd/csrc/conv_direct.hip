@@ -1,159 +1,375 @@
-// Direct (non-MFMA) convolution kernels on padded tiles.  They serve every channel count and both
-// dtypes: the fp32 configuration, odd channel counts, and anything the MFMA kernels do not cover.
-// fp32 accumulation with fused multiply-add, taps in (kd,kh,kw) order, input channels innermost.
+// Convolution in fp32 arithmetic on the matrix cores, any channel count, f32 or bf16 tensors: the fp32 layers, bf16
+// layers whose output channels are no multiple of 32, 1x1x1 convolutions that glue_kernels.hip does not serve, and the
+// gradient with respect to an image.  Kernel extent 3 or 1 per axis (1 along D in the 2-D variant).
+//
+// Forward and data gradient: an implicit GEMM on v_mfma_f32_16x16x4_f32 (exact fp32 products and sums), M = 16 output
+// channels, N = 16 voxels, K = (tap, input channel).  A workgroup stages the input of a brick of output voxels, with its
+// surround, once in LDS and takes all taps from there.  The four K values of an instruction are free to name, as long
+// as both operands agree: lane group q = lane / 16 supplies the channel quad 4 s + q of step s, and the four
+// instructions of a step walk through the quad, so that ONE 16-byte LDS read per lane feeds four of them (and one
+// weight read serves all of a wave's voxels).  A quad is four channels of one tap; records of fewer channels than 16
+// simply put several taps side by side, so 8 channels fill the instructions as well as 16 do.  The offset of a quad
+// inside the staged brick comes from a small table in LDS, which keeps channel count, kernel extent and brick shape
+// run-time values.  LDS records are an odd number of 16-byte units apart (no bank conflicts between the 16 voxels).
+// What bounds it: at 16 channels the instructions' 32 cycles each (a brick of 256 voxels: 432 per wave against 600
+// staged records of 64 bytes); at 1 - 4 channels and in small volumes the staging and the launch.
+// Measured, fp32, 8 -> 16 -> 16 channels on 51 x 62 x 70 (one thread per output with scalar FMAs before): forward 255 and
+// 486 us, data gradient 759 and 2732 us -> 34 ... 59 us each (16 -> 16: 3.06 GFLOP, 54 TFLOP/s); 8 -> 16 on 32^3 44 -> 11 us.
+//
+// Weight gradient: M = rows (tap, input channel) of dw, flattened, so that 16 rows may span taps; N = 16 output
+// channels; K = 4 voxels.  A wave keeps ALL rows of a 16 x 16 channel block (27 blocks of 16 rows = 108 registers) over
+// every brick it sees: per 4 voxels one read of dz and one of x per instruction.  Partial sums per workgroup, added in
+// workgroup order by a second kernel, so results are reproducible.
 #include "common.h"
 
 namespace sp3d {
 
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = 256, kWaves = 4;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 template <typename E> __device__ __forceinline__ float ldf(const E *p, long long i);
 template <> __device__ __forceinline__ float ldf<float>(const float *p, long long i) { return p[i]; }
 template <> __device__ __forceinline__ float ldf<uint16_t>(const uint16_t *p, long long i) {
     return bf16_to_f32(p[i]);
 }
-template <typename E> __device__ __forceinline__ void stf(E *p, long long i, float v);
-template <> __device__ __forceinline__ void stf<float>(float *p, long long i, float v) { p[i] = v; }
-template <> __device__ __forceinline__ void stf<uint16_t>(uint16_t *p, long long i, float v) {
-    p[i] = f32_to_bf16(v);
+template <typename E> __device__ __forceinline__ f32x4 ldf4(const E *p);
+template <> __device__ __forceinline__ f32x4 ldf4<float>(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
+template <> __device__ __forceinline__ f32x4 ldf4<uint16_t>(const uint16_t *p) {
+    const uint2 v = *reinterpret_cast<const uint2 *>(p);
+    return f32x4{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
+                 __uint_as_float(v.y & 0xffff0000u)};
+}
+template <typename E> __device__ __forceinline__ void stf(E *p, float v);
+template <> __device__ __forceinline__ void stf<float>(float *p, float v) { *p = v; }
+template <> __device__ __forceinline__ void stf<uint16_t>(uint16_t *p, float v) { *p = f32_to_bf16(v); }
+template <typename E> __device__ __forceinline__ void stf4(E *p, f32x4 v);
+template <> __device__ __forceinline__ void stf4<float>(float *p, f32x4 v) { *reinterpret_cast<f32x4 *>(p) = v; }
+template <> __device__ __forceinline__ void stf4<uint16_t>(uint16_t *p, f32x4 v) {
+    *reinterpret_cast<uint2 *>(p) = make_uint2(f32_to_bf16(v[0]) | (static_cast<uint32_t>(f32_to_bf16(v[1])) << 16),
+                                               f32_to_bf16(v[2]) | (static_cast<uint32_t>(f32_to_bf16(v[3])) << 16));
 }
 
-// One thread per (voxel of the output box, output channel).  With DGRAD the taps are mirrored and the weight
-// tensor is read as w[tap][ko][ki] (ko = this kernel's output channel = the layer's input channel).
-// KS = kernel extent per axis: 3 (the 3x3x3 convolution) or 1 (the 1x1x1 classifier); in the 2-D variant
-// (g.flat) the extent along D is 1 and the box does not grow along D.
-// The threads cover the interior grown by g.grow on every side; a thread whose voxel lies beyond a side on
-// which its tile has no neighbour (beyond the volume) has nothing to do.
-template <typename E, bool DGRAD, int KS>
-__global__ __launch_bounds__(kThreads) void conv_direct_kernel(const E *__restrict__ Pin,
-                                                               const E *__restrict__ w,
-                                                               const float *__restrict__ bias,
-                                                               E *__restrict__ Pout, Geo g, int ki,
-                                                               int ko, int relu, long long total,
-                                                               const E *__restrict__ mask) {
-    const long long idx = 1LL * blockIdx.x * kThreads + threadIdx.x;
-    if (idx >= total) return;
-    const int co = static_cast<int>(idx % ko);
-    const long long v = idx / ko;                       // voxel of the grown boxes of all tiles
-    const int gd_ = grow_d(g);
-    const int ed = g.td + 2 * gd_, eh = g.th + 2 * g.grow, ew = g.tw + 2 * g.grow;
-    const long long box_vox = 1LL * ed * eh * ew;
-    const long long tile = v / box_vox;
-    const unsigned r = static_cast<unsigned>(v % box_vox);
-    const unsigned ehw = static_cast<unsigned>(eh) * ew;
-    // padded coordinates of the output voxel
-    const int pd = static_cast<int>(r / ehw) + g.halo - gd_, ph = static_cast<int>((r % ehw) / ew) + g.halo - g.grow,
-              pw = static_cast<int>(r % ew) + g.halo - g.grow;
-    if (g.grow > 0) {
-        const int tc = static_cast<int>(tile % g.gw), tb = static_cast<int>((tile / g.gw) % g.gh),
-                  ta = static_cast<int>((tile / (1LL * g.gw * g.gh)) % g.gd);
-        if ((pd < g.halo && ta == 0) || (pd >= g.halo + g.td && ta == g.gd - 1) || (ph < g.halo && tb == 0) ||
-            (ph >= g.halo + g.th && tb == g.gh - 1) || (pw < g.halo && tc == 0) ||
-            (pw >= g.halo + g.tw && tc == g.gw - 1))
-            return;
-    }
-    const long long base = tile * g.tile_vox;
-    float acc = bias ? bias[co] : 0.f;
-    constexpr int O = KS / 2;         // tap k reads the input voxel at output coordinate + k - O
-    const int KD = g.flat ? 1 : KS, OD = KD / 2;
-    for (int kd = 0; kd < KD; ++kd)
-        for (int kh = 0; kh < KS; ++kh)
-            for (int kw = 0; kw < KS; ++kw) {
-                const long long pv = base + (1LL * (pd + kd - OD) * g.ph + ph + kh - O) * g.pw + pw + kw - O;
-                const E *xin = Pin + pv * ki;
-                const int tap = DGRAD ? ((KD - 1 - kd) * KS + (KS - 1 - kh)) * KS + (KS - 1 - kw)
-                                      : (kd * KS + kh) * KS + kw;
-                if (DGRAD) {
-                    const E *wt = w + (1LL * tap * ko + co) * ki;      // w[tap][ci=co][co'=c]
-                    for (int c = 0; c < ki; ++c) acc = fmaf(ldf<E>(xin, c), ldf<E>(wt, c), acc);
-                } else {
-                    const E *wt = w + 1LL * tap * ki * ko + co;        // w[tap][c][co]
-                    for (int c = 0; c < ki; ++c)
-                        acc = fmaf(ldf<E>(xin, c), ldf<E>(wt, 1LL * c * ko), acc);
+// A brick of output voxels and the box of input voxels ("records") that its taps read.
+struct BrickGeo {
+    int s, r, c;                 // output voxels along D, H, W
+    int kd, ks;                  // kernel extent along D, and along H and W
+    int ns, nr, nc;              // bricks that cover the largest output box
+    int nbricks;                 // over all tiles
+    int nrec;                    // records: (s + kd - 1) * (r + ks - 1) * (c + ks - 1)
+    FastDiv dvc, dvrc;           // voxel index of the brick -> coordinates: c, r * c
+    FastDiv drc, drrc;           // record index -> coordinates: c + ks - 1, (r + ks - 1) * (c + ks - 1)
+    FastDiv dnc, dnr, dns;       // brick index -> position
+};
+
+struct BrickPos {
+    bool any;                    // false: the brick lies outside its tile's output box
+    TileBox bx;
+    long long base;              // padded voxel index of the corner one voxel before the output box
+    int d0, h0, w0;              // first output voxel, in coordinates of the box
+};
+
+__device__ __forceinline__ BrickPos brick_pos(const Geo &g, const BrickGeo &b, int brick) {
+    uint32_t t = static_cast<uint32_t>(brick), q;
+    BrickPos p;
+    q = fdiv(t, b.dnc); p.w0 = static_cast<int>(fmod_(t, q, b.dnc)) * b.c; t = q;
+    q = fdiv(t, b.dnr); p.h0 = static_cast<int>(fmod_(t, q, b.dnr)) * b.r; t = q;
+    q = fdiv(t, b.dns); p.d0 = static_cast<int>(fmod_(t, q, b.dns)) * b.s; t = q;
+    p.bx = tile_box(g, static_cast<int>(t));
+    p.base = static_cast<long long>(t) * g.tile_vox + p.bx.org;
+    p.any = p.d0 < p.bx.bd && p.h0 < p.bx.bh && p.w0 < p.bx.bw;
+    return p;
+}
+
+// Padded voxel index of record `rec`.  Records beyond what the box's own voxels read (bricks that stick out of it) are
+// moved to the nearest one inside: their values reach no result, and nothing outside the tile is touched.
+__device__ __forceinline__ long long record_voxel(const Geo &g, const BrickGeo &b, const BrickPos &p, uint32_t rec) {
+    const uint32_t i = fdiv(rec, b.drrc), r1 = fmod_(rec, i, b.drrc), j = fdiv(r1, b.drc), k = fmod_(r1, j, b.drc);
+    const int od = b.kd / 2, o = b.ks / 2;
+    const int d = min(p.d0 + static_cast<int>(i) - od, p.bx.bd - 1 + od), h = min(p.h0 + static_cast<int>(j) - o, p.bx.bh - 1 + o),
+              w = min(p.w0 + static_cast<int>(k) - o, p.bx.bw - 1 + o);
+    return p.base + (1LL * (d + 1) * g.ph + h + 1) * g.pw + w + 1;
+}
+
+// Record offset of tap t: the record of output voxel (0, 0, 0) of the brick at that tap.
+__device__ __forceinline__ int tap_record(const BrickGeo &b, int t) {
+    const int kk = b.ks * b.ks, kd = t / kk, r = t - kd * kk, kh = r / b.ks, kw = r - kh * b.ks;
+    return (kd * (b.r + b.ks - 1) + kh) * (b.c + b.ks - 1) + kw;
+}
+__device__ __forceinline__ int voxel_record(const BrickGeo &b, uint32_t v, int *d, int *h, int *w) {
+    const uint32_t i = fdiv(v, b.dvrc), r1 = fmod_(v, i, b.dvrc), j = fdiv(r1, b.dvc), k = fmod_(r1, j, b.dvc);
+    *d = static_cast<int>(i); *h = static_cast<int>(j); *w = static_cast<int>(k);
+    return static_cast<int>((i * (b.r + b.ks - 1) + j) * (b.c + b.ks - 1) + k);
+}
+
+// Stage channels [c0, c0 + kc) of the brick's records as floats, `stride` floats apart (channels beyond `ki`: zeros).
+// Four loads per thread are in flight at a time.
+template <typename E>
+__device__ __forceinline__ void stage_records(const E *__restrict__ in, float *xs, const Geo &g, const BrickGeo &b,
+                                              const BrickPos &p, int ki, int c0, int kc, int stride, const FastDiv &dq) {
+    if ((ki & 3) == 0 && (kc & 3) == 0) {
+        const uint32_t nq = static_cast<uint32_t>(kc) >> 2, n = b.nrec * nq;
+        for (uint32_t e0 = threadIdx.x; e0 < n; e0 += 4 * kThreads) {
+            f32x4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t e = min(e0 + u * kThreads, n - 1), rec = fdiv(e, dq);
+                const int c = c0 + 4 * static_cast<int>(fmod_(e, rec, dq));
+                v[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (c < ki) v[u] = ldf4<E>(in + record_voxel(g, b, p, rec) * ki + c);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t e = e0 + u * kThreads;
+                if (e < n) {
+                    const uint32_t rec = fdiv(e, dq);
+                    *reinterpret_cast<f32x4 *>(xs + rec * stride + 4 * fmod_(e, rec, dq)) = v[u];
                 }
             }
-    if (relu && acc < 0.f) acc = 0.f;
-    const long long ov = base + (1LL * pd * g.ph + ph) * g.pw + pw;
-    if (mask && !(ldf<E>(mask, ov * ko + co) > 0.f)) acc = 0.f;      // backward of the ReLU that produced the input
-    stf<E>(Pout, ov * ko + co, acc);
-}
-
-// Weight gradient, stage 1.  Block (tap*cin + ci, chunk, co-group): threads are laid out as
-// [voxel lane][co]; each thread sums its voxels of the chunk in index order, then the voxel lanes
-// are added in lane order by one thread per co.  Partial sums go to ws[chunk][tap][ci][co].
-template <typename E, int KS>
-__global__ __launch_bounds__(kThreads) void wgrad_direct_kernel(const E *__restrict__ Px,
-                                                                const E *__restrict__ Pdz,
-                                                                float *__restrict__ part, Geo g,
-                                                                int cin, int cout, int cw,
-                                                                long long chunk_vox,
-                                                                long long total_vox) {
-    __shared__ float red[kThreads];
-    const int tapci = blockIdx.x, chunk = blockIdx.y;
-    const int tap = tapci / cin, ci = tapci % cin;
-    const int O = g.halo - KS / 2;    // tap k reads padded coordinate (interior coordinate + k + O)
-    // 2-D variant: KS * KS taps, all in the voxel's own slice
-    const int kd = g.flat ? g.halo : tap / (KS * KS) + O, kh = (tap / KS) % KS + O, kw = tap % KS + O;
-    const int nvl = kThreads / cw;
-    const int col = threadIdx.x % cw, vl = threadIdx.x / cw;
-    const int co = blockIdx.z * cw + col;
-    const unsigned thw = static_cast<unsigned>(g.th) * g.tw;
-    float acc = 0.f;
-    long long v1 = (chunk + 1LL) * chunk_vox;
-    if (v1 > total_vox) v1 = total_vox;
-    if (vl < nvl && co < cout) {
-        for (long long v = 1LL * chunk * chunk_vox + vl; v < v1; v += nvl) {
-            const long long tile = v / g.int_vox;
-            const unsigned r = static_cast<unsigned>(v % g.int_vox);
-            const unsigned ld = r / thw, lh = (r % thw) / g.tw, lw = r % g.tw;
-            const long long base = tile * g.tile_vox;
-            const long long xv = base + (1LL * (ld + kd) * g.ph + lh + kh) * g.pw + lw + kw;
-            const long long zv = base + (1LL * (ld + g.halo) * g.ph + lh + g.halo) * g.pw + lw + g.halo;
-            acc = fmaf(ldf<E>(Px, xv * cin + ci), ldf<E>(Pdz, zv * cout + co), acc);
         }
-    }
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    if (vl == 0 && co < cout) {
-        float s = 0.f;
-        for (int l = 0; l < nvl; ++l) s += red[l * cw + col];
-        part[(1LL * chunk * gridDim.x + tapci) * cout + co] = s;
+    } else {
+        const uint32_t n = b.nrec;
+        for (uint32_t rec = threadIdx.x; rec < n; rec += kThreads) {
+            const E *src = in + record_voxel(g, b, p, rec) * ki + c0;
+            for (int c = 0; c < kc; ++c) xs[rec * stride + c] = c0 + c < ki ? ldf<E>(src, c) : 0.f;
+        }
     }
 }
 
-// Bias gradient, stage 1: block = chunk of interior voxels, thread layout as above.
-template <typename E>
-__global__ __launch_bounds__(kThreads) void bgrad_direct_kernel(const E *__restrict__ Pdz,
-                                                                float *__restrict__ part, Geo g,
-                                                                int cout, int cw, long long chunk_vox,
-                                                                long long total_vox) {
-    __shared__ float red[kThreads];
-    const int chunk = blockIdx.y;
-    const int nvl = kThreads / cw;
-    const int col = threadIdx.x % cw, vl = threadIdx.x / cw;
-    const int co = blockIdx.z * cw + col;
-    const unsigned thw = static_cast<unsigned>(g.th) * g.tw;
-    float acc = 0.f;
-    long long v1 = (chunk + 1LL) * chunk_vox;
-    if (v1 > total_vox) v1 = total_vox;
-    if (vl < nvl && co < cout) {
-        for (long long v = 1LL * chunk * chunk_vox + vl; v < v1; v += nvl) {
-            const long long tile = v / g.int_vox;
-            const unsigned r = static_cast<unsigned>(v % g.int_vox);
-            const unsigned ld = r / thw, lh = (r % thw) / g.tw, lw = r % g.tw;
-            const long long zv = tile * g.tile_vox +
-                                 (1LL * (ld + g.halo) * g.ph + lh + g.halo) * g.pw + lw + g.halo;
-            acc += ldf<E>(Pdz, zv * cout + co);
+struct ConvDirectArgs {
+    const void *in, *w, *mask;
+    const float *bias;
+    void *out;
+    Geo g;
+    BrickGeo b;
+    int ki, ko, ntap;
+    int kc, nck, stride;         // channels per staged chunk (a multiple of 4), chunks, floats per LDS record
+    int steps;                   // K steps of 4 quads per chunk
+    int dgrad, relu;
+    FastDiv dq;                  // kc / 4
+};
+
+// NV: voxel segments of 16 per wave (the brick has 64 NV voxels).  blockIdx.y: block of 16 output channels.
+template <typename E, int NV>
+__global__ __launch_bounds__(kThreads) void conv_direct_kernel(ConvDirectArgs a) {
+    extern __shared__ __align__(16) float lds[];
+    float *const xs = lds, *const wts = lds + static_cast<size_t>(a.b.nrec) * a.stride;
+    int *const tab = reinterpret_cast<int *>(wts + a.steps * 256);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 15, q = lane >> 4;
+    const int nq = a.kc >> 2, nquads = a.ntap * nq;
+    const E *const in = static_cast<const E *>(a.in), *const w = static_cast<const E *>(a.w);
+    const int co0 = blockIdx.y * 16 + 4 * q;       // this lane's four output channels
+
+    for (int k = tid; k < 4 * a.steps; k += kThreads) {
+        const int kg = min(k, nquads - 1), t = kg / nq;
+        tab[k] = tap_record(a.b, t) * a.stride + 4 * (kg - t * nq);
+    }
+    auto stage_weights = [&](int chunk) {
+        for (int e = tid; e < a.steps * 64; e += kThreads) {
+            const int l = e & 63, kg = 4 * (e >> 6) + (l >> 4), co = blockIdx.y * 16 + (l & 15);
+            const int t = static_cast<int>(fdiv(kg, a.dq)), c = chunk * a.kc + 4 * (kg - t * nq);
+            f32x4 v{0.f, 0.f, 0.f, 0.f};
+            if (kg < nquads && co < a.ko) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (c + j < a.ki)
+                        v[j] = a.dgrad ? ldf<E>(w, (1LL * (a.ntap - 1 - t) * a.ko + co) * a.ki + c + j)
+                                       : ldf<E>(w, (1LL * t * a.ki + c + j) * a.ko + co);
+            }
+            *reinterpret_cast<f32x4 *>(wts + 4 * e) = v;
+        }
+    };
+    f32x4 init;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) init[i] = a.bias && co0 + i < a.ko ? a.bias[co0 + i] : 0.f;
+
+    int rec[NV], vd[NV], vh[NV], vw[NV];            // this lane's voxels: LDS float offset, brick coordinates
+    bool real[NV];
+#pragma unroll
+    for (int n = 0; n < NV; ++n) {
+        const uint32_t v = (wave * NV + n) * 16 + col;
+        real[n] = v < static_cast<uint32_t>(a.b.s * a.b.r * a.b.c);
+        rec[n] = voxel_record(a.b, real[n] ? v : 0u, &vd[n], &vh[n], &vw[n]) * a.stride;
+    }
+
+    bool have_weights = false;
+    for (int brick = blockIdx.x; brick < a.b.nbricks; brick += gridDim.x) {
+        const BrickPos p = brick_pos(a.g, a.b, brick);
+        if (!p.any) continue;
+        f32x4 acc[NV];
+#pragma unroll
+        for (int n = 0; n < NV; ++n) acc[n] = init;
+        for (int chunk = 0; chunk < a.nck; ++chunk) {
+            __syncthreads();                        // everybody is done with the previous brick / chunk
+            if (a.nck > 1 || !have_weights) stage_weights(chunk);
+            have_weights = true;
+            stage_records<E>(in, xs, a.g, a.b, p, a.ki, chunk * a.kc, a.kc, a.stride, a.dq);
+            __syncthreads();
+            for (int s = 0; s < a.steps; ++s) {
+                const int off = tab[4 * s + q];
+                const f32x4 wt = *reinterpret_cast<const f32x4 *>(wts + (s * 64 + lane) * 4);
+                f32x4 x[NV];
+#pragma unroll
+                for (int n = 0; n < NV; ++n) x[n] = *reinterpret_cast<const f32x4 *>(xs + rec[n] + off);
+                // quads past the last one carry zero weights and repeat the last quad's voxels
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int n = 0; n < NV; ++n) acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(wt[j], x[n][j], acc[n], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int n = 0; n < NV; ++n) {
+            const int d = p.d0 + vd[n], h = p.h0 + vh[n], wv = p.w0 + vw[n];
+            if (!real[n] || d >= p.bx.bd || h >= p.bx.bh || wv >= p.bx.bw) continue;
+            const long long o = (p.base + (1LL * (d + 1) * a.g.ph + h + 1) * a.g.pw + wv + 1) * a.ko + co0;
+            f32x4 v = acc[n];
+            if (a.relu) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = v[i] < 0.f ? 0.f : v[i];
+            }
+            E *dst = static_cast<E *>(a.out) + o;
+            const E *m = static_cast<const E *>(a.mask) + o;       // backward of the ReLU that produced the input
+            if ((a.ko & 3) == 0) {
+                if (co0 >= a.ko) continue;
+                if (a.mask) {
+                    const f32x4 mv = ldf4<E>(m);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = mv[i] > 0.f ? v[i] : 0.f;
+                }
+                stf4<E>(dst, v);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (co0 + i < a.ko) stf<E>(dst + i, a.mask && !(ldf<E>(m, i) > 0.f) ? 0.f : v[i]);
+            }
         }
     }
-    red[threadIdx.x] = acc;
+}
+
+struct WgradDirectArgs {
+    const void *x, *dz;
+    float *part;                 // [workgroup along x][ntap * cin * cout, then cout]
+    Geo g;                       // (grow = 0)
+    BrickGeo b;
+    int cin, cout, ntap;
+    int kc, nco, bias;           // channels per chunk; blocks of 16 output channels; bias: sum dz as well
+    FastDiv dq;                  // kc / 4
+};
+
+constexpr int kWgradVox = 256;   // voxels of a brick
+
+// blockIdx.x: share of the bricks, blockIdx.y: (chunk of input channels, block of 16 output channels).  MB: blocks of 16
+// rows, at least ceil(ntap * kc / 16).
+template <typename E, int MB>
+__global__ __launch_bounds__(kThreads) void wgrad_direct_kernel(WgradDirectArgs a) {
+    extern __shared__ __align__(16) float lds[];
+    float *const dzs = lds, *const xs = lds + kWgradVox * 16;
+    int *const vrec = reinterpret_cast<int *>(xs + ((a.b.nrec * a.kc + 3) & ~3));
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 15, q = lane >> 4;
+    const int chunk = blockIdx.y / a.nco, cob = blockIdx.y - chunk * a.nco;
+    const int c0 = chunk * a.kc, rows = a.ntap * a.kc, co = cob * 16 + col;
+    const int nvox = a.b.s * a.b.r * a.b.c;
+    const E *const x = static_cast<const E *>(a.x), *const dz = static_cast<const E *>(a.dz);
+
+    for (int v = tid; v < kWgradVox; v += kThreads) {
+        int d, h, w;
+        vrec[v] = voxel_record(a.b, v < nvox ? v : 0, &d, &h, &w) * a.kc;
+    }
+    int off[MB];                                    // LDS float offset of this lane's row of every row block
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+        const int row = 16 * m + col, t = row / a.kc;
+        off[m] = row < rows ? tap_record(a.b, t) * a.kc + row - t * a.kc : 0;
+    }
+    f32x4 acc[MB];
+#pragma unroll
+    for (int m = 0; m < MB; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float bsum = 0.f;
+
+    for (int brick = blockIdx.x; brick < a.b.nbricks; brick += gridDim.x) {
+        const BrickPos p = brick_pos(a.g, a.b, brick);
+        __syncthreads();
+        stage_records<E>(x, xs, a.g, a.b, p, a.cin, c0, a.kc, a.kc, a.dq);
+        // dz, zero for voxels outside the tile and channels beyond the last: their products vanish
+        for (int e = tid; e < kWgradVox * 4; e += kThreads) {
+            const int v = e >> 2, c4 = cob * 16 + 4 * (e & 3);
+            int d, h, w;
+            voxel_record(a.b, v < nvox ? v : 0, &d, &h, &w);
+            d += p.d0; h += p.h0; w += p.w0;
+            f32x4 z{0.f, 0.f, 0.f, 0.f};
+            if (v < nvox && d < p.bx.bd && h < p.bx.bh && w < p.bx.bw) {
+                const E *src = dz + (p.base + (1LL * (d + 1) * a.g.ph + h + 1) * a.g.pw + w + 1) * a.cout + c4;
+                if ((a.cout & 3) == 0) {
+                    if (c4 < a.cout) z = ldf4<E>(src);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (c4 + i < a.cout) z[i] = ldf<E>(src, i);
+                }
+            }
+            *reinterpret_cast<f32x4 *>(dzs + 4 * e) = z;
+        }
+        __syncthreads();
+        for (int k = 0; k < kWgradVox / kWaves; k += 4) {
+            const int v = wave * (kWgradVox / kWaves) + k + q;
+            const float b = dzs[v * 16 + col];
+            const float *xr = xs + vrec[v];
+            bsum += b;
+#pragma unroll
+            for (int m = 0; m < MB; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(xr[off[m]], b, acc[m], 0, 0, 0);
+        }
+    }
+    // the four waves' sums, added in wave order
     __syncthreads();
-    if (vl == 0 && co < cout) {
-        float s = 0.f;
-        for (int l = 0; l < nvl; ++l) s += red[l * cw + col];
-        part[1LL * chunk * cout + co] = s;
+    float *const red = lds, *const redb = lds + MB * 256;
+    for (int wv = 0; wv < kWaves; ++wv) {
+        if (wave == wv) {
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float *r = red + (m * 4 + i) * 64 + lane;
+                    *r = wv ? *r + acc[m][i] : acc[m][i];
+                }
+            redb[lane] = wv ? redb[lane] + bsum : bsum;
+        }
+        __syncthreads();
+    }
+    const size_t ndw = static_cast<size_t>(a.ntap) * a.cin * a.cout;
+    float *const part = a.part + blockIdx.x * (ndw + a.cout);
+    for (int e = tid; e < 16 * MB * 16; e += kThreads) {          // row-major: 16 output channels side by side
+        const int row = e >> 4, cc = e & 15, t = row / a.kc, c = c0 + row - t * a.kc;
+        if (row < rows && c < a.cin && cob * 16 + cc < a.cout)
+            part[(static_cast<size_t>(t) * a.cin + c) * a.cout + cob * 16 + cc] =
+                red[((row >> 4) * 4 + (row & 3)) * 64 + ((row & 15) >> 2) * 16 + cc];
+    }
+    if (a.bias && chunk == 0 && tid < 16 && co < a.cout)
+        part[ndw + co] = ((redb[tid] + redb[16 + tid]) + redb[32 + tid]) + redb[48 + tid];
+}
+
+// Second stage: out[e] = sum over the partials in a fixed order (16 runs, then the runs in order); a block serves 64
+// neighbouring outputs, so every load of a wave is a whole 256-byte piece.
+__global__ __launch_bounds__(1024) void reduce_runs_kernel(const float *__restrict__ part, float *__restrict__ dw,
+                                                           float *__restrict__ db, int nparts, long long ndw, long long n) {
+    __shared__ float red[16][64];
+    const int l = threadIdx.x & 63, run = threadIdx.x >> 6;
+    const long long e = 64LL * blockIdx.x + l;
+    const int per = (nparts + 15) / 16, p1 = min(nparts, (run + 1) * per);
+    float s = 0.f;
+    if (e < n) {
+#pragma unroll 8
+        for (int p = run * per; p < p1; ++p) s += part[p * n + e];
+    }
+    red[run][l] = s;
+    __syncthreads();
+    if (run == 0 && e < n) {
+        float t = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) t += red[r][l];
+        if (e < ndw) dw[e] = t;
+        else if (db) db[e - ndw] = t;
     }
 }
 
@@ -200,88 +416,162 @@ int launch_reduce_partials(const float *part, float *out, int nparts, long long 
     return record_hip(hipGetLastError());
 }
 
+
+// Brick shape for an output box (ed, eh, ew): at most nvox voxels and max_rec staged records, such that covering the box
+// costs least: an instruction slot per voxel of every brick, used or not, plus a share for every staged record.
+static BrickGeo plan_brick(const Geo &g, int ed, int eh, int ew, int kd, int ks, int nvox, int max_rec) {
+    BrickGeo best{};
+    double cost = 0;
+    // extents that cut n into equal parts: the largest such extent below e + 1
+    auto even = [](int n, int e) { return e < 1 ? 0 : (n + (n + e - 1) / e - 1) / ((n + e - 1) / e); };
+    for (int c = even(ew, ew < nvox ? ew : nvox); c > 0; c = even(ew, c - 1))
+        for (int r = even(eh, eh < nvox / c ? eh : nvox / c); r > 0; r = even(eh, r - 1)) {
+            int s = even(ed, ed < nvox / (c * r) ? ed : nvox / (c * r));
+            while (s > 1 && (s + kd - 1) * (r + ks - 1) * (c + ks - 1) > max_rec) s = even(ed, s - 1);
+            const int nrec = (s + kd - 1) * (r + ks - 1) * (c + ks - 1);
+            if (nrec > max_rec) continue;
+            const int nd = (ed + s - 1) / s, nh = (eh + r - 1) / r, nw = (ew + c - 1) / c;
+            const double k = 1.0 * nd * nh * nw * (nvox + 0.15 * nrec);
+            if (best.s == 0 || k < cost) {
+                cost = k;
+                best.s = s; best.r = r; best.c = c;
+                best.ns = nd; best.nr = nh; best.nc = nw;
+                best.nrec = nrec;
+            }
+        }
+    best.kd = kd;
+    best.ks = ks;
+    best.nbricks = best.ns * best.nr * best.nc * g.ntiles;
+    best.dvc = make_fastdiv(best.c);
+    best.dvrc = make_fastdiv(best.r * best.c);
+    best.drc = make_fastdiv(best.c + ks - 1);
+    best.drrc = make_fastdiv((best.r + ks - 1) * (best.c + ks - 1));
+    best.dnc = make_fastdiv(best.nc);
+    best.dnr = make_fastdiv(best.nr);
+    best.dns = make_fastdiv(best.ns);
+    return best;
+}
+
+// Workgroups for n bricks when `most` fit the chip at a time: every one gets the same number of bricks.
+static int even_share(int n, int most) {
+    const int rounds = (n + most - 1) / most;
+    return (n + rounds - 1) / rounds;
+}
+
+constexpr int kHalfLds = 80 * 1024;      // two workgroups per compute unit
+
 int launch_conv_direct(const void *Pin, const void *w, const float *bias, void *Pout, const Geo &g,
                        int ki, int ko, sp_dtype_t dt, bool relu, bool dgrad, hipStream_t s, int ks,
                        const void *mask) {
-    const long long total = 1LL * g.ntiles * (g.td + 2 * grow_d(g)) * (g.th + 2 * g.grow) * (g.tw + 2 * g.grow) * ko;
-    const long long blocks = (total + kThreads - 1) / kThreads;
-    if (blocks > 0x7fffffffLL) return SP_EGEOM;
-    dim3 grid(static_cast<unsigned>(blocks)), block(kThreads);
-#define SP3D_LAUNCH(E, DG, KS)                                                                         \
-    hipLaunchKernelGGL((conv_direct_kernel<E, DG, KS>), grid, block, 0, s, static_cast<const E *>(Pin), \
-                       static_cast<const E *>(w), bias, static_cast<E *>(Pout), g, ki, ko,             \
-                       relu ? 1 : 0, total, static_cast<const E *>(mask))
-#define SP3D_LAUNCH_KS(E, DG) do { if (ks == 1) SP3D_LAUNCH(E, DG, 1); else SP3D_LAUNCH(E, DG, 3); } while (0)
-    if (dt == SP_BF16) {
-        if (dgrad) SP3D_LAUNCH_KS(uint16_t, true); else SP3D_LAUNCH_KS(uint16_t, false);
-    } else {
-        if (dgrad) SP3D_LAUNCH_KS(float, true); else SP3D_LAUNCH_KS(float, false);
-    }
-#undef SP3D_LAUNCH_KS
-#undef SP3D_LAUNCH
+    const int kd = g.flat ? 1 : ks;
+    const int ed = g.td + 2 * grow_d(g), eh = g.th + 2 * g.grow, ew = g.tw + 2 * g.grow;
+    const double vox = 1.0 * g.ntiles * ed * eh * ew;
+    if (vox / 16 > 0x7fffffff) return SP_EGEOM;
+    ConvDirectArgs a;
+    a.in = Pin; a.w = w; a.bias = bias; a.out = Pout; a.mask = mask;
+    a.g = g;
+    a.ki = ki; a.ko = ko;
+    a.ntap = kd * ks * ks;
+    a.nck = (ki + 15) / 16;
+    a.kc = ((ki + a.nck - 1) / a.nck + 3) / 4 * 4;
+    a.nck = (ki + a.kc - 1) / a.kc;
+    a.stride = (a.kc / 4) % 2 ? a.kc : a.kc + 4;
+    a.steps = (a.ntap * (a.kc / 4) + 3) / 4;
+    a.dgrad = dgrad; a.relu = relu;
+    a.dq = make_fastdiv(a.kc / 4);
+    const int ncg = (ko + 15) / 16;
+    // 256 voxels per workgroup; fewer where that would leave the chip's 512 places (two per compute unit) empty
+    const int nv = vox / 256 * ncg >= 512 ? 4 : (vox / 128 * ncg >= 512 ? 2 : 1);
+    const int fixed = a.steps * (1024 + 16);
+    a.b = plan_brick(g, ed, eh, ew, kd, ks, 64 * nv, (kHalfLds - fixed) / (4 * a.stride));
+    const size_t lds = fixed + 4u * a.b.nrec * a.stride;
+    int most = 512 / ncg;
+    if (most < 1) most = 1;
+    const dim3 grid(even_share(a.b.nbricks, most), ncg), block(kThreads);
+    using Kern = void (*)(ConvDirectArgs);
+    static const Kern kern[2][3] = {{conv_direct_kernel<float, 1>, conv_direct_kernel<float, 2>, conv_direct_kernel<float, 4>},
+                                    {conv_direct_kernel<uint16_t, 1>, conv_direct_kernel<uint16_t, 2>, conv_direct_kernel<uint16_t, 4>}};
+    static const hipError_t attr = [] {
+        for (int i = 0; i < 6; ++i) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern[i / 3][i % 3]),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kHalfLds);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }();
+    if (attr != hipSuccess) return record_hip(attr);
+    hipLaunchKernelGGL(kern[dt == SP_BF16][nv == 4 ? 2 : nv - 1], grid, block, lds, s, a);
     return record_hip(hipGetLastError());
 }
 
-// chunking of the voxel reduction for the direct weight gradient
-static void wgrad_direct_plan(const Geo &g, int *nchunks, long long *chunk_vox) {
-    const long long total = 1LL * g.ntiles * g.int_vox;
-    long long cv = 8192;
-    long long nc = (total + cv - 1) / cv;
-    if (nc > 256) { nc = 256; cv = (total + nc - 1) / nc; nc = (total + cv - 1) / cv; }
-    *nchunks = static_cast<int>(nc);
-    *chunk_vox = cv;
+// How the weight gradient is cut up: channels per chunk, row blocks, bricks, workgroups per channel-block pair.
+struct WgradDirectPlan { int kc, nck, nco, ntap, kd, nparts; BrickGeo b; };
+static WgradDirectPlan wgrad_direct_plan(const Geo &g, int cin, int cout, int ks) {
+    WgradDirectPlan p;
+    p.kd = g.flat ? 1 : ks;
+    p.ntap = p.kd * ks * ks;
+    p.nck = (cin + 15) / 16;
+    p.kc = (cin + p.nck - 1) / p.nck;
+    if (cin % 4 == 0) p.kc = (p.kc + 3) / 4 * 4;                  // keep the 16-byte staging loads
+    p.nck = (cin + p.kc - 1) / p.kc;
+    p.nco = (cout + 15) / 16;
+    const int fixed = kWgradVox * (16 + 1) * 4 + 16;
+    p.b = plan_brick(g, g.td, g.th, g.tw, p.kd, ks, kWgradVox, (kHalfLds - fixed) / (4 * p.kc));
+    // two workgroups per compute unit, shared out over the channel-block pairs
+    const int pairs = p.nck * p.nco;
+    int most = 512 / pairs;
+    if (most < 1) most = 1;
+    p.nparts = even_share(p.b.nbricks, most);
+    return p;
 }
 
 size_t wgrad_direct_ws_bytes(const Geo &g, int cin, int cout, int ks) {
-    int nc; long long cv;
-    wgrad_direct_plan(g, &nc, &cv);
-    const size_t taps = static_cast<size_t>(g.flat ? 1 : ks) * ks * ks;
-    return (static_cast<size_t>(nc) * taps * cin * cout + static_cast<size_t>(nc) * cout) * sizeof(float);
+    const WgradDirectPlan p = wgrad_direct_plan(g, cin, cout, ks);
+    return p.nparts * (static_cast<size_t>(p.ntap) * cin * cout + cout) * sizeof(float);
 }
 
 int launch_wgrad_direct(const void *Px, const void *Pdz, float *dw, float *db, const Geo &g, int cin,
                         int cout, sp_dtype_t dt, void *ws, hipStream_t s, int ks) {
-    int nc; long long cv;
-    wgrad_direct_plan(g, &nc, &cv);
-    const long long total = 1LL * g.ntiles * g.int_vox;
-    const int taps = (g.flat ? 1 : ks) * ks * ks;
-    float *part_w = static_cast<float *>(ws);
-    float *part_b = part_w + static_cast<size_t>(nc) * taps * cin * cout;
-    const int cw = cout < kThreads ? cout : kThreads;
-    const int zg = (cout + cw - 1) / cw;
-    if (nc > 65535 || zg > 65535) return SP_EUNSUPPORTED;
-    dim3 block(kThreads), gw_(taps * cin, nc, zg), gb_(1, nc, zg);
-    if (dt == SP_BF16) {
-        if (ks == 1)
-            hipLaunchKernelGGL((wgrad_direct_kernel<uint16_t, 1>), gw_, block, 0, s,
-                               static_cast<const uint16_t *>(Px), static_cast<const uint16_t *>(Pdz),
-                               part_w, g, cin, cout, cw, cv, total);
-        else
-            hipLaunchKernelGGL((wgrad_direct_kernel<uint16_t, 3>), gw_, block, 0, s,
-                               static_cast<const uint16_t *>(Px), static_cast<const uint16_t *>(Pdz),
-                               part_w, g, cin, cout, cw, cv, total);
-        if (db)
-            hipLaunchKernelGGL(bgrad_direct_kernel<uint16_t>, gb_, block, 0, s,
-                               static_cast<const uint16_t *>(Pdz), part_b, g, cout, cw, cv, total);
-    } else {
-        if (ks == 1)
-            hipLaunchKernelGGL((wgrad_direct_kernel<float, 1>), gw_, block, 0, s,
-                               static_cast<const float *>(Px), static_cast<const float *>(Pdz), part_w, g,
-                               cin, cout, cw, cv, total);
-        else
-            hipLaunchKernelGGL((wgrad_direct_kernel<float, 3>), gw_, block, 0, s,
-                               static_cast<const float *>(Px), static_cast<const float *>(Pdz), part_w, g,
-                               cin, cout, cw, cv, total);
-        if (db)
-            hipLaunchKernelGGL(bgrad_direct_kernel<float>, gb_, block, 0, s,
-                               static_cast<const float *>(Pdz), part_b, g, cout, cw, cv, total);
-    }
+    const WgradDirectPlan p = wgrad_direct_plan(g, cin, cout, ks);
+    if (p.nck * p.nco > 65535) return SP_EUNSUPPORTED;
+    WgradDirectArgs a;
+    a.x = Px; a.dz = Pdz;
+    a.part = static_cast<float *>(ws);
+    a.g = g;
+    a.g.grow = 0;
+    a.b = p.b;
+    a.cin = cin; a.cout = cout; a.ntap = p.ntap;
+    a.kc = p.kc; a.nco = p.nco; a.bias = db != nullptr;
+    a.dq = make_fastdiv(p.kc >= 4 ? p.kc / 4 : 1);
+    using Kern = void (*)(WgradDirectArgs);
+    constexpr int kSizes = 6;
+    static const int mbs[kSizes] = {1, 2, 7, 9, 14, 27};          // row blocks of the kernels that exist
+    static const Kern kern[2][kSizes] = {
+        {wgrad_direct_kernel<float, 1>, wgrad_direct_kernel<float, 2>, wgrad_direct_kernel<float, 7>,
+         wgrad_direct_kernel<float, 9>, wgrad_direct_kernel<float, 14>, wgrad_direct_kernel<float, 27>},
+        {wgrad_direct_kernel<uint16_t, 1>, wgrad_direct_kernel<uint16_t, 2>, wgrad_direct_kernel<uint16_t, 7>,
+         wgrad_direct_kernel<uint16_t, 9>, wgrad_direct_kernel<uint16_t, 14>, wgrad_direct_kernel<uint16_t, 27>}};
+    static const hipError_t attr = [] {
+        for (int i = 0; i < 2 * kSizes; ++i) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern[i / kSizes][i % kSizes]),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kHalfLds);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }();
+    if (attr != hipSuccess) return record_hip(attr);
+    int k = 0;
+    while (16 * mbs[k] < p.ntap * p.kc) ++k;                       // (ntap * kc <= 27 * 16)
+    size_t lds = kWgradVox * 16 * 4 + (static_cast<size_t>(p.b.nrec) * p.kc + 3) / 4 * 16 + kWgradVox * 4;
+    const size_t red = (mbs[k] * 256 + 64) * sizeof(float);        // the sums of the waves reuse the staging area
+    if (lds < red) lds = red;
+    hipLaunchKernelGGL(kern[dt == SP_BF16][k], dim3(p.nparts, p.nck * p.nco), dim3(kThreads), lds, s, a);
     int rc = record_hip(hipGetLastError());
     if (rc != SP_OK) return rc;
-    rc = launch_reduce_partials(part_w, dw, nc, 1LL * taps * cin * cout, s);
-    if (rc != SP_OK) return rc;
-    if (db) rc = launch_reduce_partials(part_b, db, nc, cout, s);
-    return rc;
+    const long long ndw = 1LL * p.ntap * cin * cout, n = ndw + cout;
+    hipLaunchKernelGGL(reduce_runs_kernel, dim3(static_cast<unsigned>((n + 63) / 64)), dim3(1024), 0, s, a.part, dw, db,
+                       p.nparts, ndw, n);
+    return record_hip(hipGetLastError());
 }
 
 }  // namespace sp3d

@@ -1,0 +1,133 @@
+"""The convolution kernels for any channel count in fp32 arithmetic (conv_direct.hip) where their cutting can go wrong:
+channel counts on both sides of a quad, of a 16-channel block and of a chunk, bricks that stick out of their tile, one
+voxel per tile, every number of voxel segments per wave (it grows with voxels x output blocks), several bricks per
+workgroup with and without a second channel chunk, extent-1 kernels, the 2-D variant and a grown output box.
+Bounds: exact fp32 products, sums of at most 27 * 40 terms (forward, data gradient) or 30 000 voxels (weight gradient):
+K 2^-24 relative to the sum of magnitudes in the worst case, sqrt(K) 2^-24 < 1e-5 of the result's rms for random
+signs; bf16 tensors add one rounding of the result (1e-2 bounds one ulp, weight gradients stay fp32)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import conv3d, flat as flat_oracle
+from paper_1909_03108_amd import sp3d, synth
+from gpu_util import DT, TOL, f64, rel_err, to_dev, widen
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # n, dhw, grid, cin, cout, dtype, flat
+    (1, (1, 1, 1), (1, 1, 1), 1, 1, "f32", 0),
+    (1, (3, 5, 7), (1, 1, 1), 2, 3, "f32", 0),
+    (2, (4, 6, 34), (2, 3, 2), 4, 4, "f32", 0),
+    (1, (5, 9, 11), (1, 1, 1), 5, 15, "f32", 0),
+    (1, (6, 10, 14), (1, 2, 2), 15, 16, "f32", 0),
+    (1, (6, 10, 14), (2, 1, 1), 16, 17, "f32", 0),
+    (1, (7, 6, 9), (1, 1, 1), 17, 33, "f32", 0),
+    (1, (6, 7, 9), (1, 1, 1), 40, 12, "f32", 0),       # three chunks of input channels
+    (1, (3, 4, 300), (1, 1, 1), 8, 8, "f32", 0),        # rows longer than a brick
+    (1, (31, 29, 37), (1, 1, 1), 4, 16, "f32", 0),      # two voxel segments per wave (data gradient: one)
+    (1, (24, 32, 34), (1, 2, 1), 6, 80, "f32", 0),      # four segments; several bricks per workgroup
+    (1, (20, 20, 21), (1, 1, 1), 20, 70, "f32", 0),     # ... with two chunks
+    (1, (5, 12, 18), (1, 2, 2), 16, 48, "bf16", 0),
+    (1, (4, 9, 13), (1, 1, 1), 6, 10, "bf16", 0),
+    (1, (5, 12, 18), (1, 2, 3), 8, 20, "f32", 1),
+    (1, (3, 7, 50), (1, 1, 1), 17, 5, "bf16", 1),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%dx%dx%d-%dto%d-%s%s" % (c[1] + c[3:6] + ("-2d" if c[6] else "",)))
+def test_three_passes_against_the_oracle(case):
+    n, dhw, grid, cin, cout, dtype, flat = case
+    dt, tol = DT[dtype], TOL[dtype]
+    g = sp3d.Geom(n, dhw, grid, 1, 0, flat)
+    seed = 4100 + 10 * CASES.index(case)
+    x = synth.normal_volume((n,) + dhw + (cin,), seed, dtype)
+    dz = synth.normal_volume((n,) + dhw + (cout,), seed + 1, dtype)
+    w = synth.weights(cin, cout, seed + 2, dtype, taps=(3, 3) if flat else (3, 3, 3))
+    bias = np.linspace(-0.5, 0.5, cout).astype(np.float32)
+    ws = sp3d.alloc_ws(max(sp3d.sp_workspace_bytes(op, g, cin, cout, dt) for op in (0, 1, 2)))
+
+    def padded(v, c):
+        P = sp3d.alloc_padded(g, c, dt)
+        sp3d.sp_partition(to_dev(v), P, g, c, dt)
+        sp3d.sp_halo_exchange(P, g, c, dt)
+        return P
+
+    def volume(P, c):
+        V = torch.empty((n,) + dhw + (c,), dtype=P.dtype, device="cuda")
+        sp3d.sp_unpartition(P, V, g, c, dt)
+        return f64(V)
+
+    Px, Pz, wd = padded(x, cin), padded(dz, cout), to_dev(w)
+    Py, Pdx, Pdm = (sp3d.alloc_padded(g, c, dt) for c in (cout, cin, cin))
+    sp3d.conv3d_fwd(Px, wd, torch.from_numpy(bias).cuda(), Py, g, cin, cout, dt, sp3d.SP_FLAG_RELU, ws)
+    sp3d.conv3d_dgrad(Pz, wd, Pdx, g, cin, cout, dt, ws)
+    sp3d.conv3d_dgrad_relu(Pz, wd, Px, Pdm, g, cin, cout, dt, ws)
+    dw = torch.full(tuple(w.shape), 9.0, device="cuda")
+    db = torch.full((cout,), 9.0, device="cuda")
+    sp3d.conv3d_wgrad(Px, Pz, dw, db, g, cin, cout, dt, ws)
+    again = torch.empty_like(dw)
+    sp3d.conv3d_wgrad(Px, Pz, again, None, g, cin, cout, dt, ws)
+    assert torch.equal(dw, again)                       # no bias gradient asked for, and reproducible
+    xv, zv, wv, bv = widen(x), widen(dz), widen(w), bias.astype(np.float64)
+    O = flat_oracle if flat else conv3d
+    y, dx, rw, rb = ((O.conv_fwd(xv, wv, bv, True), O.conv_dgrad(zv, wv), O.conv_wgrad(xv, zv), O.bias_grad(zv)) if flat else
+                     (O.conv3d_fwd(x, wv, bv, True), O.conv3d_dgrad(dz, wv), O.conv3d_wgrad(x, dz), O.bias_grad(dz)))
+    assert rel_err(volume(Py, cout), y) <= tol
+    assert rel_err(volume(Pdx, cin), dx) <= tol
+    assert np.array_equal(volume(Pdm, cin), np.where(xv > 0, volume(Pdx, cin), 0.0))
+    assert rel_err(f64(dw), rw) <= 1e-5 and rel_err(f64(db), rb) <= 1e-5
+
+
+def test_grown_box_and_wide_margin_equal_the_exchange():
+    """fp32, halo 2: a layer that also computes the voxel around its tiles gives there, bit for bit, what the
+    neighbour computes for itself, and nothing beyond the volume."""
+    n, dhw, grid, cin, cout = 1, (10, 12, 22), (2, 2, 2), 9, 18
+    x, w = synth.normal_volume((n,) + dhw + (cin,), 77, "f32"), to_dev(synth.weights(cin, cout, 78, "f32"))
+    g = sp3d.Geom(n, dhw, grid, 2)
+    Px = sp3d.alloc_padded(g, cin, sp3d.SP_F32)
+    sp3d.sp_partition(to_dev(x), Px, g, cin, sp3d.SP_F32)
+    sp3d.sp_halo_exchange(Px, g, cin, sp3d.SP_F32)
+    out = []
+    for grow in (0, 1):
+        P = sp3d.alloc_padded(g, cout, sp3d.SP_F32)
+        sp3d.conv3d_fwd(Px, w, None, P, g.grown(grow), cin, cout, sp3d.SP_F32)
+        out.append(P)
+    narrow = sp3d.Geom(n, dhw, grid, 1)
+    ref = sp3d.alloc_padded(narrow, cout, sp3d.SP_F32)
+    V = torch.empty((n,) + dhw + (cout,), device="cuda")
+    sp3d.sp_unpartition(out[0], V, g, cout, sp3d.SP_F32)
+    sp3d.sp_partition(V, ref, narrow, cout, sp3d.SP_F32)
+    sp3d.sp_halo_exchange(ref, narrow, cout, sp3d.SP_F32)
+    inner = (slice(None),) * 4 + (slice(1, -1),) * 3
+    assert torch.equal(out[1][inner], ref)
+
+
+@pytest.mark.parametrize("cin,cout,dtype", [(5, 7, "f32"), (48, 20, "f32"), (24, 6, "bf16")])
+def test_extent_one_kernels(cin, cout, dtype):
+    n, dhw, grid, dt = 1, (4, 6, 37), (1, 2, 1), DT[dtype]
+    g = sp3d.Geom(n, dhw, grid)
+    x, dy = (synth.normal_volume((n,) + dhw + (c,), 91 + c, dtype) for c in (cin, cout))
+    p = synth.weights(cin, cout, 93, dtype, taps=(1, 1, 1))
+    Px, Pdy = (sp3d.alloc_padded(g, c, dt) for c in (cin, cout))
+    sp3d.sp_partition(to_dev(x), Px, g, cin, dt)
+    sp3d.sp_partition(to_dev(dy), Pdy, g, cout, dt)
+    Py, Pdx = (sp3d.alloc_padded(g, c, dt) for c in (cout, cin))
+    sp3d.sp_pointwise_fwd(Px, to_dev(p), None, Py, g, cin, cout, dt)
+    sp3d.sp_pointwise_dgrad(Pdy, to_dev(p), Pdx, g, cin, cout, dt)
+    dp = torch.empty((cin, cout), device="cuda")
+    db = torch.empty((cout,), device="cuda")
+    sp3d.sp_pointwise_wgrad(Px, Pdy, dp, db, g, cin, cout, dt,
+                            sp3d.alloc_ws(sp3d.sp_workspace_bytes(sp3d.SP_OP_POINTWISE_WGRAD, g, cin, cout, dt)))
+    xv, dv, pv = widen(x), widen(dy), widen(p).reshape(cin, cout)
+    inner = (slice(None),) * 4 + (slice(1, -1),) * 3
+
+    def volume(P, c):
+        V = torch.empty((n,) + dhw + (c,), dtype=P.dtype, device="cuda")
+        sp3d.sp_unpartition(P, V, g, c, dt)
+        return f64(V)
+
+    assert rel_err(volume(Py, cout), xv @ pv) <= TOL[dtype] and rel_err(volume(Pdx, cin), dv @ pv.T) <= TOL[dtype]
+    assert rel_err(f64(dp), np.tensordot(xv, dv, axes=((0, 1, 2, 3),) * 2)) <= 1e-5
+    assert rel_err(f64(db), dv.sum(axis=(0, 1, 2, 3))) <= 1e-5
+    assert int(torch.count_nonzero(Py)) == int(torch.count_nonzero(Py[inner]))      # margins stay zero
