@@ -212,7 +212,14 @@ __global__ __launch_bounds__(kThreads) void conv_direct_kernel(ConvDirectArgs a)
                 f32x4 x[NV];
 #pragma unroll
                 for (int n = 0; n < NV; ++n) x[n] = *reinterpret_cast<const f32x4 *>(xs + rec[n] + off);
-                // quads past the last one carry zero weights and repeat the last quad's voxels
+                // quads past the last one repeat the last quad's voxels; both operands are zero there (zero weights
+                // alone would turn an infinite voxel into NaN)
+                if (4 * s + 3 >= nquads) {
+#pragma unroll
+                    for (int n = 0; n < NV; ++n)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) x[n][j] = 4 * s + q < nquads ? x[n][j] : 0.f;
+                }
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -273,10 +280,6 @@ __global__ __launch_bounds__(kThreads) void wgrad_direct_kernel(WgradDirectArgs 
     const int nvox = a.b.s * a.b.r * a.b.c;
     const E *const x = static_cast<const E *>(a.x), *const dz = static_cast<const E *>(a.dz);
 
-    for (int v = tid; v < kWgradVox; v += kThreads) {
-        int d, h, w;
-        vrec[v] = voxel_record(a.b, v < nvox ? v : 0, &d, &h, &w) * a.kc;
-    }
     int off[MB];                                    // LDS float offset of this lane's row of every row block
 #pragma unroll
     for (int m = 0; m < MB; ++m) {
@@ -292,14 +295,17 @@ __global__ __launch_bounds__(kThreads) void wgrad_direct_kernel(WgradDirectArgs 
         const BrickPos p = brick_pos(a.g, a.b, brick);
         __syncthreads();
         stage_records<E>(x, xs, a.g, a.b, p, a.cin, c0, a.kc, a.kc, a.dq);
-        // dz, zero for voxels outside the tile and channels beyond the last: their products vanish
+        // dz, zero for voxels outside the tile and channels beyond the last; x counts as zero at those voxels as well
+        // (vrec < 0), so that the products vanish also where a neighbour's record holds an infinity
         for (int e = tid; e < kWgradVox * 4; e += kThreads) {
             const int v = e >> 2, c4 = cob * 16 + 4 * (e & 3);
             int d, h, w;
-            voxel_record(a.b, v < nvox ? v : 0, &d, &h, &w);
+            const int vr = voxel_record(a.b, v < nvox ? v : 0, &d, &h, &w) * a.kc;
             d += p.d0; h += p.h0; w += p.w0;
+            const bool live = v < nvox && d < p.bx.bd && h < p.bx.bh && w < p.bx.bw;
+            if ((e & 3) == 0) vrec[v] = live ? vr : -1;
             f32x4 z{0.f, 0.f, 0.f, 0.f};
-            if (v < nvox && d < p.bx.bd && h < p.bx.bh && w < p.bx.bw) {
+            if (live) {
                 const E *src = dz + (p.base + (1LL * (d + 1) * a.g.ph + h + 1) * a.g.pw + w + 1) * a.cout + c4;
                 if ((a.cout & 3) == 0) {
                     if (c4 < a.cout) z = ldf4<E>(src);
@@ -312,13 +318,27 @@ __global__ __launch_bounds__(kThreads) void wgrad_direct_kernel(WgradDirectArgs 
             *reinterpret_cast<f32x4 *>(dzs + 4 * e) = z;
         }
         __syncthreads();
-        for (int k = 0; k < kWgradVox / kWaves; k += 4) {
-            const int v = wave * (kWgradVox / kWaves) + k + q;
-            const float b = dzs[v * 16 + col];
-            const float *xr = xs + vrec[v];
+        // whole quads of voxels of a brick inside its box first; where x has to be masked, a loop of its own (with the
+        // mask in the main loop the 8 -> 16 -> 16 pair's weight gradients took 110 -> 165 us)
+        constexpr int kShare = kWgradVox / kWaves;
+        const bool inside = p.d0 + a.b.s <= p.bx.bd && p.h0 + a.b.r <= p.bx.bh && p.w0 + a.b.c <= p.bx.bw;
+        const int mine = min(max(nvox - wave * kShare, 0), kShare), whole = inside ? mine & ~3 : 0;
+        const int v0 = wave * kShare + q;
+        for (int k = 0; k < whole; k += 4) {
+            const float b = dzs[(v0 + k) * 16 + col];
+            const float *xr = xs + vrec[v0 + k];
             bsum += b;
 #pragma unroll
             for (int m = 0; m < MB; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(xr[off[m]], b, acc[m], 0, 0, 0);
+        }
+        for (int k = whole; k < mine; k += 4) {
+            const float b = dzs[(v0 + k) * 16 + col];
+            const int vr = vrec[v0 + k];
+            const float *xr = xs + max(vr, 0);
+            bsum += b;
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+                acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr < 0 ? 0.f : xr[off[m]], b, acc[m], 0, 0, 0);
         }
     }
     // the four waves' sums, added in wave order

@@ -131,3 +131,30 @@ def test_extent_one_kernels(cin, cout, dtype):
     assert rel_err(f64(dp), np.tensordot(xv, dv, axes=((0, 1, 2, 3),) * 2)) <= 1e-5
     assert rel_err(f64(db), dv.sum(axis=(0, 1, 2, 3))) <= 1e-5
     assert int(torch.count_nonzero(Py)) == int(torch.count_nonzero(Py[inner]))      # margins stay zero
+
+
+@pytest.mark.parametrize("dhw, cin, cout", [((4, 9, 13), 8, 8), ((5, 7, 9), 4, 6), ((3, 5, 7), 3, 5)])
+def test_infinite_voxels_stay_infinities(dhw, cin, cout):
+    """Matrix-instruction slots that stand for no tap or no voxel multiply zero by zero, never zero by a voxel: with one
+    infinite value in the input and finite, non-zero weights every output is an infinity or finite, none is NaN, and the
+    weight gradient is not NaN where that voxel meets a non-zero gradient only or none at all."""
+    g, dt = sp3d.Geom(1, dhw, (1, 1, 1)), DT["f32"]
+    x = synth.normal_volume((1,) + dhw + (cin,), 4400, "f32")
+    x[0, -1, -1, -1, 0] = np.inf                        # last voxel: next to slots of bricks that stick out of the tile
+    dz = np.abs(synth.normal_volume((1,) + dhw + (cout,), 4401, "f32")) + np.float32(0.5)
+    w = np.abs(synth.weights(cin, cout, 4402, "f32")) + np.float32(0.01)
+    ws = sp3d.alloc_ws(max(sp3d.sp_workspace_bytes(op, g, cin, cout, dt) for op in (0, 1, 2)))
+    Px, Pz, Py = (sp3d.alloc_padded(g, c, dt) for c in (cin, cout, cout))
+    sp3d.sp_partition(to_dev(x), Px, g, cin, dt)
+    sp3d.sp_partition(to_dev(dz), Pz, g, cout, dt)
+    sp3d.conv3d_fwd(Px, to_dev(w), None, Py, g, cin, cout, dt, 0, ws)
+    Y = torch.empty((1,) + dhw + (cout,), device="cuda")
+    sp3d.sp_unpartition(Py, Y, g, cout, dt)
+    near = torch.zeros((1,) + dhw + (1,), dtype=torch.bool, device="cuda")
+    near[0, -2:, -2:, -2:] = True                       # the voxels whose kernel covers it
+    assert torch.equal(torch.isinf(Y), near.expand_as(Y)) and not torch.isnan(Y).any()
+    dw = torch.zeros((3, 3, 3, cin, cout), device="cuda")
+    sp3d.conv3d_wgrad(Px, Pz, dw, None, g, cin, cout, dt, ws)
+    hit = torch.zeros_like(dw, dtype=torch.bool)
+    hit[1:, 1:, 1:, 0] = True                           # taps through which an existing voxel reads the last one
+    assert torch.equal(torch.isinf(dw), hit) and not torch.isnan(dw).any()
