@@ -36,30 +36,53 @@ namespace {
 // input channels k = 32i + 16*half + 8*(lane/32) + e of output channel m = 32j + lane%32.
 // Forward reads w[tap][k][m]; data-grad reads w[26-tap][m][k] (taps mirrored, roles swapped), where
 // the kernel's input channels are the layer's output channels.  ki / ko = channel counts as the
-// kernel sees them (ki in, ko out).
-__global__ __launch_bounds__(256) void pack_weights_kernel(const uint16_t *__restrict__ w,
-                                                           uint16_t *__restrict__ wpack, int ki, int ko,
-                                                           int dgrad, int flat) {
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    const int per_pair = NFRAG * 64 * 8;
-    const int pairs = (ki / C) * (ko / C);
-    if (idx >= per_pair * pairs) return;
-    const int pair = idx / per_pair, i = idx % per_pair;
-    const int ci = pair / (ko / C), cj = pair % (ko / C);
-    const int e = i & 7, lane = (i >> 3) & 63, half = (i >> 9) & 1, tap = i >> 10;
-    const int m = C * cj + (lane & 31), k = C * ci + 16 * half + 8 * (lane >> 5) + e;
-    // forward: w[tap][cin = k][cout = m] (row length ko); dgrad: w[26-tap][cin = m][cout = k] (row length ki)
-    if (flat) {
-        // w[3][3][..][..]: its 9 taps are the kernel's taps 9..17 (kd = 1); the other fragments are never loaded
-        // and stay unwritten
-        const int t9 = tap - 9;
-        if (t9 >= 0 && t9 < 9)
-            wpack[idx] = dgrad ? w[(static_cast<size_t>(8 - t9) * ko + m) * ki + k]
-                               : w[(static_cast<size_t>(t9) * ki + k) * ko + m];
+// kernel sees them (ki in, ko out).  The 2-D variant's nine taps w[3][3][..][..] sit in the slots 9 .. 17 (kd = 1);
+// its other slots are never loaded and stay unwritten.
+// A wave packs the two fragments of one (chunk, block, tap), a 32 x 32 square of w, neighbouring waves neighbouring
+// blocks, so that the 64-byte rows of four waves are one run of memory.  In the data gradient's order a lane's eight
+// values lie side by side; the forward order is transposed in LDS, rows 34 elements apart so that the eight reads of
+// a lane and those of its 31 neighbours fall into different banks.  What bounds it: HBM for wide layers (one pass over
+// w, one over wpack), the launch for narrow ones.  (One thread per element, 2-byte loads kilobytes apart, 27 slots
+// also in 2-D, took four times as long: 1024 -> 1024 channels, 2-D, 39 -> 9.1 us (18.9 MB in, as much out: 4.1 TB/s), 512
+// -> 512 12.8 -> 5.6 us; 3-D 1024 -> 1024 21.7 us (5.2 TB/s); a launch alone is 4 us.)
+constexpr int kPackWaves = 4, kPackRow = 34;
+__global__ __launch_bounds__(64 * kPackWaves) void pack_weights_kernel(const uint16_t *__restrict__ w,
+                                                                       uint4 *__restrict__ wpack, int nci, int nco,
+                                                                       int ntap, int dgrad) {
+    __shared__ __align__(16) uint16_t square[kPackWaves][C * kPackRow];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int id = blockIdx.x * kPackWaves + wave;
+    const bool real = id < nci * nco * ntap;
+    const int u = real ? id : 0;
+    const int cj = u % nco, t = (u / nco) % ntap, ci = u / (nco * ntap);
+    const int ki = C * nci, ko = C * nco;
+    uint4 *dst = wpack + (static_cast<size_t>(ci * nco + cj) * NFRAG + 2 * (t + (ntap == 9 ? 9 : 0))) * 64 + lane;
+    if (dgrad) {
+        const uint16_t *src = w + (static_cast<size_t>(ntap - 1 - t) * ko + C * cj + (lane & 31)) * ki + C * ci + 8 * (lane >> 5);
+        const uint4 v0 = *reinterpret_cast<const uint4 *>(src), v1 = *reinterpret_cast<const uint4 *>(src + 16);
+        if (real) {
+            dst[0] = v0;
+            dst[64] = v1;
+        }
         return;
     }
-    wpack[idx] = dgrad ? w[(static_cast<size_t>(26 - tap) * ko + m) * ki + k]
-                       : w[(static_cast<size_t>(tap) * ki + k) * ko + m];
+    const uint16_t *src = w + (static_cast<size_t>(t) * ki + C * ci + (lane >> 2)) * ko + C * cj + 8 * (lane & 3);
+    uint16_t *sq = square[wave];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint4 v = *reinterpret_cast<const uint4 *>(src + static_cast<size_t>(16 * i) * ko);
+        uint32_t *d = reinterpret_cast<uint32_t *>(sq + (16 * i + (lane >> 2)) * kPackRow + 8 * (lane & 3));
+        d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+        const uint16_t *col = sq + (16 * half + 8 * (lane >> 5)) * kPackRow + (lane & 31);
+        uint32_t v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = col[2 * e * kPackRow] | static_cast<uint32_t>(col[(2 * e + 1) * kPackRow]) << 16;
+        if (real) dst[64 * half] = make_uint4(v[0], v[1], v[2], v[3]);
+    }
 }
 
 // Per-wave state of the march that the side work of a step needs.
@@ -540,9 +563,9 @@ int launch_conv_mfma(const void *Pin, const void *w, const float *bias, void *Po
     if (bits && (!conv_mfma_bits_supported(g, ki, ko, SP_BF16) || (split && split->out2) || mask || (!dgrad && !relu)))
         return SP_EUNSUPPORTED;
     const int nci = ki / C, nco = ko / C;
-    const int pack_elems = nci * nco * NFRAG * 64 * 8;
-    hipLaunchKernelGGL(pack_weights_kernel, dim3((pack_elems + 255) / 256), dim3(256), 0, s,
-                       static_cast<const uint16_t *>(w), static_cast<uint16_t *>(ws), ki, ko, dgrad ? 1 : 0, g.flat);
+    const int ntap = taps_of(g);
+    hipLaunchKernelGGL(pack_weights_kernel, dim3((nci * nco * ntap + kPackWaves - 1) / kPackWaves), dim3(64 * kPackWaves), 0,
+                       s, static_cast<const uint16_t *>(w), static_cast<uint4 *>(ws), nci, nco, ntap, dgrad ? 1 : 0);
     int rc = record_hip(hipGetLastError());
     if (rc != SP_OK) return rc;
     // wide layers on few voxels: one launch that keeps the sums in registers over all input channels
