@@ -507,10 +507,7 @@ static PatchPlan plan_patches(const Geo &g, int ki, int ko) {
     const int ed = g.td + 2 * grow_d(g), eh = g.th + 2 * g.grow, ew = g.tw + 2 * g.grow;
     p.nh = (eh + ph - 1) / ph;
     p.nw = (ew + PW - 1) / PW;
-    // D chunk: whole box depth unless that leaves the chip short of workgroups
     const long long base = 1LL * g.ntiles * p.nh * p.nw * nco;
-    int dchunk = ed;
-    while (base * ((ed + dchunk - 1) / dchunk) < 1024 && dchunk > 16) dchunk = (dchunk + 1) / 2;
     // 2-D variant, tiles narrower than half a patch: up to 4 slices side by side (see fold_col); the tile's
     // slice count and the D chunk must be multiples of it
     p.fold = 1;
@@ -520,8 +517,23 @@ static PatchPlan plan_patches(const Geo &g, int ki, int ko) {
         if (f > 4) f = 4;
         while (f > 1 && g.td % f) --f;
         p.fold = f;
-        dchunk = (dchunk + f - 1) / f * f;
     }
+    // D chunk: what costs least if the 256 compute units (one workgroup each: LDS) take the workgroups in rounds, a
+    // round lasting as long as its march - the chunk's planes, the two of the surround (and two that drain the hand-over
+    // between the two chunks of a pair), and what a march costs before its first plane, in steps: the weights and three
+    // planes on their way, about 6 us = 4 plane steps in 3-D and 16 of the shorter ones in 2-D (2 ... 8 and 4 ... 16
+    // measured within 1 %).  Before, a chunk was never below 16 planes: 8 workgroups for a layer on 32^3.  256 -> 256 on
+    // 32^3 (128 workgroups of 16 planes -> 256 of 8): 48 -> 35 us a launch; training step of the four-level network on 32^3 2.02 -> 1.55 ms;
+    // 32 -> 32 on 128^3 (512 workgroups of 16 planes -> 256 of 32) 117 -> 104 us.
+    const int steps = (ed + p.fold - 1) / p.fold, over = (g.flat ? 16 : 4) + (p.pairs ? 4 : 2);
+    int best = steps;
+    long long cost = 0;
+    for (int k = 1; k <= steps && (k == 1 || base * k <= 4096); ++k) {
+        const int d = (steps + k - 1) / k;
+        const long long c = (base * ((steps + d - 1) / d) + 255) / 256 * (d + over);
+        if (k == 1 || c < cost) { cost = c; best = d; }
+    }
+    const int dchunk = best * p.fold;
     p.dchunk = dchunk;
     p.nd = (ed + dchunk - 1) / dchunk;
     p.nblocks = base * p.nd;
