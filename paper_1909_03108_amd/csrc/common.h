@@ -152,8 +152,9 @@ int launch_conv_mfma(const void *Pin, const void *w, const float *bias, void *Po
 // wide layers on few voxels: output-stationary implicit GEMM on the packed weights (conv_gemm.hip);
 // launch_conv_mfma hands such layers over after packing
 bool conv_gemm_preferred(const Geo &g, int ki, int ko);
-int launch_conv_gemm(const void *Pin, const void *wpack, const float *bias, void *Pout, const Geo &g, int ki, int ko,
-                     bool relu, hipStream_t s, const void *mask, const ConvSplit *split);
+size_t conv_gemm_ws_bytes(const Geo &g, int ki, int ko);      // behind the packed weights
+int launch_conv_gemm(const void *Pin, const void *wpack, void *part, const float *bias, void *Pout, const Geo &g, int ki,
+                     int ko, bool relu, hipStream_t s, const void *mask, const ConvSplit *split);
 
 // single-input-channel first layer (conv_c1.hip)
 bool conv_c1_supported(const Geo &g, int cin, int cout, sp_dtype_t dt);

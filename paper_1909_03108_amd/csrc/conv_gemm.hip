@@ -1,62 +1,59 @@
-// bf16 3x3 (2-D variant, geometry flag `flat`) and 3x3x3 convolution for wide layers on few voxels - the bottom
-// levels of the 2-D U-Net (Sec. 3: 512 and 1024 filters on tiles of 16 x 16 voxels and less) and the 16^3 level of
-// the 3-D one - as an output-stationary implicit GEMM on the gfx950 matrix cores.  Serves conv3d_fwd and, on weights packed with
-// mirrored taps and swapped channel roles, conv3d_dgrad, like the plane-marching kernels of conv_mfma.hip.
+// bf16 3x3 (2-D variant, geometry flag `flat`) and 3x3x3 convolution for layers on few voxels - the bottom levels of
+// the 2-D U-Net (Sec. 3: 512 and 1024 filters on tiles of 16 x 16 voxels and less) and of the 3-D one, and every level
+// of a network on a small patch - as an output-stationary implicit GEMM on the gfx950 matrix cores.  Serves conv3d_fwd
+// and, on weights packed with mirrored taps and swapped channel roles, conv3d_dgrad, like the plane-marching kernels of
+// conv_mfma.hip.
 //
 // Why a second kernel family.  The marching kernels keep the weights of ONE pair of input chunks in
 // registers and stream voxels past them; a layer with 1024 input channels is 16 launches that hand fp32
 // partial sums to each other through memory, and on tiles of 8 x 8 voxels each launch is a march of a few
-// steps in a mostly empty patch.  Here the roles are swapped: a workgroup owns 256 output voxels x 128 output
-// channels, keeps their sums in registers (8 accumulators of 32 x 32 per wave) over ALL taps and input
-// channels, and streams the weights: one launch per layer, no partial sums, and voxels are numbered across
-// rows, slices and tiles, so every MFMA column is a real voxel whatever the tile shape.  (With the 3x3x3 kernel
-// the marching kernels do three times the MFMAs per staged byte; they are level with this family at 32^3 voxels
-// and ahead beyond, so in 3-D it serves the smallest level only: see conv_gemm_preferred.)
+// steps in a mostly empty patch.  Here the roles are swapped: a workgroup owns a tile of output voxels x output
+// channels, keeps their sums in registers over a run of K (kernel rows x input chunks), and streams weights and
+// voxels: voxels are numbered across rows, slices and tiles, so every MFMA column is a real voxel whatever the tile
+// shape, and where tiles are fewer than compute units the K loop is split between `nsplit` workgroups, whose fp32 sums a
+// second launch adds in order.
 //
-// Operands (v_mfma_f32_32x32x16_bf16, A = weights [32 output channels][16 input channels], B = voxels
-// [16 input channels][32 voxels]).  B: lane l supplies voxel l % 32, channels 8 (l / 32) .. + 7 of the
-// 16-channel half: 16 contiguous bytes of the NDHWC record of the voxel one tap away, one global load per
-// lane and fragment, no LDS (the taps of a kernel row re-read the same records from the vector cache).
-// A: the packed fragments of conv_mfma.hip (1 KB each, lane-major), shared by the four waves of a workgroup
-// through LDS: a K step is one 32-channel input chunk x one kernel row (kw = 0, 1, 2): 24 fragments for the
-// workgroup's 4 output blocks, double buffered; they and the B fragments of a step are fetched two steps
-// ahead; one barrier per step (48 MFMAs per wave).
+// A K step is one kernel row (three taps kw) x one 32-channel input chunk.  Both operands come through LDS by
+// direct loads, NS stages deep (one barrier per step, placed before the step's last MFMA group, so that the next
+// step's first fragments are read behind it while that group runs):
+//   A (weights): the packed fragments of conv_mfma.hip, 1 KB each, lane-major.
+//   B (voxels): the records (32 channels, 64 bytes) of the padded rows that the tile's voxels touch, each ONCE for the
+//     three taps of the row: voxel q of a box row of ew voxels is record (q / ew) (ew + 2) + q % ew, and the taps read
+//     this record and the two after it.  The 16-byte pieces of a record sit in the order piece ^ (record / 4 % 4), so
+//     that the 16-byte reads of 16 neighbouring voxels fall into 16 different bank groups.
+// (v_mfma_f32_32x32x16_bf16, A = weights [32 output channels][16 input channels], B = voxels [16 input channels][32
+// voxels]; four waves, two along output channels x two along voxels.)
+// What bounds it: in its first form the B fragments were fetched by the lanes themselves, 16 bytes of 64 different
+// lines per load, and the vector cache's one line per clock held the step at 0.9 (128 voxels) and 2.1 us (256 voxels),
+// three times its MFMAs; with up to 32 workgroups and no split the bottom level of the 3-D network took 250 us a layer.
+// Now, first form -> this one: 1024 -> 1024 on 8^3 voxels (3-D) 250 -> 31 + 9 us (its 57 MB of weights: 7 us of HBM), 512 ->
+// 512 on 16^3 150 -> 64 + 9 us (0.9 PFLOP/s), 2-D on two slices 1024 -> 1024 on 16 x 16 88 -> 22 + 6 us (a launch, a pipeline
+// of three stages and 12 steps: latency), 512 -> 512 on 16 slices of 32 x 32 115 -> 100 us.
 //
-// Output box growth, two input tensors (concatenation without a copy), two output tensors, bias, ReLU and the
-// ReLU mask of the data gradient behave as in conv_mfma.hip.  The order of the additions is fixed (kernel rows,
-// then chunks, then taps), so results are reproducible and do not depend on the voxel's position.
-#include "common.h"
+// Output box growth, two input tensors (concatenation without a copy), two output tensors, bias, ReLU, the ReLU mask
+// of the data gradient, its one-bit forms and gathered halos behave as in conv_mfma.hip.  The order of the additions
+// is fixed (kernel rows, then chunks, then taps within a split; then the splits), and the split depends on the layer's
+// interior voxel count and channels only, so results are reproducible and depend neither on the voxel's position nor on
+// the tile grid.
+#include "conv_mfma_common.h"
 
 namespace sp3d {
 
+using namespace convk;
+
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-// (a plain vector type: arrays of the runtime's uint4 class stayed in scratch memory - 12 stores and 12 loads per
-// K step, each with a wait that drained the voxel-fragment loads in flight)
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int C = 32;                            // channels of a chunk / block
-constexpr int CB = 4;                            // output blocks per workgroup
-constexpr int VBMAX = 2;                         // 32-voxel segments per wave: 2, or 1 for layers that would
-                                                 // otherwise leave half of the compute units without a workgroup
-constexpr int kWaves = 4, kThreads = 256;
-constexpr int wg_vox(int vb) { return kWaves * vb * 32; }      // 256 (or 128) output voxels per workgroup
+// (a plain vector type: arrays of the runtime's uint4 class stay in scratch memory)
+constexpr int kGemmWaves = 4, kGemmThreads = 256;
 constexpr int ROW = 3;                           // taps per K step (one row of the kernel)
-constexpr int STAGE_FRAGS = CB * ROW * 2;        // 24 weight fragments (1 KB each) per K step
-constexpr int STAGE_U4 = STAGE_FRAGS * 64;       // in 16-byte pieces: 6 per thread
-constexpr int STAGE_LOADS = STAGE_U4 / kThreads;
-constexpr int STAGE_BYTES = STAGE_FRAGS * 1024;
-constexpr int LDS_BYTES = 2 * STAGE_BYTES;       // 49152
 constexpr int NTAP_PACK = 27;                    // packed weights: 27 tap slots per (chunk, block); the 3x3 kernel of the
                                                  // 2-D variant sits in 9 .. 17 (the taps with kd = 1)
-// kernel rows (kd, kh) of a K loop: 3 in the 2-D variant (KD = 1), 9 in 3-D (KD = 3)
-constexpr int nrows(int KD) { return 3 * KD; }
-
-enum Epilogue { kNone = 0, kRelu = 1, kMask = 2 };
+constexpr int wg_vox(int vb) { return 128 * vb; }
+// Cutting of a workgroup: CBW output blocks per wave (2 CBW per workgroup), VB x 128 voxels, BL wave loads of 16 records
+// per wave and step.
+constexpr int stage_bytes(int cbw, int bl) { return (2 * cbw * ROW * 2 + 4 * bl) * 1024; }
+// LDS stages: four for wide workgroups, one per compute unit; three where two workgroups then share one
+constexpr int stages(int cbw, int bl) { return cbw == 2 && 4 * stage_bytes(2, bl) <= 160 * 1024 ? 4 : 3; }
 
 struct GemmArgs {
     const uint16_t *in;      // input channels [0, in_ca): in_cs channels per voxel
@@ -68,35 +65,27 @@ struct GemmArgs {
     uint16_t *out2;          // output channels [out_ca, ko): out2_cs per voxel (NULL: one tensor)
     int out_cs, out2_cs, out_ca;
     const uint16_t *mask;    // kMask: tensor laid out like `out`; results are zeroed where it is not positive
+    uint16_t *bits;          // kMaskBits (read) / kReluBits (written)
+    float4 *part;            // nsplit > 1: fp32 sums in fragment order (see part_index)
     Geo g;
     int nci, nco;            // input chunks, output blocks
-    int nvg;                 // voxel groups of wg_vox(VB)
-    int nblocks;             // nvg * nco / CB real workgroups (grid is rounded up to a multiple of 8)
+    int nrows;               // kernel rows (kd, kh): 3 in the 2-D variant, 9 in 3-D
+    int nsplit;              // workgroups that share the K loop of a tile
+    int nvg;                 // voxel groups of 128 VB
+    int nblocks;             // tiles: nvg * nco / (2 CBW); times nsplit real workgroups (grid: rounded up to 8)
     int nvox;                // ntiles * ed * eh * ew: voxels of the largest output box, every tile
     int ed, eh, ew;          // largest output box of the grid (interior grown on both sides)
-    FastDiv dbox, dplane, drow;      // ed * eh * ew, eh * ew, ew
+    int epi, gather;
+    int relu_keeps_nan;      // ReLU: any NaN stays; otherwise one with the sign set becomes 0, as in the marching kernels
+    FastDiv drow, drec, deh, ded;    // ew, ew + 2, eh, ed
 };
 
-__device__ __forceinline__ uint32_t pack2(float a, float b) {
-    union { bf16x2 v; uint32_t u; } r;
-    r.v = __builtin_convertvector(f32x2{a, b}, bf16x2);
-    return r.u;
+// 16 bytes per lane from global memory straight into LDS: lane l's data lands at dst + 16 l (dst is wave-uniform and
+// travels in M0).  Written as assembly because the compiler, when it knows of such a load, waits for ALL outstanding ones
+// before every LDS read; the kernel waits for exactly the loads it needs.
+__device__ __forceinline__ void dma16(const void *src, uint32_t dst) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst) : "memory");
 }
-
-// two bf16 in a word -> 0xffff in each half whose value is positive (not zero, not negative, not NaN)
-__device__ __forceinline__ uint32_t positive_halves(uint32_t v) {
-    const uint32_t lo = v & 0xffffu, hi = v >> 16;
-    return ((lo - 1u) < 0x7f80u ? 0x0000ffffu : 0u) | ((hi - 1u) < 0x7f80u ? 0xffff0000u : 0u);
-}
-
-// Per-thread state of the K loop.
-struct Ctx {
-    long long pv[VBMAX];         // padded voxel index of this lane's output voxel in segment s
-    int hi;                      // lane / 32: which 8 channels of a 16-channel half this lane supplies
-    int tid;
-    int cg;                      // first output block of the workgroup / CB
-    long long plane, row;        // voxel strides of the padded tile
-};
 
 // Source of input chunk i: tensor, channels per voxel, channel offset.
 struct InSrc { const uint16_t *base; int cs, co; };
@@ -106,201 +95,318 @@ __device__ __forceinline__ InSrc in_src(const GemmArgs &a, int i) {
     return InSrc{a.in, a.in_cs, c0};
 }
 
-// Voxel offset of kernel row r (= kh in the 2-D variant, 3 kd + kh in 3-D) at kw = 0, relative to the output voxel.
-template <int KD>
-__device__ __forceinline__ long long row_offset(const Ctx &c, int r) {
-    if (KD == 1) return (r - 1) * c.row - 1;
-    const int kd = r / 3, kh = r - 3 * kd;
-    return (kd - 1) * c.plane + (kh - 1) * c.row - 1;
+struct BoxPos { int tile, d, h, w; };
+// box row index (over all tiles) -> tile, d, h
+__device__ __forceinline__ BoxPos row_pos(const GemmArgs &a, uint32_t row) {
+    BoxPos p;
+    const uint32_t t = fdiv(row, a.deh), tile = fdiv(t, a.ded);
+    p.h = static_cast<int>(fmod_(row, t, a.deh));
+    p.d = static_cast<int>(fmod_(t, tile, a.ded));
+    p.tile = static_cast<int>(tile);
+    p.w = 0;
+    return p;
 }
 
-// next K step, clamped to the last one.  Kernel rows outermost, chunks inside: a voxel's record of two
-// neighbouring chunks is one 128-byte line, so the second chunk finds in the vector cache what the first fetched
-template <int KD>
-__device__ __forceinline__ void advance(const GemmArgs &a, int &i, int &r) {
-    int ni = i + 1, nr = r;
-    if (ni == a.nci) { ni = 0; ++nr; }
-    if (nr < nrows(KD)) { i = ni; r = nr; }
+// Output voxel q: padded voxel index, and whether it exists (past the end, or outside the box of a tile without a
+// neighbour on that side: no).
+struct OutVox { long long pv; bool ok; };
+__device__ __forceinline__ OutVox out_vox(const GemmArgs &a, int q) {
+    const uint32_t qq = static_cast<uint32_t>(min(q, a.nvox - 1)), row = fdiv(qq, a.drow);
+    BoxPos p = row_pos(a, row);
+    p.w = static_cast<int>(fmod_(qq, row, a.drow));
+    const TileBox bx = tile_box(a.g, p.tile);
+    OutVox o;
+    o.ok = q < a.nvox && p.d < bx.bd && p.h < bx.bh && p.w < bx.bw;
+    o.pv = static_cast<long long>(p.tile) * a.g.tile_vox + bx.org + (1LL * (p.d + 1) * a.g.ph + p.h + 1) * a.g.pw + p.w + 1;
+    return o;
 }
 
-// Issue the loads of K step (chunk i, row r): this thread's share of the 24 weight fragments (to registers, on
-// their way to LDS) and this lane's B fragments of the step.
-template <int VB, int KD>
-__device__ __forceinline__ void fetch(const GemmArgs &a, const Ctx &c, int i, int r, u32x4 (&areg)[STAGE_LOADS],
-                                      bf16x8 (&b)[VB][ROW][2]) {
-    const int tap0 = (KD == 1 ? 9 : 0) + ROW * r;
+// Finished sums of one voxel, 16 channels (8 q + 4 hi + i) of output block cj: ReLU / mask, convert, 8-byte stores.
+__device__ __forceinline__ void finish(const GemmArgs &a, const f32x16 &s, int cj, int hi, const OutVox &o) {
+    if (!o.ok) return;
+    const int co = C * cj;
+    uint16_t *obase = a.out;
+    int ocs = a.out_cs, oco = co;
+    if (a.out2 && co >= a.out_ca) { obase = a.out2; ocs = a.out2_cs; oco = co - a.out_ca; }
+    uint16_t *dst = obase + o.pv * ocs + oco + 4 * hi;
+    const uint16_t *m = a.mask + o.pv * a.out_cs + co + 4 * hi;
+    uint16_t *word = a.bits + (o.pv * a.nco + cj) * 2 + hi;
+    uint32_t bits = 0;
+    if (a.epi == kMaskBits) bits = spread_word(*word);
 #pragma unroll
-    for (int j = 0; j < STAGE_LOADS; ++j) {
-        const int e = j * kThreads + c.tid;                     // piece of the stage
-        const int cb = e / (ROW * 2 * 64), x = e - cb * (ROW * 2 * 64);
-        const size_t frag0 = (static_cast<size_t>(i * a.nco + c.cg * CB + cb) * NTAP_PACK + tap0) * 2;
-        areg[j] = reinterpret_cast<const u32x4 *>(a.wpack)[frag0 * 64 + x];
-    }
-    const InSrc src = in_src(a, i);
-    const long long ro = row_offset<KD>(c, r);
+    for (int q = 0; q < 4; ++q) {
+        float v[4];
 #pragma unroll
-    for (int s = 0; s < VB; ++s) {
-        const uint16_t *p = src.base + (c.pv[s] + ro) * src.cs + src.co + 8 * c.hi;
-#pragma unroll
-        for (int kw = 0; kw < ROW; ++kw)
-#pragma unroll
-            for (int half = 0; half < 2; ++half)
-                b[s][kw][half] = *reinterpret_cast<const bf16x8 *>(p + static_cast<long long>(kw) * src.cs + 16 * half);
-    }
-}
-
-// All MFMAs of one K step: weights from LDS stage `abuf`, voxels from registers.
-template <int VB>
-__device__ __forceinline__ void contract(const char *abuf, int lane, const bf16x8 (&b)[VB][ROW][2],
-                                         f32x16 (&acc)[CB][VB]) {
-#pragma unroll
-    for (int kw = 0; kw < ROW; ++kw)
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            bf16x8 w[CB];
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-                w[cb] = *reinterpret_cast<const bf16x8 *>(abuf + ((cb * ROW + kw) * 2 + half) * 1024 + lane * 16);
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                for (int s = 0; s < VB; ++s)
-                    acc[cb][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[cb], b[s][kw][half], acc[cb][s], 0, 0, 0);
+        for (int i = 0; i < 4; ++i) {
+            v[i] = s[4 * q + i];
+            if (is_relu(a.epi)) v[i] = a.relu_keeps_nan ? (v[i] < 0.f ? 0.f : v[i]) : relu_f32(v[i]);
         }
-}
-
-// K step j on LDS stage j % 2 with the voxel fragments `bc`.  The loads of step j + 2 are issued here (voxel
-// fragments into `bn`, this thread's share of the weight fragments into `an`) and have a whole step to arrive:
-// the compiler is free to place them anywhere between the two barriers.  The weights of step j + 1, loaded during
-// step j - 1 into `aw`, go to the other LDS stage, which every wave left at the barrier that ended step j - 1.
-// (i, r) = chunk and kernel row of step j + 2; past the last step it stays there: those loads are harmless,
-// and what they fill is never read.
-template <int VB, int KD>
-__device__ __forceinline__ void step(const GemmArgs &a, const Ctx &c, char *cur, char *other, int lane, int &i, int &r,
-                                     const bf16x8 (&bc)[VB][ROW][2], bf16x8 (&bn)[VB][ROW][2],
-                                     const u32x4 (&aw)[STAGE_LOADS], u32x4 (&an)[STAGE_LOADS], f32x16 (&acc)[CB][VB]) {
-    fetch<VB, KD>(a, c, i, r, an, bn);
-    contract(cur, lane, bc, acc);
-    u32x4 *dst = reinterpret_cast<u32x4 *>(other);
+        uint2 pk = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
+        if (a.epi == kMask) {
+            const uint2 mv = *reinterpret_cast<const uint2 *>(m + 8 * q);
+            pk.x &= positive_halves(mv.x);
+            pk.y &= positive_halves(mv.y);
+        }
+        if (a.epi == kMaskBits) {
+            const uint2 mv = nibble_halves(bits, q);
+            pk.x &= mv.x;
+            pk.y &= mv.y;
+        }
+        if (a.epi == kReluBits) {
 #pragma unroll
-    for (int j = 0; j < STAGE_LOADS; ++j) dst[j * kThreads + c.tid] = aw[j];
-    __syncthreads();
-    advance<KD>(a, i, r);
+            for (int i = 0; i < 4; ++i) bits = shift_in_positive(bits, v[i]);
+        }
+        *reinterpret_cast<uint2 *>(dst + 8 * q) = pk;
+    }
+    if (a.epi == kReluBits) *word = row_word(bits);
 }
 
-template <int RELU, bool HAS_BIAS, int VB, int KD>
-__global__ __launch_bounds__(kThreads, 1) void conv_gemm_kernel(GemmArgs a) {
+// Sums of a split: unit (tile, wave, block of the wave, segment, q) x 64 lanes x 4 channels, 1 KB per unit.
+template <int CBW, int VB>
+__device__ __forceinline__ size_t part_index(const GemmArgs &a, int split, int blk, int wave, int c, int s, int lane) {
+    return (((static_cast<size_t>(split) * a.nblocks + blk) * kGemmWaves + wave) * CBW * 2 * VB + c * 2 * VB + s) * 256 + lane;
+}
+
+template <int CBW, int VB, int BL>
+__global__ __launch_bounds__(kGemmThreads, 1) void conv_gemm_kernel(GemmArgs a) {
+    constexpr int NSEG = 2 * VB, CBT = 2 * CBW, AFRAGS = CBT * ROW * 2, AL = AFRAGS / kGemmWaves, L = AL + BL;
+    constexpr int STAGE = stage_bytes(CBW, BL), NS = stages(CBW, BL);
+    static_assert((NS - 1) * L < 64, "vmcnt");
     extern __shared__ __align__(16) char lds[];
-    // workgroups of one XCD (blockIdx % 8) get consecutive logical ids: they share output blocks, i.e. weights
+    // workgroups of one XCD (blockIdx % 8) get consecutive logical ids: they share output blocks and K range, i.e. weights
     const int per_xcd = gridDim.x >> 3;
     const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (logical >= a.nblocks) return;
+    if (logical >= a.nblocks * a.nsplit) return;
     const Geo &g = a.g;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    Ctx c;
-    c.tid = tid;
-    c.hi = lane >> 5;
-    c.cg = logical / a.nvg;
-    const int vg = logical - c.cg * a.nvg;
-    c.row = g.pw;
-    c.plane = static_cast<long long>(g.ph) * g.pw;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave & 1, wn = wave >> 1, hi = lane >> 5;
+    const int vg = logical % a.nvg, u = logical / a.nvg, split = u % a.nsplit, cg = u / a.nsplit;
+    const long long prow = g.pw, pplane = static_cast<long long>(g.ph) * g.pw;
+    const int q0 = vg * wg_vox(VB);
+    auto record = [&](int q) {
+        const uint32_t row = fdiv(static_cast<uint32_t>(q), a.drow);
+        return row * (a.ew + 2) + fmod_(static_cast<uint32_t>(q), row, a.drow);
+    };
+    const uint32_t rec0 = record(q0), nrec = record(min(q0 + wg_vox(VB), a.nvox) - 1) + 3 - rec0;
 
-    // this lane's output voxels: index q over (tile, d, h, w) of the largest output box; a tile whose own box is
-    // smaller (no neighbour on that side) computes nothing for the voxels outside it
-    bool ok[VB];
+    // This lane's share of the record loads: records 16 (BL wave + j) + lane / 4, piece lane % 4 of each (stored order).
+    // Records past the last one repeat it; records of rows that a tile's own box lacks are moved inside it (both only
+    // feed results that are dropped).
+    long long rpos[BL];
+    int rflag[BL];                   // gathered halos: bit 0 / 1 first / last row with a neighbour, 2 / 3 plane
+    const long long sw = g.tile_vox - g.tw, sh = g.tile_vox * g.gw - g.th * prow, sd = g.tile_vox * g.gw * g.gh - g.td * pplane;
 #pragma unroll
-    for (int s = 0; s < VB; ++s) {
-        const long long q = (static_cast<long long>(vg * kWaves + wave) * VB + s) * 32 + (lane & 31);
-        const bool in = q < a.nvox;
-        const uint32_t qq = in ? static_cast<uint32_t>(q) : 0u;
-        const uint32_t tile = fdiv(qq, a.dbox), rb = fmod_(qq, tile, a.dbox);
-        uint32_t d = fdiv(rb, a.dplane);
-        const uint32_t rp = fmod_(rb, d, a.dplane);
-        uint32_t h = fdiv(rp, a.drow), w = fmod_(rp, h, a.drow);
-        const TileBox bx = tile_box(g, static_cast<int>(tile));
-        ok[s] = in && static_cast<int>(d) < bx.bd && static_cast<int>(h) < bx.bh && static_cast<int>(w) < bx.bw;
-        if (!ok[s]) d = h = w = 0;            // a voxel that exists: its loads stay inside the tile, its result is dropped
-        c.pv[s] = static_cast<long long>(tile) * g.tile_vox + bx.org + (d + 1) * c.plane + (h + 1) * c.row + (w + 1);
+    for (int j = 0; j < BL; ++j) {
+        const uint32_t k = min(static_cast<uint32_t>(16 * (BL * wave + j) + (lane >> 2)), nrec - 1) + rec0;
+        const uint32_t row = fdiv(k, a.drec);
+        BoxPos p = row_pos(a, row);
+        const TileBox bx = tile_box(g, p.tile);
+        p.d = min(p.d, bx.bd - 1);
+        p.h = min(p.h, bx.bh - 1);
+        p.w = min(static_cast<int>(fmod_(k, row, a.drec)), bx.bw + 1);
+        rpos[j] = static_cast<long long>(p.tile) * g.tile_vox + bx.org + (p.d + 1) * pplane + (p.h + 1) * prow + p.w;
+        rflag[j] = 0;
+        if (a.gather) {              // (host: one-voxel margins, no grown box, 3-D)
+            const int tc = p.tile % g.gw, t1 = p.tile / g.gw, tb = t1 % g.gh, ta = (t1 / g.gh) % g.gd;
+            if (p.w == 0 && tc > 0) rpos[j] -= sw;
+            if (p.w == g.tw + 1 && tc < g.gw - 1) rpos[j] += sw;
+            rflag[j] = (p.h == 0 && tb > 0 ? 1 : 0) | (p.h == g.th - 1 && tb < g.gh - 1 ? 2 : 0) |
+                       (p.d == 0 && ta > 0 ? 4 : 0) | (p.d == g.td - 1 && ta < g.gd - 1 ? 8 : 0);
+        }
+    }
+    const int piece = 8 * ((lane & 3) ^ (lane >> 4));
+    const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char *)lds));
+
+    // K range of this split
+    const int nk = a.nci * a.nrows;
+    const int k0 = static_cast<int>(1LL * split * nk / a.nsplit), k1 = static_cast<int>(1LL * (split + 1) * nk / a.nsplit);
+    int fk = k0, fr = k0 / a.nci, fi = k0 - fr * a.nci;         // next step to fetch: kernel row fr, chunk fi (innermost: the
+                                                                // record of two neighbouring chunks is one cache line)
+    auto fetch = [&](int stage) {
+        const int tap0 = (a.nrows == 3 ? 9 : 0) + ROW * fr;
+        const uint32_t dst = lds0 + stage * STAGE;
+#pragma unroll
+        for (int n = 0; n < AL; ++n) {
+            const int m = wave * AL + n, cb = m / (ROW * 2), x = m - cb * (ROW * 2);
+            const size_t frag = (static_cast<size_t>(fi * a.nco + cg * CBT + cb) * NTAP_PACK + tap0) * 2 + x;
+            dma16(a.wpack + frag * 64 + lane, dst + m * 1024);
+        }
+        const InSrc src = in_src(a, fi);
+        const int kd = a.nrows == 3 ? 1 : fr / 3, kh = a.nrows == 3 ? fr : fr - 3 * (fr / 3);
+        const long long ro = (kd - 1) * pplane + (kh - 1) * prow;
+        const long long gh = kh == 0 ? -sh : sh, gd = kd == 0 ? -sd : sd;
+        const int mh = kh == 0 ? 1 : (kh == 2 ? 2 : 0), md = kd == 0 ? 4 : (kd == 2 ? 8 : 0);
+        const uint16_t *base = src.base + src.co + piece;
+#pragma unroll
+        for (int j = 0; j < BL; ++j) {
+            long long at = rpos[j] + ro;
+            if (a.gather) at += (rflag[j] & mh ? gh : 0) + (rflag[j] & md ? gd : 0);
+            dma16(base + at * src.cs, dst + (AFRAGS + BL * wave + j) * 1024);
+        }
+        if (fk + 1 < k1) {           // past the last step the loads repeat it: what they fill is never used
+            ++fk;
+            if (++fi == a.nci) { fi = 0; ++fr; }
+        }
+    };
+
+    // this lane's read offsets inside a stage: record of its voxel in segment s, one and two records on
+    int boff[NSEG][ROW];
+#pragma unroll
+    for (int s = 0; s < NSEG; ++s) {
+        const int q = min(q0 + wn * 64 * VB + s * 32 + (lane & 31), a.nvox - 1);
+        const int r = static_cast<int>(record(q) - rec0);
+#pragma unroll
+        for (int kw = 0; kw < ROW; ++kw) boff[s][kw] = AFRAGS * 1024 + (r + kw) * 64 + ((hi ^ ((r + kw) >> 2)) & 3) * 16;
     }
 
-    // accumulators start from the bias: lane l holds channels 8 (e / 4) + 4 (l / 32) + e % 4 of a block
-    f32x16 acc[CB][VB];
+    // accumulators start from the bias (in the first split): lane l holds channels 8 (e / 4) + 4 (l / 32) + e % 4 of a block
+    f32x16 acc[CBW][NSEG];
+    const bool biased = a.bias && split == 0;
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) {
+    for (int c = 0; c < CBW; ++c) {
         f32x16 v;
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-            v[e] = HAS_BIAS ? a.bias[C * (c.cg * CB + cb) + 8 * (e >> 2) + 4 * c.hi + (e & 3)] : 0.f;
+            v[e] = biased ? a.bias[C * (cg * CBT + wm * CBW + c) + 8 * (e >> 2) + 4 * hi + (e & 3)] : 0.f;
 #pragma unroll
-        for (int s = 0; s < VB; ++s) acc[cb][s] = v;
+        for (int s = 0; s < NSEG; ++s) acc[c][s] = v;
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // (the bias: from here on only the staged loads are counted)
 
-    // K loop: 3 kernel rows x nci chunks.  Loads run two steps ahead of the MFMAs that use them, so the
-    // voxel fragments rotate through three register sets and the weight pieces through two; six steps per
-    // iteration keep every set a compile-time name (the step count is a multiple of 6: nci is even).
-    bf16x8 b0[VB][ROW][2], b1[VB][ROW][2], b2[VB][ROW][2];
-    u32x4 a0[STAGE_LOADS], a1[STAGE_LOADS];
-    char *const s0 = lds, *const s1 = lds + STAGE_BYTES;
-    int i = 0, r = 0;
-    fetch<VB, KD>(a, c, i, r, a0, b0);
-    advance<KD>(a, i, r);
-    {
-        u32x4 *dst = reinterpret_cast<u32x4 *>(s0);
+    bf16x8 wf[2][CBW], bf[2][NSEG];
+    auto read_group = [&](const char *stage, int gi) {          // (kw, K-half) group gi -> fragment set gi % 2
+        const int kw = gi >> 1, half = gi & 1;
 #pragma unroll
-        for (int j = 0; j < STAGE_LOADS; ++j) dst[j * kThreads + tid] = a0[j];
-    }
-    fetch<VB, KD>(a, c, i, r, a1, b1);
-    advance<KD>(a, i, r);
-    __syncthreads();
-    const int nk = a.nci * nrows(KD);
-    for (int k = 0; k < nk; k += 6) {
-        step<VB, KD>(a, c, s0, s1, lane, i, r, b0, b2, a1, a0, acc);
-        step<VB, KD>(a, c, s1, s0, lane, i, r, b1, b0, a0, a1, acc);
-        step<VB, KD>(a, c, s0, s1, lane, i, r, b2, b1, a1, a0, acc);
-        step<VB, KD>(a, c, s1, s0, lane, i, r, b0, b2, a0, a1, acc);
-        step<VB, KD>(a, c, s0, s1, lane, i, r, b1, b0, a1, a0, acc);
-        step<VB, KD>(a, c, s1, s0, lane, i, r, b2, b1, a0, a1, acc);
-    }
+        for (int c = 0; c < CBW; ++c)
+            wf[gi & 1][c] = *reinterpret_cast<const bf16x8 *>(stage + (((wm * CBW + c) * ROW + kw) * 2 + half) * 1024 + lane * 16);
+#pragma unroll
+        for (int s = 0; s < NSEG; ++s) bf[gi & 1][s] = *reinterpret_cast<const bf16x8 *>(stage + (boff[s][kw] ^ (half * 32)));
+    };
 
-    // epilogue: ReLU / mask, convert, 8-byte stores (4 channels of a voxel)
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) {
-        const int co = C * (c.cg * CB + cb);
-        uint16_t *obase = a.out;
-        int ocs = a.out_cs, oco = co;
-        if (a.out2 && co >= a.out_ca) { obase = a.out2; ocs = a.out2_cs; oco = co - a.out_ca; }
+    for (int i = 0; i < NS; ++i) fetch(i);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * L) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    read_group(lds, 0);
+    int cur = 0;
+    for (int k = k0; k < k1; ++k) {
+        const int nxt = cur + 1 == NS ? 0 : cur + 1;
+        const char *const stage = lds + cur * STAGE;
 #pragma unroll
-        for (int s = 0; s < VB; ++s) {
-            if (!ok[s]) continue;
-            uint16_t *o = obase + c.pv[s] * ocs + oco + 4 * c.hi;
-            const uint16_t *m = RELU == kMask ? a.mask + c.pv[s] * a.out_cs + co + 4 * c.hi : nullptr;
+        for (int gi = 0; gi < 2 * ROW; ++gi) {
+            if (gi + 1 < 2 * ROW) {
+                read_group(stage, gi + 1);
+            } else {
+                // every wave has read this step's last fragments (lgkmcnt) and the next step's loads have landed: those
+                // of the NS - 2 steps after it may stay in flight.  Behind the barrier this step's stage is free.
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * L) : "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                read_group(lds + nxt * STAGE, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (gi + 1 == 2 * ROW) fetch(cur);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float v0 = acc[cb][s][4 * q], v1 = acc[cb][s][4 * q + 1], v2 = acc[cb][s][4 * q + 2], v3 = acc[cb][s][4 * q + 3];
-                if (RELU == kRelu) {
-                    v0 = v0 < 0.f ? 0.f : v0; v1 = v1 < 0.f ? 0.f : v1;
-                    v2 = v2 < 0.f ? 0.f : v2; v3 = v3 < 0.f ? 0.f : v3;
-                }
-                uint2 pk = make_uint2(pack2(v0, v1), pack2(v2, v3));
-                if (RELU == kMask) {
-                    const uint2 mv = *reinterpret_cast<const uint2 *>(m + 8 * q);
-                    pk.x &= positive_halves(mv.x);
-                    pk.y &= positive_halves(mv.y);
-                }
-                *reinterpret_cast<uint2 *>(o + 8 * q) = pk;
+            for (int c = 0; c < CBW; ++c)
+#pragma unroll
+                for (int s = 0; s < NSEG; ++s)
+                    acc[c][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[gi & 1][c], bf[gi & 1][s], acc[c][s], 0, 0, 0);
+        }
+        cur = nxt;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the repeated loads
+
+    const int blk = cg * a.nvg + vg;
+#pragma unroll
+    for (int s = 0; s < NSEG; ++s) {
+        const OutVox o = out_vox(a, q0 + wn * 64 * VB + s * 32 + (lane & 31));
+#pragma unroll
+        for (int c = 0; c < CBW; ++c) {
+            if (a.nsplit == 1) {
+                finish(a, acc[c][s], cg * CBT + wm * CBW + c, hi, o);
+            } else {
+                float4 *p = a.part + part_index<CBW, VB>(a, split, blk, wave, c, s, lane);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    p[64 * q] = make_float4(acc[c][s][4 * q], acc[c][s][4 * q + 1], acc[c][s][4 * q + 2], acc[c][s][4 * q + 3]);
             }
         }
     }
+}
+
+// The splits' sums, added in order, and the epilogue: one thread per (unit of 16 channels, lane).
+template <int CBW, int VB>
+__global__ __launch_bounds__(kGemmThreads) void conv_gemm_join_kernel(GemmArgs a) {
+    constexpr int NSEG = 2 * VB;
+    const int lane = threadIdx.x & 63;
+    const long long unit = 4LL * blockIdx.x + (threadIdx.x >> 6);
+    if (unit >= 1LL * a.nblocks * kGemmWaves * CBW * NSEG) return;
+    int t = static_cast<int>(unit);
+    const int s = t % NSEG; t /= NSEG;
+    const int c = t % CBW; t /= CBW;
+    const int wave = t % kGemmWaves, blk = t / kGemmWaves;
+    const int cg = blk / a.nvg, vg = blk - cg * a.nvg, wm = wave & 1, wn = wave >> 1;
+    f32x16 sum;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) sum[e] = 0.f;
+#pragma unroll 4
+    for (int sp = 0; sp < a.nsplit; ++sp) {
+        const float4 *p = a.part + part_index<CBW, VB>(a, sp, blk, wave, c, s, lane);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 v = p[64 * q];
+            sum[4 * q] += v.x; sum[4 * q + 1] += v.y; sum[4 * q + 2] += v.z; sum[4 * q + 3] += v.w;
+        }
+    }
+    finish(a, sum, cg * 2 * CBW + wm * CBW + c, lane >> 5, out_vox(a, vg * wg_vox(VB) + wn * 64 * VB + s * 32 + (lane & 31)));
 }
 
 // largest output box of the grid
 struct Box { int ed, eh, ew; };
 Box max_box(const Geo &g) { return Box{g.td + 2 * grow_d(g), g.th + 2 * g.grow, g.tw + 2 * g.grow}; }
 
+struct GemmPlan { int cbw, vb, bl, nsplit, nvg, nblocks; long long nvox; };
+// records that 128 vb consecutive voxels touch at most, in wave loads of 16 per wave
+int record_loads(int vb, int ew) {
+    const int n = wg_vox(vb), rows = n % ew == 0 ? n / ew - 1 : (n + ew - 2) / ew;
+    return (n + 2 + 2 * rows + 63) / 64;
+}
+// Voxels per workgroup and splits of the K loop: what costs least in microseconds if 256 compute units take the workgroups
+// in rounds.  A step lasts about 0.3 us (its loads) + 0.35 us per 128 voxels x 64 channels, a workgroup about 6 us besides
+// (launch, first loads, stores); splitting adds a second launch and a write and a read of every sum at about 4 TB/s.  (With
+// the step taken 0.8 ... 3 times as long the networks differ by less than 0.5 %, with 0.5 times, i.e. fewer splits, they are
+// 1 % slower: what matters is a workgroup on every compute unit.)  The interior voxels alone decide, so that the order of
+// the sums is the same for every output box growth and tile grid.
+GemmPlan plan_gemm(const Geo &g, int ki, int ko) {
+    GemmPlan p;
+    const Box b = max_box(g);
+    p.nvox = 1LL * g.ntiles * b.ed * b.eh * b.ew;
+    const int nco = ko / C, nk = ki / C * (g.flat ? 3 : 9);
+    const long long nint = 1LL * g.ntiles * g.int_vox;
+    p.cbw = nco % 4 == 0 ? 2 : 1;
+    double best = 0;
+    for (int vb = 1; vb <= 2; ++vb) {
+        const long long tiles = (nint + wg_vox(vb) - 1) / wg_vox(vb) * (nco / (2 * p.cbw));
+        for (int s = 1; s == 1 || (s <= nk / 4 && s <= 64); ++s) {
+            const long long rounds = (tiles * s + 255) / 256;
+            const double us = rounds * ((nk + s - 1) / s * (0.3 + 0.35 * vb * p.cbw) + 6) +
+                              (s > 1 ? 4 + 8.0 * s * nint * ko / 4e6 : 0);
+            if ((vb == 1 && s == 1) || us < best) { best = us; p.vb = vb; p.nsplit = s; }
+        }
+    }
+    p.bl = record_loads(p.vb, b.ew);
+    if (p.vb == 2 && p.bl > 6) { p.vb = 1; p.bl = record_loads(1, b.ew); }
+    p.bl = p.vb == 2 ? (p.bl <= 5 ? 5 : 6) : (p.bl <= 3 ? 3 : (p.bl <= 4 ? 4 : 6));
+    p.nvg = static_cast<int>((p.nvox + wg_vox(p.vb) - 1) / wg_vox(p.vb));
+    p.nblocks = p.nvg * (nco / (2 * p.cbw));
+    return p;
+}
+
 }  // namespace
 
 // Layers this family takes over from the plane-marching kernels.  2-D variant (measured on 16 slices; marching ->
-// here, before this kernel's weight pieces left scratch memory): 512 channels on 32 x 32 voxels 0.37 -> 0.21 ms, 1024
+// here): 512 channels on 32 x 32 voxels 0.37 -> 0.21 ms, 1024
 // on 32 x 32 1.30 -> 0.70 ms, 1024 on 16 x 16 0.48 -> 0.37 ms; at 256 channels the marching kernels are as fast.  3-D:
 // the bottom level of a deep network only - 1024 channels on 16^3 voxels 0.80 -> 0.40 ms on a 2 x 2 x 1 grid and 1.01 ->
 // 0.39 ms on 4 x 4 x 1 (tiles of 4 x 4 x 16 voxels leave most of a marching patch empty; here every MFMA column is a real
@@ -311,12 +417,18 @@ bool conv_gemm_preferred(const Geo &g, int ki, int ko) {
     const long long nint = 1LL * g.ntiles * g.int_vox;
     const Box b = max_box(g);
     const long long nbox = 1LL * g.ntiles * b.ed * b.eh * b.ew;
-    if (ki < 512 || ki % (2 * C) != 0 || ko % (C * CB) != 0 || nbox >= (1LL << 30)) return false;
+    if (ki < 512 || ki % (2 * C) != 0 || ko % (C * 4) != 0 || nbox >= (1LL << 28)) return false;
     return nint <= (g.flat ? (1 << 16) : (1 << 13));
 }
 
-// wpack: the layer's weights in the fragment order of conv_mfma.hip (already packed, in the workspace).
-int launch_conv_gemm(const void *Pin, const void *wpack, const float *bias, void *Pout, const Geo &g, int ki, int ko,
+size_t conv_gemm_ws_bytes(const Geo &g, int ki, int ko) {
+    const GemmPlan p = plan_gemm(g, ki, ko);
+    return p.nsplit == 1 ? 0 : static_cast<size_t>(p.nsplit) * p.nvg * wg_vox(p.vb) * ko * sizeof(float);
+}
+
+// wpack: the layer's weights in the fragment order of conv_mfma.hip (already packed, in the workspace); part: the
+// conv_gemm_ws_bytes behind them.
+int launch_conv_gemm(const void *Pin, const void *wpack, void *part, const float *bias, void *Pout, const Geo &g, int ki, int ko,
                      bool relu, hipStream_t s, const void *mask, const ConvSplit *split) {
     GemmArgs a;
     a.in = static_cast<const uint16_t *>(Pin);
@@ -344,35 +456,55 @@ int launch_conv_gemm(const void *Pin, const void *wpack, const float *bias, void
     a.wpack = static_cast<const uint4 *>(wpack);
     a.bias = bias;
     a.mask = static_cast<const uint16_t *>(mask);
+    a.bits = nullptr;
+    a.part = static_cast<float4 *>(part);
     a.g = g;
     a.nci = ki / C;
     a.nco = ko / C;
+    a.nrows = g.flat ? 3 : 9;
     const Box b = max_box(g);
     a.ed = b.ed;
     a.eh = b.eh;
     a.ew = b.ew;
-    a.nvox = static_cast<int>(1LL * g.ntiles * b.ed * b.eh * b.ew);
-    a.dbox = make_fastdiv(static_cast<uint32_t>(b.ed * b.eh * b.ew));
-    a.dplane = make_fastdiv(static_cast<uint32_t>(b.eh * b.ew));
+    const GemmPlan p = plan_gemm(g, ki, ko);
+    a.nvox = static_cast<int>(p.nvox);
+    a.nsplit = p.nsplit;
+    a.nvg = p.nvg;
+    a.nblocks = p.nblocks;
+    a.epi = mask ? kMask : (relu ? kRelu : kNone);
+    a.gather = 0;
+    a.relu_keeps_nan = 1;
     a.drow = make_fastdiv(static_cast<uint32_t>(b.ew));
-    // 256 voxels per workgroup; 128 where that leaves at most half of the 256 compute units with a workgroup (the
-    // kernel is bound by its voxel-fragment loads, which then spread over twice the vector caches)
-    const int nvg2 = (a.nvox + wg_vox(2) - 1) / wg_vox(2);
-    const int vb = nvg2 * (a.nco / CB) <= 128 ? 1 : 2;
-    a.nvg = (a.nvox + wg_vox(vb) - 1) / wg_vox(vb);
-    a.nblocks = a.nvg * (a.nco / CB);
-    const unsigned grid = static_cast<unsigned>((a.nblocks + 7) / 8 * 8);
+    a.drec = make_fastdiv(static_cast<uint32_t>(b.ew + 2));
+    a.deh = make_fastdiv(static_cast<uint32_t>(b.eh));
+    a.ded = make_fastdiv(static_cast<uint32_t>(b.ed));
     using Kern = void (*)(GemmArgs);
-    // [3-D][segments per wave - 1][bias][epilogue]; a bias never comes with a mask
-#define SP3D_GEMM_TABLE(KD)                                                                                             \
-    {{{conv_gemm_kernel<kNone, false, 1, KD>, conv_gemm_kernel<kRelu, false, 1, KD>, conv_gemm_kernel<kMask, false, 1, KD>},  \
-      {conv_gemm_kernel<kNone, true, 1, KD>, conv_gemm_kernel<kRelu, true, 1, KD>, conv_gemm_kernel<kMask, false, 1, KD>}},   \
-     {{conv_gemm_kernel<kNone, false, 2, KD>, conv_gemm_kernel<kRelu, false, 2, KD>, conv_gemm_kernel<kMask, false, 2, KD>},  \
-      {conv_gemm_kernel<kNone, true, 2, KD>, conv_gemm_kernel<kRelu, true, 2, KD>, conv_gemm_kernel<kMask, false, 2, KD>}}}
-    static const Kern kern[2][2][2][3] = {SP3D_GEMM_TABLE(1), SP3D_GEMM_TABLE(3)};
-#undef SP3D_GEMM_TABLE
-    const int epi = mask ? kMask : (relu ? kRelu : kNone);
-    hipLaunchKernelGGL(kern[g.flat ? 0 : 1][vb - 1][bias ? 1 : 0][epi], dim3(grid), dim3(kThreads), LDS_BYTES, s, a);
+    // [output blocks per wave - 1][(voxels, record loads)]
+    static const Kern kern[2][5] = {{conv_gemm_kernel<1, 1, 3>, conv_gemm_kernel<1, 1, 4>, conv_gemm_kernel<1, 1, 6>,
+                                     conv_gemm_kernel<1, 2, 5>, conv_gemm_kernel<1, 2, 6>},
+                                    {conv_gemm_kernel<2, 1, 3>, conv_gemm_kernel<2, 1, 4>, conv_gemm_kernel<2, 1, 6>,
+                                     conv_gemm_kernel<2, 2, 5>, conv_gemm_kernel<2, 2, 6>}};
+    static const Kern join[2][2] = {{conv_gemm_join_kernel<1, 1>, conv_gemm_join_kernel<1, 2>},
+                                    {conv_gemm_join_kernel<2, 1>, conv_gemm_join_kernel<2, 2>}};
+    static const int bls[5] = {3, 4, 6, 5, 6};
+    // more than 64 KB of dynamic LDS has to be requested explicitly
+    static const hipError_t attr = [] {
+        for (int i = 0; i < 10; ++i) {
+            const int cbw = i / 5 + 1, bl = bls[i % 5];
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern[i / 5][i % 5]),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, stages(cbw, bl) * stage_bytes(cbw, bl));
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }();
+    if (attr != hipSuccess) return record_hip(attr);
+    const int shape = p.vb == 2 ? (p.bl == 5 ? 3 : 4) : (p.bl == 3 ? 0 : (p.bl == 4 ? 1 : 2));
+    const unsigned grid = static_cast<unsigned>((1LL * a.nblocks * a.nsplit + 7) / 8 * 8);
+    hipLaunchKernelGGL(kern[p.cbw - 1][shape], dim3(grid), dim3(kGemmThreads), stages(p.cbw, p.bl) * stage_bytes(p.cbw, p.bl), s, a);
+    int rc = record_hip(hipGetLastError());
+    if (rc != SP_OK || a.nsplit == 1) return rc;
+    const unsigned units = static_cast<unsigned>(a.nblocks) * kGemmWaves * p.cbw * 2 * p.vb;
+    hipLaunchKernelGGL(join[p.cbw - 1][p.vb - 1], dim3((units + 3) / 4), dim3(kGemmThreads), 0, s, a);
     return record_hip(hipGetLastError());
 }
 

@@ -545,7 +545,7 @@ static PatchPlan plan_patches(const Geo &g, int ki, int ko) {
 // and wave that stores results, dchunk planes x RH rows x 4 units x 1 KB (see part_unit)
 size_t conv_mfma_ws_bytes(const Geo &g, int ki, int ko) {
     size_t n = pack_bytes(ki, ko);
-    if (conv_gemm_preferred(g, ki, ko)) return n;      // one launch, sums stay in registers
+    if (conv_gemm_preferred(g, ki, ko)) return n + conv_gemm_ws_bytes(g, ki, ko);
     const PatchPlan p = plan_patches(g, ki, ko);
     const int launches = p.pairs ? ki / (2 * C) : ki / C;
     if (launches > 1)
@@ -581,7 +581,8 @@ int launch_conv_mfma(const void *Pin, const void *w, const float *bias, void *Po
     int rc = record_hip(hipGetLastError());
     if (rc != SP_OK) return rc;
     // wide layers on few voxels: one launch that keeps the sums in registers over all input channels
-    if (conv_gemm_preferred(g, ki, ko)) return launch_conv_gemm(Pin, ws, bias, Pout, g, ki, ko, relu, s, mask, split);
+    if (conv_gemm_preferred(g, ki, ko))
+        return launch_conv_gemm(Pin, ws, static_cast<char *>(ws) + pack_bytes(ki, ko), bias, Pout, g, ki, ko, relu, s, mask, split);
     ConvArgs a;
     a.in = static_cast<const uint16_t *>(Pin);
     a.bias = bias;

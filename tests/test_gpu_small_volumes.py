@@ -70,3 +70,20 @@ CHUNKS = [  # n, dhw, grid, cin, cout, flat
 @pytest.mark.parametrize("case", CHUNKS, ids=lambda c: "%dx%dx%d-%dto%d%s" % (c[1] + c[3:5] + ("-2d" if c[5] else "",)))
 def test_short_marches(case):
     three_passes(*case, seed=5100 + 10 * CHUNKS.index(case))
+
+
+GEMM = [  # wide layers: the implicit GEMM (conv_gemm.hip); dhw and grid set the row length its record loads are sized for
+    (1, (1, 1, 1), (1, 1, 1), 512, 512, 0),
+    (2, (3, 5, 1), (1, 1, 1), 512, 512, 0),         # rows of 1 voxel: 3 records per voxel
+    (1, (4, 6, 4), (2, 2, 2), 512, 512, 0),         # 2
+    (1, (3, 7, 3), (1, 1, 1), 576, 512, 0),         # 3; 18 input chunks
+    (1, (5, 6, 13), (1, 3, 1), 512, 512, 0),
+    (1, (2, 3, 70), (1, 1, 1), 512, 512, 0),
+    (3, (2, 10, 140), (1, 1, 1), 512, 512, 1),      # 2-D; rows longer than a tile of 128 voxels
+    (1, (16, 28, 28), (1, 4, 4), 512, 512, 1),      # 256 voxels per workgroup, rows of 7
+]
+
+
+@pytest.mark.parametrize("case", GEMM, ids=lambda c: "%dx%dx%d-%dto%d%s" % (c[1] + c[3:5] + ("-2d" if c[5] else "",)))
+def test_wide_layers_on_few_voxels(case):
+    three_passes(*case, seed=5300 + 10 * GEMM.index(case))
