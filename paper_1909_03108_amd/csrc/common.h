@@ -149,12 +149,16 @@ int launch_conv_mfma(const void *Pin, const void *w, const float *bias, void *Po
                      const void *mask = nullptr, const ConvSplit *split = nullptr, bool gather = false,
                      void *bits = nullptr);
 
-// wide layers on few voxels: output-stationary implicit GEMM on the packed weights (conv_gemm.hip);
-// launch_conv_mfma hands such layers over after packing
-bool conv_gemm_preferred(const Geo &g, int ki, int ko);
+// layers on few voxels: output-stationary implicit GEMM on the packed weights (conv_gemm.hip); launch_conv_mfma hands
+// the layers for which it is the faster family over after packing
+bool conv_gemm_supported(const Geo &g, int ki, int ko);
+double conv_gemm_us(const Geo &g, int ki, int ko);            // estimated time
+// the wide layers on the fewest voxels: served by this family alone, without gathered halos and one-bit masks
+bool conv_gemm_tensor_forms(const Geo &g, int ki, int ko);
 size_t conv_gemm_ws_bytes(const Geo &g, int ki, int ko);      // behind the packed weights
 int launch_conv_gemm(const void *Pin, const void *wpack, void *part, const float *bias, void *Pout, const Geo &g, int ki,
-                     int ko, bool relu, hipStream_t s, const void *mask, const ConvSplit *split);
+                     int ko, bool relu, bool dgrad, hipStream_t s, const void *mask, const ConvSplit *split, bool gather,
+                     void *bits);
 
 // single-input-channel first layer (conv_c1.hip)
 bool conv_c1_supported(const Geo &g, int cin, int cout, sp_dtype_t dt);

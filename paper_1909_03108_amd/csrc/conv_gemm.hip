@@ -366,18 +366,17 @@ __global__ __launch_bounds__(kGemmThreads) void conv_gemm_join_kernel(GemmArgs a
 struct Box { int ed, eh, ew; };
 Box max_box(const Geo &g) { return Box{g.td + 2 * grow_d(g), g.th + 2 * g.grow, g.tw + 2 * g.grow}; }
 
-struct GemmPlan { int cbw, vb, bl, nsplit, nvg, nblocks; long long nvox; };
+struct GemmPlan { int cbw, vb, bl, nsplit, nvg, nblocks; long long nvox; double us; };
 // records that 128 vb consecutive voxels touch at most, in wave loads of 16 per wave
 int record_loads(int vb, int ew) {
     const int n = wg_vox(vb), rows = n % ew == 0 ? n / ew - 1 : (n + ew - 2) / ew;
     return (n + 2 + 2 * rows + 63) / 64;
 }
 // Voxels per workgroup and splits of the K loop: what costs least in microseconds if 256 compute units take the workgroups
-// in rounds.  A step lasts about 0.3 us (its loads) + 0.35 us per 128 voxels x 64 channels, a workgroup about 6 us besides
-// (launch, first loads, stores); splitting adds a second launch and a write and a read of every sum at about 4 TB/s.  (With
-// the step taken 0.8 ... 3 times as long the networks differ by less than 0.5 %, with 0.5 times, i.e. fewer splits, they are
-// 1 % slower: what matters is a workgroup on every compute unit.)  The interior voxels alone decide, so that the order of
-// the sums is the same for every output box growth and tile grid.
+// in rounds.  Fitted to 352 measured layers (64 ... 1024 channels, 64 ... 1 million voxels, 2-D and 3-D; 10 % rms): a step
+// lasts 0.41 us per 128 voxels x 64 channels, a workgroup 10.7 us besides (launch, first loads, stores); splitting adds a
+// second launch and a write and a read of every sum at about 6 TB/s.  The interior voxels alone decide, so that the order
+// of the sums is the same for every output box growth and tile grid.
 GemmPlan plan_gemm(const Geo &g, int ki, int ko) {
     GemmPlan p;
     const Box b = max_box(g);
@@ -385,14 +384,13 @@ GemmPlan plan_gemm(const Geo &g, int ki, int ko) {
     const int nco = ko / C, nk = ki / C * (g.flat ? 3 : 9);
     const long long nint = 1LL * g.ntiles * g.int_vox;
     p.cbw = nco % 4 == 0 ? 2 : 1;
-    double best = 0;
+    p.us = 0;
     for (int vb = 1; vb <= 2; ++vb) {
         const long long tiles = (nint + wg_vox(vb) - 1) / wg_vox(vb) * (nco / (2 * p.cbw));
-        for (int s = 1; s == 1 || (s <= nk / 4 && s <= 64); ++s) {
+        for (int s = 1; s == 1 || (s <= nk / 4 && s <= 64 && tiles * s <= 1024); ++s) {
             const long long rounds = (tiles * s + 255) / 256;
-            const double us = rounds * ((nk + s - 1) / s * (0.3 + 0.35 * vb * p.cbw) + 6) +
-                              (s > 1 ? 4 + 8.0 * s * nint * ko / 4e6 : 0);
-            if ((vb == 1 && s == 1) || us < best) { best = us; p.vb = vb; p.nsplit = s; }
+            const double us = 4 + rounds * ((nk + s - 1) / s * 0.41 * vb * p.cbw + 10.7) + (s > 1 ? 2 + 8.0 * s * nint * ko / 6e6 : 0);
+            if ((vb == 1 && s == 1) || us < p.us) { p.us = us; p.vb = vb; p.nsplit = s; }
         }
     }
     p.bl = record_loads(p.vb, b.ew);
@@ -405,21 +403,18 @@ GemmPlan plan_gemm(const Geo &g, int ki, int ko) {
 
 }  // namespace
 
-// Layers this family takes over from the plane-marching kernels.  2-D variant (measured on 16 slices; marching ->
-// here): 512 channels on 32 x 32 voxels 0.37 -> 0.21 ms, 1024
-// on 32 x 32 1.30 -> 0.70 ms, 1024 on 16 x 16 0.48 -> 0.37 ms; at 256 channels the marching kernels are as fast.  3-D:
-// the bottom level of a deep network only - 1024 channels on 16^3 voxels 0.80 -> 0.40 ms on a 2 x 2 x 1 grid and 1.01 ->
-// 0.39 ms on 4 x 4 x 1 (tiles of 4 x 4 x 16 voxels leave most of a marching patch empty; here every MFMA column is a real
-// voxel), 512 -> 1024 0.37 -> 0.19 ms; on 32^3 voxels (512 channels) the two families are level (0.55 - 0.64 ms either way)
-// and on 64^3 the marching kernels win, because a staged plane feeds 27 taps there and 9 here.  The criterion looks
-// at the tile interiors only, so a layer is served by the same family whatever its output box growth.
-bool conv_gemm_preferred(const Geo &g, int ki, int ko) {
-    const long long nint = 1LL * g.ntiles * g.int_vox;
+bool conv_gemm_supported(const Geo &g, int ki, int ko) {
     const Box b = max_box(g);
-    const long long nbox = 1LL * g.ntiles * b.ed * b.eh * b.ew;
-    if (ki < 512 || ki % (2 * C) != 0 || ko % (C * 4) != 0 || nbox >= (1LL << 28)) return false;
-    return nint <= (g.flat ? (1 << 16) : (1 << 13));
+    // (records are numbered in 32 bits: up to three per voxel)
+    return ki % C == 0 && ko % (2 * C) == 0 && 1LL * g.ntiles * b.ed * b.eh * b.ew < (1LL << 28);
 }
+
+bool conv_gemm_tensor_forms(const Geo &g, int ki, int ko) {
+    return conv_gemm_supported(g, ki, ko) && ki >= 512 && ki % (2 * C) == 0 && ko % (4 * C) == 0 &&
+           1LL * g.ntiles * g.int_vox <= (g.flat ? (1 << 16) : (1 << 13));
+}
+
+double conv_gemm_us(const Geo &g, int ki, int ko) { return plan_gemm(g, ki, ko).us; }
 
 size_t conv_gemm_ws_bytes(const Geo &g, int ki, int ko) {
     const GemmPlan p = plan_gemm(g, ki, ko);
@@ -429,7 +424,7 @@ size_t conv_gemm_ws_bytes(const Geo &g, int ki, int ko) {
 // wpack: the layer's weights in the fragment order of conv_mfma.hip (already packed, in the workspace); part: the
 // conv_gemm_ws_bytes behind them.
 int launch_conv_gemm(const void *Pin, const void *wpack, void *part, const float *bias, void *Pout, const Geo &g, int ki, int ko,
-                     bool relu, hipStream_t s, const void *mask, const ConvSplit *split) {
+                     bool relu, bool dgrad, hipStream_t s, const void *mask, const ConvSplit *split, bool gather, void *bits) {
     GemmArgs a;
     a.in = static_cast<const uint16_t *>(Pin);
     a.in2 = nullptr;
@@ -456,7 +451,7 @@ int launch_conv_gemm(const void *Pin, const void *wpack, void *part, const float
     a.wpack = static_cast<const uint4 *>(wpack);
     a.bias = bias;
     a.mask = static_cast<const uint16_t *>(mask);
-    a.bits = nullptr;
+    a.bits = static_cast<uint16_t *>(bits);
     a.part = static_cast<float4 *>(part);
     a.g = g;
     a.nci = ki / C;
@@ -471,9 +466,9 @@ int launch_conv_gemm(const void *Pin, const void *wpack, void *part, const float
     a.nsplit = p.nsplit;
     a.nvg = p.nvg;
     a.nblocks = p.nblocks;
-    a.epi = mask ? kMask : (relu ? kRelu : kNone);
-    a.gather = 0;
-    a.relu_keeps_nan = 1;
+    a.epi = bits ? (dgrad ? kMaskBits : kReluBits) : (mask ? kMask : (relu ? kRelu : kNone));
+    a.gather = gather ? 1 : 0;
+    a.relu_keeps_nan = conv_gemm_tensor_forms(g, ki, ko) ? 1 : 0;
     a.drow = make_fastdiv(static_cast<uint32_t>(b.ew));
     a.drec = make_fastdiv(static_cast<uint32_t>(b.ew + 2));
     a.deh = make_fastdiv(static_cast<uint32_t>(b.eh));

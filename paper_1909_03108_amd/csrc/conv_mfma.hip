@@ -496,7 +496,7 @@ static size_t pack_bytes(int ki, int ko) {
 }
 
 // How a layer is cut into workgroups (the same for every launch of the layer).
-struct PatchPlan { int nh, nw, dchunk, nd; long long nblocks; bool pairs; int fold, fold_w; };
+struct PatchPlan { int nh, nw, dchunk, nd; long long nblocks; bool pairs; int fold, fold_w; };      // dchunk: a multiple of fold
 static PatchPlan plan_patches(const Geo &g, int ki, int ko) {
     PatchPlan p;
     const int nco = ko / C;
@@ -527,11 +527,11 @@ static PatchPlan plan_patches(const Geo &g, int ki, int ko) {
     // 32 -> 32 on 128^3 (512 workgroups of 16 planes -> 256 of 32) 117 -> 104 us.
     const int steps = (ed + p.fold - 1) / p.fold, over = (g.flat ? 16 : 4) + (p.pairs ? 4 : 2);
     int best = steps;
-    long long cost = 0;
-    for (int k = 1; k <= steps && (k == 1 || base * k <= 4096); ++k) {
+    long long cost = (base + 255) / 256 * (steps + over);
+    for (int k = 2; k <= steps && base * k <= 2048; ++k) {
         const int d = (steps + k - 1) / k;
-        const long long c = (base * ((steps + d - 1) / d) + 255) / 256 * (d + over);
-        if (k == 1 || c < cost) { cost = c; best = d; }
+        const int c = (static_cast<int>(base) * ((steps + d - 1) / d) + 255) / 256 * (d + over);
+        if (c < cost) { cost = c; best = d; }
     }
     const int dchunk = best * p.fold;
     p.dchunk = dchunk;
@@ -540,12 +540,39 @@ static PatchPlan plan_patches(const Geo &g, int ki, int ko) {
     return p;
 }
 
+// Which family serves a layer: the marching kernels of this file, or the implicit GEMM of conv_gemm.hip.  The marching
+// kernels reuse a staged plane for 27 (9) taps and win where the volume fills the chip with long marches; they lose where
+// a launch per pair of input chunks carries little work (few voxels, many channels), where stacks of slices are thin and
+// where patches are mostly empty.  Both times are estimated from what bounds them, marching: launches x (rounds of the
+// 256 compute units x (start + planes) + launch) + the partial sums between launches.  The constants are fitted to 352
+// layers measured with both families (64 ... 1024 channels, 64 ... 1 million voxels; 8 % and 10 % rms); choosing by the
+// estimates costs 0.8 % over the better family of each.  Measured, marching -> GEMM: 3-D 256 -> 256 channels on 4^3 53 ->
+// 21 us, on 16^3 79 -> 34, on 32^3 146 -> 122, 128 -> 128 on 28 x 44 x 52 96 -> 71, on 64^3 207 against 267 (stays);
+// 2-D 256 -> 256 on 16 x 64^2 152 -> 107, on 16 x 128^2 627 -> 398, 128 -> 128 on 2 x 256^2 173 -> 73, 64 -> 64 on
+// 16 x 256^2 142 against 254 (stays).  The estimate is that of the whole volume as one tile, so that a layer takes the
+// same family, and sums in the same order, on every tile grid and with every output box growth.
+static bool prefer_gemm(const Geo &g, int ki, int ko) {
+    if (!conv_gemm_supported(g, ki, ko)) return false;
+    if (conv_gemm_tensor_forms(g, ki, ko)) return true;
+    Geo v = g;
+    v.ntiles = g.n;
+    v.td = g.td * g.gd; v.th = g.th * g.gh; v.tw = g.tw * g.gw;
+    v.grow = 0;
+    const PatchPlan p = plan_patches(v, ki, ko);
+    const int launches = p.pairs ? ki / (2 * C) : ki / C;
+    const double rounds = static_cast<double>((p.nblocks + 255) / 256), planes = p.dchunk / p.fold;
+    const double sums = 8.0 * g.ntiles * g.int_vox * ko * (launches - 1);             // bytes written and read
+    const double us = g.flat ? 4 + launches * rounds * (6.6 + 1.4 * planes) + sums / 9.2e6
+                             : 4 + launches * (rounds * (5.7 + (p.pairs ? 2.5 : 2.0) * planes) + 4.5) + sums / 8.3e6;
+    return conv_gemm_us(g, ki, ko) < us;
+}
+
 // workspace: packed weight fragments, then (layers that need more than one launch: more than one input
 // chunk, or more than one pair of chunks when Cin is a multiple of 64) the fp32 partial sums: per workgroup
 // and wave that stores results, dchunk planes x RH rows x 4 units x 1 KB (see part_unit)
 size_t conv_mfma_ws_bytes(const Geo &g, int ki, int ko) {
     size_t n = pack_bytes(ki, ko);
-    if (conv_gemm_preferred(g, ki, ko)) return n + conv_gemm_ws_bytes(g, ki, ko);
+    if (prefer_gemm(g, ki, ko)) return n + conv_gemm_ws_bytes(g, ki, ko);
     const PatchPlan p = plan_patches(g, ki, ko);
     const int launches = p.pairs ? ki / (2 * C) : ki / C;
     if (launches > 1)
@@ -554,17 +581,17 @@ size_t conv_mfma_ws_bytes(const Geo &g, int ki, int ko) {
 }
 
 bool conv_mfma_gather_supported(const Geo &g, int ki, int ko, sp_dtype_t dt) {
-    // the marching kernels on a one-voxel margin, interiors only; per-lane offsets to the H / W neighbours (and
+    // one-voxel margins, interiors only, 3-D; in the marching kernels per-lane offsets to the H / W neighbours (and
     // their sum at an edge) must fit the 32-bit staging offsets
-    if (!conv_mfma_supported(g, ki, ko, dt) || g.halo != 1 || g.grow != 0 || g.flat || conv_gemm_preferred(g, ki, ko))
+    if (!conv_mfma_supported(g, ki, ko, dt) || g.halo != 1 || g.grow != 0 || g.flat || conv_gemm_tensor_forms(g, ki, ko))
         return false;
     const long long lim = ki % (2 * C) == 0 ? 0x3fffffffLL : 0x7fffffffLL;       // see conv_mfma_supported
     return static_cast<long long>(g.tile_vox) * (g.gw + 1) * (ki > ko ? ki : ko) < lim;
 }
 
 bool conv_mfma_bits_supported(const Geo &g, int ki, int ko, sp_dtype_t dt) {
-    // the 3-D marching kernels (the wide-layer GEMM form and the 2-D variant keep the mask tensor)
-    return conv_mfma_supported(g, ki, ko, dt) && !g.flat && !conv_gemm_preferred(g, ki, ko);
+    // the 3-D kernels (the widest layers on the fewest voxels and the 2-D variant keep the mask tensor)
+    return conv_mfma_supported(g, ki, ko, dt) && !g.flat && !conv_gemm_tensor_forms(g, ki, ko);
 }
 
 int launch_conv_mfma(const void *Pin, const void *w, const float *bias, void *Pout, const Geo &g,
@@ -580,9 +607,9 @@ int launch_conv_mfma(const void *Pin, const void *w, const float *bias, void *Po
                        s, static_cast<const uint16_t *>(w), static_cast<uint4 *>(ws), nci, nco, ntap, dgrad ? 1 : 0);
     int rc = record_hip(hipGetLastError());
     if (rc != SP_OK) return rc;
-    // wide layers on few voxels: one launch that keeps the sums in registers over all input channels
-    if (conv_gemm_preferred(g, ki, ko))
-        return launch_conv_gemm(Pin, ws, static_cast<char *>(ws) + pack_bytes(ki, ko), bias, Pout, g, ki, ko, relu, s, mask, split);
+    if (prefer_gemm(g, ki, ko))
+        return launch_conv_gemm(Pin, ws, static_cast<char *>(ws) + pack_bytes(ki, ko), bias, Pout, g, ki, ko, relu, dgrad, s,
+                                mask, split, gather, bits);
     ConvArgs a;
     a.in = static_cast<const uint16_t *>(Pin);
     a.bias = bias;

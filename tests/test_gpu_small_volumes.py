@@ -9,6 +9,8 @@ import torch
 from oracle import conv3d, flat as flat_oracle
 from paper_1909_03108_amd import sp3d, synth
 from gpu_util import DT, TOL, f64, rel_err, to_dev, widen
+from test_gpu_gather import test_gathered_halos_equal_exchange_then_convolve as check_gathered_halos
+from test_gpu_relu_bits import test_convolutions_write_and_read_the_bits as check_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -87,3 +89,71 @@ GEMM = [  # wide layers: the implicit GEMM (conv_gemm.hip); dhw and grid set the
 @pytest.mark.parametrize("case", GEMM, ids=lambda c: "%dx%dx%d-%dto%d%s" % (c[1] + c[3:5] + ("-2d" if c[5] else "",)))
 def test_wide_layers_on_few_voxels(case):
     three_passes(*case, seed=5300 + 10 * GEMM.index(case))
+
+
+NARROW_GEMM = [  # layers the implicit GEMM takes over from the marching kernels: one and two output blocks per wave,
+                 # input chunks odd in number, both voxel tiles, every count of record loads, one and several splits
+    (1, (4, 6, 1), (2, 2, 1), 128, 64, 0),
+    (1, (5, 6, 9), (1, 2, 3), 96, 192, 0),
+    (2, (8, 12, 14), (2, 2, 2), 160, 64, 0),
+    (1, (17, 24, 33), (1, 1, 1), 128, 64, 0),
+    (1, (3, 130, 70), (1, 1, 2), 192, 64, 1),
+    (1, (1, 96, 200), (1, 2, 1), 64, 128, 1),
+    (1, (2, 256, 182), (1, 2, 26), 128, 64, 1),     # rows of 7 voxels in tiles of 256
+    (1, (2, 256, 256), (1, 2, 2), 128, 128, 1),     # several workgroups per compute unit, no split
+]
+
+
+@pytest.mark.parametrize("case", NARROW_GEMM, ids=lambda c: "%dx%dx%d-%dto%d%s" % (c[1] + c[3:5] + ("-2d" if c[5] else "",)))
+def test_layers_taken_over_by_the_implicit_gemm(case):
+    three_passes(*case, seed=5500 + 10 * NARROW_GEMM.index(case))
+
+
+@pytest.mark.parametrize("n, dhw, grid, cin, cout", [(1, (4, 4, 4), (4, 2, 2), 128, 128), (2, (6, 5, 9), (2, 1, 3), 192, 64),
+                                                     (1, (12, 18, 10), (3, 3, 2), 128, 256)])
+def test_implicit_gemm_gathers_halos_and_keeps_bits(n, dhw, grid, cin, cout):
+    check_gathered_halos(n, dhw, grid, cin, cout)
+    check_bits(n, dhw, grid, cin, cout)
+
+
+def test_implicit_gemm_grown_boxes_and_two_tensors():
+    """A grown output box on margins two voxels wide, input and output in two tensors, at odd chunk counts: bit for bit
+    what the one-voxel margins, the concatenation and the single tensor give."""
+    n, dhw, grid, ca, cb, co, dt = 1, (8, 10, 14), (2, 2, 2), 96, 64, 192, DT["bf16"]
+    g1, g2 = sp3d.Geom(n, dhw, grid), sp3d.Geom(n, dhw, grid, 2, 1)
+    x = synth.normal_volume((n,) + dhw + (ca + cb,), 5700, "bf16")
+    dz = synth.normal_volume((n,) + dhw + (co,), 5701, "bf16")
+    w = to_dev(synth.weights(ca + cb, co, 5702, "bf16"))
+
+    def padded(g, v, c):
+        P = sp3d.alloc_padded(g, c, dt)
+        sp3d.sp_partition(to_dev(np.ascontiguousarray(v)), P, g, c, dt)
+        sp3d.sp_halo_exchange(P, g, c, dt)
+        return P
+
+    def volume(g, P, c):
+        V = torch.empty((n,) + dhw + (c,), dtype=torch.bfloat16, device="cuda")
+        sp3d.sp_unpartition(P, V, g, c, dt)
+        return V
+
+    res = []
+    for g in (g1, g2):
+        ws = sp3d.alloc_ws(max(sp3d.sp_workspace_bytes(op, g, ca + cb, co, dt) for op in (0, 1)))
+        P, Pa, Pb, Z = padded(g, x, ca + cb), padded(g, x[..., :ca], ca), padded(g, x[..., ca:], cb), padded(g, dz, co)
+        Y, Y2, D = (sp3d.alloc_padded(g, c, dt) for c in (co, co, ca + cb))
+        Da, Db = sp3d.alloc_padded(g, ca, dt), sp3d.alloc_padded(g, cb, dt)
+        sp3d.conv3d_fwd(P, w, None, Y, g, ca + cb, co, dt, sp3d.SP_FLAG_RELU, ws)
+        sp3d.conv3d_fwd2(Pa, ca, Pb, cb, w, None, Y2, g, co, dt, sp3d.SP_FLAG_RELU, ws)
+        sp3d.conv3d_dgrad(Z, w, D, g, ca + cb, co, dt, ws)
+        sp3d.conv3d_dgrad2(Z, w, Da, ca, Db, cb, g, co, dt, ws)
+        assert torch.equal(Y, Y2)
+        assert torch.equal(D[..., :ca], Da) and torch.equal(D[..., ca:], Db)
+        if g is g2:                                     # the surround holds what the neighbour computed for itself
+            E = Y.clone()
+            sp3d.sp_halo_exchange(E, g, co, dt)
+            inner = (slice(None),) * 4 + (slice(1, -1),) * 3
+            assert torch.equal(E[inner], Y[inner]) and bool((Y[inner] != 0).any())
+        res.append((volume(g, Y, co), volume(g, D, ca + cb)))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+    ref = conv3d.conv3d_fwd(x, widen(synth.weights(ca + cb, co, 5702, "bf16")), None, relu=True)
+    assert rel_err(f64(res[0][0]), ref) <= TOL["bf16"]
