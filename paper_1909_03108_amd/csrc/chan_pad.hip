@@ -72,7 +72,7 @@ size_t chan_pad_fwd_ws_bytes(const Geo &g, int cin, int cout) {
 
 size_t chan_pad_wgrad_ws_bytes(const Geo &g, int cin, int cout) {
     const int cp = padded_channels(cin);
-    return tensor_bytes(g, cp) + weight_bytes(g, cp, cout, 4) + wgrad_mfma_ws_bytes(g, cp, cout);
+    return tensor_bytes(g, cp) + weight_bytes(g, cp, cout, 4) + wgrad_mfma_ws_bytes(g, cp, cout, true);
 }
 
 static int pad_tensor(const void *Px, void *dst, const Geo &g, int cin, int cp, hipStream_t s) {
@@ -109,7 +109,7 @@ int launch_wgrad_chan_pad(const void *Px, const void *Pdz, float *dw, float *db,
     int rc = pad_tensor(Px, xp, g, cin, cp, s);
     if (rc != SP_OK) return rc;
     rc = launch_wgrad_mfma(shifted(static_cast<const void *>(xp), g, cp, dt), shifted(Pdz, g, cout, dt), dwp, db, g, cp,
-                           cout, inner, s);
+                           cout, inner, s, nullptr, 0, false, true);
     if (rc != SP_OK) return rc;
     const int total = taps_of(g) * cin * cout;
     hipLaunchKernelGGL(take_weight_rows_kernel, dim3((total + kThreads - 1) / kThreads), dim3(kThreads), 0, s, dwp, dw,

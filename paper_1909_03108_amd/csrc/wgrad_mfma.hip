@@ -832,10 +832,36 @@ bool wgrad_mfma_supported(const Geo &g, int cin, int cout, sp_dtype_t dt) {
     return base * g.td < 0x7fffffffLL && 1LL * g.ph * g.pw * (cin > cout ? cin : cout) < 0x7fffffffLL;
 }
 
-size_t wgrad_mfma_ws_bytes(const Geo &g, int cin, int cout) {
+// Which family serves a layer: the marching kernels of this file, or the GEMM over voxels of wgrad_gemm.hip.  The march
+// reuses a staged x plane for 27 taps and wins in 3-D where tiles are whole patches and the volume is large; it loses where
+// patches are mostly empty, where a workgroup per channel pair has only a plane or two to march over, and in 2-D with many
+// channels (9 taps per staged plane: its LDS reads bound it).  Both times are estimated, marching: rounds of the compute
+// units x items per workgroup x (start + planes), the partial results out and in, launches.  Fitted to 227 layers measured
+// with both families (64 ... 1024 channels, 64 ... 1 million voxels; 8 % and 7 % rms); choosing by the estimates costs
+// 0.3 % over the better family of each.  Measured, marching -> GEMM: 3-D 256 -> 256 channels on 4^3 35 -> 9 us, on 8^3
+// 40 -> 19, 64 -> 64 on 32^3 48 -> 31, 256 -> 256 there 118 against 193 (stays); 1024 -> 1024 on 16^3 498 -> 285; 2-D, 16
+// slices: 1024 -> 1024 on 16 x 16 276 -> 106, 512 -> 512 on 32 x 32 217 -> 135, 256 -> 256 on 128 x 128 516 -> 431, 64 ->
+// 64 there 38 against 61 (stays).
+static bool prefer_gemm(const Geo &g, int cin, int cout) {
+    if (!wgrad_gemm_supported(g, cin, cout)) return false;
     WgradArgs a;
     plan(g, cin, cout, &a);
-    return static_cast<size_t>(a.ngroups) * (taps_of(g) * C * C + C) * sizeof(float);
+    const bool dma = g.th % PH == 0 && g.tw % PW == 0;
+    const double plane = g.flat ? (dma ? 1.34 : 1.42) : (dma ? 2.5 : 2.36), start = g.flat ? (dma ? 1.35 : 0.27) : (dma ? 0.0 : 2.17);
+    const double rounds = (a.ngroups + kMaxGroups - 1) / kMaxGroups, items = (a.nitems + a.gpp - 1) / a.gpp;
+    const double planes = (a.dchunk + a.fold - 1) / a.fold + 2;
+    const double us = 8.3 + rounds * items * (start + planes * plane) + 8192.0 * a.ngroups * taps_of(g) / 3e6 + (a.gpp >= 8 ? 1 : 0);
+    return wgrad_gemm_us(g, cin, cout) < us;
+}
+
+size_t wgrad_mfma_ws_bytes(const Geo &g, int cin, int cout, bool march_only) {
+    WgradArgs a;
+    plan(g, cin, cout, &a);
+    const size_t n = static_cast<size_t>(a.ngroups) * (taps_of(g) * C * C + C) * sizeof(float);
+    if (march_only || !prefer_gemm(g, cin, cout)) return n;
+    // never less than the marching kernels ask for: what conv3d_wgrad_static refuses does not depend on the family
+    const size_t m = wgrad_gemm_ws_bytes(g, cin, cout);
+    return m > n ? m : n;
 }
 
 bool wgrad_mfma_gather_supported(const Geo &g, int cin, int cout, sp_dtype_t dt) {
@@ -846,8 +872,9 @@ bool wgrad_mfma_gather_supported(const Geo &g, int cin, int cout, sp_dtype_t dt)
 }
 
 int launch_wgrad_mfma(const void *Px, const void *Pdz, float *dw, float *db, const Geo &g, int cin, int cout,
-                      void *ws, hipStream_t s, const void *Px2, int ca, bool gather) {
+                      void *ws, hipStream_t s, const void *Px2, int ca, bool gather, bool march_only) {
     if (gather && !wgrad_mfma_gather_supported(g, cin, cout, SP_BF16)) return SP_EUNSUPPORTED;
+    if (!march_only && prefer_gemm(g, cin, cout)) return launch_wgrad_gemm(Px, Pdz, dw, db, g, cin, cout, ws, s, Px2, ca, gather);
     WgradArgs a;
     plan(g, cin, cout, &a);
     a.gather = gather ? 1 : 0;

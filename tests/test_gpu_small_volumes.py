@@ -157,3 +157,60 @@ def test_implicit_gemm_grown_boxes_and_two_tensors():
     assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
     ref = conv3d.conv3d_fwd(x, widen(synth.weights(ca + cb, co, 5702, "bf16")), None, relu=True)
     assert rel_err(f64(res[0][0]), ref) <= TOL["bf16"]
+
+
+WGRAD_GEMM = [  # weight gradients as a GEMM over voxels: both channel tiles, every count of record loads, one and several
+                # splits, stages that end inside a row, a slice and a tile, a last stage of 1 ... 63 voxels
+    (1, (3, 4, 2), (1, 2, 1), 64, 64, 0),           # rows of 2 voxels: 128 records a stage
+    (1, (2, 2, 3), (1, 1, 1), 128, 256, 0),         # fewer voxels than a stage
+    (2, (5, 6, 7), (1, 2, 1), 192, 64, 0),
+    (1, (8, 8, 8), (2, 2, 2), 128, 128, 0),         # rows of 4
+    (1, (9, 10, 33), (1, 1, 1), 64, 128, 0),
+    (1, (3, 20, 65), (1, 1, 1), 256, 128, 1),       # a last stage of 60 voxels
+    (1, (1, 9, 129), (1, 1, 1), 128, 128, 1),
+    (1, (5, 40, 24), (1, 4, 4), 320, 64, 1),
+]
+
+
+@pytest.mark.parametrize("case", WGRAD_GEMM, ids=lambda c: "%dx%dx%d-%dto%d%s" % (c[1] + c[3:5] + ("-2d" if c[5] else "",)))
+def test_weight_gradient_as_a_gemm(case):
+    three_passes(*case, seed=5900 + 10 * WGRAD_GEMM.index(case))
+
+
+def test_weight_gradient_gemm_gathers_and_takes_two_tensors():
+    check_gathered_halos(1, (4, 16, 64), (2, 2, 2), 64, 128)
+    check_gathered_halos(1, (2, 16, 32), (2, 2, 1), 128, 128)
+    n, dhw, grid, ca, cb, co, dt = 1, (4, 6, 10), (2, 2, 1), 32, 96, 64, DT["bf16"]
+    g = sp3d.Geom(n, dhw, grid)
+    x = synth.normal_volume((n,) + dhw + (ca + cb,), 6001, "bf16")
+    dz = synth.normal_volume((n,) + dhw + (co,), 6002, "bf16")
+    P = []
+    for v in (x, x[..., :ca], x[..., ca:], dz):
+        P.append(sp3d.alloc_padded(g, v.shape[-1], dt))
+        sp3d.sp_partition(to_dev(np.ascontiguousarray(v)), P[-1], g, v.shape[-1], dt)
+        sp3d.sp_halo_exchange(P[-1], g, v.shape[-1], dt)
+    ws = sp3d.alloc_ws(sp3d.sp_workspace_bytes(2, g, ca + cb, co, dt))
+    store = torch.zeros(2 * co + 1, device="cuda")
+    dw, dw2, db, db2 = torch.empty((3, 3, 3, ca + cb, co), device="cuda"), torch.empty((3, 3, 3, ca + cb, co), device="cuda"), \
+        store[1:co + 1], store[co + 1:]                 # (a bias gradient may lie at any multiple of four bytes)
+    sp3d.conv3d_wgrad(P[0], P[3], dw, db, g, ca + cb, co, dt, ws)
+    sp3d.conv3d_wgrad2(P[1], ca, P[2], cb, P[3], dw2, db2, g, co, dt, ws)
+    assert torch.equal(dw, dw2) and torch.equal(db, db2)
+    assert rel_err(f64(dw), conv3d.conv3d_wgrad(x, dz)) <= 1e-5 and rel_err(f64(db), conv3d.bias_grad(dz)) <= 1e-5
+
+
+def test_weight_gradient_of_an_infinite_voxel():
+    """The last stage's clamped voxels are masked in both operands: an infinity in the last voxel reaches only the taps
+    and channels that read it."""
+    g, dt = sp3d.Geom(1, (3, 5, 7), (1, 1, 1)), DT["bf16"]
+    x = synth.normal_volume((1, 3, 5, 7, 64), 6101, "bf16")
+    x[0, -1, -1, -1, 5] = 0x7f80                        # + infinity
+    dz = synth.normal_volume((1, 3, 5, 7, 64), 6102, "bf16")
+    Px, Pz = sp3d.alloc_padded(g, 64, dt), sp3d.alloc_padded(g, 64, dt)
+    sp3d.sp_partition(to_dev(x), Px, g, 64, dt)
+    sp3d.sp_partition(to_dev(dz), Pz, g, 64, dt)
+    dw = torch.zeros((3, 3, 3, 64, 64), device="cuda")
+    sp3d.conv3d_wgrad(Px, Pz, dw, None, g, 64, 64, dt, sp3d.alloc_ws(sp3d.sp_workspace_bytes(2, g, 64, 64, dt)))
+    hit = torch.zeros_like(dw, dtype=torch.bool)
+    hit[1:, 1:, 1:, 5] = True
+    assert torch.equal(torch.isinf(dw), hit) and not torch.isnan(dw).any()
