@@ -70,9 +70,18 @@ size_t chan_pad_fwd_ws_bytes(const Geo &g, int cin, int cout) {
     return tensor_bytes(g, cp) + weight_bytes(g, cp, cout, 2) + conv_mfma_ws_bytes(g, cp, cout);
 }
 
+// The padded copies share conv3d_wgrad_static's buffer with the partial results: where the faster cutting would not fit and
+// the one with the fewest partial results does, that one is taken.
+static WgradFamily wgrad_family(const Geo &g, int cin, int cout) {
+    const int cp = padded_channels(cin);
+    const size_t copies = tensor_bytes(g, cp) + weight_bytes(g, cp, cout, 4);
+    return copies + wgrad_mfma_ws_bytes(g, cp, cout, kMarch) > SP_STATIC_SCRATCH_BYTES &&
+           copies + wgrad_mfma_ws_bytes(g, cp, cout, kMarchCoarse) <= SP_STATIC_SCRATCH_BYTES ? kMarchCoarse : kMarch;
+}
+
 size_t chan_pad_wgrad_ws_bytes(const Geo &g, int cin, int cout) {
     const int cp = padded_channels(cin);
-    return tensor_bytes(g, cp) + weight_bytes(g, cp, cout, 4) + wgrad_mfma_ws_bytes(g, cp, cout, true);
+    return tensor_bytes(g, cp) + weight_bytes(g, cp, cout, 4) + wgrad_mfma_ws_bytes(g, cp, cout, wgrad_family(g, cin, cout));
 }
 
 static int pad_tensor(const void *Px, void *dst, const Geo &g, int cin, int cp, hipStream_t s) {
@@ -109,7 +118,7 @@ int launch_wgrad_chan_pad(const void *Px, const void *Pdz, float *dw, float *db,
     int rc = pad_tensor(Px, xp, g, cin, cp, s);
     if (rc != SP_OK) return rc;
     rc = launch_wgrad_mfma(shifted(static_cast<const void *>(xp), g, cp, dt), shifted(Pdz, g, cout, dt), dwp, db, g, cp,
-                           cout, inner, s, nullptr, 0, false, true);
+                           cout, inner, s, nullptr, 0, false, wgrad_family(g, cin, cout));
     if (rc != SP_OK) return rc;
     const int total = taps_of(g) * cin * cout;
     hipLaunchKernelGGL(take_weight_rows_kernel, dim3((total + kThreads - 1) / kThreads), dim3(kThreads), 0, s, dwp, dw,

@@ -170,14 +170,15 @@ int launch_wgrad_c1(const void *Px, const void *Pdz, float *dw, float *db, const
                     hipStream_t s);
 
 bool wgrad_mfma_supported(const Geo &g, int cin, int cout, sp_dtype_t dt);
-// march_only: for callers whose workspace bound is that of the marching kernels
-size_t wgrad_mfma_ws_bytes(const Geo &g, int cin, int cout, bool march_only = false);
+// For callers with a workspace bound of their own: the marching kernels only, and with the fewest partial results
+enum WgradFamily { kAnyFamily = 0, kMarch = 1, kMarchCoarse = 2 };
+size_t wgrad_mfma_ws_bytes(const Geo &g, int cin, int cout, WgradFamily family = kAnyFamily);
 // Px2 (optional): the input channels [ca, cin) live in a second tensor of cin - ca channels per voxel
 // gather: margin voxels of x that have a neighbour tile are read from that tile's interior (SP_HALO_GATHER)
 bool wgrad_mfma_gather_supported(const Geo &g, int cin, int cout, sp_dtype_t dt);
 int launch_wgrad_mfma(const void *Px, const void *Pdz, float *dw, float *db, const Geo &g,
                       int cin, int cout, void *ws, hipStream_t s, const void *Px2 = nullptr, int ca = 0,
-                      bool gather = false, bool march_only = false);
+                      bool gather = false, WgradFamily family = kAnyFamily);
 // layers of at least 64 channels as a GEMM over voxels (wgrad_gemm.hip); launch_wgrad_mfma hands the layers for which it
 // is the faster family over
 bool wgrad_gemm_supported(const Geo &g, int cin, int cout);

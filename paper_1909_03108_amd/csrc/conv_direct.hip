@@ -426,7 +426,7 @@ __global__ __launch_bounds__(256) void reduce_partials_wide_kernel(const float *
 }
 
 int launch_reduce_partials(const float *part, float *out, int nparts, long long n, hipStream_t s) {
-    if (nparts >= 512 && n <= 16384) {
+    if (nparts >= 32 && n <= 16384) {          // (a serial chain of 128 loads: about 60 us; a block per output: 4)
         hipLaunchKernelGGL(reduce_partials_wide_kernel, dim3(static_cast<unsigned>(n)), dim3(256), 0, s, part, out,
                            nparts, n);
         return record_hip(hipGetLastError());

@@ -746,7 +746,13 @@ __global__ __launch_bounds__(kThreads) void wgrad_mfma_dma_kernel(WgradArgs a) {
     if (tid < C) a.part_b[slot * C + tid] = red[tid] + red[C + tid];
 }
 
-void plan(const Geo &g, int cin, int cout, WgradArgs *a) {
+// Microseconds of one work item: its start and its planes (fitted, see prefer_gemm).
+double item_us(const Geo &g, int planes) {
+    const bool dma = g.th % PH == 0 && g.tw % PW == 0;
+    return (g.flat ? (dma ? 1.35 : 0.27) : (dma ? 0.0 : 2.17)) + planes * (g.flat ? (dma ? 1.34 : 1.42) : (dma ? 2.5 : 2.36));
+}
+
+void plan(const Geo &g, int cin, int cout, WgradArgs *a, bool coarse = false) {
     const int npairs = (cin / C) * (cout / C);
     a->x_cs = cin;
     a->dz_cs = cout;
@@ -756,8 +762,6 @@ void plan(const Geo &g, int cin, int cout, WgradArgs *a) {
     int gpp = kMaxGroups / npairs;                    // about one workgroup per CU in total
     if (gpp < 1) gpp = 1;
     const long long base = 1LL * g.ntiles * a->nh * a->nw;
-    int dchunk = g.td;
-    while (base * ((g.td + dchunk - 1) / dchunk) < gpp && dchunk > 16) dchunk = (dchunk + 1) / 2;
     // 2-D variant, tiles narrower than half a patch: up to 4 slices side by side in a staged plane; the tile's
     // slice count and the D chunk must be multiples of that number (only the register-staged kernel folds: such
     // tiles are never whole patches)
@@ -768,8 +772,27 @@ void plan(const Geo &g, int cin, int cout, WgradArgs *a) {
         if (f > 4) f = 4;
         while (f > 1 && g.td % f) --f;
         a->fold = f;
-        dchunk = (dchunk + f - 1) / f * f;
     }
+    // D chunk: what costs least if the gpp workgroups of a pair take the items in rounds - an item's start and its planes
+    // with the two of the surround - and every workgroup's partial result goes out and in at about 3 TB/s.  (Halved only
+    // until there was an item per workgroup, never below 16 planes, 32 -> 32 on 32^3 ran on 8 workgroups and 99 x 156 x 210
+    // on 1 x 2 x 2 tiles on two rounds of 52 planes instead of two of 35: 43 -> 19 us and 290 -> 211 us.)  `coarse`: that rule.
+    const int steps = (g.td + a->fold - 1) / a->fold;
+    int best = steps;
+    if (coarse) {
+        int d = g.td;
+        while (base * ((g.td + d - 1) / d) < gpp && d > 16) d = (d + 1) / 2;
+        best = (d + a->fold - 1) / a->fold;
+    } else {
+        double cost = 0;
+        for (int k = 1; k <= steps && (k == 1 || base * k <= 8LL * gpp); ++k) {
+            const int d = (steps + k - 1) / k;
+            const long long items = base * ((steps + d - 1) / d), groups = items < gpp ? items : gpp;
+            const double us = (items + groups - 1) / groups * item_us(g, d + 2) + 8192.0 * groups * npairs * taps_of(g) / 3e6;
+            if (k == 1 || us < cost) { cost = us; best = d; }
+        }
+    }
+    const int dchunk = best * a->fold;
     a->dchunk = dchunk;
     a->nd = (g.td + dchunk - 1) / dchunk;
     const long long items = base * a->nd;
@@ -846,19 +869,16 @@ static bool prefer_gemm(const Geo &g, int cin, int cout) {
     if (!wgrad_gemm_supported(g, cin, cout)) return false;
     WgradArgs a;
     plan(g, cin, cout, &a);
-    const bool dma = g.th % PH == 0 && g.tw % PW == 0;
-    const double plane = g.flat ? (dma ? 1.34 : 1.42) : (dma ? 2.5 : 2.36), start = g.flat ? (dma ? 1.35 : 0.27) : (dma ? 0.0 : 2.17);
     const double rounds = (a.ngroups + kMaxGroups - 1) / kMaxGroups, items = (a.nitems + a.gpp - 1) / a.gpp;
-    const double planes = (a.dchunk + a.fold - 1) / a.fold + 2;
-    const double us = 8.3 + rounds * items * (start + planes * plane) + 8192.0 * a.ngroups * taps_of(g) / 3e6 + (a.gpp >= 8 ? 1 : 0);
+    const double us = 8.3 + rounds * items * item_us(g, (a.dchunk + a.fold - 1) / a.fold + 2) + 8192.0 * a.ngroups * taps_of(g) / 3e6 + (a.gpp >= 8 ? 1 : 0);
     return wgrad_gemm_us(g, cin, cout) < us;
 }
 
-size_t wgrad_mfma_ws_bytes(const Geo &g, int cin, int cout, bool march_only) {
+size_t wgrad_mfma_ws_bytes(const Geo &g, int cin, int cout, WgradFamily family) {
     WgradArgs a;
-    plan(g, cin, cout, &a);
+    plan(g, cin, cout, &a, family == kMarchCoarse);
     const size_t n = static_cast<size_t>(a.ngroups) * (taps_of(g) * C * C + C) * sizeof(float);
-    if (march_only || !prefer_gemm(g, cin, cout)) return n;
+    if (family != kAnyFamily || !prefer_gemm(g, cin, cout)) return n;
     // never less than the marching kernels ask for: what conv3d_wgrad_static refuses does not depend on the family
     const size_t m = wgrad_gemm_ws_bytes(g, cin, cout);
     return m > n ? m : n;
@@ -872,11 +892,11 @@ bool wgrad_mfma_gather_supported(const Geo &g, int cin, int cout, sp_dtype_t dt)
 }
 
 int launch_wgrad_mfma(const void *Px, const void *Pdz, float *dw, float *db, const Geo &g, int cin, int cout,
-                      void *ws, hipStream_t s, const void *Px2, int ca, bool gather, bool march_only) {
+                      void *ws, hipStream_t s, const void *Px2, int ca, bool gather, WgradFamily family) {
     if (gather && !wgrad_mfma_gather_supported(g, cin, cout, SP_BF16)) return SP_EUNSUPPORTED;
-    if (!march_only && prefer_gemm(g, cin, cout)) return launch_wgrad_gemm(Px, Pdz, dw, db, g, cin, cout, ws, s, Px2, ca, gather);
+    if (family == kAnyFamily && prefer_gemm(g, cin, cout)) return launch_wgrad_gemm(Px, Pdz, dw, db, g, cin, cout, ws, s, Px2, ca, gather);
     WgradArgs a;
-    plan(g, cin, cout, &a);
+    plan(g, cin, cout, &a, family == kMarchCoarse);
     a.gather = gather ? 1 : 0;
     a.x = static_cast<const uint16_t *>(Px);
     a.x2 = static_cast<const uint16_t *>(Px2);

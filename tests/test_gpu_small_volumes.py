@@ -214,3 +214,37 @@ def test_weight_gradient_of_an_infinite_voxel():
     hit = torch.zeros_like(dw, dtype=torch.bool)
     hit[1:, 1:, 1:, 5] = True
     assert torch.equal(torch.isinf(dw), hit) and not torch.isnan(dw).any()
+
+
+FINE_WGRAD = [  # D chunks of the marching weight gradient: one and two planes, a shorter last one, whole and ragged patches,
+                # and behind zero-padded input channels
+    (1, (7, 8, 32), (1, 1, 1), 32, 32, 0),
+    (1, (22, 16, 64), (2, 1, 2), 32, 96, 0),
+    (1, (13, 9, 34), (1, 1, 1), 96, 32, 0),
+    (1, (11, 6, 40), (1, 2, 1), 3, 32, 0),
+    (1, (9, 12, 10), (1, 2, 1), 32, 32, 1),         # 2-D: slices side by side
+    (1, (6, 16, 96), (1, 2, 1), 5, 64, 1),
+]
+
+
+@pytest.mark.parametrize("case", FINE_WGRAD, ids=lambda c: "%dx%dx%d-%dto%d%s" % (c[1] + c[3:5] + ("-2d" if c[5] else "",)))
+def test_short_weight_gradient_marches(case):
+    three_passes(*case, seed=6200 + 10 * FINE_WGRAD.index(case))
+
+
+@pytest.mark.parametrize("edge", [20, 40, 64])
+def test_static_scratch_takes_padded_layers(edge):
+    """Zero-padded layers share the library's own buffer between the copies and the partial results: the same bits as with
+    a workspace, whichever cutting the sizes allow."""
+    g, dt = sp3d.Geom(1, (edge,) * 3, (1, 1, 1)), DT["bf16"]
+    x, dz = (synth.normal_volume((1,) + (edge,) * 3 + (c,), 6300 + c, "bf16") for c in (3, 32))
+    Px, Pz = sp3d.alloc_padded(g, 3, dt), sp3d.alloc_padded(g, 32, dt)
+    sp3d.sp_partition(to_dev(x), Px, g, 3, dt)
+    sp3d.sp_partition(to_dev(dz), Pz, g, 32, dt)
+    need = sp3d.sp_workspace_bytes(2, g, 3, 32, dt)
+    assert need <= sp3d.SP_STATIC_SCRATCH_BYTES
+    a, b = torch.empty((3, 3, 3, 3, 32), device="cuda"), torch.empty((3, 3, 3, 3, 32), device="cuda")
+    sp3d.conv3d_wgrad(Px, Pz, a, None, g, 3, 32, dt, sp3d.alloc_ws(need))
+    sp3d.conv3d_wgrad_static(Px, Pz, b, None, g, 3, 32, dt)
+    assert torch.equal(a, b)
+    assert rel_err(f64(a), conv3d.conv3d_wgrad(x, dz)) <= 1e-5
