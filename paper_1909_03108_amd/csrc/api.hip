@@ -295,6 +295,8 @@ static int fwd_impl(const void *Px, const void *w, const float *bias, void *Py, 
     if (!conv_c1_supported(o, cin, cout, dt) && chan_pad_supported(o, cin, cout, dt)) {
         const size_t need = chan_pad_fwd_ws_bytes(o, cin, cout);
         if (!ws || ws_bytes < need || !aligned16(ws)) return SP_EWORKSPACE;
+        // (the few-channel kernel needs no copies; what the call asks of its caller does not depend on the kernel)
+        if (conv_few_supported(o, cin, cout, dt)) return launch_conv_few(Px, w, bias, Py, o, cin, cout, relu, s);
         return launch_conv_chan_pad_fwd(Px, w, bias, Py, o, cin, cout, relu, ws, s);
     }
     return launch_conv_direct(Px, w, bias, Py, o, cin, cout, dt, relu, false, s);

@@ -187,6 +187,11 @@ size_t wgrad_gemm_ws_bytes(const Geo &g, int cin, int cout);
 int launch_wgrad_gemm(const void *Px, const void *Pdz, float *dw, float *db, const Geo &g, int cin, int cout, void *ws,
                       hipStream_t s, const void *Px2, int ca, bool gather);
 
+// forward pass of a first layer with 2 ... 8 input channels (conv_few.hip)
+bool conv_few_supported(const Geo &g, int cin, int cout, sp_dtype_t dt);
+int launch_conv_few(const void *Px, const void *w, const float *bias, void *Py, const Geo &g, int cin, int cout, bool relu,
+                    hipStream_t s);
+
 // few input channels (not a multiple of 32) on the matrix cores through zero-padded copies (chan_pad.hip)
 bool chan_pad_supported(const Geo &g, int cin, int cout, sp_dtype_t dt);
 size_t chan_pad_fwd_ws_bytes(const Geo &g, int cin, int cout);

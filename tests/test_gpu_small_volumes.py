@@ -248,3 +248,53 @@ def test_static_scratch_takes_padded_layers(edge):
     sp3d.conv3d_wgrad_static(Px, Pz, b, None, g, 3, 32, dt)
     assert torch.equal(a, b)
     assert rel_err(f64(a), conv3d.conv3d_wgrad(x, dz)) <= 1e-5
+
+
+FEW = [  # first layers of 2 ... 8 channels: both record sizes, odd channel counts, bricks that stick out, several output blocks
+    (1, (1, 1, 1), (1, 1, 1), 2, 32, 0),
+    (2, (5, 6, 34), (1, 2, 1), 3, 64, 0),
+    (1, (9, 10, 66), (1, 2, 2), 4, 32, 0),
+    (1, (4, 9, 31), (2, 1, 1), 5, 96, 0),
+    (1, (10, 13, 40), (1, 1, 1), 8, 32, 0),
+    (1, (3, 8, 50), (1, 2, 1), 3, 32, 1),
+    (1, (7, 10, 36), (1, 2, 2), 7, 64, 1),
+    (1, (1, 200, 210), (1, 1, 1), 5, 32, 1),        # several bricks per workgroup
+]
+
+
+@pytest.mark.parametrize("case", FEW, ids=lambda c: "%dx%dx%d-%dto%d%s" % (c[1] + c[3:5] + ("-2d" if c[5] else "",)))
+def test_first_layers_of_few_channels(case):
+    three_passes(*case, seed=6400 + 10 * FEW.index(case))
+
+
+def test_few_channels_grown_box_and_infinities():
+    """A grown output box gives what the neighbour computes for itself; an infinite voxel reaches only the outputs that
+    read it (unused K slots are zero in both operands)."""
+    n, dhw, grid, ci, co, dt = 1, (8, 10, 70), (2, 2, 2), 3, 32, DT["bf16"]
+    x = synth.normal_volume((n,) + dhw + (ci,), 6501, "bf16")
+    w = to_dev(synth.weights(ci, co, 6502, "bf16"))
+    out = []
+    for g in (sp3d.Geom(n, dhw, grid), sp3d.Geom(n, dhw, grid, 2, 1)):
+        P, Y = sp3d.alloc_padded(g, ci, dt), sp3d.alloc_padded(g, co, dt)
+        sp3d.sp_partition(to_dev(x), P, g, ci, dt)
+        sp3d.sp_halo_exchange(P, g, ci, dt)
+        sp3d.conv3d_fwd(P, w, None, Y, g, ci, co, dt, 0, sp3d.alloc_ws(sp3d.sp_workspace_bytes(0, g, ci, co, dt)))
+        V = torch.empty((n,) + dhw + (co,), dtype=torch.bfloat16, device="cuda")
+        sp3d.sp_unpartition(Y, V, g, co, dt)
+        out.append(V)
+    E = Y.clone()
+    sp3d.sp_halo_exchange(E, g, co, dt)
+    inner = (slice(None),) * 4 + (slice(1, -1),) * 3
+    assert torch.equal(E[inner], Y[inner]) and torch.equal(out[0], out[1])
+    g = sp3d.Geom(1, (5, 6, 33), (1, 1, 1))
+    x = synth.normal_volume((1, 5, 6, 33, ci), 6503, "bf16")
+    x[0, -1, -1, -1, 0] = 0x7f80                        # + infinity
+    w = to_dev(np.where(widen(synth.weights(ci, co, 6504, "bf16")) == 0, np.uint16(0x3f80), synth.weights(ci, co, 6504, "bf16")))
+    P, Y = sp3d.alloc_padded(g, ci, dt), sp3d.alloc_padded(g, co, dt)
+    sp3d.sp_partition(to_dev(x), P, g, ci, dt)
+    sp3d.conv3d_fwd(P, w, None, Y, g, ci, co, dt, 0, sp3d.alloc_ws(sp3d.sp_workspace_bytes(0, g, ci, co, dt)))
+    V = torch.empty((1, 5, 6, 33, co), dtype=torch.bfloat16, device="cuda")
+    sp3d.sp_unpartition(Y, V, g, co, dt)
+    near = torch.zeros((1, 5, 6, 33, 1), dtype=torch.bool, device="cuda")
+    near[0, -2:, -2:, -2:] = True
+    assert torch.equal(torch.isinf(V), near.expand_as(V)) and not torch.isnan(V).any()
