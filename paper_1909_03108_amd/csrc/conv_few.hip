@@ -9,8 +9,9 @@
 // fragments of its 32 output channels stay in registers over all the bricks it visits.  Records are 8 or 16 bytes: 20 KB
 // of LDS at most, several workgroups per compute unit hide each other's loads.
 // What bounds it: the staging's 2-byte loads and their latency, then the stores of the result (HBM).
-// Measured, zero-padded copies -> this kernel: 3 -> 32 channels on 99 x 156 x 210 270 -> 144 us (its 227 MB: 35 us), 5 -> 32
-// on 16 slices of 512 x 512 320 -> 118 us.
+// Measured, zero-padded copies -> this kernel with the loads of a brick waited for in place: 3 -> 32 channels on 99 x 156 x
+// 210 270 -> 144 us (its 227 MB: 35 us), 5 -> 32 on 16 slices of 512 x 512 320 -> 118 us.  With a brick's records on their
+// way during the products of the one before it, that 3-D level (both layers, forward and backward) 1360 -> 1324 us.
 #include "conv_mfma_common.h"
 
 namespace sp3d {
@@ -26,7 +27,7 @@ struct FewArgs {
     const float *bias;
     uint16_t *out;
     Geo g;
-    int cin, cout, relu;
+    int cout, relu;
     int nd, nh, nw, nbricks;     // bricks that cover the largest output box, per axis and over all tiles
 };
 
@@ -35,10 +36,11 @@ template <> struct Rec<4> { typedef uint32_t type __attribute__((ext_vector_type
 template <> struct Rec<8> { typedef uint32_t type __attribute__((ext_vector_type(4))); };
 union FewFrag { uint32_t w[4]; bf16x8 v; };
 
-template <int CS, int KD>
+template <int CIN, int KD>
 __global__ __launch_bounds__(kFewThreads) void conv_few_kernel(FewArgs a) {
     constexpr int OD = KD / 2, RD = BD + 2 * OD, RH_ = BH + 2, RW = BW + 2, NREC = RD * RH_ * RW;
-    constexpr int NR = 3 * KD, NM = CS / 4;          // kernel rows; MFMAs per row
+    constexpr int CS = CIN <= 4 ? 4 : 8, NR = 3 * KD, NM = CS / 4;      // channels of a record; kernel rows; MFMAs per row
+    constexpr int PER = (NREC + kFewThreads - 1) / kFewThreads, NV = CIN % 2 ? CIN : CIN / 2;   // records per thread, loads per record
     typedef typename Rec<CS>::type rec_t;
     __shared__ rec_t recs[NREC];
     const Geo &g = a.g;
@@ -58,7 +60,7 @@ __global__ __launch_bounds__(kFewThreads) void conv_few_kernel(FewArgs a) {
                 for (int i = 0; i < 2; ++i) {
                     const int k = 16 * m + 8 * hi + 2 * e2 + i, kw = k / CS, c = k % CS;
                     v[i] = 0;
-                    if (kw < 3 && c < a.cin) v[i] = a.w[(static_cast<size_t>(3 * r + kw) * a.cin + c) * a.cout + co0 + col];
+                    if (kw < 3 && c < CIN) v[i] = a.w[(static_cast<size_t>(3 * r + kw) * CIN + c) * a.cout + co0 + col];
                 }
                 wf[r][m].w[e2] = v[0] | (v[1] << 16);
             }
@@ -66,29 +68,64 @@ __global__ __launch_bounds__(kFewThreads) void conv_few_kernel(FewArgs a) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) init[e] = a.bias ? a.bias[co0 + 8 * (e >> 2) + 4 * hi + (e & 3)] : 0.f;
 
-    for (int brick = blockIdx.x; brick < a.nbricks; brick += gridDim.x) {
+    struct Pos { TileBox bx; long long base; int d0, h0, w0; };
+    auto pos_of = [&](int brick) {
+        Pos p;
         int t = brick;
-        const int w0 = (t % a.nw) * BW; t /= a.nw;
-        const int h0 = (t % a.nh) * BH; t /= a.nh;
-        const int d0 = (t % a.nd) * BD; t /= a.nd;
-        const TileBox bx = tile_box(g, t);
-        if (d0 >= bx.bd || h0 >= bx.bh || w0 >= bx.bw) continue;      // (workgroup-uniform)
-        const long long base = static_cast<long long>(t) * g.tile_vox + bx.org;
-        __syncthreads();                              // everybody is done with the previous brick
-        for (int rec = threadIdx.x; rec < NREC; rec += kFewThreads) {
+        p.w0 = (t % a.nw) * BW; t /= a.nw;
+        p.h0 = (t % a.nh) * BH; t /= a.nh;
+        p.d0 = (t % a.nd) * BD; t /= a.nd;
+        p.bx = tile_box(g, t);
+        p.base = static_cast<long long>(t) * g.tile_vox + p.bx.org;
+        return p;
+    };
+    // next brick of this workgroup that its tile's box reaches (nbricks: none)
+    auto next = [&](int brick, Pos *p) {
+        for (; brick < a.nbricks; brick += gridDim.x) {
+            *p = pos_of(brick);
+            if (p->d0 < p->bx.bd && p->h0 < p->bx.bh && p->w0 < p->bx.bw) break;
+        }
+        return brick;
+    };
+    // The records of a brick, on their way from memory while the brick before it is computed.  Even channel counts are
+    // loaded two values at a time (a record starts at a multiple of four bytes).
+    uint32_t raw[PER][NV];
+    auto load = [&](const Pos &p) {
+#pragma unroll
+        for (int n = 0; n < PER; ++n) {
             // records beyond what the box's own voxels read are moved to the nearest one inside: they reach no result
+            const int rec = min(static_cast<int>(threadIdx.x) + n * kFewThreads, NREC - 1);
             const int i = rec / (RH_ * RW), j = rec / RW % RH_, k = rec % RW;
-            const int d = min(d0 + i - OD, bx.bd - 1 + OD), h = min(h0 + j - 1, bx.bh), w = min(w0 + k - 1, bx.bw);
-            const uint16_t *src = a.in + (base + (1LL * (d + 1) * g.ph + h + 1) * g.pw + w + 1) * a.cin;
+            const int d = min(p.d0 + i - OD, p.bx.bd - 1 + OD), h = min(p.h0 + j - 1, p.bx.bh), w = min(p.w0 + k - 1, p.bx.bw);
+            const uint16_t *src = a.in + (p.base + (1LL * (d + 1) * g.ph + h + 1) * g.pw + w + 1) * CIN;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) raw[n][v] = CIN % 2 ? src[v] : reinterpret_cast<const uint32_t *>(src)[v];
+        }
+    };
+
+    Pos p;
+    int brick = next(blockIdx.x, &p);
+    if (brick >= a.nbricks) return;
+    load(p);
+    while (brick < a.nbricks) {
+        __syncthreads();                              // everybody is done with the previous brick
+#pragma unroll
+        for (int n = 0; n < PER; ++n) {
             rec_t v;
 #pragma unroll
             for (int c = 0; c < CS; c += 2) {
-                const uint32_t lo = c < a.cin ? src[c] : 0u, hv = c + 1 < a.cin ? src[c + 1] : 0u;
-                v[c / 2] = lo | (hv << 16);
+                const uint32_t lo = c < CIN ? raw[n][c % NV] : 0u, hv = c + 1 < CIN ? raw[n][(c + 1) % NV] : 0u;
+                v[c / 2] = CIN % 2 ? lo | (hv << 16) : (c < CIN ? raw[n][(c / 2) % NV] : 0u);
             }
-            recs[rec] = v;
+            if (threadIdx.x + n * kFewThreads < NREC) recs[threadIdx.x + n * kFewThreads] = v;
         }
+        const Pos now = p;
+        brick = next(brick + gridDim.x, &p);
+        const TileBox &bx = now.bx;
+        const long long base = now.base;
+        const int d0 = now.d0, h0 = now.h0, w0 = now.w0;
         __syncthreads();
+        if (brick < a.nbricks) load(p);
         const int d = d0 + wave;
         if (d >= bx.bd) continue;                     // (wave-uniform; the barriers are at the top of the loop)
 #pragma unroll
@@ -151,7 +188,7 @@ int launch_conv_few(const void *Px, const void *w, const float *bias, void *Py, 
     a.bias = bias;
     a.out = static_cast<uint16_t *>(Py);
     a.g = g;
-    a.cin = cin; a.cout = cout; a.relu = relu;
+    a.cout = cout; a.relu = relu;
     a.nd = (g.td + 2 * grow_d(g) + BD - 1) / BD;
     a.nh = (g.th + 2 * g.grow + BH - 1) / BH;
     a.nw = (g.tw + 2 * g.grow + BW - 1) / BW;
@@ -160,8 +197,11 @@ int launch_conv_few(const void *Px, const void *w, const float *bias, void *Py, 
     const int nco = cout / C, most = nco >= 1024 ? 1 : 1024 / nco, rounds = (a.nbricks + most - 1) / most;
     const dim3 grid((a.nbricks + rounds - 1) / rounds, nco);
     using Kern = void (*)(FewArgs);
-    static const Kern kern[2][2] = {{conv_few_kernel<4, 3>, conv_few_kernel<4, 1>}, {conv_few_kernel<8, 3>, conv_few_kernel<8, 1>}};
-    hipLaunchKernelGGL(kern[cin > 4][g.flat], grid, dim3(kFewThreads), 0, s, a);
+    static const Kern kern[7][2] = {{conv_few_kernel<2, 3>, conv_few_kernel<2, 1>}, {conv_few_kernel<3, 3>, conv_few_kernel<3, 1>},
+                                    {conv_few_kernel<4, 3>, conv_few_kernel<4, 1>}, {conv_few_kernel<5, 3>, conv_few_kernel<5, 1>},
+                                    {conv_few_kernel<6, 3>, conv_few_kernel<6, 1>}, {conv_few_kernel<7, 3>, conv_few_kernel<7, 1>},
+                                    {conv_few_kernel<8, 3>, conv_few_kernel<8, 1>}};
+    hipLaunchKernelGGL(kern[cin - 2][g.flat], grid, dim3(kFewThreads), 0, s, a);
     return record_hip(hipGetLastError());
 }
 
