@@ -179,6 +179,8 @@ bool wgrad_mfma_gather_supported(const Geo &g, int cin, int cout, sp_dtype_t dt)
 int launch_wgrad_mfma(const void *Px, const void *Pdz, float *dw, float *db, const Geo &g,
                       int cin, int cout, void *ws, hipStream_t s, const void *Px2 = nullptr, int ca = 0,
                       bool gather = false, WgradFamily family = kAnyFamily);
+// partial results per channel pair of the marching kernels' coarsest cutting
+int wgrad_march_groups(const Geo &g, int cin, int cout);
 // layers of at least 64 channels as a GEMM over voxels (wgrad_gemm.hip); launch_wgrad_mfma hands the layers for which it
 // is the faster family over
 bool wgrad_gemm_supported(const Geo &g, int cin, int cout);

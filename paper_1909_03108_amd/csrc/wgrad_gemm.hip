@@ -19,8 +19,8 @@
 // What bounds it: LDS reads - 20 transposing reads (10 KB) per wave and 24 MFMAs, 104 of the 128 bytes per clock when the
 // matrix cores are full - and for few voxels the launches.  (Four waves of 64 x 64 channels read less but need 192
 // accumulators: the compiler then moved them between the halves of the register file in every stage, 450 TFLOP/s.)
-// Measured: 1024 -> 1024 channels, 2-D, 16 slices of 32 x 32: 372 us, 0.83 PFLOP/s (marching 850); 256 -> 256, 128 x 128:
-// 431 us, 0.72 PFLOP/s; 64 -> 64 on 32^3 31 us.
+// Measured: 1024 -> 1024 channels, 2-D, 16 slices of 32 x 32 425 us, 0.73 PFLOP/s (marching 850; with one running sum over all
+// products 376 us, see STAGED); 512 -> 512 there 140 us (one running sum; marching 219); 64 -> 64 on 32^3 32 us (marching 48).
 #include "common.h"
 
 #include <type_traits>
@@ -77,7 +77,9 @@ __device__ __forceinline__ s16x4 tr_read(const char *p) {
 }
 union Frag { struct { s16x4 lo, hi; } s; u32x4 w; bf16x8 v; };
 
-template <int T, int LX, bool GATHER>
+// STAGED: the products of a stage are summed from zero and then added to the running sums, which are rounded once per stage
+// instead of eight times per instruction (an MFMA adds its 32 products four at a time).
+template <int T, int LX, bool GATHER, bool STAGED>
 __global__ __launch_bounds__(128 * T, T / 2) void wgrad_gemm_kernel(WgradGemmArgs a) {
     constexpr int NI = 2, NJ = T;                    // blocks of 16 input and output channels per wave: 32 x 16 T
     constexpr int NS = stages(T, LX), STAGE = stage_bytes(T, LX), ZOFF = T * LX * 1024;
@@ -105,7 +107,7 @@ __global__ __launch_bounds__(128 * T, T / 2) void wgrad_gemm_kernel(WgradGemmArg
     // Table of stage s, one entry per thread: threads [0, 16 LX) the x records, [128, 192) the dz voxels.  The two are one
     // computation on different numbers (record numbers in rows of tw + 2, tap (kd, kh), column w; voxel numbers in rows of
     // tw, centre, column w + 1), and threads without an entry write a spare word: no branch in the loop.
-    const bool zthread = tid >= 128;
+    const bool zthread = wave >= 2;
     const Div31 &dw0 = a.drec, &dw1 = a.drow;
     const uint32_t fm = zthread ? dw1.m : dw0.m, fs = zthread ? dw1.shift : dw0.shift;
     const int fw = zthread ? g.tw : g.tw + 2, centre = zthread ? pplane + prow + 1 : kd * pplane + kh * prow;
@@ -159,7 +161,8 @@ __global__ __launch_bounds__(128 * T, T / 2) void wgrad_gemm_kernel(WgradGemmArg
         return tr_read(st + (wj * (NJ / 2) + (n >> 1)) * (LZ * 1024) + (base ^ ((n & 1) << 5)));
     };
 
-    f32x4 acc[3][NI][NJ], accb[NJ];
+    f32x4 acc[3][NI][NJ];
+    double accb[NJ];
 #pragma unroll
     for (int t = 0; t < 3; ++t)
 #pragma unroll
@@ -167,7 +170,8 @@ __global__ __launch_bounds__(128 * T, T / 2) void wgrad_gemm_kernel(WgradGemmArg
 #pragma unroll
             for (int j = 0; j < NJ; ++j) acc[t][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) accb[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NJ; ++j) accb[j] = 0.0;
+    const f32x4 zero{0.f, 0.f, 0.f, 0.f};
     Frag ones;
     ones.w = u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
     const bool bias_wave = a.bias && r == 0 && ti == 0 && wi == 0;
@@ -190,8 +194,8 @@ __global__ __launch_bounds__(128 * T, T / 2) void wgrad_gemm_kernel(WgradGemmArg
             for (int kw = 0; kw < 3; ++kw) xoff[b][kw] = (rec + kw) * 64 + ((((rec + kw) >> 2) & 1) << 5) + quad * 8;
         }
     };
-    auto read_x = [&](const char *st, int gi) {       // group gi = (half of the stage, kw) -> fragment set gi % 2
-        const int kb = gi / 3, kw = gi % 3;
+    auto read_x = [&](const char *st, int gi) {       // group gi = (kw, half of the stage) -> fragment set gi % 2
+        const int kb = gi & 1, kw = gi >> 1;
 #pragma unroll
         for (int n = 0; n < NI; ++n) {
             xf[gi & 1][n].s.lo = xread(st, xoff[2 * kb][kw], n);
@@ -217,11 +221,12 @@ __global__ __launch_bounds__(128 * T, T / 2) void wgrad_gemm_kernel(WgradGemmArg
         const int nxt = cur + 1 == NS ? 0 : cur + 1;
         const char *const st = lds + cur * STAGE;
         const int ahead = min(s + NS, s1 - 1);
+        f32x4 sum[NI][NJ];                            // STAGED: of the stage's 64 voxels
 #pragma unroll
         for (int gi = 0; gi < 6; ++gi) {
-            const int kb = gi / 3, kw = gi % 3;
+            const int kb = gi & 1, kw = gi >> 1;
+            if (gi == 0) read_z(st, 1);
             if (gi == 1) fill(ahead);
-            if (gi == 2) read_z(st, 1);
             if (gi < 5) {
                 read_x(st, gi + 1);
             } else {
@@ -252,13 +257,23 @@ __global__ __launch_bounds__(128 * T, T / 2) void wgrad_gemm_kernel(WgradGemmArg
             }
             if (kw == 0 && bias) {
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) accb[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones.v, zf[kb][j].v, accb[j], 0, 0, 0);
+                for (int j = 0; j < NJ; ++j) accb[j] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones.v, zf[kb][j].v, zero, 0, 0, 0)[0];
             }
 #pragma unroll
             for (int i = 0; i < NI; ++i)
 #pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    acc[kw][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[gi & 1][i].v, zf[kb][j].v, acc[kw][i][j], 0, 0, 0);
+                for (int j = 0; j < NJ; ++j) {
+                    if (STAGED)
+                        sum[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[gi & 1][i].v, zf[kb][j].v, kb ? sum[i][j] : zero, 0, 0, 0);
+                    else
+                        acc[kw][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[gi & 1][i].v, zf[kb][j].v, acc[kw][i][j], 0, 0, 0);
+                }
+            if (STAGED && kb) {
+#pragma unroll
+                for (int i = 0; i < NI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) acc[kw][i][j] += sum[i][j];
+            }
         }
         cur = nxt;
     };
@@ -286,25 +301,40 @@ __global__ __launch_bounds__(128 * T, T / 2) void wgrad_gemm_kernel(WgradGemmArg
     if (bias_wave && lane < 16) {                     // row 0 of the ones-product: the column sums
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
-            a.out_b[split * a.out_stride + C * T * tj + 16 * (wj * NJ + j) + lane] = accb[j][0];
+            a.out_b[split * a.out_stride + C * T * tj + 16 * (wj * NJ + j) + lane] = static_cast<float>(accb[j]);
     }
 }
 
-// dw and db as the splits' sums in order, four values per thread (ndw and cout are multiples of four; db may lie anywhere).
+// dw and db as the splits' sums in fp64, four values per thread and run (ndw and cout are multiples of four; db may lie
+// anywhere): run r adds the splits r, r + 4, ... in order, then the runs are added.  A block serves 64 neighbouring fours.
+// What bounds it: HBM for wide layers, the chain of loads for narrow ones, which the runs cut to a quarter.
 __global__ __launch_bounds__(kThreads) void wgrad_gemm_join_kernel(const float4 *__restrict__ part, float4 *__restrict__ dw,
                                                                    float *__restrict__ db, long long ndw4, long long n4, int nsplit) {
-    const long long e = 1LL * blockIdx.x * kThreads + threadIdx.x;
-    if (e >= n4) return;
-    float4 s = part[e];
-#pragma unroll 4
-    for (int p = 1; p < nsplit; ++p) {
-        const float4 v = part[p * n4 + e];
-        s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    __shared__ double red[3][4][64];
+    const int l = threadIdx.x & 63, run = threadIdx.x >> 6;
+    const long long e = 64LL * blockIdx.x + l;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    if (e < n4) {
+#pragma unroll 8
+        for (int p = run; p < nsplit; p += 4) {
+            const float4 v = part[p * n4 + e];
+            s[0] += v.x; s[1] += v.y; s[2] += v.z; s[3] += v.w;
+        }
     }
-    if (e < ndw4) dw[e] = s;
-    else if (db) {
-        float *d = db + 4 * (e - ndw4);
-        d[0] = s.x; d[1] = s.y; d[2] = s.z; d[3] = s.w;
+    if (run) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) red[run - 1][i][l] = s[i];
+    }
+    __syncthreads();
+    if (run || e >= n4) return;
+    float f[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f[i] = static_cast<float>((s[i] + red[0][i][l]) + (red[1][i][l] + red[2][i][l]));
+    if (e < ndw4) {
+        dw[e] = make_float4(f[0], f[1], f[2], f[3]);
+    } else if (db) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) db[4 * (e - ndw4) + i] = f[i];
     }
 }
 
@@ -312,7 +342,7 @@ __global__ __launch_bounds__(kThreads) void wgrad_gemm_join_kernel(const float4 
 // measured layers (7 % rms): a stage lasts 1.37 us (128 x 128 channels; 0.87 us 64 x 64), a workgroup 4.2 us besides; the
 // splits' sums are written and read at 5.8 TB/s.  They stay within SP_STATIC_SCRATCH_BYTES, so that conv3d_wgrad_static takes
 // every layer it takes with the marching kernels.
-struct Plan { int t, lx, nsplit, nblocks; double us; };
+struct Plan { int t, lx, nsplit, nblocks, staged; double us; };
 Plan plan(const Geo &g, int cin, int cout) {
     Plan p;
     p.t = cin % (4 * C) == 0 && cout % (4 * C) == 0 ? 4 : 2;
@@ -331,6 +361,12 @@ Plan plan(const Geo &g, int cin, int cout) {
         if (s == 1 || us < p.us) { p.us = us; p.nsplit = s; }
     }
     p.nblocks = static_cast<int>(tiles * p.nsplit);
+    // The running sums may be no longer than those of the marching kernels, which add up two halves of every workgroup's
+    // voxels.  Where the splits are as many, one sum over all products is exact enough; where they are fewer, a sum per stage
+    // keeps the error below theirs (against 64 bits, marching, one sum, per stage: 512 -> 64 on 18 x 16 x 16 1.1e-7, 2.2e-7,
+    // 1.1e-7; 128 -> 512 on 17 x 24 x 22 2.7e-7, 2.8e-7, 1.2e-7; 2-D 128 -> 64 on 2 x 288 x 256 2.9e-7, 3.8e-7, 1.6e-7).  It costs
+    // 32 (T = 4) additions per wave for 16 products: 1024 -> 1024, 2-D, 16 x 32 x 32 376 -> 426 us.
+    p.staged = p.nsplit < 2 * wgrad_march_groups(g, cin, cout);
     return p;
 }
 
@@ -375,17 +411,17 @@ int launch_wgrad_gemm(const void *Px, const void *Pdz, float *dw, float *db, con
     a.dth = make_div31(g.th);
     a.dtd = make_div31(g.td);
     using Kern = void (*)(WgradGemmArgs);
-    // [tile][record groups; gathered halos: whole 8 x 32 patches, rows of at least 32]
-    static const Kern kern[2][4] = {{wgrad_gemm_kernel<2, 5, false>, wgrad_gemm_kernel<2, 6, false>, wgrad_gemm_kernel<2, 8, false>,
-                                     wgrad_gemm_kernel<2, 5, true>},
-                                    {wgrad_gemm_kernel<4, 5, false>, wgrad_gemm_kernel<4, 6, false>, wgrad_gemm_kernel<4, 8, false>,
-                                     wgrad_gemm_kernel<4, 5, true>}};
+    // [staged][tile][record groups; gathered halos: whole 8 x 32 patches, rows of at least 32]
+#define SP3D_TILES(T, S) {wgrad_gemm_kernel<T, 5, false, S>, wgrad_gemm_kernel<T, 6, false, S>, wgrad_gemm_kernel<T, 8, false, S>, \
+                          wgrad_gemm_kernel<T, 5, true, S>}
+    static const Kern kern[2][2][4] = {{SP3D_TILES(2, false), SP3D_TILES(4, false)}, {SP3D_TILES(2, true), SP3D_TILES(4, true)}};
+#undef SP3D_TILES
     static const int lxs[4] = {5, 6, 8, 5};
     // more than 64 KB of dynamic LDS has to be requested explicitly
     static const hipError_t attr = [] {
-        for (int i = 0; i < 8; ++i) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern[i / 4][i % 4]),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(i / 4 ? 4 : 2, lxs[i % 4]));
+        for (int i = 0; i < 16; ++i) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern[i / 8][i / 4 % 2][i % 4]),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(i / 4 % 2 ? 4 : 2, lxs[i % 4]));
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
@@ -393,11 +429,11 @@ int launch_wgrad_gemm(const void *Px, const void *Pdz, float *dw, float *db, con
     if (attr != hipSuccess) return record_hip(attr);
     if (gather && p.lx != 5) return SP_EUNSUPPORTED;
     const int k = gather ? 3 : (p.lx == 5 ? 0 : (p.lx == 6 ? 1 : 2));
-    hipLaunchKernelGGL(kern[p.t / 2 - 1][k], dim3(static_cast<unsigned>((p.nblocks + 7) / 8 * 8)), dim3(128 * p.t), lds_bytes(p.t, p.lx), s, a);
+    hipLaunchKernelGGL(kern[p.staged][p.t / 2 - 1][k], dim3(static_cast<unsigned>((p.nblocks + 7) / 8 * 8)), dim3(128 * p.t), lds_bytes(p.t, p.lx), s, a);
     int rc = record_hip(hipGetLastError());
     if (rc != SP_OK || p.nsplit == 1) return rc;
     const long long n4 = (ndw + cout) / 4;
-    hipLaunchKernelGGL(wgrad_gemm_join_kernel, dim3(static_cast<unsigned>((n4 + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
+    hipLaunchKernelGGL(wgrad_gemm_join_kernel, dim3(static_cast<unsigned>((n4 + 63) / 64)), dim3(kThreads), 0, s,
                        static_cast<const float4 *>(ws), reinterpret_cast<float4 *>(dw), db, ndw / 4, n4, p.nsplit);
     return record_hip(hipGetLastError());
 }

@@ -855,6 +855,12 @@ bool wgrad_mfma_supported(const Geo &g, int cin, int cout, sp_dtype_t dt) {
     return base * g.td < 0x7fffffffLL && 1LL * g.ph * g.pw * (cin > cout ? cin : cout) < 0x7fffffffLL;
 }
 
+int wgrad_march_groups(const Geo &g, int cin, int cout) {
+    WgradArgs a;
+    plan(g, cin, cout, &a, true);
+    return a.gpp;
+}
+
 // Which family serves a layer: the marching kernels of this file, or the GEMM over voxels of wgrad_gemm.hip.  The march
 // reuses a staged x plane for 27 taps and wins in 3-D where tiles are whole patches and the volume is large; it loses where
 // patches are mostly empty, where a workgroup per channel pair has only a plane or two to march over, and in 2-D with many

@@ -1,0 +1,55 @@
+"""Weight gradients against 64 bits: the error of the fp32 sums, in the 2-norm over the 2-norm of the result.
+
+Bounds.  A rounding of a running sum s is off by at most 2^-24 |s|, by 2^-24 |s| / sqrt(3) in the root mean square; where
+products of random sign are added, s grows like the square root of their number, so that a chain of n roundings ends
+sqrt(n / 2) 2^-24 / sqrt(3) off the result.  The reference is the
+same sum tap by tap in torch's float64."""
+import math
+
+import pytest
+import torch
+
+from paper_1909_03108_amd import sp3d, synth
+from gpu_util import DT, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def chain(n):
+    return math.sqrt(n / 6) * 2.0 ** -24
+
+
+def off(got, ref):
+    return float((got.double() - ref).norm() / ref.norm())
+
+
+def weight_gradient(n, dhw, grid, cin, cout, dtype, flat, seed=7100):
+    """errors of dw and db"""
+    g, dt = sp3d.Geom(n, dhw, grid, 1, 0, flat), DT[dtype]
+    x, dz = (to_dev(synth.normal_volume((n,) + dhw + (c,), seed + i, dtype)) for i, c in enumerate((cin, cout)))
+    P = []
+    for v, c in ((x, cin), (dz, cout)):
+        P.append(sp3d.alloc_padded(g, c, dt))
+        sp3d.sp_partition(v, P[-1], g, c, dt)
+        sp3d.sp_halo_exchange(P[-1], g, c, dt)
+    dw = torch.empty((9 if flat else 27, cin, cout), device="cuda")
+    db = torch.empty((cout,), device="cuda")
+    sp3d.conv3d_wgrad(P[0], P[1], dw, db, g, cin, cout, dt, sp3d.alloc_ws(sp3d.sp_workspace_bytes(2, g, cin, cout, dt)))
+    D, H, W = dhw
+    xp = torch.nn.functional.pad(x.double(), (0, 0, 1, 1, 1, 1) + ((0, 0) if flat else (1, 1)))
+    z = dz.double().reshape(-1, cout)
+    ref = torch.stack([xp[:, a:a + D, b:b + H, c:c + W].reshape(-1, cin).t() @ z
+                       for a in range(1 if flat else 3) for b in range(3) for c in range(3)])
+    return off(dw, ref), off(db, z.sum(0))
+
+
+# As a GEMM over voxels: each split adds its stages of 64 voxels to a running sum, 24 of them at most in these layers; inside
+# a stage the sums of up to 64 voxels are rounded at most 32 times: chain(24 + 32 / 2).  (With running sums that every
+# product was added to: 2.2e-7, 2.8e-7, 2.0e-7, 3.0e-7; bias gradient of the last 1.3e-7.)
+@pytest.mark.parametrize("n, dhw, grid, cin, cout, flat", [
+    (1, (18, 16, 16), (1, 1, 4), 512, 64, 0), (1, (17, 24, 22), (1, 2, 2), 128, 512, 0), (1, (34, 22, 20), (2, 2, 4), 128, 64, 0),
+    (2, (1, 184, 241), (1, 4, 1), 128, 64, 1)])
+def test_gemm_over_voxels_adds_stage_by_stage(n, dhw, grid, cin, cout, flat):
+    dw, db = weight_gradient(n, dhw, grid, cin, cout, "bf16", flat)
+    assert dw <= chain(24 + 16), dw
+    assert db <= 2.0 ** -24, db
