@@ -773,23 +773,24 @@ void plan(const Geo &g, int cin, int cout, WgradArgs *a, bool coarse = false) {
         while (f > 1 && g.td % f) --f;
         a->fold = f;
     }
-    // D chunk: what costs least if the gpp workgroups of a pair take the items in rounds - an item's start and its planes
-    // with the two of the surround - and every workgroup's partial result goes out and in at about 3 TB/s.  (Halved only
-    // until there was an item per workgroup, never below 16 planes, 32 -> 32 on 32^3 ran on 8 workgroups and 99 x 156 x 210
-    // on 1 x 2 x 2 tiles on two rounds of 52 planes instead of two of 35: 43 -> 19 us and 290 -> 211 us.)  `coarse`: that rule.
+    // D chunk: halved until there is an item per workgroup, never below 16 planes (`coarse`: that and no more); below that,
+    // what costs least if the gpp workgroups of a pair take the items in rounds - an item's start and its planes with the two
+    // of the surround - and every workgroup's partial result goes out and in at about 3 TB/s.  (The first rule alone ran 32 ->
+    // 32 on 32^3 on 8 workgroups and 99 x 156 x 210 on 1 x 2 x 2 tiles on two rounds of 52 planes instead of two of 35: 43 ->
+    // 19 us and 290 -> 211 us.)  Longer chunks than the first rule's are not taken: fewer workgroups have longer chains of fp32
+    // sums (64 -> 96 on 74 x 38 x 69, 17 % more error for 10 % of the time).
     const int steps = (g.td + a->fold - 1) / a->fold;
-    int best = steps;
-    if (coarse) {
-        int d = g.td;
-        while (base * ((g.td + d - 1) / d) < gpp && d > 16) d = (d + 1) / 2;
-        best = (d + a->fold - 1) / a->fold;
-    } else {
+    int d0 = g.td;
+    while (base * ((g.td + d0 - 1) / d0) < gpp && d0 > 16) d0 = (d0 + 1) / 2;
+    int best = (d0 + a->fold - 1) / a->fold;
+    if (!coarse) {
+        const int k0 = (steps + best - 1) / best;
         double cost = 0;
-        for (int k = 1; k <= steps && (k == 1 || base * k <= 8LL * gpp); ++k) {
+        for (int k = k0; k <= steps && (k == k0 || base * k <= 8LL * gpp); ++k) {
             const int d = (steps + k - 1) / k;
             const long long items = base * ((steps + d - 1) / d), groups = items < gpp ? items : gpp;
             const double us = (items + groups - 1) / groups * item_us(g, d + 2) + 8192.0 * groups * npairs * taps_of(g) / 3e6;
-            if (k == 1 || us < cost) { cost = us; best = d; }
+            if (k == k0 || us < cost) { cost = us; best = d; }
         }
     }
     const int dchunk = best * a->fold;
