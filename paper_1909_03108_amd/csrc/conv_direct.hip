@@ -270,7 +270,7 @@ constexpr int kWgradVox = 256;   // voxels of a brick
 // blockIdx.x: share of the bricks, blockIdx.y: (chunk of input channels, block of 16 output channels).  MB: blocks of 16
 // rows, at least ceil(ntap * kc / 16).
 template <typename E, int MB>
-__global__ __launch_bounds__(kThreads) void wgrad_direct_kernel(WgradDirectArgs a) {
+__global__ __launch_bounds__(kThreads, 2) void wgrad_direct_kernel(WgradDirectArgs a) {
     extern __shared__ __align__(16) float lds[];
     float *const dzs = lds, *const xs = lds + kWgradVox * 16;
     int *const vrec = reinterpret_cast<int *>(xs + ((a.b.nrec * a.kc + 3) & ~3));
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(kThreads) void wgrad_direct_kernel(WgradDirectArgs 
     f32x4 acc[MB];
 #pragma unroll
     for (int m = 0; m < MB; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float bsum = 0.f;
+    double bsum = 0.0;
 
     for (int brick = blockIdx.x; brick < a.b.nbricks; brick += gridDim.x) {
         const BrickPos p = brick_pos(a.g, a.b, brick);
@@ -318,32 +318,58 @@ __global__ __launch_bounds__(kThreads) void wgrad_direct_kernel(WgradDirectArgs 
             *reinterpret_cast<f32x4 *>(dzs + 4 * e) = z;
         }
         __syncthreads();
-        // whole quads of voxels of a brick inside its box first; where x has to be masked, a loop of its own (with the
-        // mask in the main loop the 8 -> 16 -> 16 pair's weight gradients took 110 -> 165 us)
-        constexpr int kShare = kWgradVox / kWaves;
+        // 16 voxels at a time, summed from zero and then added: the chain that rounds against the whole sum is 16 times
+        // shorter (1 -> 8 channels on 132 x 112 x 115, error against 64 bits 8.8e-7 -> 2.1e-7).  Voxels of a brick inside its
+        // box first; where x has to be masked, a loop of its own (with the mask in the main loop the 8 -> 16 -> 16 pair's
+        // weight gradients took 110 -> 165 us)
+        constexpr int kShare = kWgradVox / kWaves, MG = MB % 9 == 0 ? 9 : (MB % 7 == 0 ? 7 : MB);
         const bool inside = p.d0 + a.b.s <= p.bx.bd && p.h0 + a.b.r <= p.bx.bh && p.w0 + a.b.c <= p.bx.bw;
-        const int mine = min(max(nvox - wave * kShare, 0), kShare), whole = inside ? mine & ~3 : 0;
+        const int mine = min(max(nvox - wave * kShare, 0), kShare), whole = inside ? mine & ~15 : 0;
         const int v0 = wave * kShare + q;
-        for (int k = 0; k < whole; k += 4) {
-            const float b = dzs[(v0 + k) * 16 + col];
-            const float *xr = xs + vrec[v0 + k];
-            bsum += b;
+        auto sixteen = [&](int k, auto masked_tag) {
+            constexpr bool masked = decltype(masked_tag)::value;
+            float b[4];
+            int vr[4];
 #pragma unroll
-            for (int m = 0; m < MB; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(xr[off[m]], b, acc[m], 0, 0, 0);
-        }
-        for (int k = whole; k < mine; k += 4) {
-            const float b = dzs[(v0 + k) * 16 + col];
-            const int vr = vrec[v0 + k];
-            const float *xr = xs + max(vr, 0);
-            bsum += b;
+            for (int n = 0; n < 4; ++n) {
+                b[n] = dzs[(v0 + k + 4 * n) * 16 + col];
+                vr[n] = vrec[v0 + k + 4 * n];
+            }
+            bsum += (b[0] + b[1]) + (b[2] + b[3]);
+            // steps (group of row blocks, quad of voxels); the x values of a step are read before the products of the last
+            constexpr int NG = MB / MG;
+            float xv[2][MG];
+            f32x4 t[MG];
+            auto read = [&](int i) {
+                const float *xr = xs + (masked ? max(vr[i & 3], 0) : vr[i & 3]);
+                const uint32_t keep = masked && vr[i & 3] < 0 ? 0u : 0xffffffffu;     // (no branch around the load)
 #pragma unroll
-            for (int m = 0; m < MB; ++m)
-                acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr < 0 ? 0.f : xr[off[m]], b, acc[m], 0, 0, 0);
-        }
+                for (int m = 0; m < MG; ++m) {
+                    const float x = xr[off[(i >> 2) * MG + m]];
+                    xv[i & 1][m] = masked ? __uint_as_float(__float_as_uint(x) & keep) : x;
+                }
+            };
+            read(0);
+#pragma unroll
+            for (int i = 0; i < 4 * NG; ++i) {
+                if (i + 1 < 4 * NG) read(i + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int m = 0; m < MG; ++m)
+                    t[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[i & 1][m], b[i & 3], i & 3 ? t[m] : f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                if ((i & 3) == 3) {
+#pragma unroll
+                    for (int m = 0; m < MG; ++m) acc[(i >> 2) * MG + m] += t[m];
+                }
+            }
+        };
+        for (int k = 0; k < whole; k += 16) sixteen(k, std::false_type{});
+        for (int k = whole; k < mine; k += 16) sixteen(k, std::true_type{});
     }
     // the four waves' sums, added in wave order
     __syncthreads();
-    float *const red = lds, *const redb = lds + MB * 256;
+    float *const red = lds;
+    double *const redb = reinterpret_cast<double *>(lds + MB * 256);
     for (int wv = 0; wv < kWaves; ++wv) {
         if (wave == wv) {
 #pragma unroll
@@ -366,7 +392,7 @@ __global__ __launch_bounds__(kThreads) void wgrad_direct_kernel(WgradDirectArgs 
                 red[((row >> 4) * 4 + (row & 3)) * 64 + ((row & 15) >> 2) * 16 + cc];
     }
     if (a.bias && chunk == 0 && tid < 16 && co < a.cout)
-        part[ndw + co] = ((redb[tid] + redb[16 + tid]) + redb[32 + tid]) + redb[48 + tid];
+        part[ndw + co] = static_cast<float>((redb[tid] + redb[16 + tid]) + (redb[32 + tid] + redb[48 + tid]));
 }
 
 // Second stage: out[e] = sum over the partials in a fixed order (16 runs, then the runs in order); a block serves 64
@@ -583,7 +609,7 @@ int launch_wgrad_direct(const void *Px, const void *Pdz, float *dw, float *db, c
     int k = 0;
     while (16 * mbs[k] < p.ntap * p.kc) ++k;                       // (ntap * kc <= 27 * 16)
     size_t lds = kWgradVox * 16 * 4 + (static_cast<size_t>(p.b.nrec) * p.kc + 3) / 4 * 16 + kWgradVox * 4;
-    const size_t red = (mbs[k] * 256 + 64) * sizeof(float);        // the sums of the waves reuse the staging area
+    const size_t red = mbs[k] * 256 * sizeof(float) + 64 * sizeof(double);        // the sums of the waves reuse the staging area
     if (lds < red) lds = red;
     hipLaunchKernelGGL(kern[dt == SP_BF16][k], dim3(p.nparts, p.nck * p.nco), dim3(kThreads), lds, s, a);
     int rc = record_hip(hipGetLastError());

@@ -53,3 +53,12 @@ def test_gemm_over_voxels_adds_stage_by_stage(n, dhw, grid, cin, cout, flat):
     dw, db = weight_gradient(n, dhw, grid, cin, cout, "bf16", flat)
     assert dw <= chain(24 + 16), dw
     assert db <= 2.0 ** -24, db
+
+
+# fp32: 16 voxels at a time; a workgroup has at most 16 bricks of 256 voxels, a quarter each for its waves: 64 sums of 16 in a
+# chain, 4 waves, 512 workgroups in 16 runs: chain(16 + 64 + 4 + 32 + 16), and 15 % for the scatter of a norm over 216 values
+# (three times 1 / sqrt(2 * 216)).  (Running sums over all voxels: 8.8e-7, 6.1e-7.)
+@pytest.mark.parametrize("n, dhw, grid, cin, cout", [(1, (132, 112, 115), (1, 4, 1), 1, 8), (2, (132, 80, 114), (4, 4, 2), 8, 16)])
+def test_fp32_weight_gradient_adds_sixteen_voxels_at_a_time(n, dhw, grid, cin, cout):
+    dw, _ = weight_gradient(n, dhw, grid, cin, cout, "f32", 0)
+    assert dw <= 1.15 * chain(132), dw
