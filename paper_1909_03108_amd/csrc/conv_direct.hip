@@ -2,7 +2,7 @@
 // layers whose output channels are no multiple of 32, 1x1x1 convolutions that glue_kernels.hip does not serve, and the
 // gradient with respect to an image.  Kernel extent 3 or 1 per axis (1 along D in the 2-D variant).
 //
-// Forward and data gradient: an implicit GEMM on v_mfma_f32_16x16x4_f32 (exact fp32 products and sums), M = 16 output
+// Forward and data gradient: an implicit GEMM on v_mfma_f32_16x16x4_f32 (fp32 products and sums), M = 16 output
 // channels, N = 16 voxels, K = (tap, input channel).  A workgroup stages the input of a brick of output voxels, with its
 // surround, once in LDS and takes all taps from there.  The four K values of an instruction are free to name, as long
 // as both operands agree: lane group q = lane / 16 supplies the channel quad 4 s + q of step s, and the four
@@ -104,7 +104,9 @@ __device__ __forceinline__ int voxel_record(const BrickGeo &b, uint32_t v, int *
 }
 
 // Stage channels [c0, c0 + kc) of the brick's records as floats, `stride` floats apart (channels beyond `ki`: zeros).
-// Four loads per thread are in flight at a time.
+// Four loads per thread are in flight at a time, two times four where the channels do not come in whole quads (dq divides by
+// the number of quads, the last one partial); a loop over the channels of a record where the
+// quads would be less than three quarters full (weight gradient of 1 -> 24 on 63 x 96 x 113: 77 us, in quads 85).
 template <typename E>
 __device__ __forceinline__ void stage_records(const E *__restrict__ in, float *xs, const Geo &g, const BrickGeo &b,
                                               const BrickPos &p, int ki, int c0, int kc, int stride, const FastDiv &dq) {
@@ -128,11 +130,33 @@ __device__ __forceinline__ void stage_records(const E *__restrict__ in, float *x
                 }
             }
         }
-    } else {
-        const uint32_t n = b.nrec;
-        for (uint32_t rec = threadIdx.x; rec < n; rec += kThreads) {
+    } else if (kc < 3 * ((kc + 3) >> 2)) {
+        for (uint32_t rec = threadIdx.x; rec < static_cast<uint32_t>(b.nrec); rec += kThreads) {
             const E *src = in + record_voxel(g, b, p, rec) * ki + c0;
             for (int c = 0; c < kc; ++c) xs[rec * stride + c] = c0 + c < ki ? ldf<E>(src, c) : 0.f;
+        }
+    } else {
+        const uint32_t nq = static_cast<uint32_t>(kc + 3) >> 2, n = b.nrec * nq;
+        for (uint32_t e0 = threadIdx.x; e0 < n; e0 += 2 * kThreads) {
+            float v[2][4];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const uint32_t e = min(e0 + u * kThreads, n - 1), rec = fdiv(e, dq);
+                const int c = c0 + 4 * static_cast<int>(fmod_(e, rec, dq));
+                const E *src = in + record_voxel(g, b, p, rec) * ki + c;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[u][j] = c + j < ki ? ldf<E>(src, j) : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const uint32_t e = e0 + u * kThreads;
+                if (e >= n) continue;
+                const uint32_t rec = fdiv(e, dq);
+                const int c = 4 * static_cast<int>(fmod_(e, rec, dq));
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (c + j < kc) xs[rec * stride + c + j] = v[u][j];
+            }
         }
     }
 }
@@ -262,10 +286,11 @@ struct WgradDirectArgs {
     BrickGeo b;
     int cin, cout, ntap;
     int kc, nco, bias;           // channels per chunk; blocks of 16 output channels; bias: sum dz as well
-    FastDiv dq;                  // kc / 4
+    int share;                   // voxels of a brick per wave
+    FastDiv dq, dkc;             // ceil(kc / 4), kc
 };
 
-constexpr int kWgradVox = 256;   // voxels of a brick
+constexpr int kWgradVox = 256;   // voxels of a brick at most
 
 // blockIdx.x: share of the bricks, blockIdx.y: (chunk of input channels, block of 16 output channels).  MB: blocks of 16
 // rows, at least ceil(ntap * kc / 16).
@@ -280,11 +305,16 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_direct_kernel(WgradDirectAr
     const int nvox = a.b.s * a.b.r * a.b.c;
     const E *const x = static_cast<const E *>(a.x), *const dz = static_cast<const E *>(a.dz);
 
-    int off[MB];                                    // LDS float offset of this lane's row of every row block
+    // LDS float offset of this lane's row of every row block (the taps' records come from a table: they take three
+    // divisions by run-time values, 27 times in every lane)
+    int *const taps = reinterpret_cast<int *>(lds);
+    if (tid < a.ntap) taps[tid] = tap_record(a.b, tid) * a.kc;
+    __syncthreads();
+    int off[MB];
 #pragma unroll
     for (int m = 0; m < MB; ++m) {
-        const int row = 16 * m + col, t = row / a.kc;
-        off[m] = row < rows ? tap_record(a.b, t) * a.kc + row - t * a.kc : 0;
+        const int row = 16 * m + col, t = static_cast<int>(fdiv(row, a.dkc));
+        off[m] = row < rows ? taps[min(t, a.ntap - 1)] + row - t * a.kc : 0;
     }
     f32x4 acc[MB];
 #pragma unroll
@@ -297,7 +327,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_direct_kernel(WgradDirectAr
         stage_records<E>(x, xs, a.g, a.b, p, a.cin, c0, a.kc, a.kc, a.dq);
         // dz, zero for voxels outside the tile and channels beyond the last; x counts as zero at those voxels as well
         // (vrec < 0), so that the products vanish also where a neighbour's record holds an infinity
-        for (int e = tid; e < kWgradVox * 4; e += kThreads) {
+        for (int e = tid; e < kWaves * a.share * 4; e += kThreads) {
             const int v = e >> 2, c4 = cob * 16 + 4 * (e & 3);
             int d, h, w;
             const int vr = voxel_record(a.b, v < nvox ? v : 0, &d, &h, &w) * a.kc;
@@ -322,10 +352,10 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_direct_kernel(WgradDirectAr
         // shorter (1 -> 8 channels on 132 x 112 x 115, error against 64 bits 8.8e-7 -> 2.1e-7).  Voxels of a brick inside its
         // box first; where x has to be masked, a loop of its own (with the mask in the main loop the 8 -> 16 -> 16 pair's
         // weight gradients took 110 -> 165 us)
-        constexpr int kShare = kWgradVox / kWaves, MG = MB % 9 == 0 ? 9 : (MB % 7 == 0 ? 7 : MB);
+        constexpr int MG = MB % 9 == 0 ? 9 : (MB % 7 == 0 ? 7 : MB);
         const bool inside = p.d0 + a.b.s <= p.bx.bd && p.h0 + a.b.r <= p.bx.bh && p.w0 + a.b.c <= p.bx.bw;
-        const int mine = min(max(nvox - wave * kShare, 0), kShare), whole = inside ? mine & ~15 : 0;
-        const int v0 = wave * kShare + q;
+        const int mine = min(max(nvox - wave * a.share, 0), a.share), whole = inside ? mine & ~15 : 0;
+        const int v0 = wave * a.share + q;
         auto sixteen = [&](int k, auto masked_tag) {
             constexpr bool masked = decltype(masked_tag)::value;
             float b[4];
@@ -386,7 +416,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_direct_kernel(WgradDirectAr
     const size_t ndw = static_cast<size_t>(a.ntap) * a.cin * a.cout;
     float *const part = a.part + blockIdx.x * (ndw + a.cout);
     for (int e = tid; e < 16 * MB * 16; e += kThreads) {          // row-major: 16 output channels side by side
-        const int row = e >> 4, cc = e & 15, t = row / a.kc, c = c0 + row - t * a.kc;
+        const int row = e >> 4, cc = e & 15, t = static_cast<int>(fdiv(row, a.dkc)), c = c0 + row - t * a.kc;
         if (row < rows && c < a.cin && cob * 16 + cc < a.cout)
             part[(static_cast<size_t>(t) * a.cin + c) * a.cout + cob * 16 + cc] =
                 red[((row >> 4) * 4 + (row & 3)) * 64 + ((row & 15) >> 2) * 16 + cc];
@@ -551,7 +581,7 @@ int launch_conv_direct(const void *Pin, const void *w, const float *bias, void *
 }
 
 // How the weight gradient is cut up: channels per chunk, row blocks, bricks, workgroups per channel-block pair.
-struct WgradDirectPlan { int kc, nck, nco, ntap, kd, nparts; BrickGeo b; };
+struct WgradDirectPlan { int kc, nck, nco, ntap, kd, nparts, share; BrickGeo b; };
 static WgradDirectPlan wgrad_direct_plan(const Geo &g, int cin, int cout, int ks) {
     WgradDirectPlan p;
     p.kd = g.flat ? 1 : ks;
@@ -561,10 +591,15 @@ static WgradDirectPlan wgrad_direct_plan(const Geo &g, int cin, int cout, int ks
     if (cin % 4 == 0) p.kc = (p.kc + 3) / 4 * 4;                  // keep the 16-byte staging loads
     p.nck = (cin + p.kc - 1) / p.kc;
     p.nco = (cout + 15) / 16;
-    const int fixed = kWgradVox * (16 + 1) * 4 + 16;
-    p.b = plan_brick(g, g.td, g.th, g.tw, p.kd, ks, kWgradVox, (kHalfLds - fixed) / (4 * p.kc));
+    const int fixed = kWgradVox * (16 + 1) * 4 + 16, pairs = p.nck * p.nco;
+    // fewer voxels per brick where full ones would leave compute units without a workgroup: a wave of a full brick has 432
+    // instructions of 32 cycles one after the other (16 -> 3 on 7 x 6 x 5 28.9 -> 19.7 us, one thread per product before 16.3;
+    // 17 -> 4 on 7 x 9 x 14 40 -> 20, before 21)
+    int vox = kWgradVox;
+    while (vox > 64 && 1.0 * g.ntiles * g.int_vox / vox * pairs < 256) vox /= 2;
+    p.share = vox / kWaves;
+    p.b = plan_brick(g, g.td, g.th, g.tw, p.kd, ks, vox, (kHalfLds - fixed) / (4 * p.kc));
     // two workgroups per compute unit, shared out over the channel-block pairs
-    const int pairs = p.nck * p.nco;
     int most = 512 / pairs;
     if (most < 1) most = 1;
     p.nparts = even_share(p.b.nbricks, most);
@@ -588,7 +623,9 @@ int launch_wgrad_direct(const void *Px, const void *Pdz, float *dw, float *db, c
     a.b = p.b;
     a.cin = cin; a.cout = cout; a.ntap = p.ntap;
     a.kc = p.kc; a.nco = p.nco; a.bias = db != nullptr;
-    a.dq = make_fastdiv(p.kc >= 4 ? p.kc / 4 : 1);
+    a.share = p.share;
+    a.dq = make_fastdiv((p.kc + 3) / 4);
+    a.dkc = make_fastdiv(p.kc);
     using Kern = void (*)(WgradDirectArgs);
     constexpr int kSizes = 6;
     static const int mbs[kSizes] = {1, 2, 7, 9, 14, 27};          // row blocks of the kernels that exist
