@@ -105,8 +105,9 @@ __device__ __forceinline__ int voxel_record(const BrickGeo &b, uint32_t v, int *
 
 // Stage channels [c0, c0 + kc) of the brick's records as floats, `stride` floats apart (channels beyond `ki`: zeros).
 // Four loads per thread are in flight at a time, two times four where the channels do not come in whole quads (dq divides by
-// the number of quads, the last one partial); a loop over the channels of a record where the
-// quads would be less than three quarters full (weight gradient of 1 -> 24 on 63 x 96 x 113: 77 us, in quads 85).
+// the number of quads, the last one partial); a loop over the channels of a record where that is
+// a single quad or the quads are less than three quarters full (weight gradient of 1 -> 24 on 63 x 96 x 113: 77 us, in quads
+// 85; 3 -> 3 on 98 x 122 x 180 216, in quads 235).
 template <typename E>
 __device__ __forceinline__ void stage_records(const E *__restrict__ in, float *xs, const Geo &g, const BrickGeo &b,
                                               const BrickPos &p, int ki, int c0, int kc, int stride, const FastDiv &dq) {
@@ -130,7 +131,7 @@ __device__ __forceinline__ void stage_records(const E *__restrict__ in, float *x
                 }
             }
         }
-    } else if (kc < 3 * ((kc + 3) >> 2)) {
+    } else if (kc < 4 || kc < 3 * ((kc + 3) >> 2)) {
         for (uint32_t rec = threadIdx.x; rec < static_cast<uint32_t>(b.nrec); rec += kThreads) {
             const E *src = in + record_voxel(g, b, p, rec) * ki + c0;
             for (int c = 0; c < kc; ++c) xs[rec * stride + c] = c0 + c < ki ? ldf<E>(src, c) : 0.f;
