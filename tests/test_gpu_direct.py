@@ -158,3 +158,26 @@ def test_infinite_voxels_stay_infinities(dhw, cin, cout):
     hit = torch.zeros_like(dw, dtype=torch.bool)
     hit[1:, 1:, 1:, 0] = True                           # taps through which an existing voxel reads the last one
     assert torch.equal(torch.isinf(dw), hit) and not torch.isnan(dw).any()
+
+
+def one_voxel(c):
+    """geometry, (x, dz) in padded tiles, their values"""
+    g = sp3d.Geom(1, (1, 1, 1), (1, 1, 1))
+    v = [to_dev(synth.normal_volume((1, 1, 1, 1, c), 4500 + i, "f32")) for i in (0, 1)]
+    P = [sp3d.alloc_padded(g, c, sp3d.SP_F32) for _ in v]
+    for V, p in zip(v, P):
+        sp3d.sp_partition(V, p, g, c, sp3d.SP_F32)
+    return g, P, [V.view(-1) for V in v]
+
+
+def test_weight_gradient_of_more_values_than_threads():
+    """3600 -> 3600 channels: 350 million values, 64 to a workgroup of 1024 threads, are more threads than a launch has.  Of one
+    voxel only the middle tap is not zero, and it is a product each."""
+    c = 3600
+    g, P, (x, dz) = one_voxel(c)
+    dw, db = torch.full((27, c, c), 9.0, device="cuda"), torch.empty((c,), device="cuda")
+    sp3d.conv3d_wgrad(P[0], P[1], dw, db, g, c, c, sp3d.SP_F32,
+                      sp3d.alloc_ws(sp3d.sp_workspace_bytes(sp3d.SP_OP_WGRAD, g, c, c, sp3d.SP_F32)))
+    assert torch.equal(dw[13], torch.outer(x, dz)) and torch.equal(db, dz)
+    dw[13] = 0
+    assert not dw.any()
