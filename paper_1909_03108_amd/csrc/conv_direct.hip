@@ -286,14 +286,14 @@ struct WgradDirectArgs {
     Geo g;                       // (grow = 0)
     BrickGeo b;
     int cin, cout, ntap;
-    int kc, nco, bias;           // channels per chunk; blocks of 16 output channels; bias: sum dz as well
+    int kc, bias;                // channels per chunk; bias: sum dz as well
     int share;                   // voxels of a brick per wave
     FastDiv dq, dkc;             // ceil(kc / 4), kc
 };
 
 constexpr int kWgradVox = 256;   // voxels of a brick at most
 
-// blockIdx.x: share of the bricks, blockIdx.y: (chunk of input channels, block of 16 output channels).  MB: blocks of 16
+// blockIdx.x: share of the bricks, blockIdx.y: block of 16 output channels, blockIdx.z: chunk of input channels.  MB: blocks of 16
 // rows, at least ceil(ntap * kc / 16).
 template <typename E, int MB>
 __global__ __launch_bounds__(kThreads, 2) void wgrad_direct_kernel(WgradDirectArgs a) {
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_direct_kernel(WgradDirectAr
     float *const dzs = lds, *const xs = lds + kWgradVox * 16;
     int *const vrec = reinterpret_cast<int *>(xs + ((a.b.nrec * a.kc + 3) & ~3));
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 15, q = lane >> 4;
-    const int chunk = blockIdx.y / a.nco, cob = blockIdx.y - chunk * a.nco;
+    const int chunk = blockIdx.z, cob = blockIdx.y;
     const int c0 = chunk * a.kc, rows = a.ntap * a.kc, co = cob * 16 + col;
     const int nvox = a.b.s * a.b.r * a.b.c;
     const E *const x = static_cast<const E *>(a.x), *const dz = static_cast<const E *>(a.dz);
@@ -619,7 +619,6 @@ size_t wgrad_direct_ws_bytes(const Geo &g, int cin, int cout, int ks) {
 int launch_wgrad_direct(const void *Px, const void *Pdz, float *dw, float *db, const Geo &g, int cin,
                         int cout, sp_dtype_t dt, void *ws, hipStream_t s, int ks) {
     const WgradDirectPlan p = wgrad_direct_plan(g, cin, cout, ks);
-    if (p.nck * p.nco > 65535) return SP_EUNSUPPORTED;
     WgradDirectArgs a;
     a.x = Px; a.dz = Pdz;
     a.part = static_cast<float *>(ws);
@@ -627,7 +626,7 @@ int launch_wgrad_direct(const void *Px, const void *Pdz, float *dw, float *db, c
     a.g.grow = 0;
     a.b = p.b;
     a.cin = cin; a.cout = cout; a.ntap = p.ntap;
-    a.kc = p.kc; a.nco = p.nco; a.bias = db != nullptr;
+    a.kc = p.kc; a.bias = db != nullptr;
     a.share = p.share;
     a.dq = make_fastdiv((p.kc + 3) / 4);
     a.dkc = make_fastdiv(p.kc);
@@ -653,7 +652,7 @@ int launch_wgrad_direct(const void *Px, const void *Pdz, float *dw, float *db, c
     size_t lds = kWgradVox * 16 * 4 + (static_cast<size_t>(p.b.nrec) * p.kc + 3) / 4 * 16 + kWgradVox * 4;
     const size_t red = mbs[k] * 256 * sizeof(float) + 64 * sizeof(double);        // the sums of the waves reuse the staging area
     if (lds < red) lds = red;
-    hipLaunchKernelGGL(kern[dt == SP_BF16][k], dim3(p.nparts, p.nck * p.nco), dim3(kThreads), lds, s, a);
+    hipLaunchKernelGGL(kern[dt == SP_BF16][k], dim3(p.nparts, p.nco, p.nck), dim3(kThreads), lds, s, a);
     int rc = record_hip(hipGetLastError());
     if (rc != SP_OK) return rc;
     const long long ndw = 1LL * p.ntap * cin * cout, n = ndw + cout;

@@ -181,3 +181,13 @@ def test_weight_gradient_of_more_values_than_threads():
     assert torch.equal(dw[13], torch.outer(x, dz)) and torch.equal(db, dz)
     dw[13] = 0
     assert not dw.any()
+
+
+def test_weight_gradient_of_the_widest_layers():
+    """4096 -> 4096 channels: 65536 pairs of channel blocks, one more than a grid has rows."""
+    c = 4096
+    g, P, (x, dz) = one_voxel(c)
+    dw, db = torch.empty((c, c), device="cuda"), torch.empty((c,), device="cuda")
+    sp3d.sp_pointwise_wgrad(P[0], P[1], dw, db, g, c, c, sp3d.SP_F32,
+                            sp3d.alloc_ws(sp3d.sp_workspace_bytes(sp3d.SP_OP_POINTWISE_WGRAD, g, c, c, sp3d.SP_F32)))
+    assert torch.equal(dw, torch.outer(x, dz)) and torch.equal(db, dz)
