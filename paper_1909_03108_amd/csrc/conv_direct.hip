@@ -70,8 +70,8 @@ struct BrickPos {
     int d0, h0, w0;              // first output voxel, in coordinates of the box
 };
 
-__device__ __forceinline__ BrickPos brick_pos(const Geo &g, const BrickGeo &b, int brick) {
-    uint32_t t = static_cast<uint32_t>(brick), q;
+__device__ __forceinline__ BrickPos brick_pos(const Geo &g, const BrickGeo &b, uint32_t brick) {
+    uint32_t t = brick, q;
     BrickPos p;
     q = fdiv(t, b.dnc); p.w0 = static_cast<int>(fmod_(t, q, b.dnc)) * b.c; t = q;
     q = fdiv(t, b.dnr); p.h0 = static_cast<int>(fmod_(t, q, b.dnr)) * b.r; t = q;
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(kThreads) void conv_direct_kernel(ConvDirectArgs a)
     }
 
     bool have_weights = false;
-    for (int brick = blockIdx.x; brick < a.b.nbricks; brick += gridDim.x) {
+    for (uint32_t brick = blockIdx.x; brick < static_cast<uint32_t>(a.b.nbricks); brick += gridDim.x) {
         const BrickPos p = brick_pos(a.g, a.b, brick);
         if (!p.any) continue;
         f32x4 acc[NV];
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_direct_kernel(WgradDirectAr
     for (int m = 0; m < MB; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
     double bsum = 0.0;
 
-    for (int brick = blockIdx.x; brick < a.b.nbricks; brick += gridDim.x) {
+    for (uint32_t brick = blockIdx.x; brick < static_cast<uint32_t>(a.b.nbricks); brick += gridDim.x) {
         const BrickPos p = brick_pos(a.g, a.b, brick);
         __syncthreads();
         stage_records<E>(x, xs, a.g, a.b, p, a.cin, c0, a.kc, a.kc, a.dq);
@@ -535,8 +535,8 @@ static BrickGeo plan_brick(const Geo &g, int ed, int eh, int ew, int kd, int ks,
 
 // Workgroups for n bricks when `most` fit the chip at a time: every one gets the same number of bricks.
 static int even_share(int n, int most) {
-    const int rounds = (n + most - 1) / most;
-    return (n + rounds - 1) / rounds;
+    const int rounds = static_cast<int>((n + most - 1LL) / most);
+    return static_cast<int>((n + rounds - 1LL) / rounds);
 }
 
 constexpr int kHalfLds = 80 * 1024;      // two workgroups per compute unit
