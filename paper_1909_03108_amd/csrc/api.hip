@@ -168,6 +168,34 @@ size_t sp_workspace_bytes(int op, const sp_geom_t *g, int cin, int cout, sp_dtyp
     }
 }
 
+// Which kernels a call takes and how it is cut: host logic only, for the tests that have to reach a certain kernel; not part
+// of the C ABI.  op: SP_OP_* or 16 / 17, the 1x1x1 convolution's forward pass and data gradient.  Returns kRoute*; detail:
+// marching forward / data gradient {two chunks per launch, slices side by side, D chunk, launches}, implicit GEMM {output blocks
+// per wave, tiles of 128 voxels, record loads, splits}, marching weight gradient {whole patches, slices side by side, D chunk,
+// workgroups per channel pair}, GEMM over voxels {channel chunks of a tile, record groups, splits, summed by stage}.
+int sp3d_route(int op, const sp_geom_t *g, int cin, int cout, sp_dtype_t dt, int *detail) {
+    Geo o;
+    if (make_geo(g, &o) != SP_OK || !chan_ok(cin) || !chan_ok(cout) || !dtype_ok(dt)) return kRouteNone;
+    switch (op) {
+    case SP_OP_FWD:
+        if (conv_mfma_supported(o, cin, cout, dt)) return conv_mfma_route(o, cin, cout, detail);
+        if (conv_c1_supported(o, cin, cout, dt)) return o.grow == 0 ? kRouteC1 : conv_direct_route(o, cin, cout, dt, false);
+        if (chan_pad_supported(o, cin, cout, dt)) return conv_few_supported(o, cin, cout, dt) ? kRouteFew : kRoutePadded;
+        return conv_direct_route(o, cin, cout, dt, false);
+    case SP_OP_DGRAD:
+        if (conv_mfma_supported(o, cout, cin, dt)) return conv_mfma_route(o, cout, cin, detail);
+        return conv_direct_route(o, cout, cin, dt, true);
+    case SP_OP_WGRAD:
+        if (conv_c1_supported(o, cin, cout, dt)) return kRouteC1;
+        if (wgrad_mfma_supported(o, cin, cout, dt)) return wgrad_mfma_route(o, cin, cout, detail);
+        return chan_pad_supported(o, cin, cout, dt) ? kRoutePadded : kRouteBricks;
+    case SP_OP_POINTWISE_WGRAD: return pointwise_small_supported(o, cin, cout, dt) ? kRouteHead : kRouteBricks;
+    case 16: return pointwise_small_supported(o, cin, cout, dt) ? kRouteHead : conv_direct_route(o, cin, cout, dt, false, 1);
+    case 17: return pointwise_small_supported(o, cin, cout, dt) ? kRouteHead : conv_direct_route(o, cout, cin, dt, true, 1);
+    default: return kRouteNone;
+    }
+}
+
 const char *sp_strerror(int code) {
     switch (code) {
     case SP_OK: return "ok";

@@ -82,6 +82,13 @@ int launch_relu_bits(const void *y, void *bits, size_t blocks, hipStream_t s);
 int launch_conv_direct(const void *Pin, const void *w, const float *bias, void *Pout, const Geo &g,
                        int cin, int cout, sp_dtype_t dt, bool relu, bool dgrad, hipStream_t s, int ks = 3,
                        const void *mask = nullptr);
+// Which kernels a call takes, and how it is cut (sp3d_route in api.hip)
+enum { kRouteNone = 0, kRouteC1, kRouteMarch, kRouteGemm, kRouteFew, kRoutePadded, kRouteBricks, kRouteThreads, kRouteHead };
+int conv_direct_route(const Geo &g, int ki, int ko, sp_dtype_t dt, bool dgrad, int ks = 3);
+int conv_mfma_route(const Geo &g, int ki, int ko, int *detail);         // detail: four numbers, see sp3d_route
+void conv_gemm_detail(const Geo &g, int ki, int ko, int *detail);
+int wgrad_mfma_route(const Geo &g, int cin, int cout, int *detail);
+void wgrad_gemm_detail(const Geo &g, int cin, int cout, int *detail);
 size_t wgrad_direct_ws_bytes(const Geo &g, int cin, int cout, int ks = 3);
 int launch_wgrad_direct(const void *Px, const void *Pdz, float *dw, float *db, const Geo &g,
                         int cin, int cout, sp_dtype_t dt, void *ws, hipStream_t s, int ks = 3);

@@ -280,6 +280,50 @@ __global__ __launch_bounds__(kThreads) void conv_direct_kernel(ConvDirectArgs a)
     }
 }
 
+// One thread per (voxel of the output box, output channel), scalar FMAs: where a call has so few products that staging bricks
+// costs more than they do (see prefer_threads).  KS = kernel extent per axis; with `dgrad` the taps are mirrored and w is read
+// as w[tap][ko][ki].  A thread whose voxel lies beyond a side on which its tile has no neighbour has nothing to do.
+// What bounds it: the loads, one line per lane at worst, and the chain of ntap * ki products per thread.
+template <typename E, bool DGRAD, int KS>
+__global__ __launch_bounds__(kThreads) void conv_threads_kernel(const E *__restrict__ in, const E *__restrict__ w,
+                                                                const float *__restrict__ bias, E *__restrict__ out, Geo g, int ki,
+                                                                int ko, int relu, long long total, const E *__restrict__ mask) {
+    const int gd_ = grow_d(g), ed = g.td + 2 * gd_, eh = g.th + 2 * g.grow, ew = g.tw + 2 * g.grow;
+    const long long box_vox = 1LL * ed * eh * ew;
+    const unsigned ehw = static_cast<unsigned>(eh) * ew;
+    constexpr int O = KS / 2;
+    const int KD = g.flat ? 1 : KS, OD = KD / 2;
+    const long long idx = 1LL * blockIdx.x * kThreads + threadIdx.x;
+    if (idx >= total) return;
+    const int co = static_cast<int>(idx % ko);
+    const long long v = idx / ko, tile = v / box_vox;
+    const unsigned r = static_cast<unsigned>(v % box_vox);
+    // padded coordinates of the output voxel
+    const int pd = static_cast<int>(r / ehw) + g.halo - gd_, ph = static_cast<int>((r % ehw) / ew) + g.halo - g.grow,
+              pw = static_cast<int>(r % ew) + g.halo - g.grow;
+    if (g.grow > 0) {
+        const int tc = static_cast<int>(tile % g.gw), tb = static_cast<int>((tile / g.gw) % g.gh),
+                  ta = static_cast<int>((tile / (1LL * g.gw * g.gh)) % g.gd);
+        if ((pd < g.halo && ta == 0) || (pd >= g.halo + g.td && ta == g.gd - 1) || (ph < g.halo && tb == 0) ||
+            (ph >= g.halo + g.th && tb == g.gh - 1) || (pw < g.halo && tc == 0) || (pw >= g.halo + g.tw && tc == g.gw - 1))
+            return;
+    }
+    const long long base = tile * g.tile_vox;
+    float acc = bias ? bias[co] : 0.f;
+    for (int kd = 0; kd < KD; ++kd)
+        for (int kh = 0; kh < KS; ++kh)
+            for (int kw = 0; kw < KS; ++kw) {
+                const E *x = in + (base + (1LL * (pd + kd - OD) * g.ph + ph + kh - O) * g.pw + pw + kw - O) * ki;
+                const int tap = DGRAD ? ((KD - 1 - kd) * KS + KS - 1 - kh) * KS + KS - 1 - kw : (kd * KS + kh) * KS + kw;
+                const E *wt = DGRAD ? w + (1LL * tap * ko + co) * ki : w + 1LL * tap * ki * ko + co;
+                for (int c = 0; c < ki; ++c) acc = fmaf(ldf<E>(x, c), ldf<E>(wt, DGRAD ? c : 1LL * c * ko), acc);
+            }
+    if (relu && acc < 0.f) acc = 0.f;
+    const long long o = (base + (1LL * pd * g.ph + ph) * g.pw + pw) * ko + co;
+    if (mask && !(ldf<E>(mask, o) > 0.f)) acc = 0.f;      // backward of the ReLU that produced the input
+    stf<E>(out + o, acc);
+}
+
 struct WgradDirectArgs {
     const void *x, *dz;
     float *part;                 // [workgroup along x][ntap * cin * cout, then cout]
@@ -541,6 +585,70 @@ static int even_share(int n, int most) {
 
 constexpr int kHalfLds = 80 * 1024;      // two workgroups per compute unit
 
+// How a call is cut up, apart from the shape of its bricks: channels per chunk, chunks, K steps, blocks of 16 output channels,
+// voxel segments per wave.  `vox`: voxels to compute.
+struct ConvDirectPlan { int ntap, kc, nck, steps, ncg, nv; };
+static ConvDirectPlan conv_direct_plan(double vox, int ntap, int ki, int ko) {
+    ConvDirectPlan p;
+    p.ntap = ntap;
+    p.nck = (ki + 15) / 16;
+    p.kc = ((ki + p.nck - 1) / p.nck + 3) / 4 * 4;
+    p.nck = (ki + p.kc - 1) / p.kc;
+    p.steps = (ntap * (p.kc / 4) + 3) / 4;
+    p.ncg = (ko + 15) / 16;
+    // 256 voxels per workgroup; fewer where that would leave the chip's 512 places (two per compute unit) empty
+    p.nv = vox / 256 * p.ncg >= 512 ? 4 : (vox / 128 * p.ncg >= 512 ? 2 : 1);
+    return p;
+}
+
+// Whether a thread per output is taken instead of bricks: unless bricks are estimated at less than 0.60 (extent 1) or 0.85
+// (extent 3) of its time.  Estimates in microseconds, threads: launch + waves x (outputs, taps, products: the lines of x and w
+// that a wave touches per channel) + the chain of a thread; bricks: launch + rounds of 512 workgroups x chunks x (staged quads,
+// K steps).  Fitted to 1356 calls measured both ways (1 ... 128 channels, 9 voxels ... 5 million, 2-D and 3-D; 24 % and 11 %
+// rms: hence the margins, with which four of them take more than 5 % longer than with a thread per output; without one 60 do).
+// Measured, threads against bricks: 1x1x1 40 -> 3 on 44 x 32 x 44, bf16, 8 against 17 us, 4 -> 2 on 102 x 110 x 134 16 against 67,
+// data gradient of 16 -> 128 on 90 x 96 x 68, fp32, 2122 against 149; 3x3x3 1 -> 3 on 84 x 131 x 138, bf16, 68 against 124, 8 ->
+// 16 on 32^3, fp32, 44 against 11.  Only what does not depend on the tile grid and on the growth of the output box counts, so
+// that a voxel is computed in one order of sums on all of them.
+static bool prefer_threads(const Geo &g, int ki, int ko, sp_dtype_t dt, bool dgrad, int ks) {
+    const double vox = 1.0 * g.ntiles * g.int_vox, es = static_cast<double>(elem_size(dt));
+    const ConvDirectPlan p = conv_direct_plan(vox, (g.flat ? 1 : ks) * ks * ks, ki, ko);
+    static const double c[2][13] = {{6.83, 0.110, 0.0375, 0.0073, 0.0027, 0.0016, 0.0268, 5.16, 1.35, 0.271, 0.592, 0.476, 2.64},
+                                    {5.35, 0.000, 0.0144, 0.0105, 0.0019, 0.0015, 0.0536, 3.97, 1.13, 1.276, 3.205, 0.258, 0.574}};
+    const double *k = c[ks == 3];
+    const auto most = [](double a, double b) { return a > b ? a : b; };
+    const double row = ki * es < 64 ? ki * es / 64 : 1, lanes = ko < 64 ? ko : 64;      // lines of a record; output channels of a wave
+    const double xl = most(1, 64 / lanes * row), wl = most(1, lanes * (dgrad ? row : es / 64));
+    const double threads = k[0] + vox * ko / 64e3 * (k[1] + k[2] * p.ntap + p.ntap * ki * (k[3] + k[4] * xl + k[5] * wl)) + k[6] * p.ntap * ki;
+    const double surround = ks == 1 ? 1.0 : (g.flat ? 1.9 : 3.0);                       // staged records per voxel
+    const double quads = 64e-3 * p.nv * surround * (ki % 4 ? p.kc * k[11] : p.kc / 4);
+    const double places = p.ncg < 512 ? 512 / p.ncg : 1, wgs = vox / (64 * p.nv);
+    const double rounds = wgs <= places ? 1 : static_cast<double>(static_cast<long long>((wgs + places - 1) / places));
+    const double bricks = k[7] + rounds * (k[8] + p.nck * (k[9] + k[10] * quads + k[12] * p.steps * p.nv / 4));
+    return !(bricks < (ks == 1 ? 0.60 : 0.85) * threads);
+}
+
+int conv_direct_route(const Geo &g, int ki, int ko, sp_dtype_t dt, bool dgrad, int ks) {
+    return prefer_threads(g, ki, ko, dt, dgrad, ks) ? kRouteThreads : kRouteBricks;
+}
+
+static int launch_conv_threads(const void *Pin, const void *w, const float *bias, void *Pout, const Geo &g, int ki, int ko,
+                               sp_dtype_t dt, bool relu, bool dgrad, hipStream_t s, int ks, const void *mask, long long total) {
+    const dim3 grid(static_cast<unsigned>((total + kThreads - 1) / kThreads)), block(kThreads);
+    const auto launch = [&](auto kern, auto e) {
+        typedef decltype(e) E;
+        hipLaunchKernelGGL(kern, grid, block, 0, s, static_cast<const E *>(Pin), static_cast<const E *>(w), bias,
+                           static_cast<E *>(Pout), g, ki, ko, relu ? 1 : 0, total, static_cast<const E *>(mask));
+        return record_hip(hipGetLastError());
+    };
+    const uint16_t h = 0;
+    if (dt == SP_BF16)
+        return ks == 1 ? (dgrad ? launch(conv_threads_kernel<uint16_t, true, 1>, h) : launch(conv_threads_kernel<uint16_t, false, 1>, h))
+                       : (dgrad ? launch(conv_threads_kernel<uint16_t, true, 3>, h) : launch(conv_threads_kernel<uint16_t, false, 3>, h));
+    return ks == 1 ? (dgrad ? launch(conv_threads_kernel<float, true, 1>, 0.f) : launch(conv_threads_kernel<float, false, 1>, 0.f))
+                   : (dgrad ? launch(conv_threads_kernel<float, true, 3>, 0.f) : launch(conv_threads_kernel<float, false, 3>, 0.f));
+}
+
 int launch_conv_direct(const void *Pin, const void *w, const float *bias, void *Pout, const Geo &g,
                        int ki, int ko, sp_dtype_t dt, bool relu, bool dgrad, hipStream_t s, int ks,
                        const void *mask) {
@@ -548,21 +656,20 @@ int launch_conv_direct(const void *Pin, const void *w, const float *bias, void *
     const int ed = g.td + 2 * grow_d(g), eh = g.th + 2 * g.grow, ew = g.tw + 2 * g.grow;
     const double vox = 1.0 * g.ntiles * ed * eh * ew;
     if (vox / 16 > 0x7fffffff) return SP_EGEOM;
+    if (prefer_threads(g, ki, ko, dt, dgrad, ks) && vox * ko < 0xffffff00u)              // (a launch has less than 2^32 threads)
+        return launch_conv_threads(Pin, w, bias, Pout, g, ki, ko, dt, relu, dgrad, s, ks, mask, 1LL * g.ntiles * ed * eh * ew * ko);
+    const ConvDirectPlan p = conv_direct_plan(vox, kd * ks * ks, ki, ko);
     ConvDirectArgs a;
     a.in = Pin; a.w = w; a.bias = bias; a.out = Pout; a.mask = mask;
     a.g = g;
     a.ki = ki; a.ko = ko;
-    a.ntap = kd * ks * ks;
-    a.nck = (ki + 15) / 16;
-    a.kc = ((ki + a.nck - 1) / a.nck + 3) / 4 * 4;
-    a.nck = (ki + a.kc - 1) / a.kc;
+    a.ntap = p.ntap;
+    a.kc = p.kc; a.nck = p.nck;
     a.stride = (a.kc / 4) % 2 ? a.kc : a.kc + 4;
-    a.steps = (a.ntap * (a.kc / 4) + 3) / 4;
+    a.steps = p.steps;
     a.dgrad = dgrad; a.relu = relu;
     a.dq = make_fastdiv(a.kc / 4);
-    const int ncg = (ko + 15) / 16;
-    // 256 voxels per workgroup; fewer where that would leave the chip's 512 places (two per compute unit) empty
-    const int nv = vox / 256 * ncg >= 512 ? 4 : (vox / 128 * ncg >= 512 ? 2 : 1);
+    const int ncg = p.ncg, nv = p.nv;
     const int fixed = a.steps * (1024 + 16);
     a.b = plan_brick(g, ed, eh, ew, kd, ks, 64 * nv, (kHalfLds - fixed) / (4 * a.stride));
     const size_t lds = fixed + 4u * a.b.nrec * a.stride;

@@ -416,6 +416,11 @@ bool conv_gemm_tensor_forms(const Geo &g, int ki, int ko) {
 
 double conv_gemm_us(const Geo &g, int ki, int ko) { return plan_gemm(g, ki, ko).us; }
 
+void conv_gemm_detail(const Geo &g, int ki, int ko, int *detail) {
+    const GemmPlan p = plan_gemm(g, ki, ko);
+    detail[0] = p.cbw; detail[1] = p.vb; detail[2] = p.bl; detail[3] = p.nsplit;
+}
+
 size_t conv_gemm_ws_bytes(const Geo &g, int ki, int ko) {
     const GemmPlan p = plan_gemm(g, ki, ko);
     return p.nsplit == 1 ? 0 : static_cast<size_t>(p.nsplit) * p.nvg * wg_vox(p.vb) * ko * sizeof(float);

@@ -567,6 +567,16 @@ static bool prefer_gemm(const Geo &g, int ki, int ko) {
     return conv_gemm_us(g, ki, ko) < us;
 }
 
+int conv_mfma_route(const Geo &g, int ki, int ko, int *detail) {
+    if (prefer_gemm(g, ki, ko)) {
+        conv_gemm_detail(g, ki, ko, detail);
+        return kRouteGemm;
+    }
+    const PatchPlan p = plan_patches(g, ki, ko);
+    detail[0] = p.pairs; detail[1] = p.fold; detail[2] = p.dchunk; detail[3] = p.pairs ? ki / (2 * C) : ki / C;
+    return kRouteMarch;
+}
+
 // workspace: packed weight fragments, then (layers that need more than one launch: more than one input
 // chunk, or more than one pair of chunks when Cin is a multiple of 64) the fp32 partial sums: per workgroup
 // and wave that stores results, dchunk planes x RH rows x 4 units x 1 KB (see part_unit)

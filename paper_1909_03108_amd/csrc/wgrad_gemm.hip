@@ -379,6 +379,11 @@ bool wgrad_gemm_supported(const Geo &g, int cin, int cout) {
 
 double wgrad_gemm_us(const Geo &g, int cin, int cout) { return plan(g, cin, cout).us; }
 
+void wgrad_gemm_detail(const Geo &g, int cin, int cout, int *detail) {
+    const Plan p = plan(g, cin, cout);
+    detail[0] = p.t; detail[1] = p.lx; detail[2] = p.nsplit; detail[3] = p.staged;
+}
+
 size_t wgrad_gemm_ws_bytes(const Geo &g, int cin, int cout) {
     const Plan p = plan(g, cin, cout);
     return p.nsplit == 1 ? 0 : p.nsplit * (static_cast<size_t>(taps_of(g)) * cin * cout + cout) * sizeof(float);

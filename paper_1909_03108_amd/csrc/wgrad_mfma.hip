@@ -881,6 +881,17 @@ static bool prefer_gemm(const Geo &g, int cin, int cout) {
     return wgrad_gemm_us(g, cin, cout) < us;
 }
 
+int wgrad_mfma_route(const Geo &g, int cin, int cout, int *detail) {
+    if (prefer_gemm(g, cin, cout)) {
+        wgrad_gemm_detail(g, cin, cout, detail);
+        return kRouteGemm;
+    }
+    WgradArgs a;
+    plan(g, cin, cout, &a);
+    detail[0] = g.th % PH == 0 && g.tw % PW == 0; detail[1] = a.fold; detail[2] = a.dchunk; detail[3] = a.gpp;
+    return kRouteMarch;
+}
+
 size_t wgrad_mfma_ws_bytes(const Geo &g, int cin, int cout, WgradFamily family) {
     WgradArgs a;
     plan(g, cin, cout, &a, family == kMarchCoarse);

@@ -1,4 +1,5 @@
 """Helpers for the GPU parity tests: host<->device plumbing and the error metric."""
+import ctypes
 import sys
 import time
 
@@ -60,6 +61,16 @@ def guard_alloc(shape, dtype, fill):
 
 def guards_intact(buf, fill):
     return bool((buf[:4096] == fill).all() and (buf[-4096:] == fill).all())
+
+
+ROUTES = ["none", "first layer", "march", "gemm", "few", "padded", "bricks", "threads", "head"]
+OP_POINTWISE_FWD, OP_POINTWISE_DGRAD = 16, 17
+
+
+def route(op, g, cin, cout, dt):
+    """(kernel family that the call takes, four numbers that say how it is cut): see sp3d_route in csrc/api.hip"""
+    detail = (ctypes.c_int * 4)()
+    return ROUTES[sp3d.lib().sp3d_route(op, ctypes.byref(g), cin, cout, dt, detail)], tuple(detail)
 
 
 _T0 = time.time()

@@ -11,7 +11,7 @@ import torch
 
 from oracle import conv3d, flat as flat_oracle
 from paper_1909_03108_amd import sp3d, synth
-from gpu_util import DT, TOL, f64, rel_err, to_dev, widen
+from gpu_util import DT, TOL, f64, rel_err, route, to_dev, widen
 
 pytestmark = pytest.mark.gpu
 
@@ -32,6 +32,11 @@ CASES = [  # n, dhw, grid, cin, cout, dtype, flat
     (1, (4, 9, 13), (1, 1, 1), 6, 10, "bf16", 0),
     (1, (5, 12, 18), (1, 2, 3), 8, 20, "f32", 1),
     (1, (3, 7, 50), (1, 1, 1), 17, 5, "bf16", 1),
+    (1, (9, 14, 30), (1, 2, 2), 1, 3, "bf16", 0),       # a thread per output
+    (2, (5, 8, 12), (1, 2, 2), 2, 2, "f32", 0),
+    (1, (4, 20, 30), (1, 2, 2), 3, 2, "bf16", 1),
+    (1, (7, 30, 22), (1, 2, 1), 6, 5, "f32", 1),
+    (1, (40, 34, 36), (1, 2, 2), 1, 4, "f32", 0),
 ]
 
 
@@ -103,7 +108,33 @@ def test_grown_box_and_wide_margin_equal_the_exchange():
     assert torch.equal(out[1][inner], ref)
 
 
-@pytest.mark.parametrize("cin,cout,dtype", [(5, 7, "f32"), (48, 20, "f32"), (24, 6, "bf16")])
+def test_grown_box_of_a_thread_per_output_equals_the_exchange():
+    """The same with a thread per output, on a grid whose tiles have neighbours on one side, on both and on none."""
+    n, dhw, grid, cin, cout, dt = 2, (9, 8, 15), (3, 1, 3), 1, 3, sp3d.SP_F32
+    x, w = to_dev(synth.normal_volume((n,) + dhw + (cin,), 79, "f32")), to_dev(synth.weights(cin, cout, 80, "f32"))
+    out = []
+    for halo, grow in ((1, 0), (2, 0), (2, 1)):
+        g = sp3d.Geom(n, dhw, grid, halo, grow)
+        Px, Py = sp3d.alloc_padded(g, cin, dt), sp3d.alloc_padded(g, cout, dt)
+        assert route(sp3d.SP_OP_FWD, g, cin, cout, dt)[0] == "threads"
+        sp3d.sp_partition(x, Px, g, cin, dt)
+        sp3d.sp_halo_exchange(Px, g, cin, dt)
+        sp3d.conv3d_fwd(Px, w, None, Py, g, cin, cout, dt)
+        if not grow:
+            V = torch.empty((n,) + dhw + (cout,), device="cuda")
+            sp3d.sp_unpartition(Py, V, g, cout, dt)
+        out.append(Py if grow else V)
+    narrow = sp3d.Geom(n, dhw, grid)
+    ref = sp3d.alloc_padded(narrow, cout, dt)
+    sp3d.sp_partition(out[0], ref, narrow, cout, dt)
+    sp3d.sp_halo_exchange(ref, narrow, cout, dt)
+    inner = (slice(None),) * 4 + (slice(1, -1),) * 3
+    assert torch.equal(out[0], out[1]) and torch.equal(out[2][inner], ref)
+    assert rel_err(f64(out[0]), conv3d.conv3d_fwd(f64(x), f64(w))) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("cin,cout,dtype", [(5, 7, "f32"), (48, 20, "f32"), (24, 6, "bf16"), (130, 600, "f32"), (130, 40, "bf16"),
+                                              (256, 600, "bf16")])
 def test_extent_one_kernels(cin, cout, dtype):
     n, dhw, grid, dt = 1, (4, 6, 37), (1, 2, 1), DT[dtype]
     g = sp3d.Geom(n, dhw, grid)

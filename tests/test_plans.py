@@ -3,6 +3,8 @@ import random
 
 import pytest
 
+import test_gpu_direct as direct
+from gpu_util import DT, OP_POINTWISE_DGRAD, OP_POINTWISE_FWD, route
 from paper_1909_03108_amd import sp3d
 
 
@@ -39,3 +41,31 @@ def test_weight_gradient_never_sums_in_fewer_parts(dhw, grid, cin, cout):
     one = (27 * 32 * 32 + 32) * 4
     parts = coarse_groups(g, cin, cout) * (cin // 32) * (cout // 32)
     assert sp3d.sp_workspace_bytes(sp3d.SP_OP_WGRAD, g, cin, cout, sp3d.SP_BF16) >= parts * one
+
+
+def test_calls_of_few_products_take_a_thread_per_output():
+    """Staging bricks costs more there: 1x1x1 layers of few channels and image-like 3x3x3 ones (measured: csrc/conv_direct.hip,
+    prefer_threads).  The choice is the same on every tile grid, margin width and output box growth."""
+    f32, bf16 = sp3d.SP_F32, sp3d.SP_BF16
+    for op, dhw, cin, cout, dt in ((OP_POINTWISE_FWD, (44, 32, 44), 40, 3, bf16), (OP_POINTWISE_FWD, (44, 32, 34), 64, 4, f32),
+                                   (OP_POINTWISE_DGRAD, (128, 112, 92), 1, 4, f32), (OP_POINTWISE_FWD, (102, 110, 134), 4, 2, bf16),
+                                   (sp3d.SP_OP_FWD, (84, 130, 138), 1, 3, bf16), (sp3d.SP_OP_DGRAD, (50, 36, 46), 2, 3, f32)):
+        for grid, halo, grow in (((1, 1, 1), 1, 0), ((2, 2, 1), 1, 0), ((1, 2, 2), 2, 0), ((2, 1, 2), 2, 1)):
+            assert route(op, sp3d.Geom(1, dhw, grid, halo, grow), cin, cout, dt)[0] == "threads", (op, dhw, grid)
+    for op, dhw, cin, cout, dt in ((OP_POINTWISE_DGRAD, (90, 96, 68), 16, 128, f32), (sp3d.SP_OP_FWD, (32, 32, 32), 8, 16, f32),
+                                   (sp3d.SP_OP_DGRAD, (51, 62, 70), 16, 16, f32)):
+        assert route(op, sp3d.Geom(1, dhw, (1, 1, 1)), cin, cout, dt)[0] == "bricks", (op, dhw)
+
+
+def test_the_direct_tests_meet_both_kernels():
+    met = set()
+    for n, dhw, grid, cin, cout, dtype, flat in direct.CASES:
+        for op in (sp3d.SP_OP_FWD, sp3d.SP_OP_DGRAD):
+            met.add((op, route(op, sp3d.Geom(n, dhw, grid, 1, 0, flat), cin, cout, DT[dtype])[0], dtype, flat))
+    assert {(op, r, d) for op in (0, 1) for r in ("bricks", "threads") for d in ("f32", "bf16")} <= {m[:3] for m in met}
+    assert {(r, f) for r in ("bricks", "threads") for f in (0, 1)} <= {(m[1], m[3]) for m in met}
+    g = sp3d.Geom(1, (4, 6, 37), (1, 2, 1))
+    for cin, cout, dtype, fwd, dgrad in ((5, 7, "f32", "threads", "threads"), (130, 600, "f32", "bricks", "bricks"),
+                                         (130, 40, "bf16", "threads", "bricks"), (256, 600, "bf16", "bricks", "bricks")):
+        assert route(OP_POINTWISE_FWD, g, cin, cout, DT[dtype])[0] == fwd
+        assert route(OP_POINTWISE_DGRAD, g, cin, cout, DT[dtype])[0] == dgrad
