@@ -338,9 +338,10 @@ __global__ __launch_bounds__(kThreads) void wgrad_gemm_join_kernel(const float4 
     }
 }
 
-// Splits of the voxels: what costs least in microseconds if 256 compute units take the workgroups in rounds.  Fitted to 227
-// measured layers (7 % rms): a stage lasts 1.37 us (128 x 128 channels; 0.87 us 64 x 64), a workgroup 4.2 us besides; the
-// splits' sums are written and read at 5.8 TB/s.  They stay within SP_STATIC_SCRATCH_BYTES, so that conv3d_wgrad_static takes
+// Splits of the voxels: what costs least in microseconds if 256 compute units take the workgroups in rounds, those of 64 x 64
+// channels two at a time (LDS).  Fitted to 382 measured layers (6 % rms): a stage lasts 1.37 us (128 x 128 channels; 1.59 summed
+// by stage), 0.96 us (64 x 64; 1.2 for both of a pair of workgroups), a workgroup 8.8 and 7 us besides, launch included; the
+// splits' sums are written and read at 5.4 TB/s.  They stay within SP_STATIC_SCRATCH_BYTES, so that conv3d_wgrad_static takes
 // every layer it takes with the marching kernels.
 struct Plan { int t, lx, nsplit, nblocks, staged; double us; };
 Plan plan(const Geo &g, int cin, int cout) {
@@ -352,12 +353,16 @@ Plan plan(const Geo &g, int cin, int cout) {
     const long long nvox = 1LL * g.ntiles * g.int_vox, stages = (nvox + V - 1) / V;
     const long long tiles = (g.flat ? 3LL : 9LL) * (cin / (C * p.t)) * (cout / (C * p.t));
     const double bytes = 4.0 * (1.0 * taps_of(g) * cin * cout + cout);
+    const int groups = wgrad_march_groups(g, cin, cout);
     p.us = 0;
     p.nsplit = 1;
     for (int s = 1; s <= 256 && s <= stages && (s == 1 || (s * bytes <= SP_STATIC_SCRATCH_BYTES && tiles * s <= 1024)); ++s) {
-        const long long rounds = (tiles * s + 255) / 256;
-        const double us = 4 + rounds * (static_cast<double>((stages + s - 1) / s) * (p.t == 4 ? 1.37 : 0.87) + 4.2) +
-                          (s > 1 ? 1.9 + 2 * s * bytes / 5.8e6 : 0);
+        const long long wgs = tiles * s, left = wgs % 512;
+        const bool staged = s < 2 * groups;
+        const double n = static_cast<double>((stages + s - 1) / s);
+        double us = s > 1 ? 2.4 + 2 * s * bytes / 5.4e6 : 0;
+        if (p.t == 4) us += (wgs + 255) / 256 * (n * (staged ? 1.59 : 1.37) + 8.8);
+        else us += (wgs / 512 + (left > 256)) * (n * 1.2 + 7) + (left > 0 && left <= 256 ? n * 0.97 + 7 : 0);
         if (s == 1 || us < p.us) { p.us = us; p.nsplit = s; }
     }
     p.nblocks = static_cast<int>(tiles * p.nsplit);
@@ -366,7 +371,7 @@ Plan plan(const Geo &g, int cin, int cout) {
     // keeps the error below theirs (against 64 bits, marching, one sum, per stage: 512 -> 64 on 18 x 16 x 16 1.1e-7, 2.2e-7,
     // 1.1e-7; 128 -> 512 on 17 x 24 x 22 2.7e-7, 2.8e-7, 1.2e-7; 2-D 128 -> 64 on 2 x 288 x 256 2.9e-7, 3.8e-7, 1.6e-7).  It costs
     // 32 (T = 4) additions per wave for 16 products: 1024 -> 1024, 2-D, 16 x 32 x 32 376 -> 426 us.
-    p.staged = p.nsplit < 2 * wgrad_march_groups(g, cin, cout);
+    p.staged = p.nsplit < 2 * groups;
     return p;
 }
 

@@ -746,10 +746,17 @@ __global__ __launch_bounds__(kThreads) void wgrad_mfma_dma_kernel(WgradArgs a) {
     if (tid < C) a.part_b[slot * C + tid] = red[tid] + red[C + tid];
 }
 
-// Microseconds of one work item: its start and its planes (fitted, see prefer_gemm).
-double item_us(const Geo &g, int planes) {
-    const bool dma = g.th % PH == 0 && g.tw % PW == 0;
-    return (g.flat ? (dma ? 1.35 : 0.27) : (dma ? 0.0 : 2.17)) + planes * (g.flat ? (dma ? 1.34 : 1.42) : (dma ? 2.5 : 2.36));
+// Estimated microseconds of a cutting into `items` items of `planes` planes (surround included) per channel pair, on `gpp`
+// workgroups per pair: launches, rounds of the compute units x items x (start, planes), and the partial sums out and in - in at
+// less than half the rate where eight neighbouring lanes share an output (see reduce_wgrad_kernel).  The columns are 3-D and
+// 2-D, ragged and whole 8 x 32 patches.  Fitted to 382 layers, each cut coarsely and finely (64 ... 1024 channels, 64 ... 4
+// million voxels; 7 % rms).
+double march_us(const Geo &g, int planes, long long items, long long gpp, int npairs) {
+    static const double base[4] = {14.6, 5.0, 10.2, 3.2}, start[4] = {0.77, 0, 0, 2.7}, plane[4] = {2.39, 2.75, 1.48, 1.38};
+    const int k = 2 * g.flat + (g.th % PH == 0 && g.tw % PW == 0);
+    const double groups = static_cast<double>(gpp) * npairs, bytes = 4096.0 * groups * taps_of(g);
+    const double rounds = (gpp * npairs + kMaxGroups - 1) / kMaxGroups * ((items + gpp - 1) / gpp);
+    return base[k] + rounds * (start[k] + planes * plane[k]) + bytes / 6.5e6 + (gpp >= 8 ? 0.5 + bytes / 2.4e6 : bytes / 6.1e6);
 }
 
 void plan(const Geo &g, int cin, int cout, WgradArgs *a, bool coarse = false) {
@@ -773,24 +780,27 @@ void plan(const Geo &g, int cin, int cout, WgradArgs *a, bool coarse = false) {
         while (f > 1 && g.td % f) --f;
         a->fold = f;
     }
-    // D chunk: halved until there is an item per workgroup, never below 16 planes (`coarse`: that and no more); below that,
-    // what costs least if the gpp workgroups of a pair take the items in rounds - an item's start and its planes with the two
-    // of the surround - and every workgroup's partial result goes out and in at about 3 TB/s.  (The first rule alone ran 32 ->
-    // 32 on 32^3 on 8 workgroups and 99 x 156 x 210 on 1 x 2 x 2 tiles on two rounds of 52 planes instead of two of 35: 43 ->
-    // 19 us and 290 -> 211 us.)  Longer chunks than the first rule's are not taken: fewer workgroups have longer chains of fp32
-    // sums (64 -> 96 on 74 x 38 x 69, 17 % more error for 10 % of the time).
+    // D chunk: halved until there is an item per workgroup, never below 16 planes (`coarse`: that and no more); below that, the
+    // one of least estimated cost where that saves at least 8 %.  (The first rule alone ran 32 -> 32 on 32^3 on 8 workgroups
+    // and 99 x 156 x 210 on 1 x 2 x 2 tiles on two rounds of 52 planes instead of two of 35: 43 -> 19 us and 290 -> 211 us.
+    // With partial sums priced at 3 TB/s out and in, cutting finer cost time where it took a pair from 4 to 8 workgroups: 512
+    // -> 64 on 10 x 11 x 10 48 -> 60 us, 192 -> 128 on 22 x 16 x 27 48 -> 53.)  Longer chunks than the first rule's are not
+    // taken: fewer workgroups have longer chains of fp32 sums (64 -> 96 on 74 x 38 x 69, 11 % more error for 10 % of the time).
     const int steps = (g.td + a->fold - 1) / a->fold;
     int d0 = g.td;
     while (base * ((g.td + d0 - 1) / d0) < gpp && d0 > 16) d0 = (d0 + 1) / 2;
     int best = (d0 + a->fold - 1) / a->fold;
     if (!coarse) {
+        const auto cost = [&](int d) {
+            const long long items = base * ((steps + d - 1) / d);
+            return march_us(g, d + 2, items, items < gpp ? items : gpp, npairs);
+        };
         const int k0 = (steps + best - 1) / best;
-        double cost = 0;
-        for (int k = k0; k <= steps && (k == k0 || base * k <= 8LL * gpp); ++k) {
+        double least = 0.92 * cost(best);
+        for (int k = k0; k <= steps && base * k <= 8LL * gpp; ++k) {
             const int d = (steps + k - 1) / k;
-            const long long items = base * ((steps + d - 1) / d), groups = items < gpp ? items : gpp;
-            const double us = (items + groups - 1) / groups * item_us(g, d + 2) + 8192.0 * groups * npairs * taps_of(g) / 3e6;
-            if (k == k0 || us < cost) { cost = us; best = d; }
+            const double us = cost(d);
+            if (d <= best && us < least) { least = us; best = d; }
         }
     }
     const int dchunk = best * a->fold;
@@ -865,20 +875,17 @@ int wgrad_march_groups(const Geo &g, int cin, int cout) {
 // Which family serves a layer: the marching kernels of this file, or the GEMM over voxels of wgrad_gemm.hip.  The march
 // reuses a staged x plane for 27 taps and wins in 3-D where tiles are whole patches and the volume is large; it loses where
 // patches are mostly empty, where a workgroup per channel pair has only a plane or two to march over, and in 2-D with many
-// channels (9 taps per staged plane: its LDS reads bound it).  Both times are estimated, marching: rounds of the compute
-// units x items per workgroup x (start + planes), the partial results out and in, launches.  Fitted to 227 layers measured
-// with both families (64 ... 1024 channels, 64 ... 1 million voxels; 8 % and 7 % rms); choosing by the estimates costs
-// 0.3 % over the better family of each.  Measured, marching -> GEMM: 3-D 256 -> 256 channels on 4^3 35 -> 9 us, on 8^3
-// 40 -> 19, 64 -> 64 on 32^3 48 -> 31, 256 -> 256 there 118 against 193 (stays); 1024 -> 1024 on 16^3 498 -> 285; 2-D, 16
-// slices: 1024 -> 1024 on 16 x 16 276 -> 106, 512 -> 512 on 32 x 32 217 -> 135, 256 -> 256 on 128 x 128 516 -> 431, 64 ->
-// 64 there 38 against 61 (stays).
+// channels (9 taps per staged plane: its LDS reads bound it).  Both times are estimated (march_us; plan in wgrad_gemm.hip, 6 %
+// rms) and the GEMM is taken where it is ahead by 7 %; over the 382 layers that costs 0.1 % over the better family of each, and
+// none is slower than on the march.  Measured, marching -> GEMM: 3-D 256 -> 256 channels on 4^3 33 -> 10 us, on 8^3 43 -> 21,
+// 64 -> 64 on 32^3 48 -> 32; 1024 -> 1024 on 16^3 458 -> 319; 2-D, 16 slices: 1024 -> 1024 on 16 x 16 274 -> 118, 512 -> 512 on
+// 32 x 32 219 -> 140; 2-D 128 -> 128 on 2 x 32 x 64 16 against 21 (stays), 64 -> 64 on 2 x 1 x 64 x 64 13.2 against 15.5 (stays).
 static bool prefer_gemm(const Geo &g, int cin, int cout) {
     if (!wgrad_gemm_supported(g, cin, cout)) return false;
     WgradArgs a;
     plan(g, cin, cout, &a);
-    const double rounds = (a.ngroups + kMaxGroups - 1) / kMaxGroups, items = (a.nitems + a.gpp - 1) / a.gpp;
-    const double us = 8.3 + rounds * items * item_us(g, (a.dchunk + a.fold - 1) / a.fold + 2) + 8192.0 * a.ngroups * taps_of(g) / 3e6 + (a.gpp >= 8 ? 1 : 0);
-    return wgrad_gemm_us(g, cin, cout) < us;
+    const double us = march_us(g, (a.dchunk + a.fold - 1) / a.fold + 2, a.nitems, a.gpp, a.ngroups / a.gpp);
+    return wgrad_gemm_us(g, cin, cout) < 0.93 * us;
 }
 
 int wgrad_mfma_route(const Geo &g, int cin, int cout, int *detail) {
