@@ -518,20 +518,28 @@ static PatchPlan plan_patches(const Geo &g, int ki, int ko) {
         while (f > 1 && g.td % f) --f;
         p.fold = f;
     }
-    // D chunk: what costs least if the 256 compute units (one workgroup each: LDS) take the workgroups in rounds, a
+    // D chunk: the whole depth, halved until there are 1024 workgroups but never below 16 planes; or, where that is estimated to
+    // save at least 5 %, what costs least if the 256 compute units (one workgroup each: LDS) take the workgroups in rounds, a
     // round lasting as long as its march - the chunk's planes, the two of the surround (and two that drain the hand-over
     // between the two chunks of a pair), and what a march costs before its first plane, in steps: the weights and three
     // planes on their way, about 6 us = 4 plane steps in 3-D and 16 of the shorter ones in 2-D (2 ... 8 and 4 ... 16
-    // measured within 1 %).  Before, a chunk was never below 16 planes: 8 workgroups for a layer on 32^3.  256 -> 256 on
-    // 32^3 (128 workgroups of 16 planes -> 256 of 8): 48 -> 35 us a launch; training step of the four-level network on 32^3 2.02 -> 1.55 ms;
-    // 32 -> 32 on 128^3 (512 workgroups of 16 planes -> 256 of 32) 117 -> 104 us.
+    // measured within 1 %).  (The first rule alone gives 8 workgroups to a layer on 32^3: 256 -> 256 there (128 workgroups of 16
+    // planes -> 256 of 8) 48 -> 35 us a launch, 32 -> 32 on 128^3 (512 of 16 -> 256 of 32) 117 -> 104 us.  Taken on any saving, the
+    // second cost time where it only merged chunks: 64 -> 256 on 38 x 34 x 47, 2 x 2 x 1 tiles, 99 -> 107 us, 192 -> 64 on 64 x 147
+    // x 116 839 -> 896; less than a workgroup per compute unit takes a tenth more than its round: 512 -> 96 on 40 x 76 x 66 as 171
+    // workgroups 906 us, as 684 825.)
     const int steps = (ed + p.fold - 1) / p.fold, over = (g.flat ? 16 : 4) + (p.pairs ? 4 : 2);
-    int best = steps;
-    long long cost = (base + 255) / 256 * (steps + over);
-    for (int k = 2; k <= steps && base * k <= 2048; ++k) {
+    const auto cost = [&](int d) {
+        const long long n = base * ((steps + d - 1) / d);
+        return static_cast<double>((n + 255) / 256 * (d + over)) * (n < 256 ? 1.1 : 1.0);
+    };
+    int d0 = ed;
+    while (base * ((ed + d0 - 1) / d0) < 1024 && d0 > 16) d0 = (d0 + 1) / 2;
+    int best = (d0 + p.fold - 1) / p.fold;
+    double least = 0.95 * cost(best);
+    for (int k = 1; k == 1 || (k <= steps && base * k <= 2048); ++k) {
         const int d = (steps + k - 1) / k;
-        const int c = (static_cast<int>(base) * ((steps + d - 1) / d) + 255) / 256 * (d + over);
-        if (c < cost) { cost = c; best = d; }
+        if (cost(d) < least) { least = cost(d); best = d; }
     }
     const int dchunk = best * p.fold;
     p.dchunk = dchunk;
