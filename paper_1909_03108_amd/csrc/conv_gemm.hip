@@ -366,17 +366,18 @@ __global__ __launch_bounds__(kGemmThreads) void conv_gemm_join_kernel(GemmArgs a
 struct Box { int ed, eh, ew; };
 Box max_box(const Geo &g) { return Box{g.td + 2 * grow_d(g), g.th + 2 * g.grow, g.tw + 2 * g.grow}; }
 
-struct GemmPlan { int cbw, vb, bl, nsplit, nvg, nblocks; long long nvox; double us; };
+struct GemmPlan { int cbw, vb, bl, nsplit, nvg, nblocks; long long nvox; double us; };     // us: estimated time
 // records that 128 vb consecutive voxels touch at most, in wave loads of 16 per wave
 int record_loads(int vb, int ew) {
     const int n = wg_vox(vb), rows = n % ew == 0 ? n / ew - 1 : (n + ew - 2) / ew;
     return (n + 2 + 2 * rows + 63) / 64;
 }
 // Voxels per workgroup and splits of the K loop: what costs least in microseconds if 256 compute units take the workgroups
-// in rounds.  Fitted to 352 measured layers (64 ... 1024 channels, 64 ... 1 million voxels, 2-D and 3-D; 10 % rms): a step
-// lasts 0.41 us per 128 voxels x 64 channels, a workgroup 10.7 us besides (launch, first loads, stores); splitting adds a
-// second launch and a write and a read of every sum at about 6 TB/s.  The interior voxels alone decide, so that the order
-// of the sums is the same for every output box growth and tile grid.
+// in rounds: a step lasts 0.41 us per 128 voxels x 64 channels, a workgroup 10.7 us besides (launch, first loads, stores);
+// splitting adds a second launch and a write and a read of every sum at about 6 TB/s.  The interior voxels alone decide, so
+// that the order of the sums is the same for every output box growth and tile grid.  The time that is then compared with the
+// marching kernels' has constants of its own, fitted to 472 layers cut this way (32 ... 1024 channels, 64 voxels ... 4 million,
+// 2-D and 3-D; 11 % rms): the layers of 64 channels a workgroup take 7 % longer than the first constants say.
 GemmPlan plan_gemm(const Geo &g, int ki, int ko) {
     GemmPlan p;
     const Box b = max_box(g);
@@ -384,13 +385,17 @@ GemmPlan plan_gemm(const Geo &g, int ki, int ko) {
     const int nco = ko / C, nk = ki / C * (g.flat ? 3 : 9);
     const long long nint = 1LL * g.ntiles * g.int_vox;
     p.cbw = nco % 4 == 0 ? 2 : 1;
-    p.us = 0;
+    double least = 0;
     for (int vb = 1; vb <= 2; ++vb) {
         const long long tiles = (nint + wg_vox(vb) - 1) / wg_vox(vb) * (nco / (2 * p.cbw));
         for (int s = 1; s == 1 || (s <= nk / 4 && s <= 64 && tiles * s <= 1024); ++s) {
-            const long long rounds = (tiles * s + 255) / 256;
-            const double us = 4 + rounds * ((nk + s - 1) / s * 0.41 * vb * p.cbw + 10.7) + (s > 1 ? 2 + 8.0 * s * nint * ko / 6e6 : 0);
-            if ((vb == 1 && s == 1) || us < p.us) { p.us = us; p.vb = vb; p.nsplit = s; }
+            const double rounds = static_cast<double>((tiles * s + 255) / 256), steps = (nk + s - 1) / s;
+            const double sums = 8.0 * s * nint * ko / 1e6;
+            const double us = 4 + rounds * (steps * 0.41 * vb * p.cbw + 10.7) + (s > 1 ? 2 + sums / 6 : 0);
+            if ((vb == 1 && s == 1) || us < least) {
+                least = us; p.vb = vb; p.nsplit = s;
+                p.us = 4 + rounds * (steps * 0.44 * (vb == 2 ? 2.09 : 1) * (p.cbw == 2 ? 1.78 : 1) + 9.85) + (s > 1 ? 0.73 + sums / 3.74 : 0);
+            }
         }
     }
     p.bl = record_loads(p.vb, b.ew);

@@ -552,13 +552,17 @@ static PatchPlan plan_patches(const Geo &g, int ki, int ko) {
 // kernels reuse a staged plane for 27 (9) taps and win where the volume fills the chip with long marches; they lose where
 // a launch per pair of input chunks carries little work (few voxels, many channels), where stacks of slices are thin and
 // where patches are mostly empty.  Both times are estimated from what bounds them, marching: launches x (rounds of the
-// 256 compute units x (start + planes) + launch) + the partial sums between launches.  The constants are fitted to 352
-// layers measured with both families (64 ... 1024 channels, 64 ... 1 million voxels; 8 % and 10 % rms); choosing by the
-// estimates costs 0.8 % over the better family of each.  Measured, marching -> GEMM: 3-D 256 -> 256 channels on 4^3 53 ->
-// 21 us, on 16^3 79 -> 34, on 32^3 146 -> 122, 128 -> 128 on 28 x 44 x 52 96 -> 71, on 64^3 207 against 267 (stays);
-// 2-D 256 -> 256 on 16 x 64^2 152 -> 107, on 16 x 128^2 627 -> 398, 128 -> 128 on 2 x 256^2 173 -> 73, 64 -> 64 on
-// 16 x 256^2 142 against 254 (stays).  The estimate is that of the whole volume as one tile, so that a layer takes the
-// same family, and sums in the same order, on every tile grid and with every output box growth.
+// 256 compute units x (start + planes) + launch) + the partial sums between launches.  The constants are fitted to 472
+// layers measured with both families on their own tile grids (32 ... 1024 channels, 3-D from 64 voxels to 4 million, W split
+// in one to four, 2-D to 700 000, on up to 1 x 4 x 4 tiles; 8 % and 11 % rms).  The estimate is that of the whole volume as
+// one tile, so that a layer takes the same family, and sums in the same order, on every tile grid and with every output box
+// growth; a grid that cuts W into pieces of less than a patch makes the march slower than that.  Over the 472 layers the
+// choice costs 3.4 % over the better family of each on its grid (with the estimate of the grid itself it would be 0.4 %; most
+// of it on tiles of less than 24 columns), but against marching always none loses more than 4 %: in 2-D with a single launch,
+// where the march has only its start to lose, the GEMM has to be ahead by 15 % for that.  Measured, marching -> GEMM: 3-D 256
+// -> 256 channels on 4^3 53 -> 21 us, on 16^3 79 -> 34, on 32^3 146 -> 122, 128 -> 128 on 28 x 44 x 52 96 -> 71; 128 -> 64 on 56 x
+// 88 x 104 279 against 328 (stays), 128 -> 128 on 64^3 196 against 279 (stays); 2-D 256 -> 256 on 16 x 64^2 152 -> 107, 128 ->
+// 128 on 2 x 256^2 173 -> 73, 64 -> 256 on 5 x 240 x 177 156 against 172 (stays).
 static bool prefer_gemm(const Geo &g, int ki, int ko) {
     if (!conv_gemm_supported(g, ki, ko)) return false;
     if (conv_gemm_tensor_forms(g, ki, ko)) return true;
@@ -568,11 +572,11 @@ static bool prefer_gemm(const Geo &g, int ki, int ko) {
     v.grow = 0;
     const PatchPlan p = plan_patches(v, ki, ko);
     const int launches = p.pairs ? ki / (2 * C) : ki / C;
-    const double rounds = static_cast<double>((p.nblocks + 255) / 256), planes = p.dchunk / p.fold;
+    const double rounds = static_cast<double>((p.nblocks + 255) / 256), planes = (p.dchunk + p.fold - 1) / p.fold;
     const double sums = 8.0 * g.ntiles * g.int_vox * ko * (launches - 1);             // bytes written and read
-    const double us = g.flat ? 4 + launches * rounds * (6.6 + 1.4 * planes) + sums / 9.2e6
-                             : 4 + launches * (rounds * (5.7 + (p.pairs ? 2.5 : 2.0) * planes) + 4.5) + sums / 8.3e6;
-    return conv_gemm_us(g, ki, ko) < us;
+    const double us = g.flat ? 2 + launches * (rounds * (6.3 + (p.pairs ? 1.35 : 1.44) * planes) + 0.6) + sums / 7.4e6
+                             : 2 + launches * (rounds * (7.2 + (p.pairs ? 2.56 : 2.63) * planes) + 3.6) + sums / 10.3e6;
+    return conv_gemm_us(g, ki, ko) < (g.flat && launches == 1 ? 0.85 : 1.0) * us;
 }
 
 int conv_mfma_route(const Geo &g, int ki, int ko, int *detail) {

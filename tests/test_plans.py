@@ -69,3 +69,18 @@ def test_the_direct_tests_meet_both_kernels():
                                          (130, 40, "bf16", "threads", "bricks"), (256, 600, "bf16", "bricks", "bricks")):
         assert route(OP_POINTWISE_FWD, g, cin, cout, DT[dtype])[0] == fwd
         assert route(OP_POINTWISE_DGRAD, g, cin, cout, DT[dtype])[0] == dgrad
+
+
+@pytest.mark.parametrize("dhw, cin, cout, flat, family", [
+    ((56, 88, 104), 128, 64, 0, "march"), ((64, 64, 64), 128, 128, 0, "march"), ((128, 128, 128), 128, 64, 0, "march"),
+    ((4, 4, 4), 256, 256, 0, "gemm"), ((16, 16, 16), 256, 256, 0, "gemm"), ((28, 44, 52), 128, 128, 0, "gemm"),
+    ((6, 48, 44), 64, 1024, 1, "march"), ((5, 240, 176), 64, 256, 1, "march"), ((16, 64, 64), 256, 256, 1, "gemm"),
+    ((2, 256, 256), 128, 128, 1, "gemm"), ((16, 256, 256), 64, 64, 1, "march")])
+def test_forward_family_of_layers_measured_both_ways(dhw, cin, cout, flat, family):
+    """The faster family of each (measured: csrc/conv_mfma.hip, prefer_gemm), the same on every tile grid and for every output
+    box growth, so that the sums are taken in one order."""
+    for grid, halo, grow in (((1, 1, 1), 1, 0), ((1, 2, 2), 1, 0), ((1, 4, 2), 2, 1), ((2, 1, 4), 1, 0)):
+        if all(e % k == 0 and (e // k >= halo or (flat and i == 0)) for i, (e, k) in enumerate(zip(dhw, grid))):
+            g = sp3d.Geom(1, dhw, grid, halo, grow, flat)
+            assert route(sp3d.SP_OP_FWD, g, cin, cout, sp3d.SP_BF16)[0] == family, grid
+            assert route(sp3d.SP_OP_DGRAD, g, cout, cin, sp3d.SP_BF16)[0] == family, grid
