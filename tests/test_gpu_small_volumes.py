@@ -63,9 +63,11 @@ CHUNKS = [  # n, dhw, grid, cin, cout, flat
     (1, (7, 6, 20), (1, 1, 1), 64, 32, 0),          # two input chunks per launch
     (1, (22, 16, 32), (1, 2, 1), 128, 32, 0),       # ... and partial sums (first and last launch)
     (1, (33, 40, 70), (1, 1, 1), 192, 96, 0),       # ... a middle launch; chunks of several planes, a shorter last one
-    (1, (9, 12, 10), (1, 2, 1), 64, 64, 1),         # 2-D: slices side by side
+    (1, (9, 12, 10), (1, 2, 1), 64, 64, 1),
     (1, (7, 24, 66), (1, 1, 1), 32, 64, 1),
     (1, (5, 24, 66), (1, 2, 1), 128, 64, 1),
+    (1, (8, 12, 10), (1, 2, 1), 32, 64, 1),         # 2-D: two and three slices side by side
+    (2, (6, 9, 9), (1, 1, 1), 64, 32, 1),
 ]
 
 
@@ -109,6 +111,19 @@ def test_layers_taken_over_by_the_implicit_gemm(case):
     three_passes(*case, seed=5500 + 10 * NARROW_GEMM.index(case))
 
 
+SPLIT_TILES = [  # tiles of 256 voxels and several splits: both numbers of output blocks per wave, whole and ragged last tiles
+    (1, (5, 32, 32), (1, 2, 2), 512, 512, 1),
+    (1, (5, 33, 31), (1, 1, 1), 512, 512, 1),
+    (1, (2, 96, 96), (1, 2, 2), 256, 64, 0),
+    (1, (2, 94, 98), (1, 2, 2), 256, 64, 0),
+]
+
+
+@pytest.mark.parametrize("case", SPLIT_TILES, ids=lambda c: "%dx%dx%d-%dto%d%s" % (c[1] + c[3:5] + ("-2d" if c[5] else "",)))
+def test_split_sums_of_the_larger_tiles(case):
+    three_passes(*case, seed=6700 + 10 * SPLIT_TILES.index(case))
+
+
 @pytest.mark.parametrize("n, dhw, grid, cin, cout", [(1, (4, 4, 4), (4, 2, 2), 128, 128), (2, (6, 5, 9), (2, 1, 3), 192, 64),
                                                      (1, (12, 18, 10), (3, 3, 2), 128, 256)])
 def test_implicit_gemm_gathers_halos_and_keeps_bits(n, dhw, grid, cin, cout):
@@ -116,10 +131,18 @@ def test_implicit_gemm_gathers_halos_and_keeps_bits(n, dhw, grid, cin, cout):
     check_bits(n, dhw, grid, cin, cout)
 
 
-def test_implicit_gemm_grown_boxes_and_two_tensors():
+GROWN = [  # dhw, grid, ca, cb, cout: input in two tensors; output as well; tiles of 256 voxels with several splits
+    ((8, 10, 14), (2, 2, 2), 96, 64, 192),
+    ((8, 10, 14), (2, 2, 2), 96, 96, 192),
+    ((2, 96, 96), (1, 2, 2), 160, 96, 64),
+]
+
+
+@pytest.mark.parametrize("dhw, grid, ca, cb, co", GROWN)
+def test_implicit_gemm_grown_boxes_and_two_tensors(dhw, grid, ca, cb, co):
     """A grown output box on margins two voxels wide, input and output in two tensors, at odd chunk counts: bit for bit
     what the one-voxel margins, the concatenation and the single tensor give."""
-    n, dhw, grid, ca, cb, co, dt = 1, (8, 10, 14), (2, 2, 2), 96, 64, 192, DT["bf16"]
+    n, dt = 1, DT["bf16"]
     g1, g2 = sp3d.Geom(n, dhw, grid), sp3d.Geom(n, dhw, grid, 2, 1)
     x = synth.normal_volume((n,) + dhw + (ca + cb,), 5700, "bf16")
     dz = synth.normal_volume((n,) + dhw + (co,), 5701, "bf16")
@@ -177,9 +200,14 @@ def test_weight_gradient_as_a_gemm(case):
     three_passes(*case, seed=5900 + 10 * WGRAD_GEMM.index(case))
 
 
+WGRAD_GATHER = [  # gathered halos: both channel tiles, one running sum and a sum per stage
+    ((4, 16, 64), (2, 2, 2), 64, 128), ((1, 16, 32), (1, 2, 1), 64, 64), ((1, 32, 128), (1, 2, 2), 128, 128),
+    ((1, 16, 64), (1, 2, 1), 384, 384)]
+
+
 def test_weight_gradient_gemm_gathers_and_takes_two_tensors():
-    check_gathered_halos(1, (4, 16, 64), (2, 2, 2), 64, 128)
-    check_gathered_halos(1, (2, 16, 32), (2, 2, 1), 128, 128)
+    for dhw, grid, cin, cout in WGRAD_GATHER:
+        check_gathered_halos(1, dhw, grid, cin, cout)
     n, dhw, grid, ca, cb, co, dt = 1, (4, 6, 10), (2, 2, 1), 32, 96, 64, DT["bf16"]
     g = sp3d.Geom(n, dhw, grid)
     x = synth.normal_volume((n,) + dhw + (ca + cb,), 6001, "bf16")
@@ -222,8 +250,10 @@ FINE_WGRAD = [  # D chunks of the marching weight gradient: one and two planes, 
     (1, (22, 16, 64), (2, 1, 2), 32, 96, 0),
     (1, (13, 9, 34), (1, 1, 1), 96, 32, 0),
     (1, (11, 6, 40), (1, 2, 1), 3, 32, 0),
-    (1, (9, 12, 10), (1, 2, 1), 32, 32, 1),         # 2-D: slices side by side
+    (1, (9, 12, 10), (1, 2, 1), 32, 32, 1),
     (1, (6, 16, 96), (1, 2, 1), 5, 64, 1),
+    (1, (8, 12, 10), (1, 2, 1), 32, 32, 1),         # 2-D: slices side by side
+    (2, (6, 9, 9), (1, 1, 1), 64, 32, 1),
 ]
 
 
@@ -259,6 +289,7 @@ FEW = [  # first layers of 2 ... 8 channels: both record sizes, odd channel coun
     (1, (3, 8, 50), (1, 2, 1), 3, 32, 1),
     (1, (7, 10, 36), (1, 2, 2), 7, 64, 1),
     (1, (1, 200, 210), (1, 1, 1), 5, 32, 1),        # several bricks per workgroup
+    (1, (5, 7, 35), (1, 1, 1), 6, 32, 0),
 ]
 
 

@@ -4,6 +4,7 @@ import random
 import pytest
 
 import test_gpu_direct as direct
+import test_gpu_small_volumes as small
 from gpu_util import DT, OP_POINTWISE_DGRAD, OP_POINTWISE_FWD, route
 from paper_1909_03108_amd import sp3d
 
@@ -84,3 +85,57 @@ def test_forward_family_of_layers_measured_both_ways(dhw, cin, cout, flat, famil
             g = sp3d.Geom(1, dhw, grid, halo, grow, flat)
             assert route(sp3d.SP_OP_FWD, g, cin, cout, sp3d.SP_BF16)[0] == family, grid
             assert route(sp3d.SP_OP_DGRAD, g, cout, cin, sp3d.SP_BF16)[0] == family, grid
+
+
+FWD, DGRAD, WGRAD, BF16 = sp3d.SP_OP_FWD, sp3d.SP_OP_DGRAD, sp3d.SP_OP_WGRAD, sp3d.SP_BF16
+
+
+def routes(op, cases):
+    return [route(op, sp3d.Geom(n, dhw, grid, 1, 0, flat), cin, cout, BF16) for n, dhw, grid, cin, cout, flat in cases]
+
+
+def test_the_forward_gemm_tests_meet_the_gemm():
+    """tests/test_gpu_small_volumes.py runs the implicit GEMM in every shape that it is compiled in, with and without a split."""
+    met = {d[:3] + (d[3] > 1,) for op in (FWD, DGRAD) for f, d in routes(op, small.GEMM + small.NARROW_GEMM + small.SPLIT_TILES +
+                                                                          small.WGRAD_GEMM) if f == "gemm"}
+    assert {(c, v, b) for c in (1, 2) for v, b in ((1, 3), (1, 4), (1, 6), (2, 5), (2, 6))} <= {m[:3] for m in met}
+    assert {(c, v, s) for c in (1, 2) for v in (1, 2) for s in (False, True)} <= {(m[0], m[1], m[3]) for m in met}
+    for cases in (small.GEMM, small.NARROW_GEMM, small.SPLIT_TILES):
+        assert all(f == "gemm" for f, _ in routes(FWD, cases))
+    assert all(f == "gemm" for f, _ in routes(DGRAD, small.GEMM))
+    assert all(d[1] == 2 and d[3] > 1 for _, d in routes(FWD, small.SPLIT_TILES))
+    shapes = []
+    for dhw, grid, ca, cb, co in small.GROWN:
+        for g in (sp3d.Geom(1, dhw, grid), sp3d.Geom(1, dhw, grid, 2, 1)):
+            assert route(FWD, g, ca + cb, co, BF16)[0] == "gemm"
+            shapes.append((route(FWD, g, ca + cb, co, BF16)[1][1], route(DGRAD, g, ca + cb, co, BF16)[0]))
+    assert {(1, "gemm"), (2, "march")} <= set(shapes)
+
+
+def test_the_marching_tests_meet_the_march():
+    """... and the marching kernels with one and with two chunks per launch, with and without partial sums, slices side by side."""
+    fwd = routes(FWD, small.CHUNKS)
+    assert all(f == "march" for f, _ in fwd)
+    assert {(p, l > 1) for _, (p, _, _, l) in fwd} >= {(0, False), (1, False), (1, True)}
+    assert any(d < case[1][0] // case[2][0] for case, (_, (_, _, d, _)) in zip(small.CHUNKS, fwd))
+    assert {f for _, (_, f, _, _) in fwd} == {1, 2, 3}
+    wgrad = routes(WGRAD, small.FINE_WGRAD)
+    assert all(f in ("march", "padded") for f, _ in wgrad)
+    cut = [(whole, 1 < d, d < case[1][0] // case[2][0]) for case, (f, (whole, _, d, _)) in zip(small.FINE_WGRAD, wgrad) if f == "march"]
+    assert {c[0] for c in cut if c[2]} == {0, 1}
+    assert {d[1] for f, d in wgrad if f == "march"} == {1, 2, 3}
+
+
+def test_the_voxel_gemm_tests_meet_the_gemm():
+    """... and the weight gradient as a GEMM over voxels in every shape that it is compiled in."""
+    plans = routes(WGRAD, small.WGRAD_GEMM) + routes(WGRAD, [(1,) + c + (0,) for c in small.WGRAD_GATHER])
+    assert all(f == "gemm" for f, _ in plans)
+    assert {(t, x) for t in (2, 4) for x in (5, 6, 8)} <= {d[:2] for _, d in plans}
+    assert {(t, s) for t in (2, 4) for s in (0, 1)} <= {(d[0], d[3]) for _, d in plans[:len(small.WGRAD_GEMM)]}
+    assert {(t, s) for t in (2, 4) for s in (0, 1)} <= {(d[0], d[3]) for _, d in plans[len(small.WGRAD_GEMM):]}
+    assert {True, False} == {d[2] > 1 for _, d in plans}
+
+
+def test_the_few_channel_tests_meet_their_kernel():
+    assert all(f == "few" for f, _ in routes(FWD, small.FEW))
+    assert {c[3] for c in small.FEW} == set(range(2, 9))
