@@ -284,7 +284,8 @@ static int check_conv_args(const void *a, const void *b, const void *c, const sp
     return SP_OK;
 }
 
-// forward kernels that can write the one-bit ReLU mask: the 3-D marching kernels and the one-input-channel layer
+// forward kernels that can write the one-bit ReLU mask: the 3-D marching kernels, the implicit GEMM outside the widest layers on
+// the fewest voxels, and the one-input-channel layer
 static bool fwd_bits_supported(const Geo &o, int cin, int cout, sp_dtype_t dt) {
     return conv_mfma_bits_supported(o, cin, cout, dt) ||
            (!conv_mfma_supported(o, cin, cout, dt) && o.grow == 0 && conv_c1_supported(o, cin, cout, dt));
@@ -319,7 +320,7 @@ static int fwd_impl(const void *Px, const void *w, const float *bias, void *Py, 
     if (o.grow == 0 && conv_c1_supported(o, cin, cout, dt))
         return launch_conv_c1_fwd(shifted(Px, o, 1, dt), w, bias, shifted(Py, o, cout, dt), o, cout, relu, s,
                                   bits ? static_cast<char *>(bits) + interior_shift(o) * (cout / 32) * 4 : nullptr);
-    // few input channels: zero-padded copies in the workspace, then the matrix-core kernel
+    // channels no multiple of 32: zero-padded copies in the workspace, then the matrix-core kernel
     if (!conv_c1_supported(o, cin, cout, dt) && chan_pad_supported(o, cin, cout, dt)) {
         const size_t need = chan_pad_fwd_ws_bytes(o, cin, cout);
         if (!ws || ws_bytes < need || !aligned16(ws)) return SP_EWORKSPACE;

@@ -1,6 +1,7 @@
-// Layers with few input channels on the matrix cores: the input tensor and the weights are copied with their
-// input-channel axis zero-padded to a multiple of 32 (into the workspace), the matrix-core kernels run on the
-// copies, and the weight gradient drops the padding rows again.  The zero channels contribute exact zeros, so
+// Layers whose input channels are no multiple of 32 on the matrix cores: the input tensor and the weights are copied with
+// their input-channel axis zero-padded to a multiple of 32 (into the workspace), the matrix-core kernels run on the
+// copies, and the weight gradient drops the padding rows again.  (The forward pass of 2 ... 8 channels needs no copies:
+// conv_few.hip.)  The zero channels contribute exact zeros, so
 // the results are those of the unpadded contraction with the same fp32 accumulation.  The copies are plain
 // HBM-bound sweeps (one 16-byte store per thread).
 #include "common.h"
