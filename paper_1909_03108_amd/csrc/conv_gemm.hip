@@ -377,7 +377,8 @@ int record_loads(int vb, int ew) {
 // splitting adds a second launch and a write and a read of every sum at about 6 TB/s.  The interior voxels alone decide, so
 // that the order of the sums is the same for every output box growth and tile grid.  The time that is then compared with the
 // marching kernels' has constants of its own, fitted to 472 layers cut this way (32 ... 1024 channels, 64 voxels ... 4 million,
-// 2-D and 3-D; 11 % rms): the layers of 64 channels a workgroup take 7 % longer than the first constants say.
+// 2-D and 3-D; 11 % rms; `shortk`, K loops of 3 or 6 steps: 354 layers, 6 % rms): the layers of 64 channels a workgroup
+// take 7 % longer than the first constants say, and short loops do not reach the rate of a step.
 GemmPlan plan_gemm(const Geo &g, int ki, int ko) {
     GemmPlan p;
     const Box b = max_box(g);
@@ -385,6 +386,7 @@ GemmPlan plan_gemm(const Geo &g, int ki, int ko) {
     const int nco = ko / C, nk = ki / C * (g.flat ? 3 : 9);
     const long long nint = 1LL * g.ntiles * g.int_vox;
     p.cbw = nco % 4 == 0 ? 2 : 1;
+    const bool shortk = g.flat && ki <= 2 * C;
     double least = 0;
     for (int vb = 1; vb <= 2; ++vb) {
         const long long tiles = (nint + wg_vox(vb) - 1) / wg_vox(vb) * (nco / (2 * p.cbw));
@@ -394,7 +396,8 @@ GemmPlan plan_gemm(const Geo &g, int ki, int ko) {
             const double us = 4 + rounds * (steps * 0.41 * vb * p.cbw + 10.7) + (s > 1 ? 2 + sums / 6 : 0);
             if ((vb == 1 && s == 1) || us < least) {
                 least = us; p.vb = vb; p.nsplit = s;
-                p.us = 4 + rounds * (steps * 0.44 * (vb == 2 ? 2.09 : 1) * (p.cbw == 2 ? 1.78 : 1) + 9.85) + (s > 1 ? 0.73 + sums / 3.74 : 0);
+                p.us = shortk ? 3 + rounds * (steps * 0.41 * (vb == 2 ? 2.66 : 1) * (p.cbw == 2 ? 2.39 : 1) + 9) + (s > 1 ? 1.6 + sums / 3.3 : 0)
+                              : 4 + rounds * (steps * 0.44 * (vb == 2 ? 2.09 : 1) * (p.cbw == 2 ? 1.78 : 1) + 9.85) + (s > 1 ? 0.73 + sums / 3.74 : 0);
             }
         }
     }

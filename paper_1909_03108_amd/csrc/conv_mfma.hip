@@ -558,11 +558,12 @@ static PatchPlan plan_patches(const Geo &g, int ki, int ko) {
 // one tile, so that a layer takes the same family, and sums in the same order, on every tile grid and with every output box
 // growth; a grid that cuts W into pieces of less than a patch makes the march slower than that.  Over the 472 layers the
 // choice costs 3.4 % over the better family of each on its grid (with the estimate of the grid itself it would be 0.4 %; most
-// of it on tiles of less than 24 columns), but against marching always none loses more than 4 %: in 2-D with a single launch,
-// where the march has only its start to lose, the GEMM has to be ahead by 15 % for that.  Measured, marching -> GEMM: 3-D 256
-// -> 256 channels on 4^3 53 -> 21 us, on 16^3 79 -> 34, on 32^3 146 -> 122, 128 -> 128 on 28 x 44 x 52 96 -> 71; 128 -> 64 on 56 x
-// 88 x 104 279 against 328 (stays), 128 -> 128 on 64^3 196 against 279 (stays); 2-D 256 -> 256 on 16 x 64^2 152 -> 107, 128 ->
-// 128 on 2 x 256^2 173 -> 73, 64 -> 256 on 5 x 240 x 177 156 against 172 (stays).
+// of it on tiles of less than 24 columns), but against marching always none loses more than 4 %.  2-D layers of one launch
+// have constants of their own, from 354 such layers (14 % and 6 % rms), and the GEMM has to be ahead by 10 %: 1.2 % over the
+// better of each, four more than 4 % behind the march.  Measured, marching -> GEMM: 3-D 256 -> 256 channels on 4^3 53 -> 21 us,
+// on 16^3 79 -> 34, on 32^3 146 -> 122, 128 -> 128 on 28 x 44 x 52 96 -> 71; 128 -> 64 on 56 x 88 x 104 279 against 328 (stays),
+// 128 -> 128 on 64^3 196 against 279 (stays); 2-D 256 -> 256 on 16 x 64^2 152 -> 107, 128 -> 128 on 2 x 256^2 173 -> 73, 64 -> 64
+// there 42 -> 35, 64 -> 256 on 5 x 240 x 177 153 against 170 (stays).
 static bool prefer_gemm(const Geo &g, int ki, int ko) {
     if (!conv_gemm_supported(g, ki, ko)) return false;
     if (conv_gemm_tensor_forms(g, ki, ko)) return true;
@@ -574,9 +575,10 @@ static bool prefer_gemm(const Geo &g, int ki, int ko) {
     const int launches = p.pairs ? ki / (2 * C) : ki / C;
     const double rounds = static_cast<double>((p.nblocks + 255) / 256), planes = (p.dchunk + p.fold - 1) / p.fold;
     const double sums = 8.0 * g.ntiles * g.int_vox * ko * (launches - 1);             // bytes written and read
+    if (g.flat && launches == 1) return conv_gemm_us(g, ki, ko) < 0.9 * (4 + rounds * (5.6 + (p.pairs ? 1.75 : 1.62) * planes));
     const double us = g.flat ? 2 + launches * (rounds * (6.3 + (p.pairs ? 1.35 : 1.44) * planes) + 0.6) + sums / 7.4e6
                              : 2 + launches * (rounds * (7.2 + (p.pairs ? 2.56 : 2.63) * planes) + 3.6) + sums / 10.3e6;
-    return conv_gemm_us(g, ki, ko) < (g.flat && launches == 1 ? 0.85 : 1.0) * us;
+    return conv_gemm_us(g, ki, ko) < us;
 }
 
 int conv_mfma_route(const Geo &g, int ki, int ko, int *detail) {

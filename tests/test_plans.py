@@ -76,7 +76,7 @@ def test_the_direct_tests_meet_both_kernels():
     ((56, 88, 104), 128, 64, 0, "march"), ((64, 64, 64), 128, 128, 0, "march"), ((128, 128, 128), 128, 64, 0, "march"),
     ((4, 4, 4), 256, 256, 0, "gemm"), ((16, 16, 16), 256, 256, 0, "gemm"), ((28, 44, 52), 128, 128, 0, "gemm"),
     ((6, 48, 44), 64, 1024, 1, "march"), ((5, 240, 176), 64, 256, 1, "march"), ((16, 64, 64), 256, 256, 1, "gemm"),
-    ((2, 256, 256), 128, 128, 1, "gemm"), ((16, 256, 256), 64, 64, 1, "march")])
+    ((2, 256, 256), 128, 128, 1, "gemm"), ((2, 256, 256), 64, 64, 1, "gemm"), ((16, 256, 256), 64, 64, 1, "march")])
 def test_forward_family_of_layers_measured_both_ways(dhw, cin, cout, flat, family):
     """The faster family of each (measured: csrc/conv_mfma.hip, prefer_gemm), the same on every tile grid and for every output
     box growth, so that the sums are taken in one order."""
