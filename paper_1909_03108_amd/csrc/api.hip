@@ -172,7 +172,8 @@ size_t sp_workspace_bytes(int op, const sp_geom_t *g, int cin, int cout, sp_dtyp
 // of the C ABI.  op: SP_OP_* or 16 / 17, the 1x1x1 convolution's forward pass and data gradient.  Returns kRoute*; detail:
 // marching forward / data gradient {two chunks per launch, slices side by side, D chunk, launches}, implicit GEMM {output blocks
 // per wave, tiles of 128 voxels, record loads, splits}, marching weight gradient {whole patches, slices side by side, D chunk,
-// workgroups per channel pair}, GEMM over voxels {channel chunks of a tile, record groups, splits, summed by stage}.
+// workgroups per channel pair}, GEMM over voxels {channel chunks of a tile, record groups, splits, summed by stage}.  kRoutePadded:
+// input channels that are no multiple of 32 take up zero-padded rows, in copies or (weight gradient of 2 ... 8) in LDS.
 int sp3d_route(int op, const sp_geom_t *g, int cin, int cout, sp_dtype_t dt, int *detail) {
     Geo o;
     if (make_geo(g, &o) != SP_OK || !chan_ok(cin) || !chan_ok(cout) || !dtype_ok(dt)) return kRouteNone;
@@ -433,6 +434,9 @@ int conv3d_wgrad(const void *Px, const void *Pdz, float *dw, float *db, const sp
                            : (mfma ? wgrad_mfma_ws_bytes(o, cin, cout)
                                    : (pad ? chan_pad_wgrad_ws_bytes(o, cin, cout) : wgrad_direct_ws_bytes(o, cin, cout)));
     if (need && (!ws || ws_bytes < need || !aligned16(ws))) return SP_EWORKSPACE;
+    // (2 ... 8 channels need no copies; what the call asks of its caller does not depend on the kernel)
+    if (pad && conv_few_supported(o, cin, cout, dt))
+        return launch_wgrad_few(shifted(Px, o, cin, dt), shifted(Pdz, o, cout, dt), dw, db, o, cin, cout, ws, need, s);
     if (pad) return launch_wgrad_chan_pad(Px, Pdz, dw, db, o, cin, cout, dt, ws, s);
     if (c1) return launch_wgrad_c1(shifted(Px, o, 1, dt), shifted(Pdz, o, cout, dt), dw, db, o, cout, ws, s);
     if (mfma)

@@ -90,6 +90,8 @@ void conv_gemm_detail(const Geo &g, int ki, int ko, int *detail);
 int wgrad_mfma_route(const Geo &g, int cin, int cout, int *detail);
 void wgrad_gemm_detail(const Geo &g, int cin, int cout, int *detail);
 size_t wgrad_direct_ws_bytes(const Geo &g, int cin, int cout, int ks = 3);
+// partial sums [nparts][n] of a weight gradient (ndw values, then the bias gradient), added in order
+int launch_reduce_runs(const float *part, float *dw, float *db, int nparts, long long ndw, long long n, hipStream_t s);
 int launch_wgrad_direct(const void *Px, const void *Pdz, float *dw, float *db, const Geo &g,
                         int cin, int cout, sp_dtype_t dt, void *ws, hipStream_t s, int ks = 3);
 
@@ -196,10 +198,12 @@ size_t wgrad_gemm_ws_bytes(const Geo &g, int cin, int cout);
 int launch_wgrad_gemm(const void *Px, const void *Pdz, float *dw, float *db, const Geo &g, int cin, int cout, void *ws,
                       hipStream_t s, const void *Px2, int ca, bool gather);
 
-// forward pass of a first layer with 2 ... 8 input channels (conv_few.hip)
+// forward pass and weight gradient of a first layer with 2 ... 8 input channels (conv_few.hip)
 bool conv_few_supported(const Geo &g, int cin, int cout, sp_dtype_t dt);
 int launch_conv_few(const void *Px, const void *w, const float *bias, void *Py, const Geo &g, int cin, int cout, bool relu,
                     hipStream_t s);
+int launch_wgrad_few(const void *Px, const void *Pdz, float *dw, float *db, const Geo &g, int cin, int cout, void *ws,
+                     size_t ws_bytes, hipStream_t s);
 
 // few input channels (not a multiple of 32) on the matrix cores through zero-padded copies (chan_pad.hip)
 bool chan_pad_supported(const Geo &g, int cin, int cout, sp_dtype_t dt);

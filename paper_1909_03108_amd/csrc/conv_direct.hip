@@ -470,17 +470,17 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_direct_kernel(WgradDirectAr
         part[ndw + co] = static_cast<float>((redb[tid] + redb[16 + tid]) + (redb[32 + tid] + redb[48 + tid]));
 }
 
-// Second stage: out[e] = sum over the partials in a fixed order (16 runs, then the runs in order); a block serves 64
+// Second stage: out[e] = sum over the partials in a fixed order (16 runs, then the runs in order), in fp64; a block serves 64
 // neighbouring outputs, so every load of a wave is a whole 256-byte piece, and goes on to others where a launch of all of
 // them would exceed the 2^32 threads of a grid (more than 9.9 million pairs of channels).
 __global__ __launch_bounds__(1024) void reduce_runs_kernel(const float *__restrict__ part, float *__restrict__ dw,
                                                            float *__restrict__ db, int nparts, long long ndw, long long n) {
-    __shared__ float red[16][64];
+    __shared__ double red[16][64];
     const int l = threadIdx.x & 63, run = threadIdx.x >> 6;
     const int per = (nparts + 15) / 16, p1 = min(nparts, (run + 1) * per);
     for (long long e0 = 64LL * blockIdx.x; e0 < n; e0 += 64LL * gridDim.x) {
         const long long e = e0 + l;
-        float s = 0.f;
+        double s = 0.0;
         if (e < n) {
 #pragma unroll 8
             for (int p = run * per; p < p1; ++p) s += part[p * n + e];
@@ -488,11 +488,11 @@ __global__ __launch_bounds__(1024) void reduce_runs_kernel(const float *__restri
         red[run][l] = s;
         __syncthreads();
         if (run == 0 && e < n) {
-            float t = 0.f;
+            double t = 0.0;
 #pragma unroll
             for (int r = 0; r < 16; ++r) t += red[r][l];
-            if (e < ndw) dw[e] = t;
-            else if (db) db[e - ndw] = t;
+            if (e < ndw) dw[e] = static_cast<float>(t);
+            else if (db) db[e - ndw] = static_cast<float>(t);
         }
         __syncthreads();
     }
@@ -692,6 +692,13 @@ int launch_conv_direct(const void *Pin, const void *w, const float *bias, void *
     return record_hip(hipGetLastError());
 }
 
+int launch_reduce_runs(const float *part, float *dw, float *db, int nparts, long long ndw, long long n, hipStream_t s) {
+    const long long blocks = (n + 63) / 64;
+    hipLaunchKernelGGL(reduce_runs_kernel, dim3(static_cast<unsigned>(blocks < (1 << 20) ? blocks : 1 << 20)), dim3(1024), 0, s,
+                       part, dw, db, nparts, ndw, n);
+    return record_hip(hipGetLastError());
+}
+
 // How the weight gradient is cut up: channels per chunk, row blocks, bricks, workgroups per channel-block pair.
 struct WgradDirectPlan { int kc, nck, nco, ntap, kd, nparts, share; BrickGeo b; };
 static WgradDirectPlan wgrad_direct_plan(const Geo &g, int cin, int cout, int ks) {
@@ -763,10 +770,7 @@ int launch_wgrad_direct(const void *Px, const void *Pdz, float *dw, float *db, c
     int rc = record_hip(hipGetLastError());
     if (rc != SP_OK) return rc;
     const long long ndw = 1LL * p.ntap * cin * cout, n = ndw + cout;
-    const long long blocks = (n + 63) / 64;
-    hipLaunchKernelGGL(reduce_runs_kernel, dim3(static_cast<unsigned>(blocks < (1 << 20) ? blocks : 1 << 20)), dim3(1024), 0, s,
-                       a.part, dw, db, p.nparts, ndw, n);
-    return record_hip(hipGetLastError());
+    return launch_reduce_runs(a.part, dw, db, p.nparts, ndw, n, s);
 }
 
 }  // namespace sp3d

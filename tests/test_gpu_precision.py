@@ -63,3 +63,13 @@ def test_gemm_over_voxels_adds_stage_by_stage(n, dhw, grid, cin, cout, flat):
 def test_fp32_weight_gradient_adds_sixteen_voxels_at_a_time(n, dhw, grid, cin, cout):
     dw, _ = weight_gradient(n, dhw, grid, cin, cout, "f32", 0)
     assert dw <= 1.15 * chain(132), dw
+
+
+# bf16, 2 ... 8 channels: a wave's running sum of 32 products per row of a brick (rounded eight times each), four waves, and the
+# workgroups in 16 runs; every case has at most 3 bricks per workgroup: chain(3 * 4 * 8 + 4 + 48 + 16).
+@pytest.mark.parametrize("n, dhw, grid, cin, cout, flat", [
+    (1, (41, 90, 163), (1, 2, 1), 3, 32, 0), (2, (33, 50, 97), (1, 1, 1), 4, 64, 0), (1, (30, 77, 130), (2, 1, 2), 7, 32, 0),
+    (1, (33, 64, 96), (1, 1, 1), 8, 32, 0), (5, (2, 200, 258), (1, 2, 2), 5, 32, 1), (3, (4, 130, 95), (1, 1, 1), 2, 32, 1)])
+def test_few_channel_weight_gradient(n, dhw, grid, cin, cout, flat):
+    dw, db = weight_gradient(n, dhw, grid, cin, cout, "bf16", flat)
+    assert dw <= chain(164) and db <= chain(164), (dw, db)
