@@ -10,7 +10,10 @@
 // contiguous, so a B fragment is one 16-byte global load per lane and needs no LDS.  The weight fragments
 // of a workgroup's channel block are built once in LDS (forward: transposed on the way in, because the
 // product reduces over ci while u is stored [ci][co]; dgrad: already in fragment order) and re-read for
-// every 32-voxel segment.  The result lane layout - lane l holds voxel l % 32 and channels
+// every 32-voxel segment.  Segments are runs of 32 interior coarse voxels numbered across rows, slices and tiles, so that
+// a row of 8 or 26 voxels leaves no column empty (one row per segment before: the 2-D network's 1024 -> 512 on 16 slices of
+// 16 x 16 in 2 x 2 tiles: forward 111 -> 66 us, data gradient
+// 319 -> 119, weight gradient 352 -> 68).  The result lane layout - lane l holds voxel l % 32 and channels
 // 8*(i/4) + 4*(l/32) + i%4 - gives 8-byte stores.  Both kernels are bound by HBM traffic, not by the
 // matrix cores; a workgroup is persistent and its 8 waves walk over segments independently.
 // 2-D variant (geometry flag `flat`): 1x2x2 windows, 4 taps t = (b, c), u[4][cin][cout]; the fine voxel of
@@ -41,9 +44,11 @@ struct UpArgs {
     int cin, cout;
     int nblk;                // channel blocks of the output handled by different workgroups
     int wpb;                 // workgroups per channel block
-    int nseg;                // segments per coarse W row
-    int nitems;              // segments in total
+    int isub, iwave;         // first segment of a wave: isub times its workgroup's place in the block plus iwave times its own
+    uint32_t nvox;           // interior coarse voxels of all tiles
+    int nitems;              // segments of them
     int ntap;                // window positions: 8, or 4 in the 2-D variant
+    FastDiv dw, dh, dd;      // extents of a coarse tile
 };
 
 __device__ __forceinline__ uint32_t pack2(float a, float b) {
@@ -59,24 +64,22 @@ __device__ __forceinline__ int xcd_block() {
     return (gridDim.x & 7) == 0 ? (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
 }
 
-struct Item { int tile, d, h, w0; };
-__device__ __forceinline__ Item decode_item(int item, int nseg, const Geo &gc) {
-    Item o;
-    o.w0 = (item % nseg) * SEG;
-    int t = item / nseg;
-    o.h = t % gc.th; t /= gc.th;
-    o.d = t % gc.td;
-    o.tile = t / gc.td;
-    return o;
+// Padded voxel indices that belong to interior coarse voxel q (all tiles' voxels in order; past the end: the last one): its own
+// and that of the fine voxel that its tap 0 produces; the other taps' lie tap_step further on.
+struct Vox { uint32_t c, f; };
+template <typename A>
+__device__ __forceinline__ Vox voxel(const A &a, uint32_t q) {
+    q = min(q, a.nvox - 1);
+    const uint32_t r = fdiv(q, a.dw), w = fmod_(q, r, a.dw), s = fdiv(r, a.dh), h = fmod_(r, s, a.dh), t = fdiv(s, a.dd),
+                   d = fmod_(s, t, a.dd);
+    Vox v;
+    v.c = t * static_cast<uint32_t>(a.gc.tile_vox) + ((d + 1) * a.gc.ph + h + 1) * a.gc.pw + w + 1;
+    v.f = t * static_cast<uint32_t>(a.gf.tile_vox) + (((a.gf.flat ? d : 2 * d) + 1) * a.gf.ph + 2 * h + 1) * a.gf.pw + 2 * w + 1;
+    return v;
 }
-// padded voxel index of interior voxel (d, h, w) of a tile
-__device__ __forceinline__ size_t pvox(const Geo &g, int tile, int d, int h, int w) {
-    return static_cast<size_t>(tile) * g.tile_vox + (static_cast<size_t>(d + 1) * g.ph + h + 1) * g.pw + w + 1;
-}
-
-// padded voxel index of the fine voxel that tap t of coarse voxel (d, h, w) produces
-__device__ __forceinline__ size_t fvox(const Geo &gf, int tile, int d, int h, int w, int tap) {
-    return pvox(gf, tile, gf.flat ? d : 2 * d + (tap >> 2), 2 * h + ((tap >> 1) & 1), 2 * w + (tap & 1));
+// ... in elements of a tensor of c channels (uniform)
+__device__ __forceinline__ size_t tap_step(const Geo &gf, int tap, int c) {
+    return static_cast<size_t>(((gf.flat ? 0 : tap >> 2) * gf.ph + ((tap >> 1) & 1)) * gf.pw + (tap & 1)) * c;
 }
 
 // ---- forward -----------------------------------------------------------------------------------------
@@ -114,24 +117,31 @@ __global__ __launch_bounds__(kT) void upconv_fwd_mfma_kernel(UpArgs a) {
     bf16x8 b0[NKS], b1[NKS];
     auto fetch = [&](int item, bf16x8 (&b)[NKS]) {
         if (item >= a.nitems) return;
-        const Item o = decode_item(item, a.nseg, a.gc);
-        const int w = min(o.w0 + m, a.gc.tw - 1);
-        const uint16_t *px = a.in + pvox(a.gc, o.tile, o.d, o.h, w) * CIN + 8 * kh;
+        const uint16_t *px = a.in + static_cast<size_t>(voxel(a, SEG * item + m).c) * CIN + 8 * kh;
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) b[ks] = *reinterpret_cast<const bf16x8 *>(px + 16 * ks);
     };
     // Stores.  A lane of D holds 4 x 8 bytes of ONE fine voxel, and neighbouring lanes hold voxels two apart, so
     // direct stores are 8-byte pieces scattered over 4 KB.  With room in LDS (Cin <= 128) the two taps that
     // interleave along W are put together in a wave-private buffer first (64 fine voxels x 64 bytes, rows padded
-    // to 72 bytes) and written out as 16-byte pieces that are contiguous across the wave: 1 KB per instruction.
+    // to 72 bytes) and written out as 16-byte pieces that are contiguous across the wave: 1 KB per instruction (where
+    // the segment's voxels are one row).
     constexpr bool TR = NKS <= 8;
     constexpr int TROW = 72;
     char *tbuf = lds + 8 * NKS * 1024 + wave * (64 * TROW);
     const int rv = lane >> 2, rp = lane & 3;
     auto compute = [&](int item, const bf16x8 (&b)[NKS]) {
-        const Item o = decode_item(item, a.nseg, a.gc);
-        const int w = o.w0 + m;
-        const bool ok = w < a.gc.tw;
+        const uint32_t q0 = SEG * item, fine = voxel(a, q0 + m).f;
+        const bool ok = q0 + m < a.nvox;
+        // the fine voxels that this lane stores after each pair of taps: 16 j + rv of the 64, of coarse voxel 8 j + rv / 2
+        uint16_t *dst[TR ? 4 : 1];
+        if (TR) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                dst[j] = a.out + static_cast<size_t>(__shfl(fine, 8 * j + (rv >> 1)) + (rv & 1)) * a.cout + C * cb + 8 * rp;
+        } else {
+            dst[0] = a.out + static_cast<size_t>(fine) * a.cout + C * cb + 4 * kh;
+        }
 #pragma unroll 1
         for (int tap = 0; tap < a.ntap; ++tap) {
             f32x16 acc;
@@ -151,19 +161,19 @@ __global__ __launch_bounds__(kT) void upconv_fwd_mfma_kernel(UpArgs a) {
                 if (tap & 1) {
                     // both taps of this fine row are in the buffer (the LDS unit serves a wave's accesses in order)
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    uint16_t *prow = a.out + fvox(a.gf, o.tile, o.d, o.h, o.w0, tap & ~1) * a.cout + C * cb + 8 * rp;
+                    const size_t step = tap_step(a.gf, tap & ~1, a.cout);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const int fv = 16 * j + rv;                     // fine voxel of the 64
                         const uint2 lo = *reinterpret_cast<const uint2 *>(tbuf + fv * TROW + 16 * rp);
                         const uint2 hi = *reinterpret_cast<const uint2 *>(tbuf + fv * TROW + 16 * rp + 8);
-                        if (2 * o.w0 + fv < 2 * a.gc.tw)
-                            st_stream16(prow + static_cast<size_t>(fv) * a.cout, make_uint4(lo.x, lo.y, hi.x, hi.y));
+                        if (q0 + (fv >> 1) < a.nvox)
+                            st_stream16(dst[j] + step, make_uint4(lo.x, lo.y, hi.x, hi.y));
                     }
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                 }
             } else if (ok) {
-                uint16_t *py = a.out + fvox(a.gf, o.tile, o.d, o.h, w, tap) * a.cout + C * cb + 4 * kh;
+                uint16_t *py = dst[0] + tap_step(a.gf, tap, a.cout);
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     *reinterpret_cast<uint2 *>(py + 8 * q) = make_uint2(pack2(acc[4 * q], acc[4 * q + 1]),
@@ -171,7 +181,7 @@ __global__ __launch_bounds__(kT) void upconv_fwd_mfma_kernel(UpArgs a) {
             }
         }
     };
-    int item = sub * (kT / 64) + wave;
+    int item = sub * a.isub + wave * a.iwave;
     fetch(item, b0);
 #pragma unroll 1
     for (; item < a.nitems; item += 2 * stride) {
@@ -207,11 +217,10 @@ __global__ __launch_bounds__(kT) void upconv_dgrad_mfma_kernel(UpArgs a) {
     __syncthreads();
 
 #pragma unroll 1
-    for (int item = sub * (kT / 64) + wave; item < a.nitems; item += a.wpb * (kT / 64)) {
-        const Item o = decode_item(item, a.nseg, a.gc);
-        const int w = o.w0 + m;
-        const bool ok = w < a.gc.tw;
-        const int wl = ok ? w : a.gc.tw - 1;
+    for (int item = sub * a.isub + wave * a.iwave; item < a.nitems; item += a.wpb * (kT / 64)) {
+        const Vox v = voxel(a, SEG * item + m);
+        const uint16_t *dy0 = a.in + static_cast<size_t>(v.f) * COUT + 8 * kh;
+        const bool ok = SEG * item + m < a.nvox;
         f32x16 acc[GCI];
 #pragma unroll
         for (int g = 0; g < GCI; ++g)
@@ -220,7 +229,7 @@ __global__ __launch_bounds__(kT) void upconv_dgrad_mfma_kernel(UpArgs a) {
         // taps in pairs: the dy fragments of the next tap are in flight while the current one is multiplied
         bf16x8 b0[NKS], b1[NKS];
         auto fetch = [&](int tap, bf16x8 (&b)[NKS]) {
-            const uint16_t *pdy = a.in + fvox(a.gf, o.tile, o.d, o.h, wl, tap) * COUT + 8 * kh;
+            const uint16_t *pdy = dy0 + tap_step(a.gf, tap, COUT);
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) b[ks] = *reinterpret_cast<const bf16x8 *>(pdy + 16 * ks);
         };
@@ -243,7 +252,7 @@ __global__ __launch_bounds__(kT) void upconv_dgrad_mfma_kernel(UpArgs a) {
             compute(tap + 1, b1);
         }
         if (ok) {
-            uint16_t *px = a.out + pvox(a.gc, o.tile, o.d, o.h, w) * a.cin + C * cg * GCI + 4 * kh;
+            uint16_t *px = a.out + static_cast<size_t>(v.c) * a.cin + C * cg * GCI + 4 * kh;
 #pragma unroll
             for (int g = 0; g < GCI; ++g)
 #pragma unroll
@@ -276,8 +285,10 @@ struct UpWArgs {
     int cin, cout;
     int nco;                 // output-channel blocks; channel group = (ci group) * nco + co block
     int ngroups, wpg;        // channel groups, workgroups per group
-    int nseg, nitems;
+    uint32_t nvox;
+    int nitems;
     int ntap;                // window positions: 8, or 4 in the 2-D variant (waves 4..7 then have no tap)
+    FastDiv dw, dh, dd;
 };
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -351,18 +362,15 @@ __global__ __launch_bounds__(kT) void upconv_wgrad_mfma_kernel(UpWArgs a) {
     for (int i = 0; i < 4; ++i) ones.w[i] = 0x3f803f80u;
     const bool bias_group = cg == 0;
 
+    const uint16_t *dy_tap = a.dy + tap_step(a.gf, tap, a.cout) + C * cb + 8 * sc;
     auto stage = [&](int item, int slot) {
-        const Item o = decode_item(item, a.nseg, a.gc);
         char *dst = lds + slot * SLOT;
-        {
-            const int w = min(o.w0 + 16 * xq + sv, a.gc.tw - 1);
-            const uint16_t *px = a.x + pvox(a.gc, o.tile, o.d, o.h, w) * a.cin + C * cg * NCI + 8 * sc;
-            dma16_after_reads(px + C * xb, dst + xb * 2048 + xq * 1024);
-        }
+        const Vox v[2] = {voxel(a, SEG * item + sv), voxel(a, SEG * item + 16 + sv)};
+        const uint16_t *px = a.x + static_cast<size_t>(xq ? v[1].c : v[0].c) * a.cin + C * cg * NCI + 8 * sc;
+        dma16_after_reads(px + C * xb, dst + xb * 2048 + xq * 1024);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const int w = min(o.w0 + 16 * q + sv, a.gc.tw - 1);
-            const uint16_t *pz = a.dy + fvox(a.gf, o.tile, o.d, o.h, w, tap) * a.cout + C * cb + 8 * sc;
+            const uint16_t *pz = dy_tap + static_cast<size_t>(v[q].f) * a.cout;
             dma16_after_reads(pz, dst + (NCI + tap) * 2048 + q * 1024);
         }
     };
@@ -384,7 +392,7 @@ __global__ __launch_bounds__(kT) void upconv_wgrad_mfma_kernel(UpWArgs a) {
         stage(nxt <= last ? nxt : last, slot == 0 ? R - 1 : slot - 1);
         if (active) {
             const char *st = lds + slot * SLOT + tr_off;
-            const int nvalid = FULL ? 32 : a.gc.tw - (item % a.nseg) * SEG;    // real voxels of the segment
+            const int nvalid = FULL ? 32 : static_cast<int>(a.nvox - SEG * item);      // real voxels of the segment (or more)
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
                 const bf16x8 zf = tr_frag<FULL>(st + (NCI + tap) * 2048 + ks * 1024, lane, nvalid - 16 * ks);
@@ -450,18 +458,29 @@ __global__ __launch_bounds__(256) void upconv_wgrad_reduce_kernel(const float *_
     }
 }
 
+// Cuts the coarse voxels into segments; false: more voxels than an item's first one can count.
+template <typename A>
+bool segments(const Geo &gc, A *a) {
+    const long long vox = 1LL * gc.ntiles * gc.int_vox;
+    if (vox > 0x7fff0000LL) return false;
+    a->nvox = static_cast<uint32_t>(vox);
+    a->nitems = static_cast<int>((vox + SEG - 1) / SEG);
+    a->dw = make_fastdiv(gc.tw);
+    a->dh = make_fastdiv(gc.th);
+    a->dd = make_fastdiv(gc.td);
+    return true;
+}
+
 int wgrad_plan(const Geo &gc, int cin, int cout, UpWArgs *a, int *nci) {
     *nci = cin % (2 * C) == 0 ? 2 : 1;
     a->cin = cin; a->cout = cout;
     a->nco = cout / C;
     a->ngroups = (cin / (C * *nci)) * a->nco;
-    a->nseg = (gc.tw + SEG - 1) / SEG;
-    const long long items = 1LL * gc.ntiles * gc.td * gc.th * a->nseg;
-    if (items > 0x7fff0000LL) return SP_EGEOM;
-    a->nitems = static_cast<int>(items);
+    if (!segments(gc, a)) return SP_EGEOM;
+    const int items = a->nitems;
     int wpg = kGroups / a->ngroups;
     if (wpg < 1) wpg = 1;
-    if (wpg > items) wpg = static_cast<int>(items);
+    if (wpg > items) wpg = items;
     a->wpg = wpg;
     return SP_OK;
 }
@@ -498,11 +517,10 @@ __global__ __launch_bounds__(kT) void upconv_fwd_mfma_big_kernel(UpArgs a) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) bv[i] = a.bias ? a.bias[C * cb + 8 * (i >> 2) + 4 * kh + (i & 3)] : 0.f;
 #pragma unroll 1
-    for (int item = sub * (kT / 64) + wave; item < a.nitems; item += a.wpb * (kT / 64)) {
-        const Item o = decode_item(item, a.nseg, a.gc);
-        const int w = o.w0 + m;
-        const bool ok = w < a.gc.tw;
-        const uint16_t *px = a.in + pvox(a.gc, o.tile, o.d, o.h, ok ? w : a.gc.tw - 1) * a.cin + 8 * kh;
+    for (int item = sub * a.isub + wave * a.iwave; item < a.nitems; item += a.wpb * (kT / 64)) {
+        const Vox v = voxel(a, SEG * item + m);
+        const bool ok = SEG * item + m < a.nvox;
+        const uint16_t *px = a.in + static_cast<size_t>(v.c) * a.cin + 8 * kh;
         f32x16 acc;
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[i] = bv[i];
@@ -520,7 +538,7 @@ __global__ __launch_bounds__(kT) void upconv_fwd_mfma_big_kernel(UpArgs a) {
                 }
         }
         if (ok) {
-            uint16_t *py = a.out + fvox(a.gf, o.tile, o.d, o.h, w, tap) * a.cout + C * cb + 4 * kh;
+            uint16_t *py = a.out + static_cast<size_t>(v.f) * a.cout + tap_step(a.gf, tap, a.cout) + C * cb + 4 * kh;
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 *reinterpret_cast<uint2 *>(py + 8 * q) = make_uint2(pack2(acc[4 * q], acc[4 * q + 1]),
@@ -541,17 +559,15 @@ __global__ __launch_bounds__(kT) void upconv_dgrad_mfma_big_kernel(UpArgs a) {
     const uint16_t *urow = a.u + static_cast<size_t>(C * cg + m) * a.cout + 8 * kh;
     const size_t utap = static_cast<size_t>(a.cin) * a.cout;
 #pragma unroll 1
-    for (int item = sub * (kT / 64) + wave; item < a.nitems; item += a.wpb * (kT / 64)) {
-        const Item o = decode_item(item, a.nseg, a.gc);
-        const int w = o.w0 + m;
-        const bool ok = w < a.gc.tw;
-        const int wl = ok ? w : a.gc.tw - 1;
+    for (int item = sub * a.isub + wave * a.iwave; item < a.nitems; item += a.wpb * (kT / 64)) {
+        const Vox v = voxel(a, SEG * item + m);
+        const bool ok = SEG * item + m < a.nvox;
         f32x16 acc;
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 #pragma unroll 1
         for (int tap = 0; tap < a.ntap; ++tap) {
-            const uint16_t *pdy = a.in + fvox(a.gf, o.tile, o.d, o.h, wl, tap) * a.cout + 8 * kh;
+            const uint16_t *pdy = a.in + static_cast<size_t>(v.f) * a.cout + tap_step(a.gf, tap, a.cout) + 8 * kh;
             const uint16_t *pu = urow + tap * utap;
 #pragma unroll 1
             for (int k0 = 0; k0 < nks; k0 += 8) {
@@ -568,7 +584,7 @@ __global__ __launch_bounds__(kT) void upconv_dgrad_mfma_big_kernel(UpArgs a) {
             }
         }
         if (ok) {
-            uint16_t *px = a.out + pvox(a.gc, o.tile, o.d, o.h, w) * a.cin + C * cg + 4 * kh;
+            uint16_t *px = a.out + static_cast<size_t>(v.c) * a.cin + C * cg + 4 * kh;
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 *reinterpret_cast<uint2 *>(px + 8 * q) = make_uint2(pack2(acc[4 * q], acc[4 * q + 1]),
@@ -585,15 +601,16 @@ int dgrad_gci(int cin, int cout) {
 
 int plan(const Geo &gc, int nblk, UpArgs *a) {
     a->nblk = nblk;
-    a->nseg = (gc.tw + SEG - 1) / SEG;
-    const long long items = 1LL * gc.ntiles * gc.td * gc.th * a->nseg;
-    if (items > 0x7fff0000LL) return SP_EGEOM;
-    a->nitems = static_cast<int>(items);
+    if (!segments(gc, a)) return SP_EGEOM;
+    const int items = a->nitems;
     int wpb = kGroups / nblk;
     if (wpb < 1) wpb = 1;
-    const long long need = (items + kT / 64 - 1) / (kT / 64);      // workgroups that would each get one pass
-    if (wpb > need) wpb = static_cast<int>(need);
+    if (wpb > items) wpb = items;
     a->wpb = wpb;
+    // a workgroup's waves take neighbouring segments; where there are fewer than waves they are dealt out over the workgroups
+    const bool deal = items < wpb * (kT / 64);
+    a->isub = deal ? 1 : kT / 64;
+    a->iwave = deal ? wpb : 1;
     return SP_OK;
 }
 
@@ -612,8 +629,8 @@ int launch(K kernel, const UpArgs &a, int lds_bytes, hipStream_t s) {
 
 bool upconv_mfma_supported(const Geo &gf, const Geo &gc, int cin, int cout, sp_dtype_t dt) {
     if (dt != SP_BF16 || cin % C != 0 || cout % C != 0 || cin > 1024 || cout > 1024) return false;
-    // element offsets of a voxel inside the tensors stay far below 2^63; segment counts are checked in plan()
-    return 1LL * gc.ntiles * gc.td * gc.th * ((gc.tw + SEG - 1) / SEG) <= 0x7fff0000LL;
+    // (padded voxels of the fine tensor are numbered in 32 bits: 2^32 of them would take 275 GB at 32 channels)
+    return 1LL * gc.ntiles * gc.int_vox <= 0x7fff0000LL && 1LL * gf.ntiles * gf.tile_vox < (1LL << 32);
 }
 
 int launch_upconv_fwd_mfma(const void *Px, const void *u, const float *bias, void *Py, const Geo &gf, const Geo &gc,
@@ -698,7 +715,7 @@ int launch_upconv_wgrad_mfma(const void *Px, const void *Pdy, float *du, float *
     a.ntap = gf.flat ? 4 : 8;
     a.part_w = static_cast<float *>(ws);
     a.part_b = a.part_w + static_cast<size_t>(a.ngroups) * a.wpg * 8 * nci * C * C;
-    const bool full = gc.tw % SEG == 0;
+    const bool full = a.nvox % SEG == 0;
     const int lds_bytes = wg_ring_slots(nci) * wg_slot_bytes(nci);
     hipError_t e = hipSuccess;
     const dim3 grid(a.ngroups * a.wpg), block(kT);

@@ -328,3 +328,33 @@ def test_configuration_5_head_real_size():
         ref_dp += a
         ref_db += b
     assert rel_err(f64(dp), ref_dp) <= tol and rel_err(f64(db), ref_db) <= tol
+
+
+# Segments of 32 coarse voxels run across rows, slices and tiles: a voxel's forward pass and data gradient are the same sums
+# wherever its segment ends (tiles of 1, 3, 5, 15 and 45 coarse voxels along W; the last segment partial; few segments, which
+# are dealt out over the workgroups; the kernels of more than 256 channels), and the weight gradient's sums only change order.
+@pytest.mark.parametrize("dhw,cin,cout,flat", [((4, 6, 90), 64, 32, 0), ((6, 10, 90), 256, 64, 0), ((2, 2, 30), 288, 320, 0),
+                                               ((3, 12, 90), 320, 288, 1), ((5, 4, 90), 32, 256, 1)])
+def test_upconv_segments_run_across_rows_and_tiles(dhw, cin, cout, flat):
+    dt, kd = DT["bf16"], 1 if flat else 2
+    cshape = (dhw[0] // kd, dhw[1] // 2, dhw[2] // 2)
+    x, dy = draw("bf16", (1,) + cshape + (cin,), 21), draw("bf16", (1,) + dhw + (cout,), 22)
+    u = synth.weights(cin, cout, 23, "bf16", taps=(kd, 2, 2))
+    bias = torch.linspace(-1, 1, cout).cuda()
+    first = None
+    for grid in ((1, 1, 1), (1, 1, 3), (1, 1, 15), (1, 2 if dhw[1] % 4 == 0 else 1, 5)):
+        gf = sp3d.Geom(1, dhw, grid, 1, 0, flat)
+        gc = sp3d.coarse_geom(gf)
+        Px, Pdy = padded(gc, x, cin, dt), padded(gf, dy, cout, dt)
+        Py, Pdx = sp3d.alloc_padded(gf, cout, dt), sp3d.alloc_padded(gc, cin, dt)
+        du, db = torch.empty(u.shape, device="cuda"), torch.empty((cout,), device="cuda")
+        sp3d.sp_upconv2_fwd(Px, to_dev(u), bias, Py, gf, cin, cout, dt)
+        sp3d.sp_upconv2_dgrad(Pdy, to_dev(u), Pdx, gf, cin, cout, dt)
+        sp3d.sp_upconv2_wgrad(Px, Pdy, du, db, gf, cin, cout, dt,
+                              sp3d.alloc_ws(sp3d.sp_workspace_bytes(sp3d.SP_OP_UPCONV_WGRAD, gf, cin, cout, dt)))
+        out = (volume(gf, Py, cout, dt), volume(gc, Pdx, cin, dt), du, db)
+        first = first or out
+        assert torch.equal(out[0], first[0]) and torch.equal(out[1], first[1])
+        # (at most 1350 roundings in a sum of either order, each of 2^-24 of a running sum no larger than a few norms)
+        for a, b in zip(out[2:], first[2:]):
+            assert float((a - b).norm() / b.norm()) <= 2e-6
