@@ -14,7 +14,10 @@
 // What bounds it: at 16 channels the instructions' 32 cycles each (a brick of 256 voxels: 432 per wave against 600
 // staged records of 64 bytes); at 1 - 4 channels and in small volumes the staging and the launch.
 // Measured, fp32, 8 -> 16 -> 16 channels on 51 x 62 x 70 (one thread per output with scalar FMAs before): forward 255 and
-// 486 us, data gradient 759 and 2732 us -> 34 ... 59 us each (16 -> 16: 3.06 GFLOP, 54 TFLOP/s); 8 -> 16 on 32^3 44 -> 11 us.
+// 486 us, data gradient 759 and 2732 us -> 31 ... 54 us each (16 -> 16: 3.06 GFLOP, 60 TFLOP/s); 8 -> 16 on 32^3 44 -> 10 us.
+// Of the 50 us of a 16 -> 16 forward pass the products take 29 (20 at the instructions' rate), weights and launch 8, two
+// bricks of staging 10.  (Operands read at the top of the step that multiplies them: 54 us, 32 -> 32 on 64^3 190 -> 180.
+// Tried without gain: the next brick's records on their way in registers, neighbouring bricks on one XCD.)
 //
 // Weight gradient: M = rows (tap, input channel) of dw, flattened, so that 16 rows may span taps; N = 16 output
 // channels; K = 4 voxels.  A wave keeps ALL rows of a 16 x 16 channel block (27 blocks of 16 rows = 108 registers) over
@@ -190,19 +193,27 @@ __global__ __launch_bounds__(kThreads) void conv_direct_kernel(ConvDirectArgs a)
         const int kg = min(k, nquads - 1), t = kg / nq;
         tab[k] = tap_record(a.b, t) * a.stride + 4 * (kg - t * nq);
     }
+    // (four quads of weights per thread on their way at a time)
     auto stage_weights = [&](int chunk) {
-        for (int e = tid; e < a.steps * 64; e += kThreads) {
-            const int l = e & 63, kg = 4 * (e >> 6) + (l >> 4), co = blockIdx.y * 16 + (l & 15);
-            const int t = static_cast<int>(fdiv(kg, a.dq)), c = chunk * a.kc + 4 * (kg - t * nq);
-            f32x4 v{0.f, 0.f, 0.f, 0.f};
-            if (kg < nquads && co < a.ko) {
+        for (int e0 = tid; e0 < a.steps * 64; e0 += 4 * kThreads) {
+            f32x4 v[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (c + j < a.ki)
-                        v[j] = a.dgrad ? ldf<E>(w, (1LL * (a.ntap - 1 - t) * a.ko + co) * a.ki + c + j)
-                                       : ldf<E>(w, (1LL * t * a.ki + c + j) * a.ko + co);
+            for (int u = 0; u < 4; ++u) {
+                const int e = min(e0 + u * kThreads, a.steps * 64 - 1);
+                const int l = e & 63, kg = 4 * (e >> 6) + (l >> 4), co = blockIdx.y * 16 + (l & 15);
+                const int t = static_cast<int>(fdiv(kg, a.dq)), c = chunk * a.kc + 4 * (kg - t * nq);
+                v[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (kg < nquads && co < a.ko) {
+                    const E *const src = a.dgrad ? w + (1LL * (a.ntap - 1 - t) * a.ko + co) * a.ki + c : w + (1LL * t * a.ki + c) * a.ko + co;
+                    const int step = a.dgrad ? 1 : a.ko;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (c + j < a.ki) v[u][j] = ldf<E>(src, 1LL * j * step);
+                }
             }
-            *reinterpret_cast<f32x4 *>(wts + 4 * e) = v;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (e0 + u * kThreads < a.steps * 64) *reinterpret_cast<f32x4 *>(wts + 4 * (e0 + u * kThreads)) = v[u];
         }
     };
     f32x4 init;
@@ -231,24 +242,37 @@ __global__ __launch_bounds__(kThreads) void conv_direct_kernel(ConvDirectArgs a)
             have_weights = true;
             stage_records<E>(in, xs, a.g, a.b, p, a.ki, chunk * a.kc, a.kc, a.stride, a.dq);
             __syncthreads();
-            for (int s = 0; s < a.steps; ++s) {
-                const int off = tab[4 * s + q];
-                const f32x4 wt = *reinterpret_cast<const f32x4 *>(wts + (s * 64 + lane) * 4);
-                f32x4 x[NV];
+            // the operands of step s + 1 are read before the products of step s, their offset a step earlier still
+            f32x4 x[2][NV], wt[2];
+            int off = tab[q];
+            auto read = [&](int s, int b) {
+                wt[b] = *reinterpret_cast<const f32x4 *>(wts + (s * 64 + lane) * 4);
 #pragma unroll
-                for (int n = 0; n < NV; ++n) x[n] = *reinterpret_cast<const f32x4 *>(xs + rec[n] + off);
+                for (int n = 0; n < NV; ++n) x[b][n] = *reinterpret_cast<const f32x4 *>(xs + rec[n] + off);
+                off = tab[4 * min(s + 1, a.steps - 1) + q];
+            };
+            auto products = [&](int s, int b) {
                 // quads past the last one repeat the last quad's voxels; both operands are zero there (zero weights
                 // alone would turn an infinite voxel into NaN)
                 if (4 * s + 3 >= nquads) {
 #pragma unroll
                     for (int n = 0; n < NV; ++n)
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) x[n][j] = 4 * s + q < nquads ? x[n][j] : 0.f;
+                        for (int j = 0; j < 4; ++j) x[b][n][j] = 4 * s + q < nquads ? x[b][n][j] : 0.f;
                 }
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
 #pragma unroll
-                    for (int n = 0; n < NV; ++n) acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(wt[j], x[n][j], acc[n], 0, 0, 0);
+                    for (int n = 0; n < NV; ++n) acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(wt[b][j], x[b][n][j], acc[n], 0, 0, 0);
+            };
+            read(0, 0);
+            for (int s = 0; s < a.steps; s += 2) {
+                if (s + 1 < a.steps) read(s + 1, 1);
+                __builtin_amdgcn_sched_barrier(0);
+                products(s, 0);
+                if (s + 2 < a.steps) read(s + 2, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (s + 1 < a.steps) products(s + 1, 1);
             }
         }
 #pragma unroll
