@@ -19,7 +19,7 @@
 // Each workgroup writes its partial dw / db to the workspace; a second kernel adds the partials in
 // workgroup order, so the result does not depend on scheduling.
 // 2-D variant (template parameter KD = 1; geometry flag `flat`): only the taps with kd = 1 exist (x plane D
-// meets dz plane D - 1, its own slice); dw and the partials then hold 9 taps.
+// meets dz plane D - 1, its own slice); dw and the partials then hold 9 taps.  Whole patches of it have a kernel of their own.
 #include "common.h"
 
 namespace sp3d {
@@ -65,6 +65,7 @@ struct WgradArgs {
     int ngroups;          // real workgroups = pairs * gpp; grid is rounded up to a multiple of 8
     int fold, fold_w;     // 2-D variant, tiles narrower than half a patch: `fold` consecutive slices lie side by
                           // side in a staged plane, each in a strip of fold_w = tile width + 2 columns (1: none)
+    int bias;             // 0: nobody asks for the bias gradient (whole patches of the 2-D variant leave it out)
     int gather;           // 1 (direct-to-LDS kernel, 3-D): x margin voxels that have a neighbour tile are staged
                           // from that tile's interior, one tile extent further along the axis (SP_HALO_GATHER)
 };
@@ -404,7 +405,6 @@ __device__ __forceinline__ bf16x8 frag_masked(const char *p, uint32_t m) {
 
 // Same march as plane_step, with run-time ring slots: z[kd] points at dz plane D - kd, m[kd] is
 // all ones if that plane exists and zero otherwise.
-template <int KD>
 __device__ __forceinline__ void plane_step_dma(const char *xl, const char *z0, const char *z1, const char *z2,
                                                uint32_t m0, uint32_t m1, uint32_t m2, bool bias_wave,
                                                f32x4 (&acc)[27], f32x4 &accb) {
@@ -419,7 +419,7 @@ __device__ __forceinline__ void plane_step_dma(const char *xl, const char *z0, c
     for (int kw = 0; kw < 3; ++kw) xf[0][kw] = frag(xl + kw * 32);
 #pragma unroll
     for (int kd = 0; kd < 3; ++kd)
-        if (KD == 3 || kd == 1) zf[kd][0] = frag_masked(z[kd], m[kd]);
+        zf[kd][0] = frag_masked(z[kd], m[kd]);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int R = 0; R < GR + 2; ++R) {
@@ -430,13 +430,12 @@ __device__ __forceinline__ void plane_step_dma(const char *xl, const char *z0, c
         if (R + 1 < GR) {
 #pragma unroll
             for (int kd = 0; kd < 3; ++kd)
-                if (KD == 3 || kd == 1) zf[kd][(R + 1) & 3] = frag_masked(z[kd] + (R + 1) * PW * 32, m[kd]);
+                zf[kd][(R + 1) & 3] = frag_masked(z[kd] + (R + 1) * PW * 32, m[kd]);
         }
         __builtin_amdgcn_sched_barrier(0);
-        // every dz plane passes once through each kd position (masked when it does not exist); the 2-D
-        // variant only reads position 1
+        // every dz plane passes once through each kd position (masked when it does not exist)
         if (bias_wave && R < GR)      // wave-uniform
-            accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones.v, zf[KD == 1 ? 1 : 0][R & 3], accb, 0, 0, 0);
+            accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones.v, zf[0][R & 3], accb, 0, 0, 0);
 #pragma unroll
         for (int kh = 0; kh < 3; ++kh) {
             const int h = R - kh;
@@ -445,7 +444,6 @@ __device__ __forceinline__ void plane_step_dma(const char *xl, const char *z0, c
             for (int kd = 0; kd < 3; ++kd)
 #pragma unroll
                 for (int kw = 0; kw < 3; ++kw) {
-                    if (KD == 1 && kd != 1) continue;
                     const int tap = (kd * 3 + kh) * 3 + kw;
                     acc[tap] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[R & 1][kw], zf[kd][h & 3], acc[tap],
                                                                        0, 0, 0);
@@ -463,15 +461,14 @@ __device__ __forceinline__ void plane_step_dma(const char *xl, const char *z0, c
 // LDS latency with nothing to do; with the barrier behind row GR - 1 and the next plane's first fragments on
 // their way during row GR + 1 the rows follow each other without a gap.
 struct DmaPlane { const char *x; const char *z[3]; uint32_t m[3]; };
-template <int KD>
 __device__ __forceinline__ void dma_row0(const DmaPlane &pl, bf16x8 (&xf)[2][3], bf16x8 (&zf)[3][4]) {
 #pragma unroll
     for (int kw = 0; kw < 3; ++kw) xf[0][kw] = frag(pl.x + kw * 32);
 #pragma unroll
     for (int kd = 0; kd < 3; ++kd)
-        if (KD == 3 || kd == 1) zf[kd][0] = frag_masked(pl.z[kd], pl.m[kd]);
+        zf[kd][0] = frag_masked(pl.z[kd], pl.m[kd]);
 }
-template <int KD, int R0, int R1>
+template <int R0, int R1>
 __device__ __forceinline__ void plane_rows_dma(const DmaPlane &pl, const DmaPlane &nx, bool bias_wave,
                                                bf16x8 (&xf)[2][3], bf16x8 (&zf)[3][4], f32x4 (&acc)[27],
                                                f32x4 &accb) {
@@ -487,17 +484,15 @@ __device__ __forceinline__ void plane_rows_dma(const DmaPlane &pl, const DmaPlan
             if (R + 1 < GR) {
 #pragma unroll
                 for (int kd = 0; kd < 3; ++kd)
-                    if (KD == 3 || kd == 1)
-                        zf[kd][(R + 1) & 3] = frag_masked(pl.z[kd] + (R + 1) * PW * 32, pl.m[kd]);
+                    zf[kd][(R + 1) & 3] = frag_masked(pl.z[kd] + (R + 1) * PW * 32, pl.m[kd]);
             }
         } else {
-            dma_row0<KD>(nx, xf, zf);      // row GR + 1 uses xf[1] and ring slot GR - 1 only
+            dma_row0(nx, xf, zf);      // row GR + 1 uses xf[1] and ring slot GR - 1 only
         }
         __builtin_amdgcn_sched_barrier(0);
-        // every dz plane passes once through each kd position (masked when it does not exist); the 2-D
-        // variant only reads position 1
+        // every dz plane passes once through each kd position (masked when it does not exist)
         if (bias_wave && R < GR)      // wave-uniform
-            accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones.v, zf[KD == 1 ? 1 : 0][R & 3], accb, 0, 0, 0);
+            accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones.v, zf[0][R & 3], accb, 0, 0, 0);
 #pragma unroll
         for (int kh = 0; kh < 3; ++kh) {
             const int h = R - kh;
@@ -506,7 +501,6 @@ __device__ __forceinline__ void plane_rows_dma(const DmaPlane &pl, const DmaPlan
             for (int kd = 0; kd < 3; ++kd)
 #pragma unroll
                 for (int kw = 0; kw < 3; ++kw) {
-                    if (KD == 1 && kd != 1) continue;
                     const int tap = (kd * 3 + kh) * 3 + kw;
                     acc[tap] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[R & 1][kw], zf[kd][h & 3], acc[tap],
                                                                        0, 0, 0);
@@ -518,9 +512,9 @@ __device__ __forceinline__ void plane_rows_dma(const DmaPlane &pl, const DmaPlan
 
 // MID: the march with the barrier inside the step (see plane_rows_dma and the loop below); otherwise the barrier
 // ends the step.
-template <int KD, bool MID>
+template <bool MID>
 __global__ __launch_bounds__(kThreads) void wgrad_mfma_dma_kernel(WgradArgs a) {
-    constexpr int NT = KD == 1 ? 9 : 27, T0 = KD == 1 ? 9 : 0;
+    constexpr int NT = 27;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const Geo &g = a.g;
     const int per_xcd = gridDim.x >> 3;
@@ -661,14 +655,11 @@ __global__ __launch_bounds__(kThreads) void wgrad_mfma_dma_kernel(WgradArgs a) {
                 return pl;
             };
             DmaPlane cur = plane_at(0, sx, sz);
-            dma_row0<KD>(cur, xf, zf);
+            dma_row0(cur, xf, zf);
             for (int D = 0; D < nplanes; ++D) {
                 const int sxn = sx + 1 == NXB ? 0 : sx + 1, szn = sz + 1 == NZB ? 0 : sz + 1;
                 const DmaPlane nxt = plane_at(D + 1, sxn, szn);
-                // (2-D variant: x planes 0 and dn + 1 are the undefined D margins and meet no dz plane; their
-                // rows are skipped but the fragments of the next plane's first row are still read)
-                const bool live = KD == 3 || (D >= 1 && D <= dn);
-                if (live) plane_rows_dma<KD, 0, GR>(cur, nxt, bias_wave, xf, zf, acc, accb);
+                plane_rows_dma<0, GR>(cur, nxt, bias_wave, xf, zf, acc, accb);
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 __builtin_amdgcn_s_barrier();
                 {
@@ -676,8 +667,7 @@ __global__ __launch_bounds__(kThreads) void wgrad_mfma_dma_kernel(WgradArgs a) {
                     const int sz2 = sz + 2 >= NZB ? sz + 2 - NZB : sz + 2;
                     SP3D_STAGE(D + 2, sx2, sz2);
                 }
-                if (live) plane_rows_dma<KD, GR, GR + 2>(cur, nxt, bias_wave, xf, zf, acc, accb);
-                else dma_row0<KD>(nxt, xf, zf);
+                plane_rows_dma<GR, GR + 2>(cur, nxt, bias_wave, xf, zf, acc, accb);
                 cur = nxt;
                 sx = sxn;
                 sz = szn;
@@ -702,9 +692,7 @@ __global__ __launch_bounds__(kThreads) void wgrad_mfma_dma_kernel(WgradArgs a) {
                 const uint32_t m0 = D < dn ? 0xffffffffu : 0u;
                 const uint32_t m1 = (D >= 1 && D - 1 < dn) ? 0xffffffffu : 0u;
                 const uint32_t m2 = D >= 2 ? 0xffffffffu : 0u;
-                // (2-D variant: x planes 0 and dn + 1 are the undefined D margins and meet no dz plane)
-                if (KD == 3 || (D >= 1 && D <= dn))
-                    plane_step_dma<KD>(xlane + sx * XD_BYTES, zlane + sz * Z_PLANE, zlane + sz1 * Z_PLANE,
+                plane_step_dma(xlane + sx * XD_BYTES, zlane + sz * Z_PLANE, zlane + sz1 * Z_PLANE,
                                zlane + sz2m * Z_PLANE, m0, m1, m2, bias_wave, acc, accb);
                 // plane D + 1 (staged one step ago) has landed once at most this step's loads are in flight
                 asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
@@ -724,7 +712,7 @@ __global__ __launch_bounds__(kThreads) void wgrad_mfma_dma_kernel(WgradArgs a) {
     const int quad = qi * 2 + qo;
     if (kg == 1) {
 #pragma unroll
-        for (int t = T0; t < T0 + NT; ++t)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int i = 0; i < 4; ++i) red[((quad * 27 + t) * 4 + i) * 64 + lane] = acc[t][i];
     }
@@ -732,10 +720,10 @@ __global__ __launch_bounds__(kThreads) void wgrad_mfma_dma_kernel(WgradArgs a) {
     if (kg == 0) {
         float *pw = a.part_w + static_cast<size_t>(slot) * NT * C * C;
 #pragma unroll
-        for (int t = T0; t < T0 + NT; ++t)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                pw[((t - T0) * C + 16 * qi + 4 * G + i) * C + 16 * qo + p] =
+                pw[(t * C + 16 * qi + 4 * G + i) * C + 16 * qo + p] =
                     acc[t][i] + red[((quad * 27 + t) * 4 + i) * 64 + lane];
     }
     // bias partial: row 0 of the ones-product (lanes 0..15, register 0) holds the column sums of the
@@ -744,6 +732,160 @@ __global__ __launch_bounds__(kThreads) void wgrad_mfma_dma_kernel(WgradArgs a) {
     if (bias_wave && lane < 16) red[(kg * 2 + qo) * 16 + lane] = accb[0];
     __syncthreads();
     if (tid < C) a.part_b[slot * C + tid] = red[tid] + red[C + tid];
+}
+
+// ---- whole patches of the 2-D variant --------------------------------------------------------------------------------
+// Nine taps per staged plane instead of 27: with 16 x 16 quadrants per wave a plane took 352 transposing reads (2800 cycles of
+// the LDS) for 1152 cycles of MFMAs.  Here a wave owns the whole 32 x 32 channels of the pair (v_mfma_f32_32x32x16_bf16, 9 x 16
+// accumulator registers) for half of the columns of one row group, so that a read serves twice the products: 176 reads a
+// plane.  Slices do not interact, so there is no march: a step takes two units (a unit: 8 x 32 patch of one slice), waves 0 - 3
+// the first and 4 - 7 the second, and the next two are staged meanwhile into the other half of LDS; one barrier a step.
+// The eight waves' sums are added in a fixed order at the end.
+// Measured, 2-D, 16 slices, march -> this: 64 -> 64 on 256 x 256 137 -> 96 us, 128 -> 128 on 128 x 128 131 -> 91 (0.85 PFLOP/s),
+// 256 -> 256 on 64 x 64 138 -> 97; 32 -> 32 on 512 x 512 117 -> 106 (HBM: 625 MB with the surround); half of that gain is the
+// layout of the staged records; error against 64 bits 5.7e-7 -> 2.8e-7.
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+// LDS keeps whole voxel records of 64 bytes: a load fetches 16 of them (in the march's layout, halves apart, a load fetches the
+// same half of 32 records and the other half comes with another load), and 32 lanes of a transposing read cover four records,
+// 256 bytes in a row: no bank conflicts.
+constexpr int F_NX = (XVOX + 15) / 16, F_NZ = ZVOX / 16;  // staging loads of a unit: x and dz
+constexpr int F_UNIT = (F_NX + F_NZ) * 1024, F_LDS_BYTES = 4 * F_UNIT;
+constexpr int F_LOADS = (F_NX + F_NZ + 3) / 4;            // ... per wave
+static_assert(F_LDS_BYTES <= 160 * 1024 && 4 * 9 * 16 * 64 * 4 <= F_LDS_BYTES, "LDS of one CU");
+
+// One operand (32 channels x 16 voxels): lane l gets channel l % 32, voxels 8 (l / 32) ..
+__device__ __forceinline__ bf16x8 frag32(const char *p) {
+    union { struct { s16x4 lo, hi; } s; bf16x8 v; } u;
+    u.s.lo = tr_read(p);
+    u.s.hi = tr_read(p + 4 * 64);
+    return u.v;
+}
+
+__global__ __launch_bounds__(kThreads) void wgrad_mfma_flat_kernel(WgradArgs a) {
+    constexpr int NT = 9;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const Geo &g = a.g;
+    const int per_xcd = gridDim.x >> 3;
+    const int group = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (group >= a.ngroups) return;
+    const int npairs = a.ngroups / a.gpp;             // (neighbouring groups: the pairs of one share, as above)
+    const int pair = group % npairs, gsub = group / npairs;
+    const int slot = pair * a.gpp + gsub;
+    const XSrc xs = x_source(a, C * (pair / a.nco));
+    const int dz_co = C * (pair % a.nco);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int un = wave >> 2, kg = (wave >> 1) & 1, ch = wave & 1, sub = wave & 3;      // unit, row group, column half; staging share
+    const int G = lane >> 4, p = lane & 15;
+    const int at = (16 * ch + 8 * (G >> 1) + (p >> 2)) * 64 + (G & 1) * 32 + (p & 3) * 8;
+    const char *const xlane = lds + un * F_UNIT + kg * GR * XC * 64 + at;
+    const char *const zlane = lds + un * F_UNIT + F_NX * 1024 + kg * GR * PW * 64 + at;
+
+    // Staging loads sub, sub + 4, ... of this wave's unit (waves that have one less repeat their last one): lane l fetches piece
+    // l & 3 of voxel 16 group + l / 4; voxels past the end of the x plane re-fetch its last one into the padding.
+    int src[F_LOADS], dst[F_LOADS];
+#pragma unroll
+    for (int i = 0; i < F_LOADS; ++i) {
+        const int u = sub + 4 * i < F_NX + F_NZ ? sub + 4 * i : sub + 4 * i - 4;
+        const bool x = u < F_NX;
+        const int v = (x ? u : u - F_NX) * 16 + (lane >> 2), xv = min(v, XVOX - 1);
+        src[i] = (x ? ((xv / XC) * g.pw + xv % XC) * xs.cs : ((v / PW + 1) * g.pw + v % PW + 1) * a.dz_cs) + (lane & 3) * 8;
+        dst[i] = un * F_UNIT + u * 1024;
+    }
+    const int nunits = g.ntiles * g.td * a.nh * a.nw, nsteps = nunits / 2 + nunits % 2;
+    auto stage = [&](int step, int buf) {
+        int t = min(2 * step + un, nunits - 1);
+        const int w0 = t % a.nw * PW; t /= a.nw;
+        const int h0 = t % a.nh * PH; t /= a.nh;
+        const int d = t % g.td;
+        const size_t first = static_cast<size_t>(t / g.td) * g.tile_vox + (static_cast<size_t>(d + 1) * g.ph + h0) * g.pw + w0;
+        const uint16_t *const tx = xs.base + first * xs.cs + xs.co, *const tz = a.dz + first * a.dz_cs + dz_co;
+#pragma unroll
+        for (int i = 0; i < F_LOADS; ++i)
+            dma16((sub + 4 * i < F_NX ? tx : tz) + src[i], lds + 2 * F_UNIT * buf + dst[i]);
+    };
+
+    f32x16 acc[NT], accb;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        accb[i] = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t][i] = 0.f;
+    }
+    union { uint32_t w[4]; bf16x8 v; } ones;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ones.w[i] = 0x3f803f80u;
+
+    stage(gsub, 0);
+    int buf = 0;
+    for (int step = gsub; step < nsteps; step += a.gpp) {
+        // this wave's loads have landed; behind the barrier everybody's have, and every wave has read its last fragments of
+        // the step before, whose half of LDS takes the next step's loads (past the last step they repeat the last one)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        stage(min(step + a.gpp, nsteps - 1), buf ^ 1);
+        const char *const xl = xlane + 2 * F_UNIT * buf, *const zl = zlane + 2 * F_UNIT * buf;
+        buf ^= 1;
+        if (2 * step + un >= nunits) continue;        // (wave-uniform)
+        bf16x8 xf[2][3], zf[4];
+#pragma unroll
+        for (int kw = 0; kw < 3; ++kw) xf[0][kw] = frag32(xl + kw * 64);
+        zf[0] = frag32(zl);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int R = 0; R < GR + 2; ++R) {
+            if (R + 1 < GR + 2) {
+#pragma unroll
+                for (int kw = 0; kw < 3; ++kw) xf[(R + 1) & 1][kw] = frag32(xl + ((R + 1) * XC + kw) * 64);
+            }
+            if (R + 1 < GR) zf[(R + 1) & 3] = frag32(zl + (R + 1) * PW * 64);
+            __builtin_amdgcn_sched_barrier(0);
+            if (a.bias && R < GR) accb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones.v, zf[R & 3], accb, 0, 0, 0);
+#pragma unroll
+            for (int kh = 0; kh < 3; ++kh) {
+                const int h = R - kh;
+                if (h < 0 || h >= GR) continue;
+#pragma unroll
+                for (int kw = 0; kw < 3; ++kw)
+                    acc[kh * 3 + kw] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[R & 1][kw], zf[h & 3], acc[kh * 3 + kw], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // the loads past the last step
+    __syncthreads();
+    // waves 4 - 7 into 0 - 3, then those four in order
+    float *const red = reinterpret_cast<float *>(lds);
+    if (un == 1) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) red[((sub * NT + t) * 16 + i) * 64 + lane] = acc[t][i];
+    }
+    __syncthreads();
+    if (un == 0) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) red[((sub * NT + t) * 16 + i) * 64 + lane] += acc[t][i];
+    }
+    __syncthreads();
+    // register i of lane l: input channel 8 (i / 4) + 4 (l / 32) + i % 4, output channel l % 32
+    float *const pw = a.part_w + static_cast<size_t>(slot) * NT * C * C;
+    for (int e = tid; e < NT * C * C; e += kThreads) {
+        const int l = e & 63, i = (e >> 6) & 15, t = e >> 10;
+        const float s = ((red[e] + red[NT * 1024 + e]) + red[2 * NT * 1024 + e]) + red[3 * NT * 1024 + e];
+        pw[(t * C + 8 * (i >> 2) + 4 * (l >> 5) + (i & 3)) * C + (l & 31)] = s;
+    }
+    // every row of the ones-product is the column sum; row 0 sits in register 0 of lanes 0 .. 31
+    __syncthreads();
+    if (lane < C) red[wave * C + lane] = accb[0];
+    __syncthreads();
+    if (tid < C) {
+        float s = red[tid];
+        for (int w = 1; w < 8; ++w) s += red[w * C + tid];
+        a.part_b[slot * C + tid] = s;
+    }
 }
 
 // Estimated microseconds of a cutting into `items` items of `planes` planes (surround included) per channel pair, on `gpp`
@@ -923,6 +1065,7 @@ int launch_wgrad_mfma(const void *Px, const void *Pdz, float *dw, float *db, con
     WgradArgs a;
     plan(g, cin, cout, &a, family == kMarchCoarse);
     a.gather = gather ? 1 : 0;
+    a.bias = db != nullptr;
     a.x = static_cast<const uint16_t *>(Px);
     a.x2 = static_cast<const uint16_t *>(Px2);
     if (Px2) { a.x_cs = ca; a.x_ca = ca; a.x2_cs = cin - ca; }
@@ -936,20 +1079,17 @@ int launch_wgrad_mfma(const void *Px, const void *Pdz, float *dw, float *db, con
     // more than 64 KB of dynamic LDS has to be requested explicitly
     using Kern = void (*)(WgradArgs);
     static const Kern plain[2] = {wgrad_mfma_kernel<3>, wgrad_mfma_kernel<1>};          // [2-D variant]
-    static const Kern dma[2][2] = {{wgrad_mfma_dma_kernel<3, false>, wgrad_mfma_dma_kernel<1, false>},
-                                   {wgrad_mfma_dma_kernel<3, true>, wgrad_mfma_dma_kernel<1, true>}};      // [MID][2-D variant]
+    static const Kern dma[2] = {wgrad_mfma_dma_kernel<false>, wgrad_mfma_dma_kernel<true>};      // [MID]
     static const hipError_t attr = [] {
         for (int i = 0; i < 2; ++i) {
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(plain[i]),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
             if (e != hipSuccess) return e;
-            for (int m = 0; m < 2; ++m) {
-                e = hipFuncSetAttribute(reinterpret_cast<const void *>(dma[m][i]),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, DMA_LDS_BYTES);
-                if (e != hipSuccess) return e;
-            }
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(dma[i]), hipFuncAttributeMaxDynamicSharedMemorySize, DMA_LDS_BYTES);
+            if (e != hipSuccess) return e;
         }
-        return hipSuccess;
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(wgrad_mfma_flat_kernel),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, F_LDS_BYTES);
     }();
     if (attr != hipSuccess) return record_hip(attr);
     // whole patches only: the direct-to-LDS loads cannot zero-fill a ragged edge
@@ -959,9 +1099,10 @@ int launch_wgrad_mfma(const void *Px, const void *Pdz, float *dw, float *db, con
     // + 1 %, 256 + 5 %, 512 + 6 %), where many workgroups stream different planes at once and a plane takes longer
     // to arrive than a step lasts.
     const int mid = (cin / C) * (cout / C) <= 4 ? 1 : 0;
-    if (g.th % PH == 0 && g.tw % PW == 0)
-        hipLaunchKernelGGL(dma[mid][g.flat], dim3(grid), dim3(kThreads), DMA_LDS_BYTES, s, a);
-    else
+    if (g.th % PH == 0 && g.tw % PW == 0) {
+        if (g.flat) hipLaunchKernelGGL(wgrad_mfma_flat_kernel, dim3(grid), dim3(kThreads), F_LDS_BYTES, s, a);
+        else hipLaunchKernelGGL(dma[mid], dim3(grid), dim3(kThreads), DMA_LDS_BYTES, s, a);
+    } else
         hipLaunchKernelGGL(plain[g.flat], dim3(grid), dim3(kThreads), LDS_BYTES, s, a);
     int rc = record_hip(hipGetLastError());
     if (rc != SP_OK) return rc;

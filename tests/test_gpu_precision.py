@@ -73,3 +73,14 @@ def test_fp32_weight_gradient_adds_sixteen_voxels_at_a_time(n, dhw, grid, cin, c
 def test_few_channel_weight_gradient(n, dhw, grid, cin, cout, flat):
     dw, db = weight_gradient(n, dhw, grid, cin, cout, "bf16", flat)
     assert dw <= chain(164) and db <= chain(164), (dw, db)
+
+
+# 2-D, whole patches: eight waves of a workgroup add 16 products of a row to a running sum at a time (four roundings each), at most
+# eight units of four rows each in these layers; then the waves and the workgroups: chain(8 * 4 * 4 + 8 + 40).  One unit, an
+# odd number of them (half of a workgroup has nothing in its last step), more workgroups than steps, several steps.
+@pytest.mark.parametrize("n, dhw, grid, cin, cout", [
+    (1, (1, 8, 32), (1, 1, 1), 32, 32), (1, (3, 8, 32), (1, 1, 1), 64, 32), (1, (5, 24, 96), (1, 1, 1), 96, 64),
+    (3, (7, 16, 64), (1, 2, 2), 32, 64), (1, (16, 128, 128), (1, 2, 2), 64, 128)])
+def test_flat_whole_patches(n, dhw, grid, cin, cout):
+    dw, db = weight_gradient(n, dhw, grid, cin, cout, "bf16", 1)
+    assert dw <= chain(176) and db <= chain(176), (dw, db)
