@@ -94,7 +94,8 @@ struct Ctx {
     int plo, phi;               // staged planes are clamped to [plo, phi] (slices side by side: the outer two are not real)
     ptrdiff_t dlo, dhi;         // gathered halos: what to add for staged plane 0 / the last one (else 0)
     int goff[LOADS];            // per-lane source offsets of the staging loads (elements)
-    char *lds_stage;            // LDS chunk plane this wave fills (ring slot 0)
+    char *lds_stage;            // where this wave's first load goes (ring slot 0)
+    int last;                   // ... and its last one, further on: waves that have one less repeat the one before
     uint16_t *obase;            // output address of (plane 0, first row of the wave, this lane)
     const uint16_t *mbase;      // same position in the mask tensor
     uint16_t *bbase;            // this lane's word of that voxel in the one-bit mask (see relu_bit)
@@ -108,14 +109,13 @@ struct Ctx {
 // lane l supplies its own global address and the 16 bytes land at LDS base + 16*l.  Planes past the last
 // one needed are clamped (their ring slot is never read), so every step issues exactly LOADS loads.
 template <bool HAS_BIAS>
-__device__ __forceinline__ void stage(const Ctx<HAS_BIAS> &c, int dplane, int j, int lane) {
+__device__ __forceinline__ void stage(const Ctx<HAS_BIAS> &c, int dplane, int j) {
     const int dpl = min(max(dplane, c.plo), c.phi);
     const uint16_t *p = c.tin0 + static_cast<ptrdiff_t>(dpl) * static_cast<ptrdiff_t>(c.plane_elems) +
                         (dpl == 0 ? c.dlo : 0) + (dpl == c.nplanes - 1 ? c.dhi : 0);
-    char *dst = c.lds_stage + (dplane % NBUF) * PLANE_BYTES + j * 1024;
-    if (64 * j + lane < PLANE_VOX)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(p + c.goff[j]),
-                                         (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+    char *dst = c.lds_stage + (dplane % NBUF) * PLANE_BYTES + (j == LOADS - 1 ? c.last : j * kWaves * 1024);
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(p + c.goff[j]),
+                                     (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
 }
 
 // Partial sums of 4 channels of row h of plane d written by the previous input chunk.
@@ -181,8 +181,8 @@ __device__ __forceinline__ void store_unit(const Ctx<HAS_BIAS> &c, int d, const 
 // All MFMAs of one staged input plane Dp, with the step's side work spread over the six MFMA groups:
 // the staging loads of plane Dp+DIST and (EPI) the conversion and stores of output plane Dp-3, which
 // received its last contribution in step Dp-1, after which its accumulator slot returns to the bias.
-// `lbase` = this lane's read base inside the plane: voxel (first row of the wave, column lane%32),
-// chunk lane/32.  Fragments are fetched one (kw, K-half) group of RH+2 rows ahead of the MFMAs that
+// lcol[kw]: this lane's read base in ring slot 0: first row of the wave, column lane % 32 + kw, piece lane / 32 (the second K
+// half's piece is 32 bytes away, up or down).  Fragments are fetched one (kw, K-half) group of RH+2 rows ahead of the MFMAs that
 // consume them.  P = Dp mod 4: output plane Dp-kd lives in slot (P-kd) mod 4, plane Dp-3 in slot (P+1) mod 4.
 // FULL: the patch lies completely inside the tile interior, so stores need no mask (no branches in
 // the step, which lets the scheduler weave the side work between the MFMAs).
@@ -191,19 +191,18 @@ __device__ __forceinline__ void store_unit(const Ctx<HAS_BIAS> &c, int d, const 
 // plane that the next step finishes, Dp - 2, into the other set (npin, nmk), which the caller passes through
 // the wait that ends the step.
 template <int P, bool EPI, int MODE, int RELU, bool FULL, int KD, int SIDE, int NV, bool HAS_BIAS>
-__device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, int lane, const uint32_t (&lring)[2],
+__device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, const uint32_t (&lcol)[3],
                                            const bf16x8 (&wf)[NFRAG], f32x16 (&acc)[4][RH],
                                            pin_t (&pin)[RH][4], mask_t (&mk)[RH][4],
                                            pin_t (&npin)[RH][4], mask_t (&nmk)[RH][4], bf16x8 (&b0)[RH + 2]) {
     constexpr int NR = RH + 2;
     constexpr int DONE = (P + 1) & 3;
     using S = Side<MODE, RELU, KD, false>;
-    // ring slots of plane Dp and of plane Dp + 1, as a base register (slots 0, 1 / 2, 3) and an immediate that
-    // fits the instruction's 16-bit offset field
+    // ring slots of plane Dp and of plane Dp + 1: two of them are within reach of the instruction's 16-bit offset field
     constexpr int PN = (P + 1) & 3;
-    const uint32_t lbase = lring[P >> 1], lnext = lring[PN >> 1];
+    constexpr int HIGH = (P >> 1) * 2 * PLANE_BYTES, HIGHN = (PN >> 1) * 2 * PLANE_BYTES;
     constexpr int OFF = (P & 1) * PLANE_BYTES, OFFN = (PN & 1) * PLANE_BYTES;
-    static_assert(PLANE_BYTES + 2 * CH_STRIDE + ((RH + 1) * LCOLS + 2) * 16 + CH_STRIDE < 65536, "offset field");
+    static_assert(PLANE_BYTES + (RH + 1) * ROW_BYTES < 65536, "offset field");
     bf16x8 b[2][NR];
     if (SIDE != kSideNone) {
 #pragma unroll
@@ -235,9 +234,9 @@ __device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, int l
         const int kw = gi >> 1, half = gi & 1;
         if (gi + 1 < NG) {
             const int kw2 = (gi + 1) >> 1, half2 = (gi + 1) & 1;
+            const uint32_t at = (lcol[kw2] ^ (half2 * 32)) + HIGH;
 #pragma unroll
-            for (int r = 0; r < NR; ++r)
-                frag_read(b[(gi + 1) & 1][r], lbase, OFF + half2 * 2 * CH_STRIDE + (r * LCOLS + kw2) * 16);
+            for (int r = 0; r < NR; ++r) frag_read(b[(gi + 1) & 1][r], at, OFF + r * ROW_BYTES);
         } else {
             // The step's one synchronisation sits here, before its last group, not at its end: plane Dp + 1
             // must be complete (every wave's staging loads of it, issued two steps ago: loads complete in issue
@@ -253,14 +252,14 @@ __device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, int l
                        SIDE != kSideNone && S::BITS>(npin, nmk);
             __builtin_amdgcn_s_barrier();
 #pragma unroll
-            for (int r = 0; r < NR; ++r) frag_read(b[0][r], lnext, OFFN + (r * LCOLS) * 16);
+            for (int r = 0; r < NR; ++r) frag_read(b[0][r], lcol[0] + HIGHN, OFFN + r * ROW_BYTES);
         }
         // this group's fragments were read a group ago; the NR reads issued just now may stay in flight
         frag_wait<NR>(b[gi & 1]);
         // keep the reads of the next group ahead of this group's MFMAs (the scheduler would
         // otherwise sink every read to just before its first use and expose the LDS latency)
         __builtin_amdgcn_sched_barrier(0);
-        stage(c, Dp + DIST, gi, lane);
+        stage(c, Dp + DIST, gi);
         if (gi < 4) {
             if (EPI) {
                 // (the copies of the finished plane's sums out of the accumulation registers have no operand that
@@ -306,7 +305,7 @@ __device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, int l
 
 template <int MODE, bool HAS_BIAS, int RELU, int KD>
 __global__ __launch_bounds__(kThreads, 1) void conv_mfma_kernel(ConvArgs a) {
-    extern __shared__ __attribute__((aligned(16))) char lds[];   // NBUF planes of PLANE_BYTES
+    extern __shared__ __attribute__((aligned(128))) char lds[];  // NBUF planes of PLANE_BYTES
     const Geo &g = a.g;
     // Consecutive hardware workgroup ids rotate over the 8 XCDs; give each XCD a contiguous range of
     // logical ids so that patches sharing halo rows/columns meet in the same L2.
@@ -325,7 +324,7 @@ __global__ __launch_bounds__(kThreads, 1) void conv_mfma_kernel(ConvArgs a) {
     int dn = min(a.dchunk, bx.bd - d0);                                 // output planes (slices) to produce
     // the patches are laid out for the largest box of the grid; a tile at the volume border has a smaller one
     if (dn <= 0 || h0 >= bx.bh || w0 >= bx.bw) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, hi = lane >> 5;
 
     // weight fragments: 54 x 16 bytes per lane, resident for the whole march
@@ -348,22 +347,27 @@ __global__ __launch_bounds__(kThreads, 1) void conv_mfma_kernel(ConvArgs a) {
     c.nplanes = dn + 2;
     c.plo = F > 1 ? 1 : 0;
     c.phi = F > 1 ? c.nplanes - 2 : c.nplanes - 1;
-    // Wave w fills chunk plane w (channels 8w..8w+7 of every voxel); load j covers patch-local voxels
-    // 64j..64j+63.  Voxels beyond the box and its one-voxel surround (ragged patches) are clamped to a valid
-    // address; they only feed outputs that are never stored.
+    // Load j of wave w covers patch-local voxels 16 (w + 4 j) .. + 15, four lanes to a voxel, each the piece whose place is its
+    // own (see piece_at).  Voxels beyond the box and its one-voxel surround (ragged patches) are clamped to a valid
+    // address; they only feed outputs that are never stored.  Places past the last voxel take that voxel again.
+    const bool less = wave + kWaves * (LOADS - 1) >= PLANE_LOADS;
+    c.last = (LOADS - 1 - (less ? 1 : 0)) * kWaves * 1024;
+    const auto staged_voxel = [&](int j) {
+        return min(16 * (wave + kWaves * (j == LOADS - 1 && less ? j - 1 : j)) + (lane >> 2), PLANE_VOX - 1);
+    };
 #pragma unroll
     for (int j = 0; j < LOADS; ++j) {
-        const int v = 64 * j + lane;
+        const int v = staged_voxel(j);
         const FoldCol fc = fold_col(v % LCOLS, F, a.fold_w);
         const int row = min(h0 + v / LCOLS, bx.bh + 1), colv = min(w0 + fc.c, bx.bw + 1);
-        c.goff[j] = ((min(fc.s, F - 1) * g.ph + row) * g.pw + colv) * a.in_cs + wave * 8;
+        c.goff[j] = ((min(fc.s, F - 1) * g.ph + row) * g.pw + colv) * a.in_cs + 8 * piece_at(v % LCOLS, lane & 3);
     }
     c.dlo = c.dhi = 0;
     if (a.gather) {          // (host: one-voxel margins, no grown box, 3-D)
         const GatherShift gs = gather_shift(g, tile, a.in_cs);
 #pragma unroll
         for (int j = 0; j < LOADS; ++j) {
-            const int v = 64 * j + lane;
+            const int v = staged_voxel(j);
             const int row = min(h0 + v / LCOLS, bx.bh + 1), colv = min(w0 + v % LCOLS, bx.bw + 1);
             c.goff[j] += (row == 0 ? gs.hm : 0) + (row == g.th + 1 ? gs.hp : 0) + (colv == 0 ? gs.wm : 0) +
                          (colv == g.tw + 1 ? gs.wp : 0);
@@ -371,7 +375,7 @@ __global__ __launch_bounds__(kThreads, 1) void conv_mfma_kernel(ConvArgs a) {
         if (d0 == 0) c.dlo = gs.dm;
         if (d0 + dn == g.td) c.dhi = gs.dp;
     }
-    c.lds_stage = lds + wave * CH_STRIDE;
+    c.lds_stage = lds + wave * 1024;
     const OutDst od = out_dest(a, cj);
     const FoldCol oc = fold_col(col, F, a.fold_w);
     c.orow = static_cast<size_t>(g.pw) * od.cs;
@@ -401,24 +405,25 @@ __global__ __launch_bounds__(kThreads, 1) void conv_mfma_kernel(ConvArgs a) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[s][h][i] = HAS_BIAS ? c.bv[HAS_BIAS ? i : 0] : 0.f;
 
-    const char *lbase = lds + lds_off(wave * RH * LCOLS + col, hi);
+    const char *lbase = lds + wave * RH * ROW_BYTES;
     const int nplanes = c.nplanes;
 
     // Prologue: planes 0 .. DIST-1 in flight; plane 0 must have landed before the first MFMA.
 #pragma unroll
     for (int i = 0; i < DIST; ++i)
 #pragma unroll
-        for (int j = 0; j < LOADS; ++j) stage(c, i, j, lane);
+        for (int j = 0; j < LOADS; ++j) stage(c, i, j);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 
     // (the synchronisation of a step sits inside it, before its last MFMA group: see plane_step)
     constexpr int NV_STEP = (DIST - 1) * LOADS - 1;     // plane Dp + 2's loads and the step's first NG - 1
     static_assert(NG == LOADS, "one staging load per MFMA group");
-    const uint32_t lring[2] = {lds_addr(lbase), lds_addr(lbase + 2 * PLANE_BYTES)};
+    const uint32_t lcol[3] = {lds_addr(lbase + lds_off(col, hi)), lds_addr(lbase + lds_off(col + 1, hi)),
+                              lds_addr(lbase + lds_off(col + 2, hi))};
     bf16x8 b0[RH + 2];
 #pragma unroll
-    for (int r = 0; r < RH + 2; ++r) b0[r] = *reinterpret_cast<const bf16x8 *>(lbase + (r * LCOLS) * 16);
+    for (int r = 0; r < RH + 2; ++r) b0[r] = *reinterpret_cast<const bf16x8 *>(lbase + lds_off(col, hi) + r * ROW_BYTES);
 
     auto march = [&](auto full_tag) {
         constexpr bool FULL = decltype(full_tag)::value;
@@ -435,14 +440,14 @@ __global__ __launch_bounds__(kThreads, 1) void conv_mfma_kernel(ConvArgs a) {
         static_assert(LOADS - 1 + 8 >= NV_STEP, "side loads must be older than what the step's wait lets stay in flight");
         // the first three steps have no finished plane to store (nplanes >= 3 always); the third one fetches
         // what the first store needs
-        plane_step<0, false, MODE, RELU, FULL, KD, kSideNone, NV_STEP>(c, 0, lane, lring, wf, acc, pinA, mkA, pinB, mkB, b0);
-        plane_step<1, false, MODE, RELU, FULL, KD, kSideNone, NV_STEP>(c, 1, lane, lring, wf, acc, pinA, mkA, pinB, mkB, b0);
-        plane_step<2, false, MODE, RELU, FULL, KD, FETCH, (ASYNC ? LOADS - 1 : NV_STEP)>(c, 2, lane, lring, wf, acc, pinA,
+        plane_step<0, false, MODE, RELU, FULL, KD, kSideNone, NV_STEP>(c, 0, lcol, wf, acc, pinA, mkA, pinB, mkB, b0);
+        plane_step<1, false, MODE, RELU, FULL, KD, kSideNone, NV_STEP>(c, 1, lcol, wf, acc, pinA, mkA, pinB, mkB, b0);
+        plane_step<2, false, MODE, RELU, FULL, KD, FETCH, (ASYNC ? LOADS - 1 : NV_STEP)>(c, 2, lcol, wf, acc, pinA,
                                                                                         mkA, pinB, mkB, b0);
         // steps 3, 4, 5, 6, 7, ...: planes mod 4 = 3, 0, 1, 2, 3, ...
 #define SP3D_MAIN_STEP(OFF, PHASE, CP, CM, NP, NM)                                                            \
     if (D + (OFF) < nplanes)                                                                                  \
-        plane_step<PHASE, true, MODE, RELU, FULL, KD, USE, NV_STEP>(c, D + (OFF), lane, lring, wf, acc, CP, CM, NP, NM, b0);
+        plane_step<PHASE, true, MODE, RELU, FULL, KD, USE, NV_STEP>(c, D + (OFF), lcol, wf, acc, CP, CM, NP, NM, b0);
         for (int D = 3; D < nplanes; D += 4) {
             SP3D_MAIN_STEP(0, 3, pinB, mkB, pinA, mkA)
             SP3D_MAIN_STEP(1, 0, pinA, mkA, pinB, mkB)

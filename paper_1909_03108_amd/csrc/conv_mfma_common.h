@@ -21,21 +21,26 @@ constexpr int PH = RH * kWaves;             // patch rows
 constexpr int PW = 32;                      // patch columns = MFMA N
 constexpr int LROWS = PH + 2, LCOLS = PW + 2;
 constexpr int PLANE_VOX = LROWS * LCOLS;    // 340
-constexpr int LOADS = (PLANE_VOX + 63) / 64;   // wave-wide staging loads per chunk plane: 6
+constexpr int PLANE_LOADS = (PLANE_VOX + 15) / 16;            // wave-wide staging loads per plane, 16 records each: 22
+constexpr int LOADS = (PLANE_LOADS + kWaves - 1) / kWaves;    // ... per wave: 6
 constexpr int NBUF = 4;                     // LDS ring of staged planes
 constexpr int DIST = 3;                     // planes fetched ahead of the one being consumed
 constexpr int NFRAG = 27 * 2;               // weight fragments per lane (16 bytes each)
 constexpr int NG = 6;                       // (kw, K-half) groups per plane
 static_assert(LOADS == NG, "one staging load is issued per MFMA group");
 
-// LDS layout of a staged plane: four chunk planes (16-byte chunk c of every voxel record), each an
-// array of 16-byte entries indexed by the patch-local voxel.  A fragment read (32 consecutive voxels,
-// same chunk) is then 512 contiguous bytes per half wave, and every read address is one per-lane base
-// plus a compile-time offset.
-constexpr int CH_STRIDE = (PLANE_VOX + 2) * 16;     // 5472 bytes
-constexpr int PLANE_BYTES = 4 * CH_STRIDE;          // 21888 bytes
-constexpr int LDS_BYTES = NBUF * PLANE_BYTES;       // 87552 bytes
-__device__ __forceinline__ int lds_off(int v, int c) { return c * CH_STRIDE + v * 16; }
+// LDS layout of a staged plane: whole records (32 channels, 64 bytes), rows of LCOLS of them, so that a staging load fetches
+// 16 records (16 lines) instead of 16 bytes of 64 records, which the 9-tap march waited for (2-D, 16 slices, 32 -> 32 on 512 x
+// 512: forward 162 -> 149 us, masked data gradient 186 -> 179; the 27-tap march does not notice).  The 16-byte
+// pieces of a record sit in the order piece ^ (column / 4 % 4), so that the 16-byte reads of 16 neighbouring columns meet 16
+// different bank groups; the order depends on the column alone, so rows are an immediate offset apart and the K half flips bit
+// 5 of the address.
+constexpr int REC = 64, ROW_BYTES = LCOLS * REC;
+constexpr int PLANE_BYTES = PLANE_LOADS * 1024;     // 22528 bytes
+constexpr int LDS_BYTES = NBUF * PLANE_BYTES;       // 90112 bytes
+__device__ __forceinline__ int piece_at(int column, int piece) { return (piece ^ (column >> 2)) & 3; }
+// byte offset of 16-byte piece `piece` of column `column` of a row
+__device__ __forceinline__ int lds_off(int column, int piece) { return column * REC + 16 * piece_at(column, piece); }
 
 // How a launch treats the fp32 partial sums of a layer with several input chunks.
 enum Mode { kSingle = 0,   // only chunk: bias, ReLU, store bf16
