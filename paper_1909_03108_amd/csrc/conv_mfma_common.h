@@ -317,13 +317,12 @@ constexpr int NRG = 2;                      // row groups
 constexpr int PH = RH * NRG;                // 4 patch rows
 constexpr int LROWS = PH + 2;               // 6
 constexpr int PLANE_VOX = LROWS * LCOLS;    // 204 voxels of one chunk's plane
-constexpr int CP_LOADS = (PLANE_VOX + 63) / 64;      // 4 wave loads per 16-byte chunk plane
-constexpr int LOADS = 2 * CP_LOADS;         // a wave fills two of the four chunk planes of its input chunk
+constexpr int CHUNK_LOADS = (PLANE_VOX + 15) / 16;   // 13 wave loads of 16 records (see the layout above)
+constexpr int LOADS = (CHUNK_LOADS + 1) / 2;         // ... shared by the two waves of an input chunk: 7
 constexpr int NSLOT = 5;
-constexpr int CH_STRIDE = (PLANE_VOX + 2) * 16;      // 3296
-constexpr int CHUNK_BYTES = 4 * CH_STRIDE;           // 13184: one input chunk's plane
+constexpr int CHUNK_BYTES = CHUNK_LOADS * 1024;      // 13312: one input chunk's plane
 constexpr int PLANE_BYTES = 2 * CHUNK_BYTES;         // both chunks of the pair
-constexpr int RING_BYTES = NBUF * PLANE_BYTES;       // 105472
+constexpr int RING_BYTES = NBUF * PLANE_BYTES;       // 106496
 constexpr int RED_BYTES = NRG * RH * 4 * 64 * 16;    // 16384: one plane's hand-over (float4 per lane and unit)
 // Weight fragments in LDS (3-D kernel).  A wave needs 54 fragments = 216 registers beside 160 accumulators, and
 // the register allocation of these kernels was over its 512 by 30 - 80 registers: the compiler spilled weight
@@ -336,7 +335,7 @@ constexpr int RED_BYTES = NRG * RH * 4 * 64 * 16;    // 16384: one plane's hand-
 constexpr int WL_FRAGS = 12;
 constexpr int WL_BYTES = 2 * WL_FRAGS * 1024;          // 24576: both input chunks of the pair
 constexpr int WL_BASE = RING_BYTES + 2 * RED_BYTES;
-constexpr int LDS_BYTES = WL_BASE + WL_BYTES;          // 162816
+constexpr int LDS_BYTES = WL_BASE + WL_BYTES;          // 163840
 static_assert(LDS_BYTES <= 160 * 1024, "LDS of one CU");
 __host__ __device__ constexpr bool wl_in_lds(int KD, int f) {      // fragment f = (tap, half)
     return KD == 3 && ((f / 2) / 3) % 3 == 2 && (f / 2) / 9 >= 1;

@@ -41,8 +41,8 @@ struct Ctx {
     int plo, phi;               // staged planes are clamped to [plo, phi]
     ptrdiff_t dlo, dhi;         // gathered halos: what to add for staged plane 0 / the last one (else 0)
     uint32_t goff[LOADS];       // source offsets of the staging loads (bytes, biased by kOffBias)
-    bool tail_lane;             // lane has a voxel in the last (partial) load of a chunk plane
-    char *lds_stage;            // first chunk plane this wave fills, ring slot 0
+    char *lds_stage;            // where this wave's first load goes (ring slot 0)
+    int last;                   // ... and its last one, further on: the wave that has one less repeats the one before
     char *red;                  // hand-over buffer of this wave's row group (buffer 0), lane part included
     const char *wl;             // this chunk's LDS-resident weight fragments, lane part included
     uint16_t *obase;
@@ -54,16 +54,13 @@ struct Ctx {
     float bv[HAS_BIAS ? 16 : 1];
 };
 
-// staging load j (0..7) of plane `dplane`: chunk plane j / 4 of this wave's two, voxels 64 (j % 4) ..
+// staging load j of plane `dplane`
 template <bool HAS_BIAS>
 __device__ __forceinline__ void stage(const Ctx<HAS_BIAS> &c, int dplane, int j) {
     const int dpl = min(max(dplane, c.plo), c.phi);
     const uint16_t *p = c.tin0 + static_cast<ptrdiff_t>(dpl) * static_cast<ptrdiff_t>(c.plane_elems) +
                         (dpl == 0 ? c.dlo : 0) + (dpl == c.nplanes - 1 ? c.dhi : 0);
-    const char *dst = c.lds_stage + (dplane % NBUF) * PLANE_BYTES + (j / CP_LOADS) * CH_STRIDE + (j % CP_LOADS) * 1024;
-    // only the last load of a chunk plane is partial (204 = 3 x 64 + 12 voxels); j is a compile-time constant
-    // at every call site, so the other loads carry no predicate
-    if (j % CP_LOADS != CP_LOADS - 1 || c.tail_lane) dma16(p, c.goff[j], dst);
+    dma16(p, c.goff[j], c.lds_stage + (dplane % NBUF) * PLANE_BYTES + (j == LOADS - 1 ? c.last : j * 2048));
 }
 
 template <bool FULL, bool HAS_BIAS>
@@ -165,18 +162,19 @@ __device__ __forceinline__ void side_fence_row(pin_t (&p)[4], mask_t (&m)[4]) {
 // are fetched at the start of this step into the other register set (npin, nmk) and pass through the step's
 // wait; the step itself uses what the previous one fetched (pin, mk).  Without it the step loads what it needs
 // the ordinary way.
-// lcur / lnxt: this lane's LDS read base in the ring slots of planes Dp / Dp + 1; b0: the fragments of the first
+// lcol[kw]: this lane's LDS read base in ring slot 0 (see the one-chunk kernel's plane_step); scur / snxt: where the ring slots
+// of planes Dp / Dp + 1 are from there; b0: the fragments of the first
 // MFMA group, read (and waited for) by the previous step; on return those of the next step.  NV: how many
 // vector-memory operations the step's wait, which stands before its last MFMA group, lets stay in flight.
 template <int P, int ROLE, bool GIVE, bool FIN, int MODE, int RELU, bool FULL, int KD, bool SIDE, int NV, bool HAS_BIAS>
-__device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, uint32_t lcur, uint32_t lnxt,
+__device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, const uint32_t (&lcol)[3], uint32_t scur, uint32_t snxt,
                                            const bf16x8 (&wf)[NFRAG], f32x16 (&acc)[NSLOT][RH],
                                            pin_t (&pin)[RH][4], mask_t (&mk)[RH][4],
                                            pin_t (&npin)[RH][4], mask_t (&nmk)[RH][4], bf16x8 (&b0)[RH + 2]) {
     constexpr int NR = RH + 2;
     static_assert(NR == 4, "frag_wait names four fragments");
     static_assert(RH == 2, "one row to finish, one to hand over");
-    static_assert(2 * CH_STRIDE + ((RH + 1) * LCOLS + 2) * 16 < 65536, "offset field of the LDS reads");
+    static_assert((RH + 1) * ROW_BYTES < 65536, "offset field of the LDS reads");
     constexpr int FROW = ROLE, GROW = 1 - ROLE;      // the row this wave finishes / hands over
     constexpr int GSLOT = (P + 2) % NSLOT, FSLOT = (P + 1) % NSLOT;
     constexpr int NEXT = (P + 1) % NSLOT;      // slot of output plane Dp + 1: must be clean when this step ends
@@ -207,9 +205,9 @@ __device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, uint3
         const int kw = gi >> 1, half = gi & 1;
         if (gi + 1 < NG) {
             const int kw2 = (gi + 1) >> 1, half2 = (gi + 1) & 1;
+            const uint32_t at = (lcol[kw2] ^ (half2 * 32)) + scur;
 #pragma unroll
-            for (int r = 0; r < NR; ++r)
-                frag_read(b[(gi + 1) & 1][r], lcur, half2 * 2 * CH_STRIDE + (r * LCOLS + kw2) * 16);
+            for (int r = 0; r < NR; ++r) frag_read(b[(gi + 1) & 1][r], at, r * ROW_BYTES);
         } else {
             // The step's synchronisation stands here, before its last MFMA group (see the one-chunk kernel's
             // plane_step): plane Dp + 1 has landed when at most the loads of plane Dp + 2 and this step's first
@@ -219,7 +217,7 @@ __device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, uint3
             side_fence_row<NV, SIDE && S::PINS, SIDE && S::MASK && !S::BITS, SIDE && S::BITS>(npin[FROW], nmk[FROW]);
             __builtin_amdgcn_s_barrier();
 #pragma unroll
-            for (int r = 0; r < NR; ++r) frag_read(b[0][r], lnxt, (r * LCOLS) * 16);
+            for (int r = 0; r < NR; ++r) frag_read(b[0][r], lcol[0] + snxt, r * ROW_BYTES);
         }
         // this group's fragments were read a group ago; the NR reads issued just now may stay in flight
         frag_wait<NR>(b[gi & 1]);
@@ -235,9 +233,10 @@ __device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, uint3
             wl2[1] = *reinterpret_cast<const bf16x8 *>(c.wl + wl_index(2, kw, half) * 1024);
         }
         __builtin_amdgcn_sched_barrier(0);
-        // eight staging loads over six groups
+        // seven staging loads over six groups
+        static_assert(LOADS == NG + 1, "staging loads per MFMA group");
         stage(c, Dp + DIST, gi);
-        if (gi < 2) stage(c, Dp + DIST, NG + gi);
+        if (gi == 0) stage(c, Dp + DIST, NG);
         if (gi < 4) {
             // (the empty statements tie the copies out of the accumulation registers to this group; otherwise the
             // compiler emits all of them at the top of the step, in front of its first MFMA)
@@ -364,21 +363,27 @@ __device__ __forceinline__ void run(const ConvArgs &a, char *lds, int logical, i
     c.nplanes = dn + 2;
     c.plo = F > 1 ? 1 : 0;
     c.phi = F > 1 ? c.nplanes - 2 : c.nplanes - 1;
-    // this wave fills chunk planes 2 rg and 2 rg + 1 (channels 16 rg .. 16 rg + 15) of its input chunk
+    // This wave's loads rg, rg + 2, ... of its input chunk's plane: voxels 16 (rg + 2 j) .. + 15, four lanes to a voxel (see
+    // piece_at; places past the last voxel take that voxel again).
+    const bool less = rg + 2 * (LOADS - 1) >= CHUNK_LOADS;
+    c.last = (LOADS - 1 - (less ? 1 : 0)) * 2048;
+    const auto staged_voxel = [&](int j) {
+        return min(16 * (rg + 2 * (j == LOADS - 1 && less ? j - 1 : j)) + (lane >> 2), PLANE_VOX - 1);
+    };
     int goff[LOADS];            // in elements; the host has checked that twice their value fits 32 bits
 #pragma unroll
     for (int j = 0; j < LOADS; ++j) {
-        const int v = 64 * (j % CP_LOADS) + lane;
+        const int v = staged_voxel(j);
         const FoldCol fc = fold_col(v % LCOLS, F, a.fold_w);
         const int row = min(h0 + v / LCOLS, bx.bh + 1), colv = min(w0 + fc.c, bx.bw + 1);
-        goff[j] = ((min(fc.s, F - 1) * g.ph + row) * g.pw + colv) * src_cs + (2 * rg + j / CP_LOADS) * 8;   // always addressable
+        goff[j] = ((min(fc.s, F - 1) * g.ph + row) * g.pw + colv) * src_cs + 8 * piece_at(v % LCOLS, lane & 3);   // always addressable
     }
     c.dlo = c.dhi = 0;
     if (a.gather) {          // see GatherShift
         const GatherShift gs = gather_shift(g, tile, src_cs);
 #pragma unroll
         for (int j = 0; j < LOADS; ++j) {
-            const int v = 64 * (j % CP_LOADS) + lane;
+            const int v = staged_voxel(j);
             const int row = min(h0 + v / LCOLS, bx.bh + 1), colv = min(w0 + v % LCOLS, bx.bw + 1);
             goff[j] += (row == 0 ? gs.hm : 0) + (row == g.th + 1 ? gs.hp : 0) + (colv == 0 ? gs.wm : 0) +
                        (colv == g.tw + 1 ? gs.wp : 0);
@@ -388,8 +393,7 @@ __device__ __forceinline__ void run(const ConvArgs &a, char *lds, int logical, i
     }
 #pragma unroll
     for (int j = 0; j < LOADS; ++j) c.goff[j] = static_cast<uint32_t>(goff[j] * 2) + kOffBias;
-    c.tail_lane = 64 * (CP_LOADS - 1) + lane < PLANE_VOX;
-    c.lds_stage = lds + ROLE * CHUNK_BYTES + 2 * rg * CH_STRIDE;
+    c.lds_stage = lds + ROLE * CHUNK_BYTES + rg * 1024;
     c.red = lds + RING_BYTES + rg * (RH * 4 * 1024) + lane * 16;
     c.wl = lds + WL_BASE + ROLE * WL_FRAGS * 1024 + lane * 16;
     const OutDst od = out_dest(a, cj);
@@ -420,7 +424,7 @@ __device__ __forceinline__ void run(const ConvArgs &a, char *lds, int logical, i
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[s][h][i] = (ROLE == 0 && HAS_BIAS) ? c.bv[HAS_BIAS ? i : 0] : 0.f;
 
-    const char *lbase = lds + ROLE * CHUNK_BYTES + hi * CH_STRIDE + (rg * RH * LCOLS + col) * 16;
+    const char *lbase = lds + ROLE * CHUNK_BYTES + rg * RH * ROW_BYTES;
     const int nplanes = c.nplanes;
 
 #pragma unroll
@@ -432,10 +436,11 @@ __device__ __forceinline__ void run(const ConvArgs &a, char *lds, int logical, i
 
     // (a plane step synchronises inside itself, before its last MFMA group; a drain step at its end)
     constexpr int NV_STEP = (DIST - 1) * LOADS - 1;     // plane Dp + 2's loads and the step's first LOADS - 1
-    const uint32_t lring = lds_addr(lbase);
+    const uint32_t lcol[3] = {lds_addr(lbase + lds_off(col, hi)), lds_addr(lbase + lds_off(col + 1, hi)),
+                              lds_addr(lbase + lds_off(col + 2, hi))};
     bf16x8 b0[RH + 2];
 #pragma unroll
-    for (int r = 0; r < RH + 2; ++r) b0[r] = *reinterpret_cast<const bf16x8 *>(lbase + (r * LCOLS) * 16);
+    for (int r = 0; r < RH + 2; ++r) b0[r] = *reinterpret_cast<const bf16x8 *>(lbase + lds_off(col, hi) + r * ROW_BYTES);
 
     auto march = [&](auto full_tag) {
         constexpr bool FULL = decltype(full_tag)::value;
@@ -453,11 +458,11 @@ __device__ __forceinline__ void run(const ConvArgs &a, char *lds, int logical, i
         static_assert(LOADS - 1 + 4 <= NV_STEP, "a wait that covers the side loads covers the staged plane");
 #define SP3D_NV_OF(SIDES, FIN_EN) ((SIDES) ? LOADS - 1 + ((FIN_EN) ? 4 : 0) : NV_STEP)
         plane_step<0, ROLE, false, false, MODE, RELU, FULL, KD, false, NV_STEP>(
-            c, 0, lring, lring + PLANE_BYTES, wf, acc, pinA, mkA, pinB, mkB, b0);
+            c, 0, lcol, 0, PLANE_BYTES, wf, acc, pinA, mkA, pinB, mkB, b0);
         plane_step<1, ROLE, false, false, MODE, RELU, FULL, KD, false, NV_STEP>(
-            c, 1, lring + PLANE_BYTES, lring + 2 * PLANE_BYTES, wf, acc, pinA, mkA, pinB, mkB, b0);
+            c, 1, lcol, PLANE_BYTES, 2 * PLANE_BYTES, wf, acc, pinA, mkA, pinB, mkB, b0);
         plane_step<2, ROLE, false, false, MODE, RELU, FULL, KD, false, NV_STEP>(
-            c, 2, lring + 2 * PLANE_BYTES, lring + 3 * PLANE_BYTES, wf, acc, pinB, mkB, pinA, mkA, b0);
+            c, 2, lcol, 2 * PLANE_BYTES, 3 * PLANE_BYTES, wf, acc, pinB, mkB, pinA, mkA, b0);
         // Steps 3, 4, ... with slot phase Dp mod 5 as a compile-time constant (the ring slot Dp mod 4 is a
         // run-time offset: a period of 20 steps would be needed to make both constants).  The march runs two
         // steps past the last input plane; those only hand over / finish what is left.  Step 3 is the first
@@ -465,8 +470,7 @@ __device__ __forceinline__ void run(const ConvArgs &a, char *lds, int logical, i
 #define SP3D_STEP(DP, PHASE, FIN_EN, CP, CM, NP, NM)                                                       \
     if ((DP) < nplanes) {                                                                                  \
         plane_step<PHASE, ROLE, true, FIN_EN, MODE, RELU, FULL, KD, SD, SP3D_NV_OF(SD, FIN_EN)>(           \
-            c, (DP), lring + ((DP) % NBUF) * PLANE_BYTES, lring + (((DP) + 1) % NBUF) * PLANE_BYTES, wf, acc, CP, CM, \
-            NP, NM, b0);                                                                                   \
+            c, (DP), lcol, ((DP) % NBUF) * PLANE_BYTES, (((DP) + 1) % NBUF) * PLANE_BYTES, wf, acc, CP, CM, NP, NM, b0); \
     } else if ((DP) < nplanes + 2) {                                                                       \
         drain_step<PHASE, ROLE, true, FIN_EN, MODE, RELU, FULL, KD, SD>(c, (DP), acc, CP, CM, NP, NM);     \
         side_fence_row<(SD ? 0 : (DIST - 1) * LOADS), SD && S::PINS, SD && S::MASK && !S::BITS, SD && S::BITS>( \
@@ -500,7 +504,7 @@ __device__ __forceinline__ void run(const ConvArgs &a, char *lds, int logical, i
 
 template <int MODE, bool HAS_BIAS, int RELU, int KD>
 __global__ __launch_bounds__(kThreads, 1) void conv_mfma_pair_kernel(ConvArgs a) {
-    extern __shared__ __attribute__((aligned(16))) char lds[];
+    extern __shared__ __attribute__((aligned(128))) char lds[];
     const Geo &g = a.g;
     const int per_xcd = gridDim.x >> 3;
     const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
