@@ -12,6 +12,9 @@
 // converts and stores - the chunk-0 wave finishes row 0, the chunk-1 wave row 1.  A plane therefore lives in
 // an accumulator slot for five steps (three contributing, one being handed over, one being stored), hence
 // five slots.  Layers with more than one pair still go through fp32 partial sums, but half as often.
+// Planes are staged as whole 64-byte records of a chunk, like the one-chunk kernel's (chunk planes, 16 bytes of 64 records a
+// load, before): 64 -> 64, 2-D, on 16 x 256 x 256 forward 147 -> 120 us, masked data gradient 192 -> 156; four-level 3-D training
+// step on 256^3 22.34 -> 21.89 ms, six-level 44.9 -> 44.0.
 #pragma once
 #include "conv_mfma_common.h"
 

@@ -370,14 +370,18 @@ __global__ __launch_bounds__(kThreads) void wgrad_mfma_kernel(WgradArgs a) {
 //  - the bias gradient is one more MFMA per dz row with an all-ones A operand (every row of the
 //    result is the column sum), issued by one wave per SIMD.
 constexpr int NXB = 3, NZB = 5;               // ring slots: x planes D..D+2, dz planes D-2..D+2
-constexpr int XG = (XVOX + 31) / 32;          // 11 groups of 32 voxels per x plane; the last one is padded
-constexpr int XD_HALF = XG * 32 * 32 + 64;    // 11328: room for the padding voxels of the last group
-constexpr int XD_BYTES = 2 * XD_HALF;
-constexpr int DMA_STAGE_BYTES = NXB * XD_BYTES + NZB * Z_PLANE;       // 150528
+// LDS keeps whole voxel records of 64 bytes, so that a load fetches 16 of them (with the halves apart it fetched 32 bytes of
+// 32 records, and the other halves came with another load).  The two halves of a record are swapped in every second group of
+// four columns: the 32 lanes of a transposing read cover one half of eight neighbouring columns, 256 different bytes of the banks.
+// Measured, halves apart -> this, 3-D: 64 -> 64 on 128^3 440 -> 383 us, 128 -> 128 on 64^3 232 -> 207, 32 -> 32 on 256^3 781 -> 722; the
+// four-level training step on 256^3 21.89 -> 21.41 ms, the six-level one 44.0 -> 42.9.
+constexpr int XG = (XVOX + 15) / 16, ZG = ZVOX / 16;     // loads of a plane: 22 for x (the last one padded), 16 for dz
+constexpr int REC = 64;
+constexpr int XD_BYTES = XG * 1024, ZD_PLANE = ZG * 1024;
+constexpr int DMA_STAGE_BYTES = NXB * XD_BYTES + NZB * ZD_PLANE;       // 149504
 constexpr int DMA_LDS_BYTES = DMA_STAGE_BYTES > RED_BYTES ? DMA_STAGE_BYTES : RED_BYTES;
 static_assert(DMA_LDS_BYTES <= 160 * 1024, "LDS of one CU");
-// Wave loads per plane pair: 2 halves x 11 groups for x, 2 halves x 8 groups for dz.  Each of the 8
-// waves issues 3 x loads (24 slots for 22 loads: the last two waves repeat one of theirs) and 2 dz loads.
+// Each of the 8 waves issues 3 x loads (24 slots for 22 loads: the last two waves repeat one of theirs) and 2 dz loads.
 constexpr int DMA_X = 3, DMA_Z = 2, DMA_PER_WAVE = DMA_X + DMA_Z;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -395,17 +399,28 @@ __device__ __forceinline__ void dma16(const uint16_t *src, char *dst) {
                  : "memory");
 }
 
+__device__ __forceinline__ bf16x8 frag_rec(const char *p) {
+    union { struct { s16x4 lo, hi; } s; bf16x8 v; } u;
+    u.s.lo = tr_read(p);
+    u.s.hi = tr_read(p + 16 * REC);
+    return u.v;
+}
 __device__ __forceinline__ bf16x8 frag_masked(const char *p, uint32_t m) {
     union { struct { s16x4 lo, hi; } s; u32x4 w; bf16x8 v; } u;
     u.s.lo = tr_read(p);
-    u.s.hi = tr_read(p + 16 * 32);
+    u.s.hi = tr_read(p + 16 * REC);
     u.w &= m;
     return u.v;
+}
+// The lane's place in a row of records: column 4 G + p / 4 (+ kw), channel quad p % 4 of half `half`.
+__device__ __forceinline__ int rec_at(int lane, int half, int kw) {
+    const int v = 4 * (lane >> 4) + ((lane & 15) >> 2) + kw;
+    return v * REC + ((half ^ (v >> 2)) & 1) * 32 + (lane & 3) * 8;
 }
 
 // Same march as plane_step, with run-time ring slots: z[kd] points at dz plane D - kd, m[kd] is
 // all ones if that plane exists and zero otherwise.
-__device__ __forceinline__ void plane_step_dma(const char *xl, const char *z0, const char *z1, const char *z2,
+__device__ __forceinline__ void plane_step_dma(const char *xl, const int (&xkw)[3], const char *z0, const char *z1, const char *z2,
                                                uint32_t m0, uint32_t m1, uint32_t m2, bool bias_wave,
                                                f32x4 (&acc)[27], f32x4 &accb) {
     const char *z[3] = {z0, z1, z2};
@@ -416,7 +431,7 @@ __device__ __forceinline__ void plane_step_dma(const char *xl, const char *z0, c
     bf16x8 zf[3][4];
     bf16x8 xf[2][3];
 #pragma unroll
-    for (int kw = 0; kw < 3; ++kw) xf[0][kw] = frag(xl + kw * 32);
+    for (int kw = 0; kw < 3; ++kw) xf[0][kw] = frag_rec(xl + xkw[kw]);
 #pragma unroll
     for (int kd = 0; kd < 3; ++kd)
         zf[kd][0] = frag_masked(z[kd], m[kd]);
@@ -425,12 +440,12 @@ __device__ __forceinline__ void plane_step_dma(const char *xl, const char *z0, c
     for (int R = 0; R < GR + 2; ++R) {
         if (R + 1 < GR + 2) {
 #pragma unroll
-            for (int kw = 0; kw < 3; ++kw) xf[(R + 1) & 1][kw] = frag(xl + ((R + 1) * XC + kw) * 32);
+            for (int kw = 0; kw < 3; ++kw) xf[(R + 1) & 1][kw] = frag_rec(xl + xkw[kw] + (R + 1) * XC * REC);
         }
         if (R + 1 < GR) {
 #pragma unroll
             for (int kd = 0; kd < 3; ++kd)
-                zf[kd][(R + 1) & 3] = frag_masked(z[kd] + (R + 1) * PW * 32, m[kd]);
+                zf[kd][(R + 1) & 3] = frag_masked(z[kd] + (R + 1) * PW * REC, m[kd]);
         }
         __builtin_amdgcn_sched_barrier(0);
         // every dz plane passes once through each kd position (masked when it does not exist)
@@ -461,15 +476,15 @@ __device__ __forceinline__ void plane_step_dma(const char *xl, const char *z0, c
 // LDS latency with nothing to do; with the barrier behind row GR - 1 and the next plane's first fragments on
 // their way during row GR + 1 the rows follow each other without a gap.
 struct DmaPlane { const char *x; const char *z[3]; uint32_t m[3]; };
-__device__ __forceinline__ void dma_row0(const DmaPlane &pl, bf16x8 (&xf)[2][3], bf16x8 (&zf)[3][4]) {
+__device__ __forceinline__ void dma_row0(const DmaPlane &pl, const int (&xkw)[3], bf16x8 (&xf)[2][3], bf16x8 (&zf)[3][4]) {
 #pragma unroll
-    for (int kw = 0; kw < 3; ++kw) xf[0][kw] = frag(pl.x + kw * 32);
+    for (int kw = 0; kw < 3; ++kw) xf[0][kw] = frag_rec(pl.x + xkw[kw]);
 #pragma unroll
     for (int kd = 0; kd < 3; ++kd)
         zf[kd][0] = frag_masked(pl.z[kd], pl.m[kd]);
 }
 template <int R0, int R1>
-__device__ __forceinline__ void plane_rows_dma(const DmaPlane &pl, const DmaPlane &nx, bool bias_wave,
+__device__ __forceinline__ void plane_rows_dma(const DmaPlane &pl, const DmaPlane &nx, const int (&xkw)[3], bool bias_wave,
                                                bf16x8 (&xf)[2][3], bf16x8 (&zf)[3][4], f32x4 (&acc)[27],
                                                f32x4 &accb) {
     union { uint32_t w[4]; bf16x8 v; } ones;
@@ -480,14 +495,14 @@ __device__ __forceinline__ void plane_rows_dma(const DmaPlane &pl, const DmaPlan
     for (int R = R0; R < R1; ++R) {
         if (R + 1 < GR + 2) {
 #pragma unroll
-            for (int kw = 0; kw < 3; ++kw) xf[(R + 1) & 1][kw] = frag(pl.x + ((R + 1) * XC + kw) * 32);
+            for (int kw = 0; kw < 3; ++kw) xf[(R + 1) & 1][kw] = frag_rec(pl.x + xkw[kw] + (R + 1) * XC * REC);
             if (R + 1 < GR) {
 #pragma unroll
                 for (int kd = 0; kd < 3; ++kd)
-                    zf[kd][(R + 1) & 3] = frag_masked(pl.z[kd] + (R + 1) * PW * 32, pl.m[kd]);
+                    zf[kd][(R + 1) & 3] = frag_masked(pl.z[kd] + (R + 1) * PW * REC, pl.m[kd]);
             }
         } else {
-            dma_row0(nx, xf, zf);      // row GR + 1 uses xf[1] and ring slot GR - 1 only
+            dma_row0(nx, xkw, xf, zf);      // row GR + 1 uses xf[1] and ring slot GR - 1 only
         }
         __builtin_amdgcn_sched_barrier(0);
         // every dz plane passes once through each kd position (masked when it does not exist)
@@ -538,31 +553,29 @@ __global__ __launch_bounds__(kThreads) void wgrad_mfma_dma_kernel(WgradArgs a) {
     char *xbuf = lds;
     char *zbuf = lds + NXB * XD_BYTES;
     const int G = lane >> 4, p = lane & 15;
-    const int lane_off = (4 * G + (p >> 2)) * 32 + (p & 3) * 8;
-    const char *xlane = xbuf + qi * XD_HALF + lane_off + kg * GR * XC * 32;
-    const char *zlane = zbuf + qo * Z_HALF + lane_off + kg * GR * PW * 32;
+    const char *xlane = xbuf + kg * GR * XC * REC;
+    const int xkw[3] = {rec_at(lane, qi, 0), rec_at(lane, qi, 1), rec_at(lane, qi, 2)};
+    const char *zlane = zbuf + kg * GR * PW * REC + rec_at(lane, qo, 0);
 
     // Staging loads of this wave: x loads u = 2*wave, 2*wave + 1 and 16 + wave (waves 6, 7 repeat their
-    // second one), dz loads 2*wave, 2*wave + 1.  Load u covers half u / groups, voxel group u % groups;
-    // lane l fetches chunk l & 1 of voxel 32*group + l/2.  Voxels past the end of the x plane (last
-    // group) re-fetch its last voxel into the padding.
+    // second one), dz loads 2*wave, 2*wave + 1.  Load u covers voxels 16 u .. + 15: lane l fetches voxel 16 u + l / 4,
+    // the piece of 16 bytes whose place is its own.  Voxels past the end of the x plane re-fetch its last voxel into the padding.
     int gx[DMA_X], gz[DMA_Z];        // source offsets (elements) inside the item's plane
     int lx[DMA_X], lz[DMA_Z];        // LDS byte offsets inside ring slot 0
+    const auto x_load = [&](int j) { return j < 2 ? 2 * wave + j : (wave < 6 ? 16 + wave : 2 * wave + 1); };
+    const auto x_voxel = [&](int j) { return min(x_load(j) * 16 + (lane >> 2), XVOX - 1); };
+    const auto piece = [&](int column) { return ((lane & 3) ^ ((column >> 2 & 1) << 1)) * 8; };
 #pragma unroll
     for (int j = 0; j < DMA_X; ++j) {
-        const int u = j < 2 ? 2 * wave + j : (wave < 6 ? 16 + wave : 2 * wave + 1);
-        const int half = u / XG, vg = u % XG;
-        const int v = min(vg * 32 + (lane >> 1), XVOX - 1);
-        gx[j] = ((v / XC) * g.pw + v % XC) * xs.cs + half * 16 + (lane & 1) * 8;
-        lx[j] = half * XD_HALF + vg * 1024;
+        const int v = x_voxel(j);
+        gx[j] = ((v / XC) * g.pw + v % XC) * xs.cs + piece(v % XC);
+        lx[j] = x_load(j) * 1024;
     }
 #pragma unroll
     for (int j = 0; j < DMA_Z; ++j) {
-        const int u = 2 * wave + j;
-        const int half = u / (ZVOX / 32), vg = u % (ZVOX / 32);
-        const int v = vg * 32 + (lane >> 1);
-        gz[j] = ((v / PW + 1) * g.pw + v % PW + 1) * a.dz_cs + half * 16 + (lane & 1) * 8;
-        lz[j] = NXB * XD_BYTES + half * Z_HALF + vg * 1024;
+        const int u = 2 * wave + j, v = u * 16 + (lane >> 2);
+        gz[j] = ((v / PW + 1) * g.pw + v % PW + 1) * a.dz_cs + piece(v % PW);
+        lz[j] = NXB * XD_BYTES + u * 1024;
     }
 
     f32x4 acc[27];
@@ -604,8 +617,7 @@ __global__ __launch_bounds__(kThreads) void wgrad_mfma_dma_kernel(WgradArgs a) {
             const ptrdiff_t sd = (tv * g.gw * g.gh - static_cast<ptrdiff_t>(g.td) * g.ph * g.pw) * xs.cs;
 #pragma unroll
             for (int j = 0; j < DMA_X; ++j) {
-                const int u = j < 2 ? 2 * wave + j : (wave < 6 ? 16 + wave : 2 * wave + 1);
-                const int v = min((u % XG) * 32 + (lane >> 1), XVOX - 1);
+                const int v = x_voxel(j);
                 const int row = h0 + v / XC, col = w0 + v % XC;
                 gxa[j] += (row == 0 && tb > 0 ? static_cast<int>(-sh) : 0) +
                           (row == g.th + 1 && tb < g.gh - 1 ? static_cast<int>(sh) : 0) +
@@ -624,7 +636,7 @@ __global__ __launch_bounds__(kThreads) void wgrad_mfma_dma_kernel(WgradArgs a) {
         const uint16_t *px = tx + dx_ * xplane + (dx_ == 0 ? dlo : 0) + (dx_ == dn + 1 ? dhi : 0); \
         const uint16_t *pz = tz + min((D), dn - 1) * zplane;                                       \
         _Pragma("unroll") for (int j = 0; j < DMA_X; ++j) dma16(px + gxa[j], lds + lx[j] + (sx) * XD_BYTES); \
-        _Pragma("unroll") for (int j = 0; j < DMA_Z; ++j) dma16(pz + gz[j], lds + lz[j] + (sz) * Z_PLANE);  \
+        _Pragma("unroll") for (int j = 0; j < DMA_Z; ++j) dma16(pz + gz[j], lds + lz[j] + (sz) * ZD_PLANE);  \
     } while (0)
 
         if (MID) {
@@ -648,18 +660,18 @@ __global__ __launch_bounds__(kThreads) void wgrad_mfma_dma_kernel(WgradArgs a) {
                 const int sz2m = sz1 == 0 ? NZB - 1 : sz1 - 1;
                 DmaPlane pl;
                 pl.x = xlane + sxD * XD_BYTES;
-                pl.z[0] = zlane + szD * Z_PLANE; pl.z[1] = zlane + sz1 * Z_PLANE; pl.z[2] = zlane + sz2m * Z_PLANE;
+                pl.z[0] = zlane + szD * ZD_PLANE; pl.z[1] = zlane + sz1 * ZD_PLANE; pl.z[2] = zlane + sz2m * ZD_PLANE;
                 pl.m[0] = D < dn ? 0xffffffffu : 0u;
                 pl.m[1] = (D >= 1 && D - 1 < dn) ? 0xffffffffu : 0u;
                 pl.m[2] = D >= 2 ? 0xffffffffu : 0u;
                 return pl;
             };
             DmaPlane cur = plane_at(0, sx, sz);
-            dma_row0(cur, xf, zf);
+            dma_row0(cur, xkw, xf, zf);
             for (int D = 0; D < nplanes; ++D) {
                 const int sxn = sx + 1 == NXB ? 0 : sx + 1, szn = sz + 1 == NZB ? 0 : sz + 1;
                 const DmaPlane nxt = plane_at(D + 1, sxn, szn);
-                plane_rows_dma<0, GR>(cur, nxt, bias_wave, xf, zf, acc, accb);
+                plane_rows_dma<0, GR>(cur, nxt, xkw, bias_wave, xf, zf, acc, accb);
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 __builtin_amdgcn_s_barrier();
                 {
@@ -667,7 +679,7 @@ __global__ __launch_bounds__(kThreads) void wgrad_mfma_dma_kernel(WgradArgs a) {
                     const int sz2 = sz + 2 >= NZB ? sz + 2 - NZB : sz + 2;
                     SP3D_STAGE(D + 2, sx2, sz2);
                 }
-                plane_rows_dma<GR, GR + 2>(cur, nxt, bias_wave, xf, zf, acc, accb);
+                plane_rows_dma<GR, GR + 2>(cur, nxt, xkw, bias_wave, xf, zf, acc, accb);
                 cur = nxt;
                 sx = sxn;
                 sz = szn;
@@ -692,8 +704,8 @@ __global__ __launch_bounds__(kThreads) void wgrad_mfma_dma_kernel(WgradArgs a) {
                 const uint32_t m0 = D < dn ? 0xffffffffu : 0u;
                 const uint32_t m1 = (D >= 1 && D - 1 < dn) ? 0xffffffffu : 0u;
                 const uint32_t m2 = D >= 2 ? 0xffffffffu : 0u;
-                plane_step_dma(xlane + sx * XD_BYTES, zlane + sz * Z_PLANE, zlane + sz1 * Z_PLANE,
-                               zlane + sz2m * Z_PLANE, m0, m1, m2, bias_wave, acc, accb);
+                plane_step_dma(xlane + sx * XD_BYTES, xkw, zlane + sz * ZD_PLANE, zlane + sz1 * ZD_PLANE,
+                               zlane + sz2m * ZD_PLANE, m0, m1, m2, bias_wave, acc, accb);
                 // plane D + 1 (staged one step ago) has landed once at most this step's loads are in flight
                 asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
                 __builtin_amdgcn_s_barrier();
@@ -748,7 +760,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // LDS keeps whole voxel records of 64 bytes: a load fetches 16 of them (in the march's layout, halves apart, a load fetches the
 // same half of 32 records and the other half comes with another load), and 32 lanes of a transposing read cover four records,
 // 256 bytes in a row: no bank conflicts.
-constexpr int F_NX = (XVOX + 15) / 16, F_NZ = ZVOX / 16;  // staging loads of a unit: x and dz
+constexpr int F_NX = XG, F_NZ = ZG;            // staging loads of a unit: x and dz
 constexpr int F_UNIT = (F_NX + F_NZ) * 1024, F_LDS_BYTES = 4 * F_UNIT;
 constexpr int F_LOADS = (F_NX + F_NZ + 3) / 4;            // ... per wave
 static_assert(F_LDS_BYTES <= 160 * 1024 && 4 * 9 * 16 * 64 * 4 <= F_LDS_BYTES, "LDS of one CU");
