@@ -13,22 +13,26 @@
 // shape, and where tiles are fewer than compute units the K loop is split between `nsplit` workgroups, whose fp32 sums a
 // second launch adds in order.
 //
-// A K step is one kernel row (three taps kw) x one 32-channel input chunk.  Both operands come through LDS by
-// direct loads, NS stages deep (one barrier per step, placed before the step's last MFMA group, so that the next
-// step's first fragments are read behind it while that group runs):
-//   A (weights): the packed fragments of conv_mfma.hip, 1 KB each, lane-major.
-//   B (voxels): the records (32 channels, 64 bytes) of the padded rows that the tile's voxels touch, each ONCE for the
-//     three taps of the row: voxel q of a box row of ew voxels is record (q / ew) (ew + 2) + q % ew, and the taps read
-//     this record and the two after it.  The 16-byte pieces of a record sit in the order piece ^ (record / 4 % 4), so
-//     that the 16-byte reads of 16 neighbouring voxels fall into 16 different bank groups.
+// A K step is one kernel row (three taps kw) x one 32-channel input chunk.
+//   A (weights): the packed fragments of conv_mfma.hip, 1 KB each, lane-major, loaded into registers one or three steps ahead (the two
+//     waves of an output block meet in the vector cache).
+//   B (voxels): through LDS by direct loads, three stages: the records (32 channels, 64 bytes) of the padded rows that the
+//     tile's voxels touch, each ONCE for the three taps of the row: voxel q of a box row of ew voxels is record (q / ew)
+//     (ew + 2) + q % ew, and the taps read this record and the two after it.  The 16-byte pieces of a record sit in the order
+//     piece ^ (record / 4 % 4), so that the 16-byte reads of 16 neighbouring voxels fall into 16 different bank groups.
 // (v_mfma_f32_32x32x16_bf16, A = weights [32 output channels][16 input channels], B = voxels [16 input channels][32
-// voxels]; four waves, two along output channels x two along voxels.)
-// What bounds it: in its first form the B fragments were fetched by the lanes themselves, 16 bytes of 64 different
-// lines per load, and the vector cache's one line per clock held the step at 0.9 (128 voxels) and 2.1 us (256 voxels),
-// three times its MFMAs; with up to 32 workgroups and no split the bottom level of the 3-D network took 250 us a layer.
-// Now, first form -> this one: 1024 -> 1024 on 8^3 voxels (3-D) 250 -> 31 + 9 us (its 57 MB of weights: 7 us of HBM), 512 ->
-// 512 on 16^3 150 -> 64 + 9 us (0.9 PFLOP/s), 2-D on two slices 1024 -> 1024 on 16 x 16 88 -> 22 + 6 us (a launch, a pipeline
-// of three stages and 12 steps: latency), 512 -> 512 on 16 slices of 32 x 32 115 -> 100 us.
+// voxels]; four waves, two along output channels x two along voxels.)  One barrier per step, placed before the step's last
+// MFMA group, so that the next step's first fragments are read behind it while that group runs; a step's loads are issued one per
+// group, between its products.  Workgroups stay: as many as fit on the chip take one item (tile and range of K) after the
+// other, and the loads run on into the next item while this one's sums are stored.
+// What bounds it: long K loops the chip's power (512 -> 512 on 32^3 390 us = 1.19 PFLOP/s, what the vendor's GEMM reaches on the
+// card), short ones the stores and index arithmetic between items.  With both operands in LDS and a workgroup per item, LDS
+// reads and loads took as long as the products, the loads' addresses were computed while the matrix cores waited, and every
+// item began and ended alone; before -> now: 2-D, 128 -> 128 on 16 x 128^2 145 -> 92 us, 256 -> 256 on 16 x 64^2 109 -> 88, 512 ->
+// 512 on 16 x 32^2 98 -> 81, 64 -> 64 on 2 x 256^2 36 -> 23, 3-D, 256 -> 256 on 32^3 132 -> 110, 512 -> 512 on 16^3 84 -> 75 (with the
+// packing of the weights; with both operands in LDS still, staying workgroups alone gave 145 -> 127).  Layers of one
+// item per compute unit and few steps (1024 -> 1024 on 16 x 16, two slices: 31 us) wait for a launch, a pipeline of three stages and
+// a second launch that adds the splits.
 //
 // Output box growth, two input tensors (concatenation without a copy), two output tensors, bias, ReLU, the ReLU mask
 // of the data gradient, its one-bit forms and gathered halos behave as in conv_mfma.hip.  The order of the additions
@@ -36,6 +40,8 @@
 // interior voxel count and channels only, so results are reproducible and depend neither on the voxel's position nor on
 // the tile grid.
 #include "conv_mfma_common.h"
+
+#include <algorithm>
 
 namespace sp3d {
 
@@ -51,9 +57,14 @@ constexpr int NTAP_PACK = 27;                    // packed weights: 27 tap slots
 constexpr int wg_vox(int vb) { return 128 * vb; }
 // Cutting of a workgroup: CBW output blocks per wave (2 CBW per workgroup), VB x 128 voxels, BL wave loads of 16 records
 // per wave and step.
-constexpr int stage_bytes(int cbw, int bl) { return (2 * cbw * ROW * 2 + 4 * bl) * 1024; }
-// LDS stages: four for wide workgroups, one per compute unit; three where two workgroups then share one
-constexpr int stages(int cbw, int bl) { return cbw == 2 && 4 * stage_bytes(2, bl) <= 160 * 1024 ? 4 : 3; }
+constexpr int stage_bytes(int bl) { return 4 * bl * 1024; }
+// LDS stages of voxels; the step loop is unrolled by as many, so that a stage and a register set have their place at compile
+// time, and K is split in units of as many steps (kernel rows x chunks: 3 divides both 3 and 9)
+constexpr int NS = 3;
+// steps that weight fragments are loaded ahead (128 channels x 128 voxels: one, so that two workgroups fit the registers)
+constexpr int ahead(int cbw, int vb) { return cbw == 2 && vb == 1 ? 1 : NS; }
+// workgroups per compute unit
+constexpr int resident(int cbw, int vb) { return cbw == 2 && vb == 2 ? 1 : 2; }
 
 struct GemmArgs {
     const uint16_t *in;      // input channels [0, in_ca): in_cs channels per voxel
@@ -107,8 +118,8 @@ __device__ __forceinline__ BoxPos row_pos(const GemmArgs &a, uint32_t row) {
     return p;
 }
 
-// Output voxel q: padded voxel index, and whether it exists (past the end, or outside the box of a tile without a
-// neighbour on that side: no).
+// Output voxel q: whether it exists (past the end, or outside the box of a tile without a neighbour on that side: no) and
+// its padded voxel index (0 where it does not: an address that can be loaded from).
 struct OutVox { long long pv; bool ok; };
 __device__ __forceinline__ OutVox out_vox(const GemmArgs &a, int q) {
     const uint32_t qq = static_cast<uint32_t>(min(q, a.nvox - 1)), row = fdiv(qq, a.drow);
@@ -117,48 +128,77 @@ __device__ __forceinline__ OutVox out_vox(const GemmArgs &a, int q) {
     const TileBox bx = tile_box(a.g, p.tile);
     OutVox o;
     o.ok = q < a.nvox && p.d < bx.bd && p.h < bx.bh && p.w < bx.bw;
-    o.pv = static_cast<long long>(p.tile) * a.g.tile_vox + bx.org + (1LL * (p.d + 1) * a.g.ph + p.h + 1) * a.g.pw + p.w + 1;
+    o.pv = o.ok ? static_cast<long long>(p.tile) * a.g.tile_vox + bx.org + (1LL * (p.d + 1) * a.g.ph + p.h + 1) * a.g.pw + p.w + 1 : 0;
     return o;
 }
 
-// Finished sums of one voxel, 16 channels (8 q + 4 hi + i) of output block cj: ReLU / mask, convert, 8-byte stores.
-__device__ __forceinline__ void finish(const GemmArgs &a, const f32x16 &s, int cj, int hi, const OutVox &o) {
-    if (!o.ok) return;
+// What the epilogue of one voxel and output block reads: 16 bytes of the mask at channels 16 p + 8 hi, or the lane's word.
+struct EpiIn { uint4 mask[2]; uint32_t word; };
+template <int EPI>
+__device__ __forceinline__ void epi_load(const GemmArgs &a, EpiIn &in, int cj, int hi, const OutVox &o) {
+    if (EPI == kMask) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+            in.mask[p] = *reinterpret_cast<const uint4 *>(a.mask + o.pv * a.out_cs + C * cj + 16 * p + 8 * hi);
+    }
+    if (EPI == kMaskBits) in.word = a.bits[(o.pv * a.nco + cj) * 2 + hi];
+}
+
+// Finished sums of one voxel, 16 channels (8 q + 4 hi + i) of output block cj: ReLU / mask, convert, store.  The two lanes
+// of a voxel (hi = 0, 1) exchange halves, so that each holds 8 consecutive channels: 16-byte stores, 32 consecutive bytes a
+// voxel and instruction.
+template <int EPI>
+__device__ __forceinline__ void finish(const GemmArgs &a, const f32x16 &s, int cj, int hi, const OutVox &o, const EpiIn &in) {
     const int co = C * cj;
     uint16_t *obase = a.out;
     int ocs = a.out_cs, oco = co;
     if (a.out2 && co >= a.out_ca) { obase = a.out2; ocs = a.out2_cs; oco = co - a.out_ca; }
-    uint16_t *dst = obase + o.pv * ocs + oco + 4 * hi;
-    const uint16_t *m = a.mask + o.pv * a.out_cs + co + 4 * hi;
-    uint16_t *word = a.bits + (o.pv * a.nco + cj) * 2 + hi;
+    uint4 *dst = reinterpret_cast<uint4 *>(obase + o.pv * ocs + oco + 8 * hi);
     uint32_t bits = 0;
-    if (a.epi == kMaskBits) bits = spread_word(*word);
+    if (EPI == kMaskBits) bits = spread_word(in.word);
+    uint2 pk[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         float v[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             v[i] = s[4 * q + i];
-            if (is_relu(a.epi)) v[i] = a.relu_keeps_nan ? (v[i] < 0.f ? 0.f : v[i]) : relu_f32(v[i]);
+            if (is_relu(EPI)) v[i] = a.relu_keeps_nan ? (v[i] < 0.f ? 0.f : v[i]) : relu_f32(v[i]);
+            if (EPI == kReluBits) bits = shift_in_positive(bits, v[i]);
         }
-        uint2 pk = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
-        if (a.epi == kMask) {
-            const uint2 mv = *reinterpret_cast<const uint2 *>(m + 8 * q);
-            pk.x &= positive_halves(mv.x);
-            pk.y &= positive_halves(mv.y);
-        }
-        if (a.epi == kMaskBits) {
+        pk[q] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
+        if (EPI == kMaskBits) {
             const uint2 mv = nibble_halves(bits, q);
-            pk.x &= mv.x;
-            pk.y &= mv.y;
+            pk[q].x &= mv.x;
+            pk[q].y &= mv.y;
         }
-        if (a.epi == kReluBits) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) bits = shift_in_positive(bits, v[i]);
-        }
-        *reinterpret_cast<uint2 *>(dst + 8 * q) = pk;
     }
-    if (a.epi == kReluBits) *word = row_word(bits);
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const auto x = __builtin_amdgcn_permlane32_swap(pk[2 * p].x, pk[2 * p + 1].x, false, false);
+        const auto y = __builtin_amdgcn_permlane32_swap(pk[2 * p].y, pk[2 * p + 1].y, false, false);
+        uint4 v = make_uint4(x[0], y[0], x[1], y[1]);
+        if (EPI == kMask) {
+            v.x &= positive_halves(in.mask[p].x);
+            v.y &= positive_halves(in.mask[p].y);
+            v.z &= positive_halves(in.mask[p].z);
+            v.w &= positive_halves(in.mask[p].w);
+        }
+        if (o.ok) dst[2 * p] = v;
+    }
+    if (EPI == kReluBits && o.ok) a.bits[(o.pv * a.nco + cj) * 2 + hi] = row_word(bits);
+}
+
+// f(epilogue as a compile-time constant)
+template <class F>
+__device__ __forceinline__ void with_epilogue(int epi, F &&f) {
+    switch (epi) {
+    case kNone: f(std::integral_constant<int, kNone>{}); break;
+    case kRelu: f(std::integral_constant<int, kRelu>{}); break;
+    case kMask: f(std::integral_constant<int, kMask>{}); break;
+    case kMaskBits: f(std::integral_constant<int, kMaskBits>{}); break;
+    default: f(std::integral_constant<int, kReluBits>{}); break;
+    }
 }
 
 // Sums of a split: unit (tile, wave, block of the wave, segment, q) x 64 lanes x 4 channels, 1 KB per unit.
@@ -168,171 +208,273 @@ __device__ __forceinline__ size_t part_index(const GemmArgs &a, int split, int b
 }
 
 template <int CBW, int VB, int BL>
-__global__ __launch_bounds__(kGemmThreads, 1) void conv_gemm_kernel(GemmArgs a) {
-    constexpr int NSEG = 2 * VB, CBT = 2 * CBW, AFRAGS = CBT * ROW * 2, AL = AFRAGS / kGemmWaves, L = AL + BL;
-    constexpr int STAGE = stage_bytes(CBW, BL), NS = stages(CBW, BL);
-    static_assert((NS - 1) * L < 64, "vmcnt");
+__global__ __launch_bounds__(kGemmThreads, resident(CBW, VB)) void conv_gemm_kernel(GemmArgs a) {
+    constexpr int NSEG = 2 * VB, CBT = 2 * CBW, NGRP = 2 * ROW, STAGE = stage_bytes(BL), AD = ahead(CBW, VB);
     extern __shared__ __align__(16) char lds[];
-    // workgroups of one XCD (blockIdx % 8) get consecutive logical ids: they share output blocks and K range, i.e. weights
-    const int per_xcd = gridDim.x >> 3;
-    const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (logical >= a.nblocks * a.nsplit) return;
+    // Workgroups of one XCD (blockIdx % 8) share a run of consecutive items (an item: a tile and a range of K) and take them
+    // side by side: neighbours share output blocks and K range, i.e. weights.
+    const int items = a.nblocks * a.nsplit, per_xcd = (items + 7) >> 3, nslots = gridDim.x >> 3;
+    const int first = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3), end = min((static_cast<int>(blockIdx.x & 7) + 1) * per_xcd, items);
+    if (first >= end) return;
     const Geo &g = a.g;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave & 1, wn = wave >> 1, hi = lane >> 5;
-    const int vg = logical % a.nvg, u = logical / a.nvg, split = u % a.nsplit, cg = u / a.nsplit;
-    const long long prow = g.pw, pplane = static_cast<long long>(g.ph) * g.pw;
-    const int q0 = vg * wg_vox(VB);
-    auto record = [&](int q) {
+    // (voxel indices are unsigned and 32 bits wide: 2^32 voxels of at least 32 + 64 channels do not fit the memory)
+    const uint32_t prow = g.pw, pplane = static_cast<uint32_t>(g.ph) * g.pw;
+    const int nunits = a.nci * a.nrows / NS;
+    struct Item { int vg, split, cg, u0, u1; };
+    auto item_at = [&](int i) __attribute__((always_inline)) {
+        const int u = i / a.nvg;
+        Item t;
+        t.vg = i - u * a.nvg;
+        t.cg = u / a.nsplit;
+        t.split = u - t.cg * a.nsplit;
+        t.u0 = t.split * nunits / a.nsplit;
+        t.u1 = (t.split + 1) * nunits / a.nsplit;
+        return t;
+    };
+    auto record = [&](int q) __attribute__((always_inline)) {
         const uint32_t row = fdiv(static_cast<uint32_t>(q), a.drow);
         return row * (a.ew + 2) + fmod_(static_cast<uint32_t>(q), row, a.drow);
     };
-    const uint32_t rec0 = record(q0), nrec = record(min(q0 + wg_vox(VB), a.nvox) - 1) + 3 - rec0;
 
-    // This lane's share of the record loads: records 16 (BL wave + j) + lane / 4, piece lane % 4 of each (stored order).
-    // Records past the last one repeat it; records of rows that a tile's own box lacks are moved inside it (both only
-    // feed results that are dropped).
-    long long rpos[BL];
+    // The loads run ahead of the products, from one item into the next.  Voxels: NS - 1 steps.  This lane's share of them:
+    // records 16 (BL wave + j) + lane / 4, piece lane % 4 of each (stored order).  Records past the last one repeat it;
+    // records of rows that a tile's own box lacks are moved inside it (both only feed results that are dropped).
+    int fitem = first, fleft = 0, fr = 0, fi = 0;               // item, steps left of it, next kernel row and chunk (chunks
+                                                                // innermost: two neighbouring ones share a cache line)
+    uint32_t rvox[BL];
     int rflag[BL];                   // gathered halos: bit 0 / 1 first / last row with a neighbour, 2 / 3 plane
-    const long long sw = g.tile_vox - g.tw, sh = g.tile_vox * g.gw - g.th * prow, sd = g.tile_vox * g.gw * g.gh - g.td * pplane;
-#pragma unroll
-    for (int j = 0; j < BL; ++j) {
-        const uint32_t k = min(static_cast<uint32_t>(16 * (BL * wave + j) + (lane >> 2)), nrec - 1) + rec0;
-        const uint32_t row = fdiv(k, a.drec);
-        BoxPos p = row_pos(a, row);
-        const TileBox bx = tile_box(g, p.tile);
-        p.d = min(p.d, bx.bd - 1);
-        p.h = min(p.h, bx.bh - 1);
-        p.w = min(static_cast<int>(fmod_(k, row, a.drec)), bx.bw + 1);
-        rpos[j] = static_cast<long long>(p.tile) * g.tile_vox + bx.org + (p.d + 1) * pplane + (p.h + 1) * prow + p.w;
-        rflag[j] = 0;
-        if (a.gather) {              // (host: one-voxel margins, no grown box, 3-D)
-            const int tc = p.tile % g.gw, t1 = p.tile / g.gw, tb = t1 % g.gh, ta = (t1 / g.gh) % g.gd;
-            if (p.w == 0 && tc > 0) rpos[j] -= sw;
-            if (p.w == g.tw + 1 && tc < g.gw - 1) rpos[j] += sw;
-            rflag[j] = (p.h == 0 && tb > 0 ? 1 : 0) | (p.h == g.th - 1 && tb < g.gh - 1 ? 2 : 0) |
-                       (p.d == 0 && ta > 0 ? 4 : 0) | (p.d == g.td - 1 && ta < g.gd - 1 ? 8 : 0);
-        }
-    }
-    const int piece = 8 * ((lane & 3) ^ (lane >> 4));
-    const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char *)lds));
-
-    // K range of this split
-    const int nk = a.nci * a.nrows;
-    const int k0 = static_cast<int>(1LL * split * nk / a.nsplit), k1 = static_cast<int>(1LL * (split + 1) * nk / a.nsplit);
-    int fk = k0, fr = k0 / a.nci, fi = k0 - fr * a.nci;         // next step to fetch: kernel row fr, chunk fi (innermost: the
-                                                                // record of two neighbouring chunks is one cache line)
-    auto fetch = [&](int stage) {
-        const int tap0 = (a.nrows == 3 ? 9 : 0) + ROW * fr;
-        const uint32_t dst = lds0 + stage * STAGE;
-#pragma unroll
-        for (int n = 0; n < AL; ++n) {
-            const int m = wave * AL + n, cb = m / (ROW * 2), x = m - cb * (ROW * 2);
-            const size_t frag = (static_cast<size_t>(fi * a.nco + cg * CBT + cb) * NTAP_PACK + tap0) * 2 + x;
-            dma16(a.wpack + frag * 64 + lane, dst + m * 1024);
-        }
-        const InSrc src = in_src(a, fi);
-        const int kd = a.nrows == 3 ? 1 : fr / 3, kh = a.nrows == 3 ? fr : fr - 3 * (fr / 3);
-        const long long ro = (kd - 1) * pplane + (kh - 1) * prow;
-        const long long gh = kh == 0 ? -sh : sh, gd = kd == 0 ? -sd : sd;
-        const int mh = kh == 0 ? 1 : (kh == 2 ? 2 : 0), md = kd == 0 ? 4 : (kd == 2 ? 8 : 0);
-        const uint16_t *base = src.base + src.co + piece;
+    const uint32_t tvox = static_cast<uint32_t>(g.tile_vox);
+    const uint32_t sw = tvox - g.tw, sh = tvox * g.gw - g.th * prow, sd = tvox * g.gw * g.gh - g.td * pplane;
+    auto open_voxels = [&]() __attribute__((always_inline)) {
+        const Item t = item_at(fitem);
+        fleft = (t.u1 - t.u0) * NS;
+        fr = t.u0 * NS / a.nci;
+        fi = t.u0 * NS - fr * a.nci;
+        const int q0 = t.vg * wg_vox(VB);
+        const uint32_t rec0 = record(q0), nrec = record(min(q0 + wg_vox(VB), a.nvox) - 1) + 3 - rec0;
 #pragma unroll
         for (int j = 0; j < BL; ++j) {
-            long long at = rpos[j] + ro;
-            if (a.gather) at += (rflag[j] & mh ? gh : 0) + (rflag[j] & md ? gd : 0);
-            dma16(base + at * src.cs, dst + (AFRAGS + BL * wave + j) * 1024);
+            const uint32_t k = min(static_cast<uint32_t>(16 * (BL * wave + j) + (lane >> 2)), nrec - 1) + rec0;
+            const uint32_t row = fdiv(k, a.drec);
+            BoxPos p = row_pos(a, row);
+            const TileBox bx = tile_box(g, p.tile);
+            p.d = min(p.d, bx.bd - 1);
+            p.h = min(p.h, bx.bh - 1);
+            p.w = min(static_cast<int>(fmod_(k, row, a.drec)), bx.bw + 1);
+            rvox[j] = p.tile * tvox + static_cast<uint32_t>(bx.org) + (p.d + 1) * pplane + (p.h + 1) * prow + p.w;
+            rflag[j] = 0;
+            if (a.gather) {          // (host: one-voxel margins, no grown box, 3-D)
+                const int tc = p.tile % g.gw, t1 = p.tile / g.gw, tb = t1 % g.gh, ta = (t1 / g.gh) % g.gd;
+                if (p.w == 0 && tc > 0) rvox[j] -= sw;
+                if (p.w == g.tw + 1 && tc < g.gw - 1) rvox[j] += sw;
+                rflag[j] = (p.h == 0 && tb > 0 ? 1 : 0) | (p.h == g.th - 1 && tb < g.gh - 1 ? 2 : 0) |
+                           (p.d == 0 && ta > 0 ? 4 : 0) | (p.d == g.td - 1 && ta < g.gd - 1 ? 8 : 0);
+            }
         }
-        if (fk + 1 < k1) {           // past the last step the loads repeat it: what they fill is never used
-            ++fk;
+    };
+    const int piece = 8 * ((lane & 3) ^ (lane >> 4));
+    const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char *)lds)) + BL * wave * 1024;
+    // load j of the next step's records
+    auto fetch_voxels = [&](int stage, int j) __attribute__((always_inline)) {
+        const InSrc src = in_src(a, fi);
+        const int kd = a.nrows == 3 ? 1 : fr / 3, kh = a.nrows == 3 ? fr : fr - 3 * (fr / 3);
+        uint32_t at = rvox[j] + (kd - 1) * pplane + (kh - 1) * prow;
+        if (a.gather) {
+            const int mh = kh == 0 ? 1 : (kh == 2 ? 2 : 0), md = kd == 0 ? 4 : (kd == 2 ? 8 : 0);
+            at += (rflag[j] & mh ? (kh == 0 ? -sh : sh) : 0) + (rflag[j] & md ? (kd == 0 ? -sd : sd) : 0);
+        }
+        const uint64_t base = reinterpret_cast<uint64_t>(src.base + src.co + piece);
+        dma16(reinterpret_cast<const void *>(base + static_cast<uint64_t>(at) * static_cast<uint32_t>(2 * src.cs)),
+              lds0 + stage * STAGE + j * 1024);
+    };
+    // may_end: the step just fetched may be an item's last one (its phase is NS - 1)
+    auto next_voxels = [&](bool may_end) __attribute__((always_inline)) {
+        if (--fleft > 0) {
             if (++fi == a.nci) { fi = 0; ++fr; }
+        } else if (may_end && fitem + nslots < end) {
+            fitem += nslots;
+            open_voxels();
+        } else {
+            fleft = 1;               // past the last step the loads repeat it (in bounds; what they fill is never used)
+        }
+    };
+
+    // Weights: AD steps ahead, into registers, by ordinary loads (the two waves of an output block share them through the
+    // vector cache).
+    bf16x8 wf[AD][NGRP][CBW];
+    const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint4 *>(a.wpack), 0, a.nci * a.nco * NTAP_PACK * 2048, 0x00027000);
+    int witem = first, wleft = 0, wi = 0, wrow = 0, wat = 0;    // item, steps left, chunk, byte offset of (kernel row, block), with the chunk
+    auto open_weights = [&]() __attribute__((always_inline)) {
+        const Item t = item_at(witem);
+        wleft = (t.u1 - t.u0) * NS;
+        const int r = t.u0 * NS / a.nci;
+        wi = t.u0 * NS - r * a.nci;
+        wrow = ((t.cg * CBT + wm * CBW) * NTAP_PACK + (a.nrows == 3 ? 9 : 0) + ROW * r) * 2048;
+        wat = wrow + wi * a.nco * NTAP_PACK * 2048;
+    };
+    auto fetch_weights = [&](int set, int gi) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < CBW; ++c) {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(wres, lane * 16 + gi * 1024, wat + c * NTAP_PACK * 2048, 0);
+            wf[set][gi][c] = __builtin_bit_cast(bf16x8, v);
+        }
+    };
+    auto next_weights = [&](bool may_end) __attribute__((always_inline)) {
+        if (--wleft > 0) {
+            wat += a.nco * NTAP_PACK * 2048;
+            if (++wi == a.nci) { wi = 0; wrow += ROW * 2048; wat = wrow; }
+        } else if (may_end && witem + nslots < end) {
+            witem += nslots;
+            open_weights();
+        } else {
+            wleft = 1;
         }
     };
 
     // this lane's read offsets inside a stage: record of its voxel in segment s, one and two records on
     int boff[NSEG][ROW];
+    auto read_offsets = [&](int q0) __attribute__((always_inline)) {
+        const uint32_t rec0 = record(q0);
 #pragma unroll
-    for (int s = 0; s < NSEG; ++s) {
-        const int q = min(q0 + wn * 64 * VB + s * 32 + (lane & 31), a.nvox - 1);
-        const int r = static_cast<int>(record(q) - rec0);
+        for (int s = 0; s < NSEG; ++s) {
+            const int q = min(q0 + wn * 64 * VB + s * 32 + (lane & 31), a.nvox - 1);
+            const int r = static_cast<int>(record(q) - rec0);
 #pragma unroll
-        for (int kw = 0; kw < ROW; ++kw) boff[s][kw] = AFRAGS * 1024 + (r + kw) * 64 + ((hi ^ ((r + kw) >> 2)) & 3) * 16;
-    }
-
-    // accumulators start from the bias (in the first split): lane l holds channels 8 (e / 4) + 4 (l / 32) + e % 4 of a block
-    f32x16 acc[CBW][NSEG];
-    const bool biased = a.bias && split == 0;
-#pragma unroll
-    for (int c = 0; c < CBW; ++c) {
-        f32x16 v;
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-            v[e] = biased ? a.bias[C * (cg * CBT + wm * CBW + c) + 8 * (e >> 2) + 4 * hi + (e & 3)] : 0.f;
-#pragma unroll
-        for (int s = 0; s < NSEG; ++s) acc[c][s] = v;
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // (the bias: from here on only the staged loads are counted)
-
-    bf16x8 wf[2][CBW], bf[2][NSEG];
-    auto read_group = [&](const char *stage, int gi) {          // (kw, K-half) group gi -> fragment set gi % 2
-        const int kw = gi >> 1, half = gi & 1;
-#pragma unroll
-        for (int c = 0; c < CBW; ++c)
-            wf[gi & 1][c] = *reinterpret_cast<const bf16x8 *>(stage + (((wm * CBW + c) * ROW + kw) * 2 + half) * 1024 + lane * 16);
-#pragma unroll
-        for (int s = 0; s < NSEG; ++s) bf[gi & 1][s] = *reinterpret_cast<const bf16x8 *>(stage + (boff[s][kw] ^ (half * 32)));
+            for (int kw = 0; kw < ROW; ++kw) boff[s][kw] = (r + kw) * 64 + ((hi ^ ((r + kw) >> 2)) & 3) * 16;
+        }
     };
 
+    f32x16 acc[CBW][NSEG];
+    bf16x8 bf[2][NSEG];
+    auto read_group = [&](int stage, int gi) __attribute__((always_inline)) {    // (kw, K-half) group gi -> fragment set gi % 2
 #pragma unroll
-    for (int i = 0; i < NS; ++i) fetch(i);
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * L) : "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    read_group(lds, 0);
-    int cur = 0;
-    for (int k = k0; k < k1; ++k) {
-        const int nxt = cur + 1 == NS ? 0 : cur + 1;
-        const char *const stage = lds + cur * STAGE;
+        for (int s = 0; s < NSEG; ++s)
+            bf[gi & 1][s] = *reinterpret_cast<const bf16x8 *>(lds + (boff[s][gi >> 1] ^ ((gi & 1) * 32)) + stage * STAGE);
+    };
+    // One step, in phase P of NS: its voxels are in stage P, the loads of the step NS - 1 on go to the stage that the step
+    // before it left, one in each of the first BL groups; its weights are in set P (the only one if AD = 1).
+    int next_q0 = -1;                // first voxel of the next item, in an item's last unit (-1: nothing to do)
+    auto step = [&](auto phase) __attribute__((always_inline)) {
+        constexpr int P = decltype(phase)::value, SET = AD == 1 ? 0 : P;
 #pragma unroll
-        for (int gi = 0; gi < 2 * ROW; ++gi) {
-            if (gi + 1 < 2 * ROW) {
-                read_group(stage, gi + 1);
+        for (int gi = 0; gi < NGRP; ++gi) {
+            if (gi + 1 < NGRP) {
+                read_group(P, gi + 1);
             } else {
-                // every wave has read this step's last fragments (lgkmcnt) and the next step's loads have landed: those
-                // of the NS - 2 steps after it may stay in flight.  Behind the barrier this step's stage is free.
-                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * L) : "memory");
+                if (P == NS - 1 && next_q0 >= 0) read_offsets(next_q0);
+                // Every wave has read this step's last fragments (lgkmcnt) and the next step's records have landed: after
+                // the last of their loads, in group BL - 1 of the step before, there were the weight loads of that group and the ones
+                // behind it and this step's loads up to here.  Behind the barrier this step's stage is free.
+                constexpr int NEWER = (NGRP + 1 - BL) * CBW + (BL < NGRP ? BL : NGRP - 1) + (NGRP - 1) * CBW;
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(NEWER) : "memory");
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
-                read_group(lds + nxt * STAGE, 0);
+                read_group((P + 1) % NS, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
-            if (gi + 1 == 2 * ROW) fetch(cur);
 #pragma unroll
-            for (int c = 0; c < CBW; ++c)
-#pragma unroll
-                for (int s = 0; s < NSEG; ++s)
-                    acc[c][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[gi & 1][c], bf[gi & 1][s], acc[c][s], 0, 0, 0);
+            for (int m = 0; m < CBW * NSEG; ++m) {
+                const int c = m / NSEG, s = m % NSEG;
+                if (m == 1) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (gi < BL) fetch_voxels((P + NS - 1) % NS, gi);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                acc[c][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[SET][gi][c], bf[gi & 1][s], acc[c][s], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            fetch_weights(SET, gi);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        cur = nxt;
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the repeated loads
+        next_voxels((P + NS - 1) % NS == NS - 1);
+        next_weights((P + AD) % NS == NS - 1);
+    };
 
-    const int blk = cg * a.nvg + vg;
+    open_voxels();
+    open_weights();
 #pragma unroll
-    for (int s = 0; s < NSEG; ++s) {
-        const OutVox o = out_vox(a, q0 + wn * 64 * VB + s * 32 + (lane & 31));
+    for (int st = 0; st < NS - 1; ++st) {
+#pragma unroll
+        for (int j = 0; j < BL; ++j) fetch_voxels(st, j);
+        next_voxels(false);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int st = 0; st < AD; ++st) {
+#pragma unroll
+        for (int gi = 0; gi < NGRP; ++gi) fetch_weights(st, gi);
+        next_weights(st == NS - 1);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    read_offsets(item_at(first).vg * wg_vox(VB));
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * BL + AD * NGRP * CBW) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    read_group(0, 0);
+#pragma unroll 1
+    for (int item = first; item < end; item += nslots) {
+        const Item t = item_at(item);
+        const int after = item + nslots < end ? item_at(item + nslots).vg * wg_vox(VB) : -1;
+        // accumulators start from the bias (in the first split): lane l holds channels 8 (e / 4) + 4 (l / 32) + e % 4 of a block
+        const bool biased = a.bias && t.split == 0;
 #pragma unroll
         for (int c = 0; c < CBW; ++c) {
-            if (a.nsplit == 1) {
-                finish(a, acc[c][s], cg * CBT + wm * CBW + c, hi, o);
-            } else {
-                float4 *p = a.part + part_index<CBW, VB>(a, split, blk, wave, c, s, lane);
+            f32x16 v;
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    p[64 * q] = make_float4(acc[c][s][4 * q], acc[c][s][4 * q + 1], acc[c][s][4 * q + 2], acc[c][s][4 * q + 3]);
-            }
+            for (int e = 0; e < 16; ++e)
+                v[e] = biased ? a.bias[C * (t.cg * CBT + wm * CBW + c) + 8 * (e >> 2) + 4 * hi + (e & 3)] : 0.f;
+#pragma unroll
+            for (int s = 0; s < NSEG; ++s) acc[c][s] = v;
+        }
+#pragma unroll 1
+        for (int u = t.u0; u < t.u1; ++u) {
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+            next_q0 = u + 1 == t.u1 ? after : -1;
+            step(std::integral_constant<int, 2>{});
+        }
+
+        // The next item's loads are in flight meanwhile; the waits that the compiler puts behind the mask's loads are on the
+        // same counter and only ask for more than they need.
+        if (a.nsplit == 1) {
+            OutVox o[NSEG];
+#pragma unroll
+            for (int s = 0; s < NSEG; ++s) o[s] = out_vox(a, t.vg * wg_vox(VB) + wn * 64 * VB + s * 32 + (lane & 31));
+            with_epilogue(a.epi, [&](auto epi) __attribute__((always_inline)) {
+                constexpr int EPI = decltype(epi)::value;
+                const int cj = t.cg * CBT + wm * CBW;
+                constexpr int BATCH = NSEG < 2 ? NSEG : 2;       // segments whose mask values are loaded together
+#pragma unroll
+                for (int s0 = 0; s0 < NSEG; s0 += BATCH) {
+                    EpiIn in[CBW][BATCH];
+#pragma unroll
+                    for (int s = 0; s < BATCH; ++s)
+#pragma unroll
+                        for (int c = 0; c < CBW; ++c) epi_load<EPI>(a, in[c][s], cj + c, hi, o[s0 + s]);
+#pragma unroll
+                    for (int s = 0; s < BATCH; ++s)
+#pragma unroll
+                        for (int c = 0; c < CBW; ++c) finish<EPI>(a, acc[c][s0 + s], cj + c, hi, o[s0 + s], in[c][s]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            });
+        } else {
+            const int blk = t.cg * a.nvg + t.vg;
+#pragma unroll
+            for (int s = 0; s < NSEG; ++s)
+#pragma unroll
+                for (int c = 0; c < CBW; ++c) {
+                    float4 *p = a.part + part_index<CBW, VB>(a, t.split, blk, wave, c, s, lane);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        p[64 * q] = make_float4(acc[c][s][4 * q], acc[c][s][4 * q + 1], acc[c][s][4 * q + 2], acc[c][s][4 * q + 3]);
+                }
         }
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the repeated loads
 }
 
 // The splits' sums, added in order, and the epilogue: one thread per (unit of 16 channels, lane).
@@ -359,26 +501,43 @@ __global__ __launch_bounds__(kGemmThreads) void conv_gemm_join_kernel(GemmArgs a
             sum[4 * q] += v.x; sum[4 * q + 1] += v.y; sum[4 * q + 2] += v.z; sum[4 * q + 3] += v.w;
         }
     }
-    finish(a, sum, cg * 2 * CBW + wm * CBW + c, lane >> 5, out_vox(a, vg * wg_vox(VB) + wn * 64 * VB + s * 32 + (lane & 31)));
+    const OutVox o = out_vox(a, vg * wg_vox(VB) + wn * 64 * VB + s * 32 + (lane & 31));
+    const int cj = cg * 2 * CBW + wm * CBW + c, hi = lane >> 5;
+    with_epilogue(a.epi, [&](auto epi) {
+        EpiIn in;
+        epi_load<decltype(epi)::value>(a, in, cj, hi, o);
+        finish<decltype(epi)::value>(a, sum, cj, hi, o, in);
+    });
 }
 
 // largest output box of the grid
 struct Box { int ed, eh, ew; };
 Box max_box(const Geo &g) { return Box{g.td + 2 * grow_d(g), g.th + 2 * g.grow, g.tw + 2 * g.grow}; }
 
-struct GemmPlan { int cbw, vb, bl, nsplit, nvg, nblocks; long long nvox; double us; };     // us: estimated time
+// us: estimated time, by the constants of one item per workgroup; rows_us: by those of several in a row where that is so
+struct GemmPlan { int cbw, vb, bl, nsplit, nvg, nblocks; long long nvox; double us, rows_us; };
 // records that 128 vb consecutive voxels touch at most, in wave loads of 16 per wave
 int record_loads(int vb, int ew) {
     const int n = wg_vox(vb), rows = n % ew == 0 ? n / ew - 1 : (n + ew - 2) / ew;
     return (n + 2 + 2 * rows + 63) / 64;
 }
-// Voxels per workgroup and splits of the K loop: what costs least in microseconds if 256 compute units take the workgroups
-// in rounds: a step lasts 0.41 us per 128 voxels x 64 channels, a workgroup 10.7 us besides (launch, first loads, stores);
-// splitting adds a second launch and a write and a read of every sum at about 6 TB/s.  The interior voxels alone decide, so
-// that the order of the sums is the same for every output box growth and tile grid.  The time that is then compared with the
-// marching kernels' has constants of its own, fitted to 472 layers cut this way (32 ... 1024 channels, 64 voxels ... 4 million,
-// 2-D and 3-D; 11 % rms; `shortk`, K loops of 3 or 6 steps: 354 layers, 6 % rms): the layers of 64 channels a workgroup
-// take 7 % longer than the first constants say, and short loops do not reach the rate of a step.
+// Voxels per tile and splits of the K loop: what costs least in microseconds if 256 compute units take the items in rounds: a
+// step lasts 0.41 us per 128 voxels x 64 channels, an item 10.7 us besides; splitting adds a second launch and a write and a
+// read of every sum at about 6 TB/s.  The interior voxels alone decide, so that the order of the sums is the same for every
+// output box growth and tile grid.  These constants, and those of the time that is then compared with the marching kernels'
+// (fitted to 472 layers cut this way, 32 ... 1024 channels, 64 voxels ... 4 million, 2-D and 3-D; `shortk`, K loops of 3 or 6 steps:
+// 354 layers), are of the kernel of one item per workgroup; they choose where a compute unit has one item, which is
+// where little has changed (a step is 10 - 15 % shorter).  What several items in a row cost is cut_us below.
+//
+// cut_us: a compute unit works off its share of the items one after the other: per item `steps` steps and what its epilogue
+// leaves uncovered.  Two workgroups on a compute unit cover each other's, so where there are several items of few steps
+// tiles of 128 voxels are faster (2-D, 128 -> 128 on 16 x 128^2 91 against 106 us, 256 -> 256 on 16 x 64^2 81 against 88), and 256
+// where the steps count (3-D, 512 -> 512 on 32^3 390 against 404).  Measured on 31 layers with every cut, 5 % rms.
+constexpr struct { double step, item; } kCost[2][2] = {{{0.45, 1.8}, {0.72, 3.0}}, {{0.70, 2.2}, {1.36, 6.5}}};   // [CBW - 1][VB - 1]
+double cut_us(int cbw, int vb, long long tiles, int steps) {
+    const auto c = kCost[cbw - 1][vb - 1];
+    return 7 + static_cast<double>((tiles + 255) / 256) * (steps * c.step + c.item);
+}
 GemmPlan plan_gemm(const Geo &g, int ki, int ko) {
     GemmPlan p;
     const Box b = max_box(g);
@@ -387,9 +546,10 @@ GemmPlan plan_gemm(const Geo &g, int ki, int ko) {
     const long long nint = 1LL * g.ntiles * g.int_vox;
     p.cbw = nco % 4 == 0 ? 2 : 1;
     const bool shortk = g.flat && ki <= 2 * C;
+    auto tiles_of = [&](int vb) { return (nint + wg_vox(vb) - 1) / wg_vox(vb) * (nco / (2 * p.cbw)); };
     double least = 0;
     for (int vb = 1; vb <= 2; ++vb) {
-        const long long tiles = (nint + wg_vox(vb) - 1) / wg_vox(vb) * (nco / (2 * p.cbw));
+        const long long tiles = tiles_of(vb);
         for (int s = 1; s == 1 || (s <= nk / 4 && s <= 64 && tiles * s <= 1024); ++s) {
             const double rounds = static_cast<double>((tiles * s + 255) / 256), steps = (nk + s - 1) / s;
             const double sums = 8.0 * s * nint * ko / 1e6;
@@ -401,6 +561,8 @@ GemmPlan plan_gemm(const Geo &g, int ki, int ko) {
             }
         }
     }
+    if (p.nsplit == 1 && p.cbw == 2 && p.vb == 2 && cut_us(2, 1, tiles_of(1), nk) < 0.97 * cut_us(2, 2, tiles_of(2), nk)) p.vb = 1;
+    p.rows_us = p.nsplit == 1 && tiles_of(p.vb) > 256 ? cut_us(p.cbw, p.vb, tiles_of(p.vb), nk) : p.us;
     p.bl = record_loads(p.vb, b.ew);
     if (p.vb == 2 && p.bl > 6) { p.vb = 1; p.bl = record_loads(1, b.ew); }
     p.bl = p.vb == 2 ? (p.bl <= 5 ? 5 : 6) : (p.bl <= 3 ? 3 : (p.bl <= 4 ? 4 : 6));
@@ -423,6 +585,7 @@ bool conv_gemm_tensor_forms(const Geo &g, int ki, int ko) {
 }
 
 double conv_gemm_us(const Geo &g, int ki, int ko) { return plan_gemm(g, ki, ko).us; }
+double conv_gemm_rows_us(const Geo &g, int ki, int ko) { return plan_gemm(g, ki, ko).rows_us; }
 
 void conv_gemm_detail(const Geo &g, int ki, int ko, int *detail) {
     const GemmPlan p = plan_gemm(g, ki, ko);
@@ -498,17 +661,18 @@ int launch_conv_gemm(const void *Pin, const void *wpack, void *part, const float
     // more than 64 KB of dynamic LDS has to be requested explicitly
     static const hipError_t attr = [] {
         for (int i = 0; i < 10; ++i) {
-            const int cbw = i / 5 + 1, bl = bls[i % 5];
+            const int bl = bls[i % 5];
             const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern[i / 5][i % 5]),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, stages(cbw, bl) * stage_bytes(cbw, bl));
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, NS * stage_bytes(bl));
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
     }();
     if (attr != hipSuccess) return record_hip(attr);
     const int shape = p.vb == 2 ? (p.bl == 5 ? 3 : 4) : (p.bl == 3 ? 0 : (p.bl == 4 ? 1 : 2));
-    const unsigned grid = static_cast<unsigned>((1LL * a.nblocks * a.nsplit + 7) / 8 * 8);
-    hipLaunchKernelGGL(kern[p.cbw - 1][shape], dim3(grid), dim3(kGemmThreads), stages(p.cbw, p.bl) * stage_bytes(p.cbw, p.bl), s, a);
+    // as many workgroups as fit on the 256 compute units at once
+    const unsigned grid = static_cast<unsigned>((std::min(256LL * resident(p.cbw, p.vb), 1LL * a.nblocks * a.nsplit) + 7) / 8 * 8);
+    hipLaunchKernelGGL(kern[p.cbw - 1][shape], dim3(grid), dim3(kGemmThreads), NS * stage_bytes(p.bl), s, a);
     int rc = record_hip(hipGetLastError());
     if (rc != SP_OK || a.nsplit == 1) return rc;
     const unsigned units = static_cast<unsigned>(a.nblocks) * kGemmWaves * p.cbw * 2 * p.vb;
