@@ -173,6 +173,10 @@ int launch_conv_gemm(const void *Pin, const void *wpack, void *part, const float
                      int ko, bool relu, bool dgrad, hipStream_t s, const void *mask, const ConvSplit *split, bool gather,
                      void *bits);
 
+// 2-D variant, 32 input channels (conv_rows2d.hip); launch_conv_mfma hands them over after packing
+int launch_conv_rows2d(const void *Pin, const void *wpack, const float *bias, void *Pout, const Geo &g, int ko, bool relu,
+                       hipStream_t s, const void *mask, const ConvSplit *split);
+
 // single-input-channel first layer (conv_c1.hip)
 bool conv_c1_supported(const Geo &g, int cin, int cout, sp_dtype_t dt);
 // bits (optional, with relu): also writes the one-bit ReLU mask of the result (pointer shifted like Py)

@@ -8,7 +8,7 @@ import torch
 
 from oracle import conv3d, flat as flat_oracle
 from paper_1909_03108_amd import sp3d, synth
-from gpu_util import DT, TOL, f64, rel_err, to_dev, widen
+from gpu_util import DT, TOL, f64, rel_err, route, to_dev, widen
 from test_gpu_gather import test_gathered_halos_equal_exchange_then_convolve as check_gathered_halos
 from test_gpu_relu_bits import test_convolutions_write_and_read_the_bits as check_bits
 
@@ -109,6 +109,61 @@ NARROW_GEMM = [  # layers the implicit GEMM takes over from the marching kernels
 @pytest.mark.parametrize("case", NARROW_GEMM, ids=lambda c: "%dx%dx%d-%dto%d%s" % (c[1] + c[3:5] + ("-2d" if c[5] else "",)))
 def test_layers_taken_over_by_the_implicit_gemm(case):
     three_passes(*case, seed=5500 + 10 * NARROW_GEMM.index(case))
+
+
+SEVERAL_ITEMS = [  # more tiles than workgroups that fit on the chip, not a multiple of them: a workgroup goes from one to the next
+    (1, (5, 120, 126), (1, 2, 2), 128, 128, 1),     # 591 tiles, 512 workgroups
+    (1, (11, 190, 70), (1, 1, 2), 96, 64, 1),       # 572, three chunks
+    (1, (27, 60, 70), (1, 1, 2), 96, 128, 0),       # 443, 256 workgroups
+    (1, (1, 300, 260), (1, 1, 2), 32, 128, 1),      # 610 of three steps: the loads run ahead by most of an item
+]
+
+
+@pytest.mark.parametrize("case", SEVERAL_ITEMS, ids=lambda c: "%dx%dx%d-%dto%d%s" % (c[1] + c[3:5] + ("-2d" if c[5] else "",)))
+def test_several_tiles_per_workgroup(case):
+    n, dhw, grid, cin, cout, flat = case
+    family, (cbw, vb, _, splits) = route(sp3d.SP_OP_FWD, sp3d.Geom(n, dhw, grid, 1, 0, flat), cin, cout, sp3d.SP_BF16)
+    items = -(-dhw[0] * dhw[1] * dhw[2] // (128 * vb)) * (cout // (64 * cbw))
+    assert family == "gemm" and splits == 1 and items % 256 and items > (256 if (cbw, vb) == (2, 2) else 512)
+    three_passes(*case, seed=7100 + 10 * SEVERAL_ITEMS.index(case))
+
+
+ROWS = [  # 2-D, 32 input channels (conv_rows2d.hip): one row, strips of 1 ... 32 columns, fewer rows than the ring holds and one
+         # more, chunks with a shorter last one, several blocks of output channels
+    (1, (1, 1, 16), (1, 1, 1), 32, 32, 1),
+    (2, (3, 2, 33), (1, 1, 1), 32, 64, 1),
+    (1, (2, 7, 64), (1, 1, 2), 32, 32, 1),
+    (1, (3, 27, 40), (1, 3, 2), 32, 96, 1),
+    (1, (1, 301, 97), (1, 1, 1), 32, 32, 1),
+    (1, (16, 86, 65), (1, 2, 1), 32, 64, 1),
+]
+
+
+@pytest.mark.parametrize("case", ROWS, ids=lambda c: "%dx%dx%d-%dto%d" % (c[1] + c[3:5]))
+def test_row_marches(case):
+    three_passes(*case, seed=7300 + 10 * ROWS.index(case))
+
+
+def test_row_and_patch_marches_give_the_same_bits():
+    """Tiles of 15 columns lie side by side in a patch (conv_mfma.hip), one of 30 is a strip of rows."""
+    dhw, dt = (4, 21, 30), DT["bf16"]
+    x, z = (to_dev(synth.normal_volume((1,) + dhw + (32,), 7400 + i, "bf16")) for i in (0, 1))
+    w = to_dev(synth.weights(32, 32, 7402, "bf16", taps=(3, 3)))
+    res = []
+    for grid in ((1, 1, 2), (1, 1, 1)):
+        g = sp3d.Geom(1, dhw, grid, 1, 0, 1)
+        ws = sp3d.alloc_ws(max(sp3d.sp_workspace_bytes(op, g, 32, 32, dt) for op in (0, 1)))
+        P, Z, Y, D = (sp3d.alloc_padded(g, 32, dt) for _ in range(4))
+        for V, T in ((x, P), (z, Z)):
+            sp3d.sp_partition(V, T, g, 32, dt)
+            sp3d.sp_halo_exchange(T, g, 32, dt)
+        sp3d.conv3d_fwd(P, w, None, Y, g, 32, 32, dt, sp3d.SP_FLAG_RELU, ws)
+        sp3d.conv3d_dgrad_relu(Z, w, P, D, g, 32, 32, dt, ws)
+        out = [torch.empty_like(x) for _ in range(2)]
+        sp3d.sp_unpartition(Y, out[0], g, 32, dt)
+        sp3d.sp_unpartition(D, out[1], g, 32, dt)
+        res.append(out)
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
 
 
 SPLIT_TILES = [  # tiles of 256 voxels and several splits: both numbers of output blocks per wave, whole and ragged last tiles
