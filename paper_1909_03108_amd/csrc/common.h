@@ -173,8 +173,8 @@ int launch_conv_gemm(const void *Pin, const void *wpack, void *part, const float
                      int ko, bool relu, bool dgrad, hipStream_t s, const void *mask, const ConvSplit *split, bool gather,
                      void *bits);
 
-// 2-D variant, 32 input channels (conv_rows2d.hip); launch_conv_mfma hands them over after packing
-int launch_conv_rows2d(const void *Pin, const void *wpack, const float *bias, void *Pout, const Geo &g, int ko, bool relu,
+// 2-D variant, 32 or 64 input channels (conv_rows2d.hip); launch_conv_mfma hands them over after packing
+int launch_conv_rows2d(const void *Pin, const void *wpack, const float *bias, void *Pout, const Geo &g, int ki, int ko, bool relu,
                        hipStream_t s, const void *mask, const ConvSplit *split);
 
 // single-input-channel first layer (conv_c1.hip)

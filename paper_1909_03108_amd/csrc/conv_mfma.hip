@@ -691,7 +691,7 @@ int launch_conv_mfma(const void *Pin, const void *w, const float *bias, void *Po
     };
     const PatchPlan pl = plan_patches(g, ki, ko);
     // (slices side by side stay here: strips of 32 columns would be mostly empty; the bits are the same)
-    if (g.flat && ki == C && pl.fold == 1) return launch_conv_rows2d(Pin, ws, bias, Pout, g, ko, relu, s, mask, split);
+    if (g.flat && ki <= 2 * C && pl.fold == 1) return launch_conv_rows2d(Pin, ws, bias, Pout, g, ki, ko, relu, s, mask, split);
     const bool pairs = pl.pairs;
     a.nh = pl.nh;
     a.nw = pl.nw;

@@ -128,7 +128,7 @@ def test_several_tiles_per_workgroup(case):
     three_passes(*case, seed=7100 + 10 * SEVERAL_ITEMS.index(case))
 
 
-ROWS = [  # 2-D, 32 input channels (conv_rows2d.hip): one row, strips of 1 ... 32 columns, fewer rows than the ring holds and one
+ROWS = [  # 2-D, 32 and 64 input channels (conv_rows2d.hip): one row, strips of 1 ... 32 columns, fewer rows than the ring holds and one
          # more, chunks with a shorter last one, several blocks of output channels
     (1, (1, 1, 16), (1, 1, 1), 32, 32, 1),
     (2, (3, 2, 33), (1, 1, 1), 32, 64, 1),
@@ -136,6 +136,9 @@ ROWS = [  # 2-D, 32 input channels (conv_rows2d.hip): one row, strips of 1 ... 3
     (1, (3, 27, 40), (1, 3, 2), 32, 96, 1),
     (1, (1, 301, 97), (1, 1, 1), 32, 32, 1),
     (1, (16, 86, 65), (1, 2, 1), 32, 64, 1),
+    (1, (1, 1, 16), (1, 1, 1), 64, 32, 1),
+    (1, (3, 27, 40), (1, 3, 2), 64, 96, 1),
+    (1, (16, 100, 66), (1, 2, 1), 64, 64, 1),
 ]
 
 
@@ -144,24 +147,26 @@ def test_row_marches(case):
     three_passes(*case, seed=7300 + 10 * ROWS.index(case))
 
 
-def test_row_and_patch_marches_give_the_same_bits():
-    """Tiles of 15 columns lie side by side in a patch (conv_mfma.hip), one of 30 is a strip of rows."""
+@pytest.mark.parametrize("c", [32, 64])
+def test_row_and_patch_marches_give_the_same_bits(c):
+    """Tiles of 15 columns lie side by side in a patch (conv_mfma.hip, conv_mfma_pair_kernel.h), one of 30 is a strip of rows."""
     dhw, dt = (4, 21, 30), DT["bf16"]
-    x, z = (to_dev(synth.normal_volume((1,) + dhw + (32,), 7400 + i, "bf16")) for i in (0, 1))
-    w = to_dev(synth.weights(32, 32, 7402, "bf16", taps=(3, 3)))
+    x, z = (to_dev(synth.normal_volume((1,) + dhw + (c,), 7400 + i, "bf16")) for i in (0, 1))
+    w = to_dev(synth.weights(c, c, 7402, "bf16", taps=(3, 3)))
     res = []
     for grid in ((1, 1, 2), (1, 1, 1)):
         g = sp3d.Geom(1, dhw, grid, 1, 0, 1)
-        ws = sp3d.alloc_ws(max(sp3d.sp_workspace_bytes(op, g, 32, 32, dt) for op in (0, 1)))
-        P, Z, Y, D = (sp3d.alloc_padded(g, 32, dt) for _ in range(4))
+        assert {route(op, g, c, c, dt)[0] for op in (0, 1)} == {"march"}
+        ws = sp3d.alloc_ws(max(sp3d.sp_workspace_bytes(op, g, c, c, dt) for op in (0, 1)))
+        P, Z, Y, D = (sp3d.alloc_padded(g, c, dt) for _ in range(4))
         for V, T in ((x, P), (z, Z)):
-            sp3d.sp_partition(V, T, g, 32, dt)
-            sp3d.sp_halo_exchange(T, g, 32, dt)
-        sp3d.conv3d_fwd(P, w, None, Y, g, 32, 32, dt, sp3d.SP_FLAG_RELU, ws)
-        sp3d.conv3d_dgrad_relu(Z, w, P, D, g, 32, 32, dt, ws)
+            sp3d.sp_partition(V, T, g, c, dt)
+            sp3d.sp_halo_exchange(T, g, c, dt)
+        sp3d.conv3d_fwd(P, w, None, Y, g, c, c, dt, sp3d.SP_FLAG_RELU, ws)
+        sp3d.conv3d_dgrad_relu(Z, w, P, D, g, c, c, dt, ws)
         out = [torch.empty_like(x) for _ in range(2)]
-        sp3d.sp_unpartition(Y, out[0], g, 32, dt)
-        sp3d.sp_unpartition(D, out[1], g, 32, dt)
+        sp3d.sp_unpartition(Y, out[0], g, c, dt)
+        sp3d.sp_unpartition(D, out[1], g, c, dt)
         res.append(out)
     assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
 
