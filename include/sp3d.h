@@ -98,8 +98,12 @@ enum { SP_FLAG_RELU = 1 };                                /* conv3d_fwd: y = max
  *                      SP_HALO_KEEP_ZERO).  Same bits as the exchange followed by the plain call.  bf16 with
  *                      channel counts in multiples of 32, halo = 1, grow = 0, 3-D; the weight gradient also needs
  *                      tile extents along H and W in multiples of 8 and 32.  SP_EUNSUPPORTED otherwise (exchange
- *                      and call without the flag instead). */
-enum { SP_HALO_SKIP_SEND = 1, SP_HALO_KEEP_ZERO = 2, SP_HALO_GATHER = 4 };
+ *                      and call without the flag instead).
+ *   SP_HALO_EXCHANGE   conv3d_fwd*, conv3d_dgrad*: the call first does what sp_halo_exchange of its input tensor (or of
+ *                      its two) with the same opts does, in the launch that packs its weights where there is one: the
+ *                      margins of Px / Pxa, Pxb / Pdz are written.  Same bits as the two calls.  SP_EINVAL together with
+ *                      SP_HALO_GATHER; SP_EUNSUPPORTED from conv3d_wgrad*; ignored elsewhere. */
+enum { SP_HALO_SKIP_SEND = 1, SP_HALO_KEEP_ZERO = 2, SP_HALO_GATHER = 4, SP_HALO_EXCHANGE = 16 };
 enum {                                                    /* sp_workspace_bytes `op`   */
     SP_OP_FWD = 0, SP_OP_DGRAD = 1, SP_OP_WGRAD = 2,      /* the 3x3x3 convolution     */
     SP_OP_UPCONV_WGRAD = 3,                               /* sp_upconv2_wgrad          */

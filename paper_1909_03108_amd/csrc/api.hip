@@ -44,7 +44,7 @@ int make_geo(const sp_geom_t *g, Geo *out) {
     if (!g) return SP_EINVAL;
     if (g->n <= 0 || g->d <= 0 || g->h <= 0 || g->w <= 0 || g->gd <= 0 || g->gh <= 0 ||
         g->gw <= 0 || g->halo < 0 || g->grow < 0 || (g->grow > 0 && g->grow >= g->halo) ||
-        (g->flat != 0 && g->flat != 1) || (g->opts & ~(SP_HALO_SKIP_SEND | SP_HALO_KEEP_ZERO | SP_HALO_GATHER)))
+        (g->flat != 0 && g->flat != 1) || (g->opts & ~(SP_HALO_SKIP_SEND | SP_HALO_KEEP_ZERO | SP_HALO_GATHER | SP_HALO_EXCHANGE)))
         return SP_EINVAL;
     if (g->d % g->gd || g->h % g->gh || g->w % g->gw) return SP_EGEOM;
     if (g->halo < 1 || g->halo > SP_MAX_HALO) return SP_EUNSUPPORTED;
@@ -289,6 +289,11 @@ static int check_conv_args(const void *a, const void *b, const void *c, const sp
     return SP_OK;
 }
 
+// SP_HALO_EXCHANGE of a convolution whose input is Pa (and Pb); the tensors are the caller's to write.
+static Exchange exchange_of(const sp_geom_t *g, const void *Pa, int ca, const void *Pb = nullptr, int cb = 0) {
+    return Exchange{const_cast<void *>(Pa), ca, const_cast<void *>(Pb), cb, g->opts};
+}
+
 // forward kernels that can write the one-bit ReLU mask: the 3-D marching kernels, the implicit GEMM outside the widest layers on
 // the fewest voxels, and the one-input-channel layer
 static bool fwd_bits_supported(const Geo &o, int cin, int cout, sp_dtype_t dt) {
@@ -308,7 +313,8 @@ static int fwd_impl(const void *Px, const void *w, const float *bias, void *Py, 
     if (overlap(Px, pv * cin * es, Py, pv * cout * es)) return SP_EINVAL;
     const bool relu = flags & SP_FLAG_RELU;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const bool gather = g->opts & SP_HALO_GATHER;
+    const bool gather = g->opts & SP_HALO_GATHER, exchange = g->opts & SP_HALO_EXCHANGE;
+    if (gather && exchange) return SP_EINVAL;
     if (gather && !conv_mfma_gather_supported(o, cin, cout, dt)) return SP_EUNSUPPORTED;
     if (bits) {
         if (!relu) return SP_EINVAL;
@@ -320,15 +326,17 @@ static int fwd_impl(const void *Px, const void *w, const float *bias, void *Py, 
     if (conv_mfma_supported(o, cin, cout, dt)) {
         const size_t need = conv_mfma_ws_bytes(o, cin, cout);
         if (need && (!ws || ws_bytes < need || !aligned16(ws))) return SP_EWORKSPACE;
-        return launch_conv_mfma(Px, w, bias, Py, o, cin, cout, relu, false, ws, s, nullptr, nullptr, gather, bits);
+        const Exchange ex = exchange_of(g, Px, cin);
+        return launch_conv_mfma(Px, w, bias, Py, o, cin, cout, relu, false, ws, s, nullptr, nullptr, gather, bits, exchange ? &ex : nullptr);
     }
+    const bool padded = !conv_c1_supported(o, cin, cout, dt) && chan_pad_supported(o, cin, cout, dt);
+    if (padded && (!ws || ws_bytes < chan_pad_fwd_ws_bytes(o, cin, cout) || !aligned16(ws))) return SP_EWORKSPACE;
+    if (exchange && (rc = launch_halo_exchange(const_cast<void *>(Px), o, cin, dt, g->opts, s)) != SP_OK) return rc;
     if (o.grow == 0 && conv_c1_supported(o, cin, cout, dt))
         return launch_conv_c1_fwd(shifted(Px, o, 1, dt), w, bias, shifted(Py, o, cout, dt), o, cout, relu, s,
                                   bits ? static_cast<char *>(bits) + interior_shift(o) * (cout / 32) * 4 : nullptr);
     // channels no multiple of 32: zero-padded copies in the workspace, then the matrix-core kernel
-    if (!conv_c1_supported(o, cin, cout, dt) && chan_pad_supported(o, cin, cout, dt)) {
-        const size_t need = chan_pad_fwd_ws_bytes(o, cin, cout);
-        if (!ws || ws_bytes < need || !aligned16(ws)) return SP_EWORKSPACE;
+    if (padded) {
         // (the few-channel kernel needs no copies; what the call asks of its caller does not depend on the kernel)
         if (conv_few_supported(o, cin, cout, dt)) return launch_conv_few(Px, w, bias, Py, o, cin, cout, relu, s);
         return launch_conv_chan_pad_fwd(Px, w, bias, Py, o, cin, cout, relu, ws, s);
@@ -360,7 +368,8 @@ static int dgrad_impl(const void *Pdz, const void *w, const void *Pmask, void *P
     if (Pmask && (!aligned16(Pmask) || overlap(Pmask, pv * cin * es, Pdx, pv * cin * es))) return SP_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     // the kernel's "input channels" are cout and its "output channels" are cin
-    const bool gather = g->opts & SP_HALO_GATHER;
+    const bool gather = g->opts & SP_HALO_GATHER, exchange = g->opts & SP_HALO_EXCHANGE;
+    if (gather && exchange) return SP_EINVAL;
     if (gather && !conv_mfma_gather_supported(o, cout, cin, dt)) return SP_EUNSUPPORTED;
     if (bits) {
         if (!conv_mfma_bits_supported(o, cout, cin, dt)) return SP_EUNSUPPORTED;
@@ -370,9 +379,11 @@ static int dgrad_impl(const void *Pdz, const void *w, const void *Pmask, void *P
     if (conv_mfma_supported(o, cout, cin, dt)) {
         const size_t need = conv_mfma_ws_bytes(o, cout, cin);
         if (need && (!ws || ws_bytes < need || !aligned16(ws))) return SP_EWORKSPACE;
+        const Exchange ex = exchange_of(g, Pdz, cout);
         return launch_conv_mfma(Pdz, w, nullptr, Pdx, o, cout, cin, false, true, ws, s, Pmask, nullptr, gather,
-                                const_cast<void *>(bits));
+                                const_cast<void *>(bits), exchange ? &ex : nullptr);
     }
+    if (exchange && (rc = launch_halo_exchange(const_cast<void *>(Pdz), o, cout, dt, g->opts, s)) != SP_OK) return rc;
     return launch_conv_direct(Pdz, w, nullptr, Pdx, o, cout, cin, dt, false, true, s, 3, Pmask);
 }
 
@@ -430,6 +441,7 @@ int conv3d_wgrad(const void *Px, const void *Pdz, float *dw, float *db, const sp
     if (db && (reinterpret_cast<uintptr_t>(db) & 3u)) return SP_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool gather = g->opts & SP_HALO_GATHER;
+    if (g->opts & SP_HALO_EXCHANGE) return SP_EUNSUPPORTED;
     if (gather && !wgrad_mfma_gather_supported(o, cin, cout, dt)) return SP_EUNSUPPORTED;
     const bool c1 = conv_c1_supported(o, cin, cout, dt);
     const bool mfma = !c1 && wgrad_mfma_supported(o, cin, cout, dt);
@@ -482,7 +494,8 @@ static int fwd2_impl(const void *Pxa, int ca, const void *Pxb, int cb, const voi
     if ((rc = check_pair(Pxa, ca, Pxb, cb, dt)) != SP_OK) return rc;
     if (flags & ~static_cast<uint32_t>(SP_FLAG_RELU)) return SP_EINVAL;
     if (!conv_mfma_supported(o, ca + cb, cout, dt)) return SP_EUNSUPPORTED;
-    const bool gather = g->opts & SP_HALO_GATHER;
+    const bool gather = g->opts & SP_HALO_GATHER, exchange = g->opts & SP_HALO_EXCHANGE;
+    if (gather && exchange) return SP_EINVAL;
     if (gather && !conv_mfma_gather_supported(o, ca + cb, cout, dt)) return SP_EUNSUPPORTED;
     const size_t pv = static_cast<size_t>(o.ntiles) * o.tile_vox;
     if (overlap(Pxa, pv * ca * 2, Py, pv * cout * 2) || overlap(Pxb, pv * cb * 2, Py, pv * cout * 2)) return SP_EINVAL;
@@ -497,8 +510,9 @@ static int fwd2_impl(const void *Pxa, int ca, const void *Pxb, int cb, const voi
             return SP_EINVAL;
     }
     const ConvSplit sp{Pxb, ca, nullptr, 0};
+    const Exchange ex = exchange_of(g, Pxa, ca, Pxb, cb);
     return launch_conv_mfma(Pxa, w, bias, Py, o, ca + cb, cout, flags & SP_FLAG_RELU, false, ws,
-                            static_cast<hipStream_t>(stream), nullptr, &sp, gather, bits);
+                            static_cast<hipStream_t>(stream), nullptr, &sp, gather, bits, exchange ? &ex : nullptr);
 }
 
 int conv3d_fwd2(const void *Pxa, int ca, const void *Pxb, int cb, const void *w, const float *bias, void *Py,
@@ -521,7 +535,8 @@ int conv3d_dgrad2(const void *Pdz, const void *w, void *Pdxa, int ca, void *Pdxb
     if (rc != SP_OK) return rc;
     if ((rc = check_pair(Pdxa, ca, Pdxb, cb, dt)) != SP_OK) return rc;
     if (!conv_mfma_supported(o, cout, ca + cb, dt)) return SP_EUNSUPPORTED;
-    const bool gather = g->opts & SP_HALO_GATHER;
+    const bool gather = g->opts & SP_HALO_GATHER, exchange = g->opts & SP_HALO_EXCHANGE;
+    if (gather && exchange) return SP_EINVAL;
     if (gather && !conv_mfma_gather_supported(o, cout, ca + cb, dt)) return SP_EUNSUPPORTED;
     const size_t pv = static_cast<size_t>(o.ntiles) * o.tile_vox;
     if (overlap(Pdz, pv * cout * 2, Pdxa, pv * ca * 2) || overlap(Pdz, pv * cout * 2, Pdxb, pv * cb * 2) ||
@@ -530,8 +545,9 @@ int conv3d_dgrad2(const void *Pdz, const void *w, void *Pdxa, int ca, void *Pdxb
     const size_t need = conv_mfma_ws_bytes(o, cout, ca + cb);
     if (need && (!ws || ws_bytes < need || !aligned16(ws))) return SP_EWORKSPACE;
     const ConvSplit sp{nullptr, 0, Pdxb, ca};
+    const Exchange ex = exchange_of(g, Pdz, cout);
     return launch_conv_mfma(Pdz, w, nullptr, Pdxa, o, cout, ca + cb, false, true, ws,
-                            static_cast<hipStream_t>(stream), nullptr, &sp, gather);
+                            static_cast<hipStream_t>(stream), nullptr, &sp, gather, nullptr, exchange ? &ex : nullptr);
 }
 
 int conv3d_wgrad2(const void *Pxa, int ca, const void *Pxb, int cb, const void *Pdz, float *dw, float *db,
@@ -543,6 +559,7 @@ int conv3d_wgrad2(const void *Pxa, int ca, const void *Pxb, int cb, const void *
     if (db && (reinterpret_cast<uintptr_t>(db) & 3u)) return SP_EINVAL;
     if (!wgrad_mfma_supported(o, ca + cb, cout, dt)) return SP_EUNSUPPORTED;
     const bool gather = g->opts & SP_HALO_GATHER;
+    if (g->opts & SP_HALO_EXCHANGE) return SP_EUNSUPPORTED;
     if (gather && !wgrad_mfma_gather_supported(o, ca + cb, cout, dt)) return SP_EUNSUPPORTED;
     const size_t need = wgrad_mfma_ws_bytes(o, ca + cb, cout);
     if (!ws || ws_bytes < need || !aligned16(ws)) return SP_EWORKSPACE;

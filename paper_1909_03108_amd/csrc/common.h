@@ -72,6 +72,11 @@ int launch_partition(const void *vol, void *P, const Geo &g, int c, sp_dtype_t d
 int launch_halo_pack(const void *P, void *msg, const Geo &g, int c, sp_dtype_t dt, int border, hipStream_t s);
 int launch_halo_unpack(void *P, const void *msg, const Geo &g, int c, sp_dtype_t dt, int border, hipStream_t s);
 int launch_halo_exchange(void *P, const Geo &g, int c, sp_dtype_t dt, int border, hipStream_t s);
+// The bf16 tensors (channels in multiples of 32; Pb may be NULL) whose margins a convolution fills before it reads them
+// (SP_HALO_EXCHANGE), together with the packing of its weights: one launch
+struct Exchange { void *Pa; int ca; void *Pb; int cb; int border; };
+struct PackArgs;
+int launch_exchange_and_pack(const Exchange &ex, const Geo &g, const PackArgs &pack, hipStream_t s);
 int launch_relu_bwd(const void *dy, const void *y, void *dz, size_t elems, sp_dtype_t dt,
                     hipStream_t s);
 // one-bit ReLU mask of a bf16 tensor: `blocks` records of 32 channels -> one 32-bit word each
@@ -159,7 +164,7 @@ bool conv_mfma_bits_supported(const Geo &g, int cin, int cout, sp_dtype_t dt);
 int launch_conv_mfma(const void *Pin, const void *w, const float *bias, void *Pout, const Geo &g,
                      int cin, int cout, bool relu, bool dgrad, void *ws, hipStream_t s,
                      const void *mask = nullptr, const ConvSplit *split = nullptr, bool gather = false,
-                     void *bits = nullptr);
+                     void *bits = nullptr, const Exchange *ex = nullptr);
 
 // layers on few voxels: output-stationary implicit GEMM on the packed weights (conv_gemm.hip); launch_conv_mfma hands
 // the layers for which it is the faster family over after packing

@@ -24,7 +24,7 @@
 // MFMA operand roles: A = weights [M = Cout][K = 16 input channels], B = voxels [K][N = 32 voxels
 // along W], D[M = Cout][N = voxel].  Lane l of B supplies voxel l%32, channels 8*(l/32)..+7 of the
 // 16-channel half; lane l of D holds voxel l%32, channels 8*(i/4) + 4*(l/32) + i%4 for i = 0..15.
-#include "conv_mfma_common.h"
+#include "pack_weights.h"
 
 namespace sp3d {
 
@@ -32,57 +32,9 @@ using namespace convk;
 
 namespace {
 
-// Pre-swizzle the weights into MFMA A-fragment order.  wpack[chunk i][block j][tap][half][lane] = the 8
-// input channels k = 32i + 16*half + 8*(lane/32) + e of output channel m = 32j + lane%32.
-// Forward reads w[tap][k][m]; data-grad reads w[26-tap][m][k] (taps mirrored, roles swapped), where
-// the kernel's input channels are the layer's output channels.  ki / ko = channel counts as the
-// kernel sees them (ki in, ko out).  The 2-D variant's nine taps w[3][3][..][..] sit in the slots 9 .. 17 (kd = 1);
-// its other slots are never loaded and stay unwritten.
-// A wave packs the two fragments of one (chunk, block, tap), a 32 x 32 square of w, neighbouring waves neighbouring
-// blocks, so that the 64-byte rows of four waves are one run of memory.  In the data gradient's order a lane's eight
-// values lie side by side; the forward order is transposed in LDS, rows 34 elements apart so that the eight reads of
-// a lane and those of its 31 neighbours fall into different banks.  What bounds it: HBM for wide layers (one pass over
-// w, one over wpack), the launch for narrow ones.  (One thread per element, 2-byte loads kilobytes apart, 27 slots
-// also in 2-D, took four times as long: 1024 -> 1024 channels, 2-D, 39 -> 9.1 us (18.9 MB in, as much out: 4.1 TB/s), 512
-// -> 512 12.8 -> 5.6 us; 3-D 1024 -> 1024 21.7 us (5.2 TB/s); a launch alone is 4 us.)
-constexpr int kPackWaves = 4, kPackRow = 34;
-__global__ __launch_bounds__(64 * kPackWaves) void pack_weights_kernel(const uint16_t *__restrict__ w,
-                                                                       uint4 *__restrict__ wpack, int nci, int nco,
-                                                                       int ntap, int dgrad) {
-    __shared__ __align__(16) uint16_t square[kPackWaves][C * kPackRow];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int id = blockIdx.x * kPackWaves + wave;
-    const bool real = id < nci * nco * ntap;
-    const int u = real ? id : 0;
-    const int cj = u % nco, t = (u / nco) % ntap, ci = u / (nco * ntap);
-    const int ki = C * nci, ko = C * nco;
-    uint4 *dst = wpack + (static_cast<size_t>(ci * nco + cj) * NFRAG + 2 * (t + (ntap == 9 ? 9 : 0))) * 64 + lane;
-    if (dgrad) {
-        const uint16_t *src = w + (static_cast<size_t>(ntap - 1 - t) * ko + C * cj + (lane & 31)) * ki + C * ci + 8 * (lane >> 5);
-        const uint4 v0 = *reinterpret_cast<const uint4 *>(src), v1 = *reinterpret_cast<const uint4 *>(src + 16);
-        if (real) {
-            dst[0] = v0;
-            dst[64] = v1;
-        }
-        return;
-    }
-    const uint16_t *src = w + (static_cast<size_t>(t) * ki + C * ci + (lane >> 2)) * ko + C * cj + 8 * (lane & 3);
-    uint16_t *sq = square[wave];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(src + static_cast<size_t>(16 * i) * ko);
-        uint32_t *d = reinterpret_cast<uint32_t *>(sq + (16 * i + (lane >> 2)) * kPackRow + 8 * (lane & 3));
-        d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        const uint16_t *col = sq + (16 * half + 8 * (lane >> 5)) * kPackRow + (lane & 31);
-        uint32_t v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = col[2 * e * kPackRow] | static_cast<uint32_t>(col[(2 * e + 1) * kPackRow]) << 16;
-        if (real) dst[64 * half] = make_uint4(v[0], v[1], v[2], v[3]);
-    }
+__global__ __launch_bounds__(64 * kPackWaves) void pack_weights_kernel(PackArgs a) {
+    __shared__ __align__(16) PackSquares square;
+    pack_weights(a, blockIdx.x, square);
 }
 
 // Per-wave state of the march that the side work of a step needs.
@@ -642,16 +594,21 @@ bool conv_mfma_bits_supported(const Geo &g, int ki, int ko, sp_dtype_t dt) {
 
 int launch_conv_mfma(const void *Pin, const void *w, const float *bias, void *Pout, const Geo &g,
                      int ki, int ko, bool relu, bool dgrad, void *ws, hipStream_t s, const void *mask,
-                     const ConvSplit *split, bool gather, void *bits) {
+                     const ConvSplit *split, bool gather, void *bits, const Exchange *ex) {
     if (gather && !conv_mfma_gather_supported(g, ki, ko, SP_BF16)) return SP_EUNSUPPORTED;
     // one-bit mask: read by the data gradient in place of a mask tensor, written by a forward pass with ReLU
     if (bits && (!conv_mfma_bits_supported(g, ki, ko, SP_BF16) || (split && split->out2) || mask || (!dgrad && !relu)))
         return SP_EUNSUPPORTED;
     const int nci = ki / C, nco = ko / C;
     const int ntap = taps_of(g);
-    hipLaunchKernelGGL(pack_weights_kernel, dim3((nci * nco * ntap + kPackWaves - 1) / kPackWaves), dim3(64 * kPackWaves), 0,
-                       s, static_cast<const uint16_t *>(w), static_cast<uint4 *>(ws), nci, nco, ntap, dgrad ? 1 : 0);
-    int rc = record_hip(hipGetLastError());
+    const PackArgs pack{static_cast<const uint16_t *>(w), static_cast<uint4 *>(ws), nci, nco, ntap, dgrad ? 1 : 0};
+    int rc;
+    if (ex) {
+        rc = launch_exchange_and_pack(*ex, g, pack, s);
+    } else {
+        hipLaunchKernelGGL(pack_weights_kernel, dim3(pack_blocks(pack)), dim3(64 * kPackWaves), 0, s, pack);
+        rc = record_hip(hipGetLastError());
+    }
     if (rc != SP_OK) return rc;
     if (prefer_gemm(g, ki, ko))
         return launch_conv_gemm(Pin, ws, static_cast<char *>(ws) + pack_bytes(ki, ko), bias, Pout, g, ki, ko, relu, dgrad, s,

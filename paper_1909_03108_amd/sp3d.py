@@ -9,7 +9,7 @@ import os
 SP_F32, SP_BF16 = 0, 1
 SP_OK, SP_EINVAL, SP_EGEOM, SP_EUNSUPPORTED, SP_EWORKSPACE, SP_ELAUNCH = 0, -1, -2, -3, -4, -5
 SP_FLAG_RELU = 1
-SP_HALO_SKIP_SEND, SP_HALO_KEEP_ZERO, SP_HALO_GATHER = 1, 2, 4
+SP_HALO_SKIP_SEND, SP_HALO_KEEP_ZERO, SP_HALO_GATHER, SP_HALO_EXCHANGE = 1, 2, 4, 16
 SP_STATIC_SCRATCH_BYTES = 32 << 20
 SP_OP_FWD, SP_OP_DGRAD, SP_OP_WGRAD, SP_OP_UPCONV_WGRAD, SP_OP_POINTWISE_WGRAD, SP_OP_LOSS = 0, 1, 2, 3, 4, 5
 

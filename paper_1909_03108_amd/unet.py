@@ -9,7 +9,8 @@ channels `channels`, `convs` 3x3x3 conv + ReLU per level (two in the workload li
 own blocks), 2x2x2 max-pool between levels; the last level is the bottleneck; decoder levels mirror the
 encoder: 2x2x2 stride-2 transposed conv halving the channels, concat (skip, up), `convs` 3x3x3 conv +
 ReLU; a final 1x1x1 conv to `classes`.  Biases are
-zero and not passed.  Every 3x3x3 conv input is halo-exchanged first (sp_halo_exchange: pack, delivery and unpack in one pass).
+zero and not passed.  Every 3x3x3 conv input is halo-exchanged first (pack, delivery and unpack in one pass, by the
+convolution's call: SP_HALO_EXCHANGE).
 
 With `halo` = 2 the tensors carry margins that wide and two consecutive layers of a block share
 one exchange (the overlap idea of the paper's Sec. 1 applied to a short stack): the first layer of such a group
@@ -64,6 +65,7 @@ class UNet:
         # bits: a layer whose output is the next layer's input also writes the one-bit form of its ReLU mask,
         # and that layer's data gradient reads the bits instead of the activation (where both kernels can)
         self.bits = bool(bits) and halo == 1
+        self.by_conv = False                  # see _with_exchange
         self.free = {}                        # (padded shape, channels) -> released gradient buffers
         self.L = len(channels)
         self.flat = bool(flat)
@@ -141,8 +143,19 @@ class UNet:
     def _exchange(self, P, g, c):
         """All tiles share this GPU's memory, so margins are filled straight from the neighbours' interiors.
         Margins at the volume border are left alone: every padded tensor of the driver is zeroed when it is
-        allocated and nothing writes beyond the border afterwards, so they hold their zero padding already."""
-        sp3d.sp_halo_exchange(P, g.with_opts(sp3d.SP_HALO_KEEP_ZERO), c, self.dt)
+        allocated and nothing writes beyond the border afterwards, so they hold their zero padding already.
+        (Every exchange of the driver passes through here; inside _with_exchange the convolution's call does the work.)"""
+        if not self.by_conv:
+            sp3d.sp_halo_exchange(P, g.with_opts(sp3d.SP_HALO_KEEP_ZERO), c, self.dt)
+
+    def _with_exchange(self, gg, g, *inputs):
+        """Geometry `gg` for a convolution that fills the margins of its inputs [(tensor, channels)] first, in the launch that
+        packs its weights."""
+        self.by_conv = True
+        for P, c in inputs:
+            self._exchange(P, g, c)
+        self.by_conv = False
+        return gg.with_opts(sp3d.SP_HALO_EXCHANGE | sp3d.SP_HALO_KEEP_ZERO)
 
     def _mask_bits(self, name, g, cin, cout, last):
         """Buffer for the one-bit ReLU mask of layer `name`'s output, or None if the mask stays a tensor: the
@@ -157,13 +170,15 @@ class UNet:
             t = self.pool[key] = torch.empty(sp3d.sp_relu_bits_bytes(g, cout) // 2, dtype=torch.int16, device="cuda")
         return t
 
-    def _conv(self, Px, name, g, cin, cout, grow=0, bits=None):
-        """Px must hold its halos.  Returns relu(conv(Px)) as padded tiles (written: the interiors and `grow`
-        voxels around them); with `bits` the one-bit mask of the result goes there as well."""
+    def _conv(self, Px, name, g, cin, cout, grow=0, bits=None, exchange=False):
+        """Px must hold its halos (`exchange`: they are filled first).  Returns relu(conv(Px)) as padded tiles (written: the
+        interiors and `grow` voxels around them); with `bits` the one-bit mask of the result goes there as well."""
         Py = self._buf(name + ".y", g, cout)
         gg = g.grown(grow) if grow else g
         if self._x_gathered(g, cin, cout):
             gg = g.with_opts(sp3d.SP_HALO_GATHER)
+        elif exchange:
+            gg = self._with_exchange(gg, g, (Px, cin))
         if bits is not None:
             sp3d.conv3d_fwd_bits(Px, self.w[name], None, Py, bits, gg, cin, cout, self.dt, sp3d.SP_FLAG_RELU,
                                  self._ws(sp3d.SP_OP_FWD, gg, cin, cout))
@@ -188,8 +203,7 @@ class UNet:
                 if self._x_gathered(g, cin, c):
                     gg = g.with_opts(sp3d.SP_HALO_GATHER)
                 else:
-                    self._exchange(P, g, ca)
-                    self._exchange(P2, g, ca)
+                    gg = self._with_exchange(gg, g, (P, ca), (P2, ca))
                 A[name + ".x"] = (P, P2)
                 Py = self._buf(name + ".y", g, c)
                 if mb is not None:
@@ -200,10 +214,8 @@ class UNet:
                                      self._ws(sp3d.SP_OP_FWD, gg, cin, c))
                 P = Py
                 continue
-            if exch and not self._x_gathered(g, cin if k == 0 else c, c):
-                self._exchange(P, g, cin if k == 0 else c)
             A[name + ".x"] = P
-            P = self._conv(P, name, g, cin if k == 0 else c, c, grow, mb)
+            P = self._conv(P, name, g, cin if k == 0 else c, c, grow, mb, exch)
         A[block + ".y"] = P
         return P
 
@@ -316,7 +328,7 @@ class UNet:
             if self._gathers(sp3d.SP_OP_DGRAD, g, cin, cout):
                 gz = g.with_opts(sp3d.SP_HALO_GATHER)
             elif exchange:
-                self._exchange(Pdy, g, cout)
+                gz = self._with_exchange(g, g, (Pdy, cout))
             Pa, Pb = self._tmp(g, ca), self._tmp(g, ca)
             sp3d.conv3d_dgrad2(Pdy, self.w[name], Pa, ca, Pb, ca, gz, cout, dt,
                                self._ws(sp3d.SP_OP_DGRAD, g, cin, cout))          # first layer of its run: no grow
@@ -331,7 +343,7 @@ class UNet:
             if self._gathers(sp3d.SP_OP_DGRAD, g, cin, cout):
                 gg = g.with_opts(sp3d.SP_HALO_GATHER)
             elif exchange:
-                self._exchange(Pdy, g, cout)
+                gg = self._with_exchange(gg, g, (Pdy, cout))
             Pdx = self._tmp(g, cin)
             xbits = self.A.get(name + ".xbits") if mask_next else None
             if xbits is not None:

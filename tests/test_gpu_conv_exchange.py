@@ -1,0 +1,106 @@
+"""SP_HALO_EXCHANGE: a convolution that fills its input's margins first is, bit for bit, sp_halo_exchange and then the
+convolution, and leaves the margins as the exchange does; whatever launch the exchange shares."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_1909_03108_amd import sp3d, synth
+from gpu_util import DT, to_dev
+
+EXCH, KEEP = sp3d.SP_HALO_EXCHANGE, sp3d.SP_HALO_KEEP_ZERO
+
+# n, dhw, grid, cin, cout, dtype, flat, halo, grow: marching kernels, rows, implicit GEMM, few and one input channels, padded
+# copies, fp32; one tile (nothing to exchange), wide margins
+CASES = [(1, (16, 16, 64), (2, 2, 2), 32, 64, "bf16", 0, 1, 0), (2, (4, 6, 8), (2, 2, 2), 128, 128, "bf16", 0, 1, 0),
+         (1, (3, 30, 70), (1, 3, 2), 64, 32, "bf16", 1, 1, 0), (1, (8, 8, 40), (1, 1, 1), 64, 64, "bf16", 0, 1, 0),
+         (1, (9, 12, 10), (3, 2, 1), 3, 32, "bf16", 0, 1, 0), (1, (8, 12, 10), (2, 2, 1), 1, 32, "bf16", 0, 1, 0),
+         (1, (8, 12, 10), (2, 2, 1), 12, 32, "bf16", 0, 1, 0), (1, (8, 12, 10), (2, 3, 1), 5, 7, "f32", 0, 1, 0),
+         (1, (12, 12, 36), (2, 2, 1), 32, 32, "bf16", 0, 2, 1)]
+
+
+def stale(g, c, dt, seed):
+    """padded tensor with data everywhere, margins towards neighbours included, and zeros beyond the volume"""
+    P = sp3d.alloc_padded(g, c, dt)
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    V = torch.randn((g.n, g.d, g.h, g.w, c), generator=gen, device="cuda").to(P.dtype)
+    Q = sp3d.alloc_padded(g, c, dt)
+    sp3d.sp_partition(V, Q, g, c, dt)
+    sp3d.sp_halo_exchange(Q, g, c, dt)                # where it is not zero there is a neighbour (or a voxel)
+    P.copy_(torch.where(Q != 0, torch.full_like(Q, 3.0), Q))
+    sp3d.sp_partition(V, P, g, c, dt)
+    return P
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%dx%dx%d-%dto%d-%s%s" % (c[1] + c[3:6] + ("-2d" if c[6] else "",)))
+def test_convolutions_exchange_their_inputs_margins(case):
+    n, dhw, grid, cin, cout, dtype, flat, halo, grow = case
+    dt = DT[dtype]
+    g = sp3d.Geom(n, dhw, grid, halo, grow, flat)
+    ge, gx = g.with_opts(EXCH | KEEP), sp3d.Geom(n, dhw, grid, halo, 0, flat, KEEP)
+    w = to_dev(synth.weights(cin, cout, 9100, dtype, taps=(3, 3) if flat else (3, 3, 3)))
+    ws = sp3d.alloc_ws(max(16, *(sp3d.sp_workspace_bytes(op, g, cin, cout, dt) for op in (0, 1))))
+
+    def both(c, run):
+        """(input, result) of the two calls, and of the one"""
+        res = []
+        for fused in (False, True):
+            P = stale(g, c, dt, 9101)
+            if not fused:
+                sp3d.sp_halo_exchange(P, gx, c, dt)
+            res.append([P] + run(P, ge if fused else g))
+        for a, b in zip(*res):
+            assert torch.equal(a, b)
+
+    def fwd(P, gg):
+        Y = sp3d.alloc_padded(g, cout, dt)
+        sp3d.conv3d_fwd(P, w, None, Y, gg, cin, cout, dt, sp3d.SP_FLAG_RELU, ws)
+        return [Y]
+
+    def dgrad(P, gg):
+        X, M, Xm = stale(g, cin, dt, 9102), stale(g, cin, dt, 9103), stale(g, cin, dt, 9102)
+        sp3d.conv3d_dgrad(P, w, X, gg, cin, cout, dt, ws)
+        sp3d.conv3d_dgrad_relu(P, w, M, Xm, gg, cin, cout, dt, ws)
+        return [X, Xm]
+
+    both(cin, fwd)
+    both(cout, dgrad)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("ca, cb", [(32, 32), (64, 32)])
+def test_two_tensor_and_bit_forms_exchange_too(ca, cb):
+    dt, c, cout = DT["bf16"], ca + cb, 64
+    g = sp3d.Geom(1, (8, 20, 40), (2, 2, 1))
+    ge, gx = g.with_opts(EXCH | KEEP), g.with_opts(KEEP)
+    w = to_dev(synth.weights(c, cout, 9110, "bf16"))
+    ws = sp3d.alloc_ws(max(sp3d.sp_workspace_bytes(op, g, c, cout, dt) for op in (0, 1)))
+    res = []
+    for fused in (False, True):
+        gg = ge if fused else g
+        A, B, Z = stale(g, ca, dt, 9111), stale(g, cb, dt, 9112), stale(g, cout, dt, 9113)
+        if not fused:
+            for P, k in ((A, ca), (B, cb), (Z, cout)):
+                sp3d.sp_halo_exchange(P, gx, k, dt)
+        Y, Da, Db, D = (sp3d.alloc_padded(g, k, dt) for k in (cout, ca, cb, c))
+        bits = torch.zeros(sp3d.sp_relu_bits_bytes(g, cout), dtype=torch.uint8, device="cuda")
+        xbits = torch.full((sp3d.sp_relu_bits_bytes(g, c),), 0x5a, dtype=torch.uint8, device="cuda")
+        sp3d.conv3d_fwd2_bits(A, ca, B, cb, w, None, Y, bits, gg, cout, dt, sp3d.SP_FLAG_RELU, ws)
+        sp3d.conv3d_dgrad2(Z, w, Da, ca, Db, cb, gg, cout, dt, ws)
+        sp3d.conv3d_dgrad_bits(Z, w, xbits, D, gg, c, cout, dt, ws)
+        res.append([A, B, Z, Y, Da, Db, D, bits])
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
+
+
+def test_where_the_flag_is_refused():
+    L, fake = sp3d.lib(), 1 << 40
+    g = lambda opts: ctypes.byref(sp3d.Geom(1, (8, 8, 32), (2, 2, 1), opts=opts))
+    big = ctypes.c_size_t(1 << 30)
+    assert L.conv3d_fwd(fake, fake * 2, None, fake * 4, g(EXCH | sp3d.SP_HALO_GATHER), 32, 32, sp3d.SP_BF16, 0, fake * 8, big,
+                        None) == sp3d.SP_EINVAL
+    assert L.conv3d_dgrad(fake, fake * 2, fake * 4, g(EXCH | sp3d.SP_HALO_GATHER), 32, 32, sp3d.SP_BF16, fake * 8, big,
+                          None) == sp3d.SP_EINVAL
+    assert L.conv3d_wgrad(fake, fake * 2, fake * 4, None, g(EXCH), 32, 32, sp3d.SP_BF16, fake * 8, big, None) == sp3d.SP_EUNSUPPORTED
+    assert L.conv3d_wgrad(fake, fake * 2, fake * 4, None, g(EXCH), 5, 7, sp3d.SP_BF16, fake * 8, big, None) == sp3d.SP_EUNSUPPORTED
