@@ -53,6 +53,8 @@ struct Ctx {
     uint16_t *bbase;            // this lane's word of that voxel in the one-bit mask (see relu_bit)
     float *pbase;               // this lane's slot in the wave's region of the fp32 partial-sum buffer
     size_t oplane, orow;        // output elements per padded plane / per padded row
+    size_t mrow;                // from the row that the mask of the wave's first row is read from to that of the second
+    Ragged rag;                 // 3-D, ragged patches
     bool okrow[RH];             // row/column of this lane lies inside the tile interior
     float bv[HAS_BIAS ? 16 : 1];
 };
@@ -71,29 +73,29 @@ __device__ __forceinline__ void stage(const Ctx<HAS_BIAS> &c, int dplane, int j)
 }
 
 // Partial sums of 4 channels of row h of plane d written by the previous input chunk.
-template <bool FULL, bool HAS_BIAS>
+template <Edge EDGE, bool HAS_BIAS>
 __device__ __forceinline__ pin_t load_partial(const Ctx<HAS_BIAS> &c, int d, int h, int q) {
     pin_t v = pin_t{0.f, 0.f, 0.f, 0.f};
-    if (FULL || c.okrow[h]) v = *reinterpret_cast<const pin_t *>(c.pbase + part_unit(d, h, q));
+    if (EDGE != kBranches || c.okrow[h]) v = *reinterpret_cast<const pin_t *>(c.pbase + part_unit(d, h, q));
     return v;
 }
 
 // The 4 mask values that belong to one store unit (fetched at the start of the step, like the partial sums).
-template <bool FULL, bool BITS, bool HAS_BIAS>
+template <Edge EDGE, bool BITS, bool HAS_BIAS>
 __device__ __forceinline__ mask_t load_mask(const Ctx<HAS_BIAS> &c, int d, int h, int q) {
     mask_t v = mask_t{0u, 0u};
     if (BITS) {         // the row's word, kept in unit 0
-        if (q == 0 && (FULL || c.okrow[h])) v.x = c.bbase[bits_off(c, d, h)];
+        if (q == 0 && (EDGE != kBranches || c.okrow[h])) v.x = c.bbase[mask_off<EDGE>(c, d, h) >> 4];
         return v;
     }
-    if (FULL || c.okrow[h]) v = *reinterpret_cast<const mask_t *>(c.mbase + d * c.oplane + h * c.orow + 8 * q);
+    if (EDGE != kBranches || c.okrow[h]) v = *reinterpret_cast<const mask_t *>(c.mbase + mask_off<EDGE>(c, d, h) + 8 * q);
     return v;
 }
 
 // Finish 4 channels of row h of a finished plane (channels 8q + 4*(lane/32) .. +3 of this output block):
 // add the earlier chunks' partial sums if there are any, then either store the new partial (fp32) or
 // apply ReLU, convert and store bf16 (8 bytes).
-template <int MODE, int RELU, bool FULL, bool HAS_BIAS>
+template <int MODE, int RELU, Edge EDGE, bool HAS_BIAS>
 __device__ __forceinline__ void store_unit(const Ctx<HAS_BIAS> &c, int d, const f32x16 (&s)[RH],
                                            const pin_t (&pin)[RH][4], mask_t (&mk)[RH][4], int h, int q) {
     float v0 = s[h][4 * q], v1 = s[h][4 * q + 1], v2 = s[h][4 * q + 2], v3 = s[h][4 * q + 3];
@@ -102,7 +104,7 @@ __device__ __forceinline__ void store_unit(const Ctx<HAS_BIAS> &c, int d, const 
     }
     const size_t at = d * c.oplane + h * c.orow + 8 * q;
     if (MODE == kFirst || MODE == kMiddle) {
-        if (FULL || c.okrow[h]) *reinterpret_cast<float4 *>(c.pbase + part_unit(d, h, q)) = make_float4(v0, v1, v2, v3);
+        if (EDGE != kBranches || c.okrow[h]) *reinterpret_cast<float4 *>(c.pbase + part_unit(d, h, q)) = make_float4(v0, v1, v2, v3);
         return;
     }
     if (is_relu(RELU)) {
@@ -119,22 +121,17 @@ __device__ __forceinline__ void store_unit(const Ctx<HAS_BIAS> &c, int d, const 
         pk.x &= m.x;
         pk.y &= m.y;
     }
-    if (FULL || c.okrow[h]) *reinterpret_cast<uint2 *>(c.obase + at) = pk;
+    if (EDGE == kDrops) drop_store(c.rag.out + d * c.oplane, c.rag.vo[h] + 16 * q, pk);
+    else if (EDGE == kInside || c.okrow[h]) *reinterpret_cast<uint2 *>(c.obase + at) = pk;
     if (RELU == kReluBits) {
         // the row's word collects in the (otherwise unused) mask register of unit 0 and leaves with the last unit
         uint32_t n = mk[h][0].x;
         n = shift_in_positive(n, v0); n = shift_in_positive(n, v1);
         n = shift_in_positive(n, v2); n = shift_in_positive(n, v3);
         mk[h][0].x = n;
-        if (q == 3) store_bits<FULL>(c, d, mk, h);
+        if (q == 3) store_bits<EDGE>(c, d, mk, h);
     }
 }
-
-// Where the read bases of columns + 1 and + 2 are kept as two 16-bit steps from the first one, and the addresses of a group are
-// computed in the group: in the 27-tap forward passes with ReLU whose registers then just suffice or nearly so (without bias 14
-// spilled registers before, none now, 32 -> 32 on 14 x 24 x 19 14.2 us, now 13.2; with mask bits 24, now 4, 256^3 as before).  The
-// variants that spill as many either way lose up to 1 % by it, and the 9-tap ones 2 %.
-template <int KD, int RELU, bool HAS_BIAS> constexpr bool kPackCols = KD == 3 && (RELU == 4 || (RELU == 1 && !HAS_BIAS));
 
 // All MFMAs of one staged input plane Dp, with the step's side work spread over the six MFMA groups:
 // the staging loads of plane Dp+DIST and (EPI) the conversion and stores of output plane Dp-3, which
@@ -142,13 +139,13 @@ template <int KD, int RELU, bool HAS_BIAS> constexpr bool kPackCols = KD == 3 &&
 // lcol[kw]: this lane's read base in ring slot 0: first row of the wave, column lane % 32 + kw, piece lane / 32 (the second K
 // half's piece is 32 bytes away, up or down).  Fragments are fetched one (kw, K-half) group of RH+2 rows ahead of the MFMAs that
 // consume them.  P = Dp mod 4: output plane Dp-kd lives in slot (P-kd) mod 4, plane Dp-3 in slot (P+1) mod 4.
-// FULL: the patch lies completely inside the tile interior, so stores need no mask (no branches in
-// the step, which lets the scheduler weave the side work between the MFMAs).
+// EDGE: a patch that lies completely inside the tile interior needs no mask for its stores (no branches in
+// the step, which lets the scheduler weave the side work between the MFMAs; in 3-D others have none either, see Ragged).
 // SIDE (see side_load): kSideNone - the step loads its own partial sums / mask values (pin, mk) the ordinary
 // way; otherwise it uses the ones the previous step fetched (kSideUse) and first of all fetches those of the
 // plane that the next step finishes, Dp - 2, into the other set (npin, nmk), which the caller passes through
 // the wait that ends the step.
-template <int P, bool EPI, int MODE, int RELU, bool FULL, int KD, int SIDE, int NV, bool HAS_BIAS>
+template <int P, bool EPI, int MODE, int RELU, Edge EDGE, int KD, int SIDE, int NV, bool HAS_BIAS>
 __device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, const uint32_t (&lcol)[3],
                                            const bf16x8 (&wf)[NFRAG], f32x16 (&acc)[4][RH],
                                            pin_t (&pin)[RH][4], mask_t (&mk)[RH][4],
@@ -167,23 +164,23 @@ __device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, const
         for (int h = 0; h < RH; ++h)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const size_t at = (Dp - 2) * c.oplane + h * c.orow + 8 * q;
+                const size_t at = mask_off<EDGE>(c, Dp - 2, h);
                 if (S::PINS) side_load(npin[h][q], c.pbase + part_unit(Dp - 2, h, q));
-                if (S::MASK && !S::BITS) side_load(nmk[h][q], c.mbase + at);
-                if (S::BITS && q == 0) SP3D_SIDE_LOAD_BITS(nmk[h][0].x, c.bbase + bits_off(c, Dp - 2, h));
+                if (S::MASK && !S::BITS) side_load(nmk[h][q], c.mbase + at + 8 * q);
+                if (S::BITS && q == 0) SP3D_SIDE_LOAD_BITS(nmk[h][0].x, c.bbase + (at >> 4));
             }
     }
     if (SIDE == kSideNone && EPI && S::PINS) {
 #pragma unroll
         for (int h = 0; h < RH; ++h)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) pin[h][q] = load_partial<FULL>(c, Dp - 3, h, q);
+            for (int q = 0; q < 4; ++q) pin[h][q] = load_partial<EDGE>(c, Dp - 3, h, q);
     }
     if (SIDE == kSideNone && EPI && S::MASK) {
 #pragma unroll
         for (int h = 0; h < RH; ++h)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) mk[h][q] = load_mask<FULL, S::BITS>(c, Dp - 3, h, q);
+            for (int q = 0; q < 4; ++q) mk[h][q] = load_mask<EDGE, S::BITS>(c, Dp - 3, h, q);
     }
 #pragma unroll
     for (int r = 0; r < NR; ++r) b[0][r] = b0[r];       // group 0's fragments: read, and waited for, by the previous step
@@ -192,13 +189,7 @@ __device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, const
         const int kw = gi >> 1, half = gi & 1;
         if (gi + 1 < NG) {
             const int kw2 = (gi + 1) >> 1, half2 = (gi + 1) & 1;
-            uint32_t at = lcol[kw2];
-            if (kPackCols<KD, RELU, HAS_BIAS>) {
-                at = kw2 == 0 ? 0u : (kw2 == 1 ? lcol[1] & 0xffffu : lcol[1] >> 16);
-                asm volatile("" : "+v"(at));      // (not kept over the loop)
-                at += lcol[0];
-            }
-            at = (at ^ (half2 * 32)) + HIGH;
+            const uint32_t at = (lcol[kw2] ^ (half2 * 32)) + HIGH;
 #pragma unroll
             for (int r = 0; r < NR; ++r) frag_read(b[(gi + 1) & 1][r], at, OFF + r * ROW_BYTES);
         } else {
@@ -231,8 +222,8 @@ __device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, const
                 // first MFMA; passing the plane through an empty statement here makes each group's eight depend
                 // on a point inside the group, where they are woven between the MFMAs like the rest)
                 asm volatile("" : "+a"(acc[DONE][0]), "+a"(acc[DONE][1]));
-                store_unit<MODE, RELU, FULL>(c, Dp - 3, acc[DONE], pin, mk, 0, gi);
-                store_unit<MODE, RELU, FULL>(c, Dp - 3, acc[DONE], pin, mk, 1, gi);
+                store_unit<MODE, RELU, EDGE>(c, Dp - 3, acc[DONE], pin, mk, 0, gi);
+                store_unit<MODE, RELU, EDGE>(c, Dp - 3, acc[DONE], pin, mk, 1, gi);
             }
         } else {
 #pragma unroll
@@ -267,8 +258,9 @@ __device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, const
     for (int r = 0; r < NR; ++r) b0[r] = b[0][r];
 }
 
-template <int MODE, bool HAS_BIAS, int RELU, int KD>
+template <int MODE, bool HAS_BIAS, int RELU, int PATCHES>
 __global__ __launch_bounds__(kThreads, 1) void conv_mfma_kernel(ConvArgs a) {
+    constexpr int KD = kd_of(PATCHES);
     extern __shared__ __attribute__((aligned(128))) char lds[];  // NBUF planes of PLANE_BYTES
     const Geo &g = a.g;
     // Consecutive hardware workgroup ids rotate over the 8 XCDs; give each XCD a contiguous range of
@@ -351,6 +343,17 @@ __global__ __launch_bounds__(kThreads, 1) void conv_mfma_kernel(ConvArgs a) {
     c.obase = od.base + opos;
     c.mbase = a.mask + opos;
     c.bbase = a.bits + (ovox * a.nco + cj) * 2 + hi;
+    c.mrow = c.orow;
+    if (PATCHES == kRagged3) {
+        const size_t voxel0 = static_cast<size_t>(tile) * g.tile_vox + bx.org +
+                              (static_cast<size_t>(d0 + 1) * g.ph + h0 + wave * RH + 1) * g.pw + w0 + 1;
+        c.rag = ragged(g, bx, h0, w0, wave * RH, col, hi, voxel0, od.base, od.cs, od.co, a.bits, a.nco, cj);
+        // the mask's row and column nearest to the lane's inside the box
+        const int up = max(h0 + wave * RH - (bx.bh - 1), 0), left = max(w0 + col - (bx.bw - 1), 0);
+        c.mbase -= up * c.orow + static_cast<size_t>(left) * od.cs;
+        if (RELU == kMaskBits) c.bbase -= (up * c.orow + static_cast<size_t>(left) * od.cs) >> 4;
+        if (h0 + wave * RH + 1 >= bx.bh) c.mrow = 0;
+    }
     // wave `wave` of workgroup `logical`: a region of dchunk planes x RH rows x 4 units x 1 KB
     c.pbase = a.part + (static_cast<size_t>(logical) * kWaves + wave) * a.dchunk * (RH * 4 * 256) + lane * 4;
 #pragma unroll
@@ -383,19 +386,18 @@ __global__ __launch_bounds__(kThreads, 1) void conv_mfma_kernel(ConvArgs a) {
     // (the synchronisation of a step sits inside it, before its last MFMA group: see plane_step)
     constexpr int NV_STEP = (DIST - 1) * LOADS - 1;     // plane Dp + 2's loads and the step's first NG - 1
     static_assert(NG == LOADS, "one staging load per MFMA group");
-    uint32_t lcol[3] = {lds_addr(lbase + lds_off(col, hi)), lds_addr(lbase + lds_off(col + 1, hi)),
+    const uint32_t lcol[3] = {lds_addr(lbase + lds_off(col, hi)), lds_addr(lbase + lds_off(col + 1, hi)),
                         lds_addr(lbase + lds_off(col + 2, hi))};
-    if (kPackCols<KD, RELU, HAS_BIAS>) lcol[1] = (lcol[1] - lcol[0]) | (lcol[2] - lcol[0]) << 16;
     bf16x8 b0[RH + 2];
 #pragma unroll
     for (int r = 0; r < RH + 2; ++r) b0[r] = *reinterpret_cast<const bf16x8 *>(lbase + lds_off(col, hi) + r * ROW_BYTES);
 
-    auto march = [&](auto full_tag) {
-        constexpr bool FULL = decltype(full_tag)::value;
+    auto march = [&](auto edge_tag) {
+        constexpr Edge EDGE = decltype(edge_tag)::value;
         using S = Side<MODE, RELU, KD, false>;
-        // whole patches fetch their partial sums / mask values one step ahead (see side_load): steps with an even
+        // whole patches, and in 3-D all, fetch their partial sums / mask values one step ahead (see side_load): steps with an even
         // plane index use set A and fetch into set B, odd ones the other way round
-        constexpr bool ASYNC = FULL && S::ASYNC;
+        constexpr bool ASYNC = EDGE != kBranches && S::ASYNC;
         constexpr int FETCH = ASYNC ? kSideFetch : kSideNone, USE = ASYNC ? kSideUse : kSideNone;
         pin_t pinA[RH][4], pinB[RH][4];
         mask_t mkA[RH][4], mkB[RH][4];
@@ -405,14 +407,14 @@ __global__ __launch_bounds__(kThreads, 1) void conv_mfma_kernel(ConvArgs a) {
         static_assert(LOADS - 1 + 8 >= NV_STEP, "side loads must be older than what the step's wait lets stay in flight");
         // the first three steps have no finished plane to store (nplanes >= 3 always); the third one fetches
         // what the first store needs
-        plane_step<0, false, MODE, RELU, FULL, KD, kSideNone, NV_STEP>(c, 0, lcol, wf, acc, pinA, mkA, pinB, mkB, b0);
-        plane_step<1, false, MODE, RELU, FULL, KD, kSideNone, NV_STEP>(c, 1, lcol, wf, acc, pinA, mkA, pinB, mkB, b0);
-        plane_step<2, false, MODE, RELU, FULL, KD, FETCH, (ASYNC ? LOADS - 1 : NV_STEP)>(c, 2, lcol, wf, acc, pinA,
+        plane_step<0, false, MODE, RELU, EDGE, KD, kSideNone, NV_STEP>(c, 0, lcol, wf, acc, pinA, mkA, pinB, mkB, b0);
+        plane_step<1, false, MODE, RELU, EDGE, KD, kSideNone, NV_STEP>(c, 1, lcol, wf, acc, pinA, mkA, pinB, mkB, b0);
+        plane_step<2, false, MODE, RELU, EDGE, KD, FETCH, (ASYNC ? LOADS - 1 : NV_STEP)>(c, 2, lcol, wf, acc, pinA,
                                                                                         mkA, pinB, mkB, b0);
         // steps 3, 4, 5, 6, 7, ...: planes mod 4 = 3, 0, 1, 2, 3, ...
 #define SP3D_MAIN_STEP(OFF, PHASE, CP, CM, NP, NM)                                                            \
     if (D + (OFF) < nplanes)                                                                                  \
-        plane_step<PHASE, true, MODE, RELU, FULL, KD, USE, NV_STEP>(c, D + (OFF), lcol, wf, acc, CP, CM, NP, NM, b0);
+        plane_step<PHASE, true, MODE, RELU, EDGE, KD, USE, NV_STEP>(c, D + (OFF), lcol, wf, acc, CP, CM, NP, NM, b0);
         for (int D = 3; D < nplanes; D += 4) {
             SP3D_MAIN_STEP(0, 3, pinB, mkB, pinA, mkA)
             SP3D_MAIN_STEP(1, 0, pinA, mkA, pinB, mkB)
@@ -428,26 +430,28 @@ __global__ __launch_bounds__(kThreads, 1) void conv_mfma_kernel(ConvArgs a) {
 #pragma unroll
             for (int h = 0; h < RH; ++h)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) pinA[h][q] = pinB[h][q] = load_partial<FULL>(c, dn - 1, h, q);
+                for (int q = 0; q < 4; ++q) pinA[h][q] = pinB[h][q] = load_partial<EDGE>(c, dn - 1, h, q);
         }
         if (!ASYNC && S::MASK) {
 #pragma unroll
             for (int h = 0; h < RH; ++h)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) mkA[h][q] = mkB[h][q] = load_mask<FULL, S::BITS>(c, dn - 1, h, q);
+                for (int q = 0; q < 4; ++q) mkA[h][q] = mkB[h][q] = load_mask<EDGE, S::BITS>(c, dn - 1, h, q);
         }
 #pragma unroll
         for (int s = 0; s < 4; ++s)
             if (s == ((dn - 1) & 3)) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    store_unit<MODE, RELU, FULL>(c, dn - 1, acc[s], (s & 1) ? pinA : pinB, (s & 1) ? mkA : mkB, 0, q);
-                    store_unit<MODE, RELU, FULL>(c, dn - 1, acc[s], (s & 1) ? pinA : pinB, (s & 1) ? mkA : mkB, 1, q);
+                    store_unit<MODE, RELU, EDGE>(c, dn - 1, acc[s], (s & 1) ? pinA : pinB, (s & 1) ? mkA : mkB, 0, q);
+                    store_unit<MODE, RELU, EDGE>(c, dn - 1, acc[s], (s & 1) ? pinA : pinB, (s & 1) ? mkA : mkB, 1, q);
                 }
             }
     };
-    if (h0 + PH <= bx.bh && w0 + PW <= bx.bw) march(std::true_type{});
-    else march(std::false_type{});
+    if constexpr (PATCHES == kWhole3) march(std::integral_constant<Edge, kInside>{});
+    else if constexpr (PATCHES == kRagged3) march(std::integral_constant<Edge, kDrops>{});
+    else if (h0 + PH <= bx.bh && w0 + PW <= bx.bw) march(std::integral_constant<Edge, kInside>{});
+    else march(std::integral_constant<Edge, kBranches>{});
 }
 
 }  // namespace
@@ -664,15 +668,20 @@ int launch_conv_mfma(const void *Pin, const void *w, const float *bias, void *Po
     using Kern = void (*)(ConvArgs);
     // [mode][bias][epilogue]; combinations that cannot occur (bias after the first launch, ReLU or mask before
     // the last, bias together with a mask) reuse the plain variant.  MB, RB: the two bit forms.
-    // [2-D variant][mode][bias][epilogue]; the bit forms exist for the 3-D kernels only (the host refuses them
+    // [patches][mode][bias][epilogue]; the bit forms exist for the 3-D kernels only (the host refuses them
     // for 2-D geometries; their table entries repeat the plain kernel).  The two-chunk kernels have the same table
     // in their own translation unit (conv_mfma_pair.hip).
-    static const Kern kern[2][4][2][5] = {SP3D_CONV_TABLE(conv_mfma_kernel, 3, kMaskBits, kReluBits),
-                                          SP3D_CONV_TABLE(conv_mfma_kernel, 1, kNone, kNone)};
+    static const Kern kern[3][4][2][5] = {SP3D_CONV_TABLE(conv_mfma_kernel, kWhole3, kMaskBits, kReluBits),
+                                          SP3D_CONV_TABLE(conv_mfma_kernel, kRagged3, kMaskBits, kReluBits),
+                                          SP3D_CONV_TABLE(conv_mfma_kernel, kAny2, kNone, kNone)};
+    // (One patch in 32 cut by the box and kRagged3 is the faster one already: 64 -> 64 on 128 x 126 x 128 in 1 x 1 x 4 tiles, forward
+    // 422 us with whole patches and others in one launch, 368 with this, masked data gradient 505 and 368.  A grown box differs
+    // from tile to tile.)
+    const int patches = g.flat ? kAny2 : (g.grow == 0 && g.th % (pairs ? wide::PH : PH) == 0 && g.tw % PW == 0 ? kWhole3 : kRagged3);
     const int epi = bits ? (dgrad ? kMaskBits : kReluBits) : (mask ? kMask : (relu ? kRelu : kNone));
     // more than 64 KB of dynamic LDS has to be requested explicitly
     static const hipError_t attr = [] {
-        for (int i = 0; i < 80; ++i) {
+        for (int i = 0; i < 120; ++i) {
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern[i / 40][(i / 10) & 3][(i / 5) & 1][i % 5]),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
             if (e != hipSuccess) return e;
@@ -687,9 +696,9 @@ int launch_conv_mfma(const void *Pin, const void *w, const float *bias, void *Po
         if (pairs) chunk_src(2 * ci + 1, &a.in2, &a.in2_cs, &a.in2_co);
         a.wpack = static_cast<const uint4 *>(ws) + static_cast<size_t>(pairs ? 2 * ci : ci) * nco * NFRAG * 64;
         if (pairs)
-            conv_mfma_pair_launch(g.flat, mode, bias ? 1 : 0, epi, grid, s, a);
+            conv_mfma_pair_launch(patches, mode, bias ? 1 : 0, epi, grid, s, a);
         else
-            hipLaunchKernelGGL(kern[g.flat][mode][bias ? 1 : 0][epi], dim3(grid), dim3(kThreads), LDS_BYTES, s, a);
+            hipLaunchKernelGGL(kern[patches][mode][bias ? 1 : 0][epi], dim3(grid), dim3(kThreads), LDS_BYTES, s, a);
         rc = record_hip(hipGetLastError());
         if (rc != SP_OK) return rc;
     }

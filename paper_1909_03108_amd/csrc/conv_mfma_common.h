@@ -42,6 +42,14 @@ __device__ __forceinline__ int piece_at(int column, int piece) { return (piece ^
 // byte offset of 16-byte piece `piece` of column `column` of a row
 __device__ __forceinline__ int lds_off(int column, int piece) { return column * REC + 16 * piece_at(column, piece); }
 
+// The patches of a launch: 3-D, all of them whole (the box a multiple of the patch); 3-D, some not; 2-D, either kind.  (A
+// one-chunk kernel for both kinds in 3-D holds the march twice, and the registers of the one cost the other: masked data gradient
+// 32 -> 32 on 128^3 122 -> 126 us.)
+enum Patches { kWhole3 = 0, kRagged3 = 1, kAny2 = 2 };
+// How a march treats the lanes outside its tile's box: there are none; loads and stores under a condition; see Ragged.
+enum Edge { kInside, kBranches, kDrops };
+constexpr int kd_of(int patches) { return patches == kAny2 ? 1 : 3; }
+
 // How a launch treats the fp32 partial sums of a layer with several input chunks.
 enum Mode { kSingle = 0,   // only chunk: bias, ReLU, store bf16
             kFirst = 1,    // first chunk: bias, store fp32 partial
@@ -195,7 +203,7 @@ typedef uint32_t mask_t __attribute__((ext_vector_type(2)));
 // (DIST - 1) * LOADS operations outstanding) already covers them: the registers pass through that wait as
 // operands (side_fence), nothing reads them earlier, and they hold their data at every block boundary, where
 // the compiler is free to copy them.  The step that uses them needs no wait at all.  Marches over ragged
-// patches, whose loads are predicated, keep the ordinary loads.  Between a side load and the wait that covers it
+// patches of the 2-D variant, whose loads are predicated, keep the ordinary loads.  Between a side load and the wait that covers it
 // the code must be one basic block with nothing that makes the compiler move the register: a load issued under
 // a run-time condition is joined to the other path by a copy that runs before the data has arrived.
 __device__ __forceinline__ void side_load(pin_t &d, const float *p) {
@@ -264,6 +272,9 @@ __device__ __forceinline__ size_t part_unit(int d, int h, int q) { return static
 // channel block and half, against 16 elements in the tensor.
 template <class CtxT>
 __device__ __forceinline__ size_t bits_off(const CtxT &c, int d, int h) { return (d * c.oplane + h * c.orow) >> 4; }
+// ... and of the row that the mask of row h is read from (the box's last one where row h lies outside)
+template <Edge EDGE, class CtxT>
+__device__ __forceinline__ size_t mask_off(const CtxT &c, int d, int h) { return d * c.oplane + (EDGE != kDrops ? h * c.orow : (h ? c.mrow : 0)); }
 
 // ReLU on the bit pattern of an fp32 value: whatever has the sign bit set (negative values, -0, NaNs with the sign
 // set) becomes +0, everything else stays as it is - one integer maximum, where the floating-point compare and select
@@ -303,10 +314,45 @@ __device__ __forceinline__ uint2 nibble_halves(uint32_t spread, int q) {
     return make_uint2(fill_from_bit(spread, 4 * q), fill_from_bit(spread, 4 * q + 2));
 }
 
+// Ragged patches of the 3-D kernels.  Lanes outside the tile's box must not store; a store under a condition is a branch, and with
+// eight of them a step is no longer one block: its side work was not woven between the MFMAs and mask and partial sums
+// came by ordinary loads (see side_load).  Stores of such a patch go through a buffer descriptor, which drops those of a lane whose
+// offset lies outside; the mask is read from the nearest row and column of the box, and partial sums, which have a place
+// for every voxel of a patch, are stored and read without a condition.  32 -> 32 on 99 x 156 x 210 in 1 x 2 x 2 tiles, forward and
+// masked data gradient, weights packed: 220 -> 190 and 297 -> 212 us.
+constexpr uint32_t kDrop = 0x80000000u;      // a byte offset outside every descriptor
+struct Ragged {
+    uint16_t *out, *bits;                    // uniform: voxel (plane 0, first row of the wave, first column of the patch)
+    uint32_t vo[RH], bo[RH];                 // this lane's byte offsets from there in the output tensor and in the one-bit mask
+};
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(uint16_t *p) { return __builtin_amdgcn_make_buffer_rsrc(p, 0, 0x7fffffff, 0x00027000); }
+__device__ __forceinline__ void drop_store(uint16_t *base, uint32_t off, uint2 v) {
+    __builtin_amdgcn_raw_buffer_store_b64(mask_t{v.x, v.y}, plane_rsrc(base), off, 0, 0);
+}
+
 // kReluBits: write the mask word of row h of plane d that the four store units of the row collected.
-template <bool FULL, class CtxT>
+template <Edge EDGE, class CtxT>
 __device__ __forceinline__ void store_bits(const CtxT &c, int d, const mask_t (&mk)[RH][4], int h) {
-    if (FULL || c.okrow[h]) c.bbase[bits_off(c, d, h)] = row_word(mk[h][0].x);
+    if (EDGE == kDrops)
+        __builtin_amdgcn_raw_buffer_store_b16(row_word(mk[h][0].x), plane_rsrc(c.rag.bits + ((d * c.oplane) >> 4)), c.rag.bo[h], 0, 0);
+    else if (EDGE == kInside || c.okrow[h]) c.bbase[bits_off(c, d, h)] = row_word(mk[h][0].x);
+}
+
+// This lane's part of a patch of the box bx at (h0, w0), the first row of the wave being row r0 of the patch (no slices side by side).
+// voxel0: padded voxel index of (plane 0, row r0, column 0) of the patch.
+__device__ __forceinline__ Ragged ragged(const Geo &g, const TileBox &bx, int h0, int w0, int r0, int col, int hi, size_t voxel0,
+                                         uint16_t *out, int cs, int co, uint16_t *bits, int nco, int cj) {
+    Ragged r;
+    r.out = out + voxel0 * cs + co;
+    r.bits = bits + (voxel0 * nco + cj) * 2;
+#pragma unroll
+    for (int h = 0; h < RH; ++h) {
+        const bool ok = h0 + r0 + h < bx.bh && w0 + col < bx.bw;
+        const uint32_t v = static_cast<uint32_t>(h) * g.pw + col;
+        r.vo[h] = ok ? v * cs * 2 + 8 * hi : kDrop;
+        r.bo[h] = ok ? v * nco * 4 + 2 * hi : kDrop;
+    }
+    return r;
 }
 
 // ---- the two-chunk kernel (conv_mfma_pair.hip) ------------------------------------------------
@@ -346,30 +392,30 @@ __host__ __device__ constexpr int wl_index(int kd, int kw, int half) { return ((
 
 }  // namespace convk
 
-// Kernel table of a family K<mode, bias, epilogue, KD>: [mode][bias][epilogue]; combinations that cannot occur
+// Kernel table of a family K<mode, bias, epilogue, patches>: [mode][bias][epilogue]; combinations that cannot occur
 // (bias after the first launch, ReLU or mask before the last, bias together with a mask) reuse the plain variant.
 // MB, RB: the two bit forms of the epilogue (or kNone where a family does not have them).
-#define SP3D_CONV_TABLE(K, KD, MB, RB)                                                                          \
-    {{{K<kSingle, false, kNone, KD>, K<kSingle, false, kRelu, KD>, K<kSingle, false, kMask, KD>,             \
-       K<kSingle, false, MB, KD>, K<kSingle, false, RB, KD>},                                                \
-      {K<kSingle, true, kNone, KD>, K<kSingle, true, kRelu, KD>, K<kSingle, false, kMask, KD>,               \
-       K<kSingle, false, MB, KD>, K<kSingle, true, RB, KD>}},                                                \
-     {{K<kFirst, false, kNone, KD>, K<kFirst, false, kNone, KD>, K<kFirst, false, kNone, KD>,                \
-       K<kFirst, false, kNone, KD>, K<kFirst, false, kNone, KD>},                                            \
-      {K<kFirst, true, kNone, KD>, K<kFirst, true, kNone, KD>, K<kFirst, true, kNone, KD>,                   \
-       K<kFirst, true, kNone, KD>, K<kFirst, true, kNone, KD>}},                                             \
-     {{K<kMiddle, false, kNone, KD>, K<kMiddle, false, kNone, KD>, K<kMiddle, false, kNone, KD>,             \
-       K<kMiddle, false, kNone, KD>, K<kMiddle, false, kNone, KD>},                                          \
-      {K<kMiddle, false, kNone, KD>, K<kMiddle, false, kNone, KD>, K<kMiddle, false, kNone, KD>,             \
-       K<kMiddle, false, kNone, KD>, K<kMiddle, false, kNone, KD>}},                                         \
-     {{K<kLast, false, kNone, KD>, K<kLast, false, kRelu, KD>, K<kLast, false, kMask, KD>,                   \
-       K<kLast, false, MB, KD>, K<kLast, false, RB, KD>},                                                    \
-      {K<kLast, false, kNone, KD>, K<kLast, false, kRelu, KD>, K<kLast, false, kMask, KD>,                   \
-       K<kLast, false, MB, KD>, K<kLast, false, RB, KD>}}}
+#define SP3D_CONV_TABLE(K, PT, MB, RB)                                                                          \
+    {{{K<kSingle, false, kNone, PT>, K<kSingle, false, kRelu, PT>, K<kSingle, false, kMask, PT>,             \
+       K<kSingle, false, MB, PT>, K<kSingle, false, RB, PT>},                                                \
+      {K<kSingle, true, kNone, PT>, K<kSingle, true, kRelu, PT>, K<kSingle, false, kMask, PT>,               \
+       K<kSingle, false, MB, PT>, K<kSingle, true, RB, PT>}},                                                \
+     {{K<kFirst, false, kNone, PT>, K<kFirst, false, kNone, PT>, K<kFirst, false, kNone, PT>,                \
+       K<kFirst, false, kNone, PT>, K<kFirst, false, kNone, PT>},                                            \
+      {K<kFirst, true, kNone, PT>, K<kFirst, true, kNone, PT>, K<kFirst, true, kNone, PT>,                   \
+       K<kFirst, true, kNone, PT>, K<kFirst, true, kNone, PT>}},                                             \
+     {{K<kMiddle, false, kNone, PT>, K<kMiddle, false, kNone, PT>, K<kMiddle, false, kNone, PT>,             \
+       K<kMiddle, false, kNone, PT>, K<kMiddle, false, kNone, PT>},                                          \
+      {K<kMiddle, false, kNone, PT>, K<kMiddle, false, kNone, PT>, K<kMiddle, false, kNone, PT>,             \
+       K<kMiddle, false, kNone, PT>, K<kMiddle, false, kNone, PT>}},                                         \
+     {{K<kLast, false, kNone, PT>, K<kLast, false, kRelu, PT>, K<kLast, false, kMask, PT>,                   \
+       K<kLast, false, MB, PT>, K<kLast, false, RB, PT>},                                                    \
+      {K<kLast, false, kNone, PT>, K<kLast, false, kRelu, PT>, K<kLast, false, kMask, PT>,                   \
+       K<kLast, false, MB, PT>, K<kLast, false, RB, PT>}}}
 
-// conv_mfma_pair.hip: the kernels of namespace wide.  [2-D variant][mode][bias][epilogue], see launch_conv_mfma.
+// conv_mfma_pair.hip: the kernels of namespace wide.  [patches][mode][bias][epilogue], see launch_conv_mfma.
 hipError_t conv_mfma_pair_prepare();      // requests the dynamic LDS of every variant (once)
-void conv_mfma_pair_launch(int flat, int mode, int bias, int epi, unsigned grid, hipStream_t s,
+void conv_mfma_pair_launch(int patches, int mode, int bias, int epi, unsigned grid, hipStream_t s,
                            const convk::ConvArgs &a);
 
 }  // namespace sp3d

@@ -10,7 +10,7 @@ import torch
 
 from oracle import conv3d, tiling
 from paper_1909_03108_amd import sp3d, synth
-from gpu_util import DT, TOL, bits, f64, rel_err, to_dev, widen
+from gpu_util import DT, TOL, bits, f64, rel_err, route, to_dev, widen
 
 pytestmark = pytest.mark.gpu
 
@@ -305,3 +305,64 @@ def test_every_march_length_with_mask_and_partial_sums(d, cin, cout, flat):
     plain, fused = volume(Pd, cin), volume(Pf, cin)
     assert rel_err(f64(plain), ref_dx) <= TOL["bf16"]
     assert torch.equal(fused, torch.where(to_dev(xr).float() > 0, plain, torch.zeros_like(plain)))
+
+
+@pytest.mark.parametrize("grid", [(1, 8, 2), (1, 4, 6), (1, 1, 3)])     # rows of 5, 10, 40; columns of 48, 16, 32
+@pytest.mark.parametrize("cin,cout", [(32, 32), (64, 32), (96, 32), (128, 64)])
+def test_patches_cut_by_the_box_give_the_bits_of_whole_ones(grid, cin, cout):
+    """A march over patches that reach out of their tile's box drops the stores of the lanes outside and reads mask and partial
+    sums without a condition.  Every voxel's sum is the same sum in the same order whatever the tiles, so the results of a tiling
+    into such patches are, bit for bit, those of the volume as one tile, whose patches are whole: forward with bias and ReLU and
+    with the mask bits written, and the data gradient masked by a tensor and by bits.  What lies outside the boxes keeps its bits."""
+    n, dhw, dt = 1, (9, 40, 96), DT["bf16"]
+    x, dz = draw("bf16", (n,) + dhw + (cin,), 61), draw("bf16", (n,) + dhw + (cout,), 62)
+    xm = draw("bf16", (n,) + dhw + (cin,), 63)
+    w, b = to_dev(synth.weights(cin, cout, 64, "bf16")), torch.linspace(-0.5, 0.5, cout, device="cuda")
+
+    def run(gr):
+        g = sp3d.Geom(n, dhw, gr)
+        for op in (sp3d.SP_OP_FWD, sp3d.SP_OP_DGRAD):
+            assert route(op, g, cin, cout, dt)[0] == "march"
+        ws = sp3d.alloc_ws(max(sp3d.sp_workspace_bytes(op, g, cin, cout, dt) for op in (sp3d.SP_OP_FWD, sp3d.SP_OP_DGRAD)))
+
+        def padded(V, c):
+            P = sp3d.alloc_padded(g, c, dt)
+            sp3d.sp_partition(to_dev(V), P, g, c, dt)
+            sp3d.sp_halo_exchange(P, g, c, dt)
+            return P
+
+        def out(c):
+            P = sp3d.alloc_padded(g, c, dt)
+            P.fill_(7.0)
+            return P
+
+        def volume(P, c):
+            keep = torch.ones(P.shape, dtype=torch.bool, device="cuda")
+            keep[..., 1:-1, 1:-1, 1:-1, :] = False
+            assert bool((P[keep] == 7.0).all())
+            V = torch.empty((n,) + dhw + (c,), dtype=P.dtype, device="cuda")
+            sp3d.sp_unpartition(P, V, g, c, dt)
+            return V
+
+        Px, Pz, Pm = padded(x, cin), padded(dz, cout), padded(xm, cin)
+        words = torch.empty(sp3d.sp_relu_bits_bytes(g, cout) // 2, dtype=torch.int16, device="cuda").fill_(0x5a5a)
+        want = torch.empty_like(words)
+        mwords = torch.empty(sp3d.sp_relu_bits_bytes(g, cin) // 2, dtype=torch.int16, device="cuda")
+        ys, ds = [out(cout), out(cout)], [out(cin), out(cin), out(cin)]
+        sp3d.conv3d_fwd(Px, w, b, ys[0], g, cin, cout, dt, sp3d.SP_FLAG_RELU, ws)
+        sp3d.conv3d_fwd_bits(Px, w, b, ys[1], words, g, cin, cout, dt, sp3d.SP_FLAG_RELU, ws)
+        sp3d.sp_relu_bits(ys[1], want, g, cout, dt)
+        words, want = (t.view(tuple(ys[0].shape[:-1]) + (cout // 32, 2)) for t in (words, want))
+        inside = torch.zeros(words.shape, dtype=torch.bool, device="cuda")
+        inside[..., 1:-1, 1:-1, 1:-1, :, :] = True
+        assert torch.equal(words, torch.where(inside, want, torch.full_like(want, 0x5a5a)))
+        sp3d.sp_relu_bits(Pm, mwords, g, cin, dt)
+        sp3d.conv3d_dgrad(Pz, w, ds[0], g, cin, cout, dt, ws)
+        sp3d.conv3d_dgrad_relu(Pz, w, Pm, ds[1], g, cin, cout, dt, ws)
+        sp3d.conv3d_dgrad_bits(Pz, w, mwords, ds[2], g, cin, cout, dt, ws)
+        return [volume(P, cout) for P in ys] + [volume(P, cin) for P in ds]
+
+    whole, cut = run((1, 1, 1)), run(grid)
+    for a, c in zip(whole, cut):
+        assert torch.equal(a, c)
+    assert torch.equal(whole[3], whole[4])
