@@ -171,8 +171,8 @@ size_t sp_workspace_bytes(int op, const sp_geom_t *g, int cin, int cout, sp_dtyp
 // Which kernels a call takes and how it is cut: host logic only, for the tests that have to reach a certain kernel; not part
 // of the C ABI.  op: SP_OP_* or 16 / 17, the 1x1x1 convolution's forward pass and data gradient.  Returns kRoute*; detail:
 // marching forward / data gradient {two chunks per launch, slices side by side, D chunk, launches}, implicit GEMM {output blocks
-// per wave, tiles of 128 voxels, record loads, splits}, marching weight gradient {whole patches (2: 2-D ones in steps of two patches
-// of one slice), slices side by side, D chunk (2: the steps), workgroups per channel pair}, GEMM over voxels
+// per wave, tiles of 128 voxels, record loads, splits}, marching weight gradient {whole patches (2: 2-D ones patch by patch), slices
+// side by side, D chunk (2: pairs of patches of one slice), workgroups per channel pair (more than 256 in all: four pairs share one)}, GEMM over voxels
 // {channel chunks of a tile, record groups, splits, summed by stage}, weight gradient of 2 ... 8 input channels {bricks, workgroups
 // per block of output channels, rows of a brick, 0}, weight gradient on zero-padded copies {as the march's, the cutting with the
 // fewest partial sums}.

@@ -421,6 +421,40 @@ def test_flat_whole_patches_take_two_tensors(n, dhw, grid, ca, cb, co):
     assert rel_err(f64(db), flat_oracle.bias_grad(widen(dz))) <= 1e-5
 
 
+# 64 x 64 channels to a workgroup: blocks whose two halves lie in different tensors, an odd number of input blocks, several tiles and
+# entries, workgroups with a unit less than others, in one pass and in two (units, workgroups per block: 768, 112; 144, 37; 256, 18;
+# 357, 37)
+FLAT_BLOCKS = [(2, (6, 128, 128), (1, 2, 2), 32, 96, 64), (1, (4, 96, 96), (1, 1, 1), 96, 96, 128),
+               (1, (16, 64, 64), (1, 2, 1), 224, 32, 192), (1, (7, 136, 96), (1, 1, 1), 96, 96, 128)]
+
+
+@pytest.mark.parametrize("n, dhw, grid, ca, cb, co", FLAT_BLOCKS)
+def test_flat_blocks_of_four_pairs(n, dhw, grid, ca, cb, co):
+    """Four channel pairs per workgroup: the oracle's sums, the same bits from two tensors and without the bias gradient, and with
+    NaN in whatever lies outside (margins along D, workspace)."""
+    g, dt = sp3d.Geom(n, dhw, grid, 1, 0, 1), DT["bf16"]
+    family, detail = route(2, g, ca + cb, co, dt)
+    assert family == "march" and detail[0] == 2 and detail[3] * (ca + cb) * co > 256 * 32 * 32
+    x = synth.normal_volume((n,) + dhw + (ca + cb,), 6711, "bf16")
+    dz = synth.normal_volume((n,) + dhw + (co,), 6712, "bf16")
+    P = []
+    for v in (x, x[..., :ca], x[..., ca:], dz):
+        P.append(sp3d.alloc_padded(g, v.shape[-1], dt))
+        P[-1][..., 0, :, :, :] = P[-1][..., -1, :, :, :] = float("nan")
+        sp3d.sp_partition(to_dev(np.ascontiguousarray(v)), P[-1], g, v.shape[-1], dt)
+        sp3d.sp_halo_exchange(P[-1], g, v.shape[-1], dt)
+    ws = sp3d.alloc_ws(sp3d.sp_workspace_bytes(2, g, ca + cb, co, dt))
+    ws.fill_(255)
+    dw, dw2, dw3 = (torch.empty((3, 3, ca + cb, co), device="cuda") for _ in range(3))
+    db, db2 = torch.empty(co, device="cuda"), torch.empty(co, device="cuda")
+    sp3d.conv3d_wgrad(P[0], P[3], dw, db, g, ca + cb, co, dt, ws)
+    sp3d.conv3d_wgrad2(P[1], ca, P[2], cb, P[3], dw2, db2, g, co, dt, ws)
+    sp3d.conv3d_wgrad(P[0], P[3], dw3, None, g, ca + cb, co, dt, ws)
+    assert torch.equal(dw, dw2) and torch.equal(db, db2) and torch.equal(dw, dw3)
+    assert rel_err(f64(dw), flat_oracle.conv_wgrad(widen(x), widen(dz))) <= 1e-5
+    assert rel_err(f64(db), flat_oracle.bias_grad(widen(dz))) <= 1e-5
+
+
 @pytest.mark.parametrize("cin", [3, 6])                 # records of 4 and of 8 channels
 @pytest.mark.parametrize("flat", [0, 1])
 @pytest.mark.parametrize("tiles", [1, 2])
