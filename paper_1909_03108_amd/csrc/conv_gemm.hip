@@ -59,7 +59,8 @@ constexpr int wg_vox(int vb) { return 128 * vb; }
 // per wave and step.
 constexpr int stage_bytes(int bl) { return 4 * bl * 1024; }
 // LDS stages of voxels; the step loop is unrolled by as many, so that a stage and a register set have their place at compile
-// time, and K is split in units of as many steps (kernel rows x chunks: 3 divides both 3 and 9)
+// time.  A whole K loop is a multiple of as many steps (kernel rows x chunks: 3 divides both 3 and 9); the part of one that a split
+// has is any number from four up, so that items of split layers begin and end in any phase of the unrolled loop.
 constexpr int NS = 3;
 // steps that weight fragments are loaded ahead (128 channels x 128 voxels: one, so that two workgroups fit the registers)
 constexpr int ahead(int cbw, int vb) { return cbw == 2 && vb == 1 ? 1 : NS; }
@@ -207,7 +208,12 @@ __device__ __forceinline__ size_t part_index(const GemmArgs &a, int split, int b
     return (((static_cast<size_t>(split) * a.nblocks + blk) * kGemmWaves + wave) * CBW * 2 * VB + c * 2 * VB + s) * 256 + lane;
 }
 
-template <int CBW, int VB, int BL>
+// SPLIT: a.nsplit > 1.  Split s has the steps [s nk / nsplit, (s + 1) nk / nsplit), as plan_gemm prices them and in the order of the sums
+// that a K loop cut by any kernel of this family has had; with splits in whole threes the longest of them ran up to half as
+// many steps again: 128 -> 128 on 8^3 (nine splits of four steps) 17.2 -> 15.6 us, 256 -> 256 there 23.4 -> 21.9, 512 -> 512 on 4^3
+// 29.1 -> 27.5; on 134 layers 0.94 of the time, where the splits are whole threes anyway up to 1.05 (an end to look for in every
+// step).
+template <int CBW, int VB, int BL, bool SPLIT>
 __global__ __launch_bounds__(kGemmThreads, resident(CBW, VB)) void conv_gemm_kernel(GemmArgs a) {
     constexpr int NSEG = 2 * VB, CBT = 2 * CBW, NGRP = 2 * ROW, STAGE = stage_bytes(BL), AD = ahead(CBW, VB);
     extern __shared__ __align__(16) char lds[];
@@ -221,16 +227,16 @@ __global__ __launch_bounds__(kGemmThreads, resident(CBW, VB)) void conv_gemm_ker
     const int wm = wave & 1, wn = wave >> 1, hi = lane >> 5;
     // (voxel indices are unsigned and 32 bits wide: 2^32 voxels of at least 32 + 64 channels do not fit the memory)
     const uint32_t prow = g.pw, pplane = static_cast<uint32_t>(g.ph) * g.pw;
-    const int nunits = a.nci * a.nrows / NS;
-    struct Item { int vg, split, cg, u0, u1; };
+    const int nk = a.nci * a.nrows;
+    struct Item { int vg, split, cg, k0, k1; };          // voxel group, split, group of output blocks, steps [k0, k1)
     auto item_at = [&](int i) __attribute__((always_inline)) {
         const int u = i / a.nvg;
         Item t;
         t.vg = i - u * a.nvg;
-        t.cg = u / a.nsplit;
-        t.split = u - t.cg * a.nsplit;
-        t.u0 = t.split * nunits / a.nsplit;
-        t.u1 = (t.split + 1) * nunits / a.nsplit;
+        t.cg = SPLIT ? u / a.nsplit : u;
+        t.split = SPLIT ? u - t.cg * a.nsplit : 0;
+        t.k0 = SPLIT ? t.split * nk / a.nsplit : 0;
+        t.k1 = SPLIT ? (t.split + 1) * nk / a.nsplit : nk;
         return t;
     };
     auto record = [&](int q) __attribute__((always_inline)) {
@@ -249,9 +255,9 @@ __global__ __launch_bounds__(kGemmThreads, resident(CBW, VB)) void conv_gemm_ker
     const uint32_t sw = tvox - g.tw, sh = tvox * g.gw - g.th * prow, sd = tvox * g.gw * g.gh - g.td * pplane;
     auto open_voxels = [&]() __attribute__((always_inline)) {
         const Item t = item_at(fitem);
-        fleft = (t.u1 - t.u0) * NS;
-        fr = t.u0 * NS / a.nci;
-        fi = t.u0 * NS - fr * a.nci;
+        fleft = t.k1 - t.k0;
+        fr = t.k0 / a.nci;
+        fi = t.k0 - fr * a.nci;
         const int q0 = t.vg * wg_vox(VB);
         const uint32_t rec0 = record(q0), nrec = record(min(q0 + wg_vox(VB), a.nvox) - 1) + 3 - rec0;
 #pragma unroll
@@ -289,7 +295,7 @@ __global__ __launch_bounds__(kGemmThreads, resident(CBW, VB)) void conv_gemm_ker
         dma16(reinterpret_cast<const void *>(base + static_cast<uint64_t>(at) * static_cast<uint32_t>(2 * src.cs)),
               lds0 + stage * STAGE + j * 1024);
     };
-    // may_end: the step just fetched may be an item's last one (its phase is NS - 1)
+    // may_end: the step just fetched may be an item's last one (its phase is NS - 1, or the items are splits)
     auto next_voxels = [&](bool may_end) __attribute__((always_inline)) {
         if (--fleft > 0) {
             if (++fi == a.nci) { fi = 0; ++fr; }
@@ -309,9 +315,9 @@ __global__ __launch_bounds__(kGemmThreads, resident(CBW, VB)) void conv_gemm_ker
     int witem = first, wleft = 0, wi = 0, wrow = 0, wat = 0;    // item, steps left, chunk, byte offset of (kernel row, block), with the chunk
     auto open_weights = [&]() __attribute__((always_inline)) {
         const Item t = item_at(witem);
-        wleft = (t.u1 - t.u0) * NS;
-        const int r = t.u0 * NS / a.nci;
-        wi = t.u0 * NS - r * a.nci;
+        wleft = t.k1 - t.k0;
+        const int r = t.k0 / a.nci;
+        wi = t.k0 - r * a.nci;
         wrow = ((t.cg * CBT + wm * CBW) * NTAP_PACK + (a.nrows == 3 ? 9 : 0) + ROW * r) * 2048;
         wat = wrow + wi * a.nco * NTAP_PACK * 2048;
     };
@@ -355,20 +361,22 @@ __global__ __launch_bounds__(kGemmThreads, resident(CBW, VB)) void conv_gemm_ker
             bf[gi & 1][s] = *reinterpret_cast<const bf16x8 *>(lds + (boff[s][gi >> 1] ^ ((gi & 1) * 32)) + stage * STAGE);
     };
     // One step, in phase P of NS: its voxels are in stage P, the loads of the step NS - 1 on go to the stage that the step
-    // before it left, one in each of the first BL groups; its weights are in set P (the only one if AD = 1).
-    int next_q0 = -1;                // first voxel of the next item, in an item's last unit (-1: nothing to do)
-    auto step = [&](auto phase) __attribute__((always_inline)) {
+    // before it left, one in each of the first BL groups; its weights are in set P (the only one if AD = 1).  TAIL: of the
+    // workgroup's last NS - 1 steps at most, behind which there is nothing to load.
+    int next_q0 = -1;                // first voxel of the next item, in an item's last step (-1: nothing to do)
+    auto step = [&](auto phase, auto tail) __attribute__((always_inline)) {
         constexpr int P = decltype(phase)::value, SET = AD == 1 ? 0 : P;
+        constexpr bool TAIL = decltype(tail)::value;
 #pragma unroll
         for (int gi = 0; gi < NGRP; ++gi) {
             if (gi + 1 < NGRP) {
                 read_group(P, gi + 1);
             } else {
-                if (P == NS - 1 && next_q0 >= 0) read_offsets(next_q0);
+                if (!TAIL && (SPLIT || P == NS - 1) && next_q0 >= 0) read_offsets(next_q0);
                 // Every wave has read this step's last fragments (lgkmcnt) and the next step's records have landed: after
                 // the last of their loads, in group BL - 1 of the step before, there were the weight loads of that group and the ones
                 // behind it and this step's loads up to here.  Behind the barrier this step's stage is free.
-                constexpr int NEWER = (NGRP + 1 - BL) * CBW + (BL < NGRP ? BL : NGRP - 1) + (NGRP - 1) * CBW;
+                constexpr int NEWER = TAIL ? 0 : (NGRP + 1 - BL) * CBW + (BL < NGRP ? BL : NGRP - 1) + (NGRP - 1) * CBW;
                 asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(NEWER) : "memory");
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
@@ -380,17 +388,20 @@ __global__ __launch_bounds__(kGemmThreads, resident(CBW, VB)) void conv_gemm_ker
                 const int c = m / NSEG, s = m % NSEG;
                 if (m == 1) {
                     __builtin_amdgcn_sched_barrier(0);
-                    if (gi < BL) fetch_voxels((P + NS - 1) % NS, gi);
+                    if (!TAIL && gi < BL) fetch_voxels((P + NS - 1) % NS, gi);
+                    // (where the next loads are from is found between products too)
+                    if (SPLIT && !TAIL && gi == BL) next_voxels(true);
+                    if (SPLIT && (!TAIL || AD == 1) && gi == 0) next_weights(true);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 acc[c][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[SET][gi][c], bf[gi & 1][s], acc[c][s], 0, 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
-            fetch_weights(SET, gi);
+            if (!TAIL || AD == 1) fetch_weights(SET, gi);
             __builtin_amdgcn_sched_barrier(0);
         }
-        next_voxels((P + NS - 1) % NS == NS - 1);
-        next_weights((P + AD) % NS == NS - 1);
+        if (!TAIL && (!SPLIT || BL == NGRP)) next_voxels(SPLIT || (P + NS - 1) % NS == NS - 1);
+        if (!SPLIT) next_weights((P + AD) % NS == NS - 1);
     };
 
     open_voxels();
@@ -406,7 +417,7 @@ __global__ __launch_bounds__(kGemmThreads, resident(CBW, VB)) void conv_gemm_ker
     for (int st = 0; st < AD; ++st) {
 #pragma unroll
         for (int gi = 0; gi < NGRP; ++gi) fetch_weights(st, gi);
-        next_weights(st == NS - 1);
+        if (!SPLIT || st + 1 < AD) next_weights(st == NS - 1);
     }
     __builtin_amdgcn_sched_barrier(0);
     read_offsets(item_at(first).vg * wg_vox(VB));
@@ -414,11 +425,12 @@ __global__ __launch_bounds__(kGemmThreads, resident(CBW, VB)) void conv_gemm_ker
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     read_group(0, 0);
-#pragma unroll 1
-    for (int item = first; item < end; item += nslots) {
-        const Item t = item_at(item);
-        const int after = item + nslots < end ? item_at(item + nslots).vg * wg_vox(VB) : -1;
-        // accumulators start from the bias (in the first split): lane l holds channels 8 (e / 4) + 4 (l / 32) + e % 4 of a block
+    int item = first, after = -1;    // first voxel of the item after this one
+    Item t;
+    // accumulators start from the bias (in the first split): lane l holds channels 8 (e / 4) + 4 (l / 32) + e % 4 of a block
+    auto begin = [&]() __attribute__((always_inline)) {
+        t = item_at(item);
+        after = item + nslots < end ? item_at(item + nslots).vg * wg_vox(VB) : -1;
         const bool biased = a.bias && t.split == 0;
 #pragma unroll
         for (int c = 0; c < CBW; ++c) {
@@ -429,17 +441,20 @@ __global__ __launch_bounds__(kGemmThreads, resident(CBW, VB)) void conv_gemm_ker
 #pragma unroll
             for (int s = 0; s < NSEG; ++s) acc[c][s] = v;
         }
+    };
+    // The next item's loads are in flight meanwhile; the waits that the compiler puts behind the mask's loads are on the
+    // same counter and only ask for more than they need.
+    if constexpr (!SPLIT) {
 #pragma unroll 1
-        for (int u = t.u0; u < t.u1; ++u) {
-            step(std::integral_constant<int, 0>{});
-            step(std::integral_constant<int, 1>{});
-            next_q0 = u + 1 == t.u1 ? after : -1;
-            step(std::integral_constant<int, 2>{});
-        }
-
-        // The next item's loads are in flight meanwhile; the waits that the compiler puts behind the mask's loads are on the
-        // same counter and only ask for more than they need.
-        if (a.nsplit == 1) {
+        for (; item < end; item += nslots) {
+            begin();
+#pragma unroll 1
+            for (int k = 0; k < nk; k += NS) {
+                step(std::integral_constant<int, 0>{}, std::false_type{});
+                step(std::integral_constant<int, 1>{}, std::false_type{});
+                next_q0 = k + NS == nk ? after : -1;
+                step(std::integral_constant<int, 2>{}, std::false_type{});
+            }
             OutVox o[NSEG];
 #pragma unroll
             for (int s = 0; s < NSEG; ++s) o[s] = out_vox(a, t.vg * wg_vox(VB) + wn * 64 * VB + s * 32 + (lane & 31));
@@ -461,7 +476,9 @@ __global__ __launch_bounds__(kGemmThreads, resident(CBW, VB)) void conv_gemm_ker
                     __builtin_amdgcn_sched_barrier(0);
                 }
             });
-        } else {
+        }
+    } else {
+        auto put = [&]() __attribute__((always_inline)) {
             const int blk = t.cg * a.nvg + t.vg;
 #pragma unroll
             for (int s = 0; s < NSEG; ++s)
@@ -472,6 +489,40 @@ __global__ __launch_bounds__(kGemmThreads, resident(CBW, VB)) void conv_gemm_ker
                     for (int q = 0; q < 4; ++q)
                         p[64 * q] = make_float4(acc[c][s][4 * q], acc[c][s][4 * q + 1], acc[c][s][4 * q + 2], acc[c][s][4 * q + 3]);
                 }
+        };
+        int steps = 0;               // of all items
+        for (int i = first; i < end; i += nslots) {
+            const Item n = item_at(i);
+            steps += n.k1 - n.k0;
+        }
+        begin();
+        int left = t.k1 - t.k0;
+        // (an item's end behind each of the three phases, the loop's only behind all: with a way from a phase to itself, though
+        // it is never taken, the compiler waits for weights that are needed three steps later)
+        auto turn = [&](auto phase) __attribute__((always_inline)) {
+            next_q0 = left == 1 ? after : -1;
+            step(phase, std::false_type{});
+            if (--left == 0) {
+                put();
+                item += nslots;
+                if (item < end) {
+                    begin();
+                    left = t.k1 - t.k0;
+                }
+            }
+        };
+        int rest = steps;
+#pragma unroll 1
+        do {                         // (an item has four steps or more)
+            turn(std::integral_constant<int, 0>{});
+            turn(std::integral_constant<int, 1>{});
+            turn(std::integral_constant<int, 2>{});
+            rest -= NS;
+        } while (rest >= NS);
+        if (rest > 0) {
+            step(std::integral_constant<int, 0>{}, std::true_type{});
+            if (rest > 1) step(std::integral_constant<int, 1>{}, std::true_type{});
+            put();
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the repeated loads
@@ -526,8 +577,8 @@ int record_loads(int vb, int ew) {
 // read of every sum at about 6 TB/s.  The interior voxels alone decide, so that the order of the sums is the same for every
 // output box growth and tile grid.  These constants, and those of the time that is then compared with the marching kernels'
 // (fitted to 472 layers cut this way, 32 ... 1024 channels, 64 voxels ... 4 million, 2-D and 3-D; `shortk`, K loops of 3 or 6 steps:
-// 354 layers), are of the kernel of one item per workgroup; they choose where a compute unit has one item, which is
-// where little has changed (a step is 10 - 15 % shorter).  What several items in a row cost is cut_us below.
+// 354 layers), are of the kernel of one item per workgroup, and choose where a compute unit has one item: such layers have become
+// 0.9 of the time that they had then, whatever their splits.  What several items in a row cost is cut_us below.
 //
 // cut_us: a compute unit works off its share of the items one after the other: per item `steps` steps and what its epilogue
 // leaves uncovered.  Two workgroups on a compute unit cover each other's, so where there are several items of few steps
@@ -650,19 +701,21 @@ int launch_conv_gemm(const void *Pin, const void *wpack, void *part, const float
     a.deh = make_fastdiv(static_cast<uint32_t>(b.eh));
     a.ded = make_fastdiv(static_cast<uint32_t>(b.ed));
     using Kern = void (*)(GemmArgs);
-    // [output blocks per wave - 1][(voxels, record loads)]
-    static const Kern kern[2][5] = {{conv_gemm_kernel<1, 1, 3>, conv_gemm_kernel<1, 1, 4>, conv_gemm_kernel<1, 1, 6>,
-                                     conv_gemm_kernel<1, 2, 5>, conv_gemm_kernel<1, 2, 6>},
-                                    {conv_gemm_kernel<2, 1, 3>, conv_gemm_kernel<2, 1, 4>, conv_gemm_kernel<2, 1, 6>,
-                                     conv_gemm_kernel<2, 2, 5>, conv_gemm_kernel<2, 2, 6>}};
+    // [split][output blocks per wave - 1][(voxels, record loads)]
+#define SP3D_GEMM_SHAPES(CBW, SPLIT)                                                                                             \
+    {conv_gemm_kernel<CBW, 1, 3, SPLIT>, conv_gemm_kernel<CBW, 1, 4, SPLIT>, conv_gemm_kernel<CBW, 1, 6, SPLIT>,                  \
+     conv_gemm_kernel<CBW, 2, 5, SPLIT>, conv_gemm_kernel<CBW, 2, 6, SPLIT>}
+    static const Kern kern[2][2][5] = {{SP3D_GEMM_SHAPES(1, false), SP3D_GEMM_SHAPES(2, false)},
+                                       {SP3D_GEMM_SHAPES(1, true), SP3D_GEMM_SHAPES(2, true)}};
+#undef SP3D_GEMM_SHAPES
     static const Kern join[2][2] = {{conv_gemm_join_kernel<1, 1>, conv_gemm_join_kernel<1, 2>},
                                     {conv_gemm_join_kernel<2, 1>, conv_gemm_join_kernel<2, 2>}};
     static const int bls[5] = {3, 4, 6, 5, 6};
     // more than 64 KB of dynamic LDS has to be requested explicitly
     static const hipError_t attr = [] {
-        for (int i = 0; i < 10; ++i) {
+        for (int i = 0; i < 20; ++i) {
             const int bl = bls[i % 5];
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern[i / 5][i % 5]),
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern[i / 10][i / 5 % 2][i % 5]),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, NS * stage_bytes(bl));
             if (e != hipSuccess) return e;
         }
@@ -672,7 +725,7 @@ int launch_conv_gemm(const void *Pin, const void *wpack, void *part, const float
     const int shape = p.vb == 2 ? (p.bl == 5 ? 3 : 4) : (p.bl == 3 ? 0 : (p.bl == 4 ? 1 : 2));
     // as many workgroups as fit on the 256 compute units at once
     const unsigned grid = static_cast<unsigned>((std::min(256LL * resident(p.cbw, p.vb), 1LL * a.nblocks * a.nsplit) + 7) / 8 * 8);
-    hipLaunchKernelGGL(kern[p.cbw - 1][shape], dim3(grid), dim3(kGemmThreads), NS * stage_bytes(p.bl), s, a);
+    hipLaunchKernelGGL(kern[a.nsplit > 1 ? 1 : 0][p.cbw - 1][shape], dim3(grid), dim3(kGemmThreads), NS * stage_bytes(p.bl), s, a);
     int rc = record_hip(hipGetLastError());
     if (rc != SP_OK || a.nsplit == 1) return rc;
     const unsigned units = static_cast<unsigned>(a.nblocks) * kGemmWaves * p.cbw * 2 * p.vb;
