@@ -94,6 +94,53 @@ def test_two_tensor_and_bit_forms_exchange_too(ca, cb):
         assert torch.equal(a, b)
 
 
+# tiles along D alone (in 2-D nothing crosses there), one tile, tiles on every side; marching kernels, rows, implicit GEMM, few,
+# padded, fp32
+BORDERS = [(1, (4, 16, 32), (4, 1, 1), 32, 32, "bf16", 1), (2, (6, 8, 40), (2, 1, 1), 64, 64, "bf16", 1),
+           (1, (4, 6, 5), (2, 1, 1), 128, 128, "bf16", 1), (1, (8, 8, 40), (1, 1, 1), 64, 32, "bf16", 0),
+           (1, (4, 16, 33), (1, 1, 1), 32, 64, "bf16", 1), (2, (4, 6, 8), (2, 2, 2), 128, 128, "bf16", 0),
+           (1, (12, 16, 64), (2, 1, 2), 32, 32, "bf16", 0), (1, (9, 12, 10), (3, 2, 1), 3, 32, "bf16", 0),
+           (1, (8, 12, 10), (2, 1, 1), 12, 32, "bf16", 0), (1, (8, 12, 10), (1, 3, 1), 5, 7, "f32", 0)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("opts", [0, KEEP])
+@pytest.mark.parametrize("case", BORDERS, ids=lambda c: "%dx%dx%d-%dto%d-%s%s" % (c[1] + c[3:6] + ("-2d" if c[6] else "",)))
+def test_margins_at_the_border_and_along_every_axis(case, opts):
+    """Every margin, those beyond the volume too, holds something else before: with and without SP_HALO_KEEP_ZERO the call
+    writes the margins that sp_halo_exchange writes, and no others."""
+    n, dhw, grid, cin, cout, dtype, flat = case
+    dt = DT[dtype]
+    g, gx, ge = (sp3d.Geom(n, dhw, grid, 1, 0, flat, o) for o in (0, opts, opts | EXCH))
+    w = to_dev(synth.weights(cin, cout, 9120, dtype, taps=(3, 3) if flat else (3, 3, 3)))
+    ws = sp3d.alloc_ws(max(16, *(sp3d.sp_workspace_bytes(op, g, cin, cout, dt) for op in (0, 1))))
+    two = dtype == "bf16" and cin == 64                # the two-tensor form, as many channels in each
+
+    def filled(c, seed):
+        P = sp3d.alloc_padded(g, c, dt)
+        P.fill_(3.0)
+        gen = torch.Generator(device="cuda").manual_seed(seed)
+        sp3d.sp_partition(torch.randn((n,) + dhw + (c,), generator=gen, device="cuda").to(P.dtype), P, g, c, dt)
+        return P
+
+    res = []
+    for fused in (False, True):
+        gg = ge if fused else g
+        X, Z = filled(cin, 9121), filled(cout, 9122)
+        A, B = filled(32, 9123), filled(32, 9124)
+        if not fused:
+            for P, c in [(X, cin), (Z, cout)] + ([(A, 32), (B, 32)] if two else []):
+                sp3d.sp_halo_exchange(P, gx, c, dt)
+        Y, Y2, D = (sp3d.alloc_padded(g, c, dt) for c in (cout, cout, cin))
+        sp3d.conv3d_fwd(X, w, None, Y, gg, cin, cout, dt, 0, ws)
+        sp3d.conv3d_dgrad(Z, w, D, gg, cin, cout, dt, ws)
+        if two:
+            sp3d.conv3d_fwd2(A, 32, B, 32, w, None, Y2, gg, cout, dt, 0, ws)
+        res.append([X, Z, A, B, Y, Y2, D])
+    for name, a, b in zip(("input", "upstream", "first", "second", "result", "result of two", "gradient"), *res):
+        assert torch.equal(a, b), name
+
+
 def test_where_the_flag_is_refused():
     L, fake = sp3d.lib(), 1 << 40
     g = lambda opts: ctypes.byref(sp3d.Geom(1, (8, 8, 32), (2, 2, 1), opts=opts))
