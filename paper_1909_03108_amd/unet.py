@@ -65,7 +65,6 @@ class UNet:
         # bits: a layer whose output is the next layer's input also writes the one-bit form of its ReLU mask,
         # and that layer's data gradient reads the bits instead of the activation (where both kernels can)
         self.bits = bool(bits) and halo == 1
-        self.by_conv = False                  # see _with_exchange
         self.free = {}                        # (padded shape, channels) -> released gradient buffers
         self.L = len(channels)
         self.flat = bool(flat)
@@ -144,18 +143,18 @@ class UNet:
         """All tiles share this GPU's memory, so margins are filled straight from the neighbours' interiors.
         Margins at the volume border are left alone: every padded tensor of the driver is zeroed when it is
         allocated and nothing writes beyond the border afterwards, so they hold their zero padding already.
-        (Every exchange of the driver passes through here; inside _with_exchange the convolution's call does the work.)"""
-        if not self.by_conv:
+        (Every exchange of the driver passes through here, with the geometry of the call that does it: where that carries
+        SP_HALO_EXCHANGE it is the convolution's, and there is nothing to do.)"""
+        if not g.opts & sp3d.SP_HALO_EXCHANGE:
             sp3d.sp_halo_exchange(P, g.with_opts(sp3d.SP_HALO_KEEP_ZERO), c, self.dt)
 
-    def _with_exchange(self, gg, g, *inputs):
-        """Geometry `gg` for a convolution that fills the margins of its inputs [(tensor, channels)] first, in the launch that
+    def _with_exchange(self, g, *inputs):
+        """Geometry `g` for a convolution that fills the margins of its inputs [(tensor, channels)] first, in the launch that
         packs its weights."""
-        self.by_conv = True
+        gx = g.with_opts(sp3d.SP_HALO_EXCHANGE | sp3d.SP_HALO_KEEP_ZERO)
         for P, c in inputs:
-            self._exchange(P, g, c)
-        self.by_conv = False
-        return gg.with_opts(sp3d.SP_HALO_EXCHANGE | sp3d.SP_HALO_KEEP_ZERO)
+            self._exchange(P, gx, c)
+        return gx
 
     def _mask_bits(self, name, g, cin, cout, last):
         """Buffer for the one-bit ReLU mask of layer `name`'s output, or None if the mask stays a tensor: the
@@ -178,7 +177,7 @@ class UNet:
         if self._x_gathered(g, cin, cout):
             gg = g.with_opts(sp3d.SP_HALO_GATHER)
         elif exchange:
-            gg = self._with_exchange(gg, g, (Px, cin))
+            gg = self._with_exchange(gg, (Px, cin))
         if bits is not None:
             sp3d.conv3d_fwd_bits(Px, self.w[name], None, Py, bits, gg, cin, cout, self.dt, sp3d.SP_FLAG_RELU,
                                  self._ws(sp3d.SP_OP_FWD, gg, cin, cout))
@@ -203,7 +202,7 @@ class UNet:
                 if self._x_gathered(g, cin, c):
                     gg = g.with_opts(sp3d.SP_HALO_GATHER)
                 else:
-                    gg = self._with_exchange(gg, g, (P, ca), (P2, ca))
+                    gg = self._with_exchange(gg, (P, ca), (P2, ca))
                 A[name + ".x"] = (P, P2)
                 Py = self._buf(name + ".y", g, c)
                 if mb is not None:
@@ -328,7 +327,7 @@ class UNet:
             if self._gathers(sp3d.SP_OP_DGRAD, g, cin, cout):
                 gz = g.with_opts(sp3d.SP_HALO_GATHER)
             elif exchange:
-                gz = self._with_exchange(g, g, (Pdy, cout))
+                gz = self._with_exchange(g, (Pdy, cout))
             Pa, Pb = self._tmp(g, ca), self._tmp(g, ca)
             sp3d.conv3d_dgrad2(Pdy, self.w[name], Pa, ca, Pb, ca, gz, cout, dt,
                                self._ws(sp3d.SP_OP_DGRAD, g, cin, cout))          # first layer of its run: no grow
@@ -343,7 +342,7 @@ class UNet:
             if self._gathers(sp3d.SP_OP_DGRAD, g, cin, cout):
                 gg = g.with_opts(sp3d.SP_HALO_GATHER)
             elif exchange:
-                gg = self._with_exchange(gg, g, (Pdy, cout))
+                gg = self._with_exchange(gg, (Pdy, cout))
             Pdx = self._tmp(g, cin)
             xbits = self.A.get(name + ".xbits") if mask_next else None
             if xbits is not None:
