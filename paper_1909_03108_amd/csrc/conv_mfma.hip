@@ -76,7 +76,7 @@ __device__ __forceinline__ void stage(const Ctx<HAS_BIAS> &c, int dplane, int j)
 template <Edge EDGE, bool HAS_BIAS>
 __device__ __forceinline__ pin_t load_partial(const Ctx<HAS_BIAS> &c, int d, int h, int q) {
     pin_t v = pin_t{0.f, 0.f, 0.f, 0.f};
-    if (EDGE != kBranches || c.okrow[h]) v = *reinterpret_cast<const pin_t *>(c.pbase + part_unit(d, h, q));
+    if (EDGE != kBranches || c.okrow[h]) v = *reinterpret_cast<const pin_t *>(c.pbase + part_from<EDGE>(c, d, h, q));
     return v;
 }
 
@@ -104,7 +104,8 @@ __device__ __forceinline__ void store_unit(const Ctx<HAS_BIAS> &c, int d, const 
     }
     const size_t at = d * c.oplane + h * c.orow + 8 * q;
     if (MODE == kFirst || MODE == kMiddle) {
-        if (EDGE != kBranches || c.okrow[h]) *reinterpret_cast<float4 *>(c.pbase + part_unit(d, h, q)) = make_float4(v0, v1, v2, v3);
+        if (EDGE == kDrops) drop_store<0>(c.rag.part + part_unit(d, h, q), c.rag.po[h], pin_t{v0, v1, v2, v3});
+        else if (EDGE == kInside || c.okrow[h]) *reinterpret_cast<float4 *>(c.pbase + part_unit(d, h, q)) = make_float4(v0, v1, v2, v3);
         return;
     }
     if (is_relu(RELU)) {
@@ -165,7 +166,7 @@ __device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, const
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const size_t at = mask_off<EDGE>(c, Dp - 2, h);
-                if (S::PINS) side_load(npin[h][q], c.pbase + part_unit(Dp - 2, h, q));
+                if (S::PINS) side_load(npin[h][q], c.pbase + part_from<EDGE>(c, Dp - 2, h, q));
                 if (S::MASK && !S::BITS) side_load(nmk[h][q], c.mbase + at + 8 * q);
                 if (S::BITS && q == 0) SP3D_SIDE_LOAD_BITS(nmk[h][0].x, c.bbase + (at >> 4));
             }
@@ -355,7 +356,12 @@ __global__ __launch_bounds__(kThreads, 1) void conv_mfma_kernel(ConvArgs a) {
         if (h0 + wave * RH + 1 >= bx.bh) c.mrow = 0;
     }
     // wave `wave` of workgroup `logical`: a region of dchunk planes x RH rows x 4 units x 1 KB
-    c.pbase = a.part + (static_cast<size_t>(logical) * kWaves + wave) * a.dchunk * (RH * 4 * 256) + lane * 4;
+    float *const region = a.part + (static_cast<size_t>(logical) * kWaves + wave) * a.dchunk * (RH * 4 * 256);
+    c.pbase = region + lane * 4;
+    if (PATCHES == kRagged3) {
+        c.rag.part = region;
+        if (c.rag.po[0] == kDrop) c.pbase = region;
+    }
 #pragma unroll
     for (int h = 0; h < RH; ++h) c.okrow[h] = h0 + wave * RH + h < bx.bh && w0 + oc.c < bx.bw && oc.s < F;
     // the bias is folded into the accumulators: a slot starts from the bias instead of zero

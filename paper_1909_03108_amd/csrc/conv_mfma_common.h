@@ -317,18 +317,32 @@ __device__ __forceinline__ uint2 nibble_halves(uint32_t spread, int q) {
 // Ragged patches of the 3-D kernels.  Lanes outside the tile's box must not store; a store under a condition is a branch, and with
 // eight of them a step is no longer one block: its side work was not woven between the MFMAs and mask and partial sums
 // came by ordinary loads (see side_load).  Stores of such a patch go through a buffer descriptor, which drops those of a lane whose
-// offset lies outside; the mask is read from the nearest row and column of the box, and partial sums, which have a place
-// for every voxel of a patch, are stored and read without a condition.  32 -> 32 on 99 x 156 x 210 in 1 x 2 x 2 tiles, forward and
-// masked data gradient, weights packed: 220 -> 190 and 297 -> 212 us.
+// offset lies outside; the mask is read from the nearest row and column of the box.  Partial sums have a place for every voxel
+// of a patch, but where patches are mostly outside moving them all costs more than the branches did: stores are dropped too, and
+// lanes outside read what lane 0 reads.  32 -> 32 on 99 x 156 x 210 in 1 x 2 x 2 tiles, forward and masked data gradient, weights
+// packed: 220 -> 190 and 297 -> 212 us; 160 -> 32 on 89 x 98 x 80 in 1 x 1 x 2 tiles (40 columns, five launches) 408 with branches, 456
+// with all sums moved, 386 now, data gradient 160 <- 96 on 58 x 42 x 40, two entries, 286, 367 and 276.
 constexpr uint32_t kDrop = 0x80000000u;      // a byte offset outside every descriptor
 struct Ragged {
     uint16_t *out, *bits;                    // uniform: voxel (plane 0, first row of the wave, first column of the patch)
     uint32_t vo[RH], bo[RH];                 // this lane's byte offsets from there in the output tensor and in the one-bit mask
+    float *part;                             // uniform: the wave's region of the partial sums
+    uint32_t po[RH];                         // this lane's byte offset in a unit of it
+    int prow;                                // row whose sums row 1 reads
 };
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(uint16_t *p) { return __builtin_amdgcn_make_buffer_rsrc(p, 0, 0x7fffffff, 0x00027000); }
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(void *p) { return __builtin_amdgcn_make_buffer_rsrc(p, 0, 0x7fffffff, 0x00027000); }
 __device__ __forceinline__ void drop_store(uint16_t *base, uint32_t off, uint2 v) {
     __builtin_amdgcn_raw_buffer_store_b64(mask_t{v.x, v.y}, plane_rsrc(base), off, 0, 0);
 }
+
+template <int AUX>       // 2: non-temporal
+__device__ __forceinline__ void drop_store(float *base, uint32_t off, pin_t v) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), plane_rsrc(base), off, 0, AUX);
+}
+// part_unit of the unit that row h reads
+template <Edge EDGE, class CtxT>
+__device__ __forceinline__ size_t part_from(const CtxT &c, int d, int h, int q) { return part_unit(d, EDGE == kDrops && h ? c.rag.prow : h, q); }
 
 // kReluBits: write the mask word of row h of plane d that the four store units of the row collected.
 template <Edge EDGE, class CtxT>
@@ -351,7 +365,9 @@ __device__ __forceinline__ Ragged ragged(const Geo &g, const TileBox &bx, int h0
         const uint32_t v = static_cast<uint32_t>(h) * g.pw + col;
         r.vo[h] = ok ? v * cs * 2 + 8 * hi : kDrop;
         r.bo[h] = ok ? v * nco * 4 + 2 * hi : kDrop;
+        r.po[h] = ok ? 16 * (32 * hi + col) : kDrop;
     }
+    r.prow = h0 + r0 + 1 < bx.bh ? 1 : 0;
     return r;
 }
 

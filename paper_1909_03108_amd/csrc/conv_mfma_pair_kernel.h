@@ -70,7 +70,7 @@ __device__ __forceinline__ void stage(const Ctx<HAS_BIAS> &c, int dplane, int j)
 template <Edge EDGE, bool HAS_BIAS>
 __device__ __forceinline__ pin_t load_partial(const Ctx<HAS_BIAS> &c, int d, int h, int q) {
     pin_t v = pin_t{0.f, 0.f, 0.f, 0.f};
-    if (EDGE != kBranches || c.okrow[h]) v = *reinterpret_cast<const pin_t *>(c.pbase + part_unit(d, h, q));
+    if (EDGE != kBranches || c.okrow[h]) v = *reinterpret_cast<const pin_t *>(c.pbase + part_from<EDGE>(c, d, h, q));
     return v;
 }
 
@@ -103,7 +103,8 @@ __device__ __forceinline__ void finish_unit(const Ctx<HAS_BIAS> &c, int d, const
     const size_t at = d * c.oplane + h * c.orow + 8 * q;
     if (MODE == kFirst || MODE == kMiddle) {
         // (a contiguous kilobyte per wave that the next launch reads once: non-temporal)
-        if (EDGE != kBranches || c.okrow[h])
+        if (EDGE == kDrops) drop_store<2>(c.rag.part + part_unit(d, h, q), c.rag.po[h], pin_t{v0, v1, v2, v3});
+        else if (EDGE == kInside || c.okrow[h])
             __builtin_nontemporal_store(pin_t{v0, v1, v2, v3}, reinterpret_cast<pin_t *>(c.pbase + part_unit(d, h, q)));
         return;
     }
@@ -191,7 +192,7 @@ __device__ __forceinline__ void plane_step(const Ctx<HAS_BIAS> &c, int Dp, const
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const size_t at = mask_off<EDGE>(c, Dp - 3, FROW);
-            if (S::PINS) side_load(npin[FROW][q], c.pbase + part_unit(Dp - 3, FROW, q));
+            if (S::PINS) side_load(npin[FROW][q], c.pbase + part_from<EDGE>(c, Dp - 3, FROW, q));
             if (S::MASK && !S::BITS) side_load(nmk[FROW][q], c.mbase + at + 8 * q);
             if (S::BITS && q == 0) SP3D_SIDE_LOAD_BITS(nmk[FROW][0].x, c.bbase + (at >> 4));
         }
@@ -312,7 +313,7 @@ __device__ __forceinline__ void drain_step(const Ctx<HAS_BIAS> &c, int Dp, f32x1
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const size_t at = mask_off<EDGE>(c, dl, FROW);
-            if (S::PINS) side_load(npin[FROW][q], c.pbase + part_unit(dl, FROW, q));
+            if (S::PINS) side_load(npin[FROW][q], c.pbase + part_from<EDGE>(c, dl, FROW, q));
             if (S::MASK && !S::BITS) side_load(nmk[FROW][q], c.mbase + at + 8 * q);
             if (S::BITS && q == 0) SP3D_SIDE_LOAD_BITS(nmk[FROW][0].x, c.bbase + (at >> 4));
         }
@@ -425,7 +426,12 @@ __device__ __forceinline__ void run(const ConvArgs &a, char *lds, int logical, i
         if (h0 + rg * RH + 1 >= bx.bh) c.mrow = 0;
     }
     // row group rg of workgroup `logical` (both of its waves): dchunk planes x RH rows x 4 units x 1 KB
-    c.pbase = a.part + (static_cast<size_t>(logical) * NRG + rg) * a.dchunk * (RH * 4 * 256) + lane * 4;
+    float *const region = a.part + (static_cast<size_t>(logical) * NRG + rg) * a.dchunk * (RH * 4 * 256);
+    c.pbase = region + lane * 4;
+    if (PATCHES == kRagged3) {
+        c.rag.part = region;
+        if (c.rag.po[0] == kDrop) c.pbase = region;
+    }
 #pragma unroll
     for (int h = 0; h < RH; ++h) c.okrow[h] = h0 + rg * RH + h < bx.bh && w0 + oc.c < bx.bw && oc.s < F;
     if (HAS_BIAS) {
