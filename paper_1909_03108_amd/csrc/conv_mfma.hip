@@ -685,7 +685,14 @@ int launch_conv_mfma(const void *Pin, const void *w, const float *bias, void *Po
     // (One patch in 32 cut by the box and kRagged3 is the faster one already: 64 -> 64 on 128 x 126 x 128 in 1 x 1 x 4 tiles, forward
     // 422 us with whole patches and others in one launch, 368 with this, masked data gradient 505 and 368.  A grown box differs
     // from tile to tile.)
-    const int patches = g.flat ? kAny2 : (g.grow == 0 && g.th % (pairs ? wide::PH : PH) == 0 && g.tw % PW == 0 ? kWhole3 : kRagged3);
+    // The two-chunk kernel for whole patches takes others too, with branches (see conv_mfma_pair_kernel.h): on marches of one or two
+    // planes it is the faster one where sums or masks are read, as those that are fetched a step ahead are waited for twice: data gradient
+    // 32 <- 512 on 34 x 20 x 24 in 2 x 1 x 2 tiles 125 us, 133 without branches, masked 96 <- 64 on 22 x 25 x 30 in 2 x 1 x 1 18.6 and 19.5;
+    // over three planes and more kRagged3 is (0.98 of the time with three, 0.91 with more than five; forward in one launch: 0.98 with
+    // one or two, too).
+    const bool whole = g.grow == 0 && g.th % (pairs ? wide::PH : PH) == 0 && g.tw % PW == 0;
+    const bool branches = pairs && pl.dchunk <= 2 && (nci > 2 || mask || (bits && dgrad));
+    const int patches = g.flat ? kAny2 : (whole || branches ? kWhole3 : kRagged3);
     const int epi = bits ? (dgrad ? kMaskBits : kReluBits) : (mask ? kMask : (relu ? kRelu : kNone));
     // more than 64 KB of dynamic LDS has to be requested explicitly
     static const hipError_t attr = [] {

@@ -42,9 +42,9 @@ __device__ __forceinline__ int piece_at(int column, int piece) { return (piece ^
 // byte offset of 16-byte piece `piece` of column `column` of a row
 __device__ __forceinline__ int lds_off(int column, int piece) { return column * REC + 16 * piece_at(column, piece); }
 
-// The patches of a launch: 3-D, all of them whole (the box a multiple of the patch); 3-D, some not; 2-D, either kind.  (A
-// one-chunk kernel for both kinds in 3-D holds the march twice, and the registers of the one cost the other: masked data gradient
-// 32 -> 32 on 128^3 122 -> 126 us.)
+// The patches of a launch: 3-D, all of them whole (the box a multiple of the patch), in the two-chunk kernel also short marches over
+// either kind; 3-D, some not whole; 2-D, either kind.  (A one-chunk kernel for both kinds in 3-D holds the march twice, and the
+// registers of the one cost the other: masked data gradient 32 -> 32 on 128^3 122 -> 126 us.)
 enum Patches { kWhole3 = 0, kRagged3 = 1, kAny2 = 2 };
 // How a march treats the lanes outside its tile's box: there are none; loads and stores under a condition; see Ragged.
 enum Edge { kInside, kBranches, kDrops };
