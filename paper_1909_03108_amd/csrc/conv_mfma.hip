@@ -55,6 +55,7 @@ struct Ctx {
     size_t oplane, orow;        // output elements per padded plane / per padded row
     size_t mrow;                // from the row that the mask of the wave's first row is read from to that of the second
     Ragged rag;                 // 3-D, ragged patches
+    RaggedPart rpart;
     bool okrow[RH];             // row/column of this lane lies inside the tile interior
     float bv[HAS_BIAS ? 16 : 1];
 };
@@ -104,7 +105,7 @@ __device__ __forceinline__ void store_unit(const Ctx<HAS_BIAS> &c, int d, const 
     }
     const size_t at = d * c.oplane + h * c.orow + 8 * q;
     if (MODE == kFirst || MODE == kMiddle) {
-        if (EDGE == kDrops) drop_store<0>(c.rag.part + part_unit(d, h, q), c.rag.po[h], pin_t{v0, v1, v2, v3});
+        if (EDGE == kDrops) drop_store<0>(c.rpart, d, h, q, pin_t{v0, v1, v2, v3});
         else if (EDGE == kInside || c.okrow[h]) *reinterpret_cast<float4 *>(c.pbase + part_unit(d, h, q)) = make_float4(v0, v1, v2, v3);
         return;
     }
@@ -358,9 +359,9 @@ __global__ __launch_bounds__(kThreads, 1) void conv_mfma_kernel(ConvArgs a) {
     // wave `wave` of workgroup `logical`: a region of dchunk planes x RH rows x 4 units x 1 KB
     float *const region = a.part + (static_cast<size_t>(logical) * kWaves + wave) * a.dchunk * (RH * 4 * 256);
     c.pbase = region + lane * 4;
-    if (PATCHES == kRagged3) {
-        c.rag.part = region;
-        if (c.rag.po[0] == kDrop) c.pbase = region;
+    if (PATCHES == kRagged3 && MODE != kSingle) {
+        c.rpart = ragged_part(bx, h0, w0, wave * RH, col, lane, region);
+        if (c.rpart.off[0] == kDrop) c.pbase = region;
     }
 #pragma unroll
     for (int h = 0; h < RH; ++h) c.okrow[h] = h0 + wave * RH + h < bx.bh && w0 + oc.c < bx.bw && oc.s < F;

@@ -326,23 +326,25 @@ constexpr uint32_t kDrop = 0x80000000u;      // a byte offset outside every desc
 struct Ragged {
     uint16_t *out, *bits;                    // uniform: voxel (plane 0, first row of the wave, first column of the patch)
     uint32_t vo[RH], bo[RH];                 // this lane's byte offsets from there in the output tensor and in the one-bit mask
-    float *part;                             // uniform: the wave's region of the partial sums
-    uint32_t po[RH];                         // this lane's byte offset in a unit of it
-    int prow;                                // row whose sums row 1 reads
+};
+struct RaggedPart {
+    float *base;                             // uniform: the wave's region of the partial sums
+    uint32_t off[RH];                        // this lane's byte offset in a unit of it
+    int row1;                                // row whose sums row 1 reads
 };
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(void *p) { return __builtin_amdgcn_make_buffer_rsrc(p, 0, 0x7fffffff, 0x00027000); }
 __device__ __forceinline__ void drop_store(uint16_t *base, uint32_t off, uint2 v) {
     __builtin_amdgcn_raw_buffer_store_b64(mask_t{v.x, v.y}, plane_rsrc(base), off, 0, 0);
 }
 
-template <int AUX>       // 2: non-temporal
-__device__ __forceinline__ void drop_store(float *base, uint32_t off, pin_t v) {
+template <int AUX>       // partial sums into row h of plane d; AUX 2: non-temporal
+__device__ __forceinline__ void drop_store(const RaggedPart &p, int d, int h, int q, pin_t v) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), plane_rsrc(base), off, 0, AUX);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), plane_rsrc(p.base), p.off[h], static_cast<int>(4 * part_unit(d, h, q)), AUX);
 }
 // part_unit of the unit that row h reads
 template <Edge EDGE, class CtxT>
-__device__ __forceinline__ size_t part_from(const CtxT &c, int d, int h, int q) { return part_unit(d, EDGE == kDrops && h ? c.rag.prow : h, q); }
+__device__ __forceinline__ size_t part_from(const CtxT &c, int d, int h, int q) { return part_unit(d, EDGE == kDrops && h ? c.rpart.row1 : h, q); }
 
 // kReluBits: write the mask word of row h of plane d that the four store units of the row collected.
 template <Edge EDGE, class CtxT>
@@ -365,9 +367,15 @@ __device__ __forceinline__ Ragged ragged(const Geo &g, const TileBox &bx, int h0
         const uint32_t v = static_cast<uint32_t>(h) * g.pw + col;
         r.vo[h] = ok ? v * cs * 2 + 8 * hi : kDrop;
         r.bo[h] = ok ? v * nco * 4 + 2 * hi : kDrop;
-        r.po[h] = ok ? 16 * (32 * hi + col) : kDrop;
     }
-    r.prow = h0 + r0 + 1 < bx.bh ? 1 : 0;
+    return r;
+}
+__device__ __forceinline__ RaggedPart ragged_part(const TileBox &bx, int h0, int w0, int r0, int col, int lane, float *region) {
+    RaggedPart r;
+    r.base = region;
+#pragma unroll
+    for (int h = 0; h < RH; ++h) r.off[h] = h0 + r0 + h < bx.bh && w0 + col < bx.bw ? 16 * lane : kDrop;
+    r.row1 = h0 + r0 + 1 < bx.bh ? 1 : 0;
     return r;
 }
 

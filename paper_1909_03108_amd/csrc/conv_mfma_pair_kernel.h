@@ -54,6 +54,7 @@ struct Ctx {
     float *pbase;
     size_t oplane, orow, mrow;
     Ragged rag;
+    RaggedPart rpart;
     bool okrow[RH];
     float bv[HAS_BIAS ? 16 : 1];
 };
@@ -103,7 +104,7 @@ __device__ __forceinline__ void finish_unit(const Ctx<HAS_BIAS> &c, int d, const
     const size_t at = d * c.oplane + h * c.orow + 8 * q;
     if (MODE == kFirst || MODE == kMiddle) {
         // (a contiguous kilobyte per wave that the next launch reads once: non-temporal)
-        if (EDGE == kDrops) drop_store<2>(c.rag.part + part_unit(d, h, q), c.rag.po[h], pin_t{v0, v1, v2, v3});
+        if (EDGE == kDrops) drop_store<2>(c.rpart, d, h, q, pin_t{v0, v1, v2, v3});
         else if (EDGE == kInside || c.okrow[h])
             __builtin_nontemporal_store(pin_t{v0, v1, v2, v3}, reinterpret_cast<pin_t *>(c.pbase + part_unit(d, h, q)));
         return;
@@ -428,9 +429,9 @@ __device__ __forceinline__ void run(const ConvArgs &a, char *lds, int logical, i
     // row group rg of workgroup `logical` (both of its waves): dchunk planes x RH rows x 4 units x 1 KB
     float *const region = a.part + (static_cast<size_t>(logical) * NRG + rg) * a.dchunk * (RH * 4 * 256);
     c.pbase = region + lane * 4;
-    if (PATCHES == kRagged3) {
-        c.rag.part = region;
-        if (c.rag.po[0] == kDrop) c.pbase = region;
+    if (PATCHES == kRagged3 && MODE != kSingle) {
+        c.rpart = ragged_part(bx, h0, w0, rg * RH, col, lane, region);
+        if (c.rpart.off[0] == kDrop) c.pbase = region;
     }
 #pragma unroll
     for (int h = 0; h < RH; ++h) c.okrow[h] = h0 + rg * RH + h < bx.bh && w0 + oc.c < bx.bw && oc.s < F;
