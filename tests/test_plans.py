@@ -186,3 +186,12 @@ def test_the_flat_whole_patch_tests_meet_both_kernels():
         assert all(f == "march" for f, _ in plans) and {d[0] for _, d in plans} == {1, 2}
     for dhw, cin, cout, whole in (((1, 32, 96), 32, 32, 1), ((2, 24, 32), 32, 32, 1), ((16, 256, 256), 32, 64, 2), ((12, 512, 512), 64, 64, 2)):
         assert route(WGRAD, sp3d.Geom(1, dhw, (1, 1, 1), 1, 0, 1), cin, cout, BF16)[1][0] == whole
+
+
+def test_flat_weight_gradients_of_more_pairs_than_compute_units():
+    """Where a compute unit takes several channel pairs one after the other, each start has its price: few steps each are the
+    GEMM's (measured: csrc/wgrad_mfma.hip, launch_plan), long ones the march's."""
+    for n, dhw, cin, cout, kind in ((1, (2, 16, 32), 1024, 320, "gemm"), (1, (1, 16, 64), 768, 768, "gemm"),
+                                    (1, (9, 16, 32), 1024, 1024, "gemm"), (2, (5, 16, 192), 1024, 1024, "march"),
+                                    (4, (1, 96, 128), 1024, 512, "march")):
+        assert route(sp3d.SP_OP_WGRAD, sp3d.Geom(n, dhw, (1, 1, 1), flat=1), cin, cout, sp3d.SP_BF16)[0] == kind, (dhw, cin, cout)
