@@ -195,3 +195,16 @@ def test_flat_weight_gradients_of_more_pairs_than_compute_units():
                                     (1, (9, 16, 32), 1024, 1024, "gemm"), (2, (5, 16, 192), 1024, 1024, "march"),
                                     (4, (1, 96, 128), 1024, 512, "march")):
         assert route(sp3d.SP_OP_WGRAD, sp3d.Geom(n, dhw, (1, 1, 1), flat=1), cin, cout, sp3d.SP_BF16)[0] == kind, (dhw, cin, cout)
+
+
+def test_the_row_tests_meet_the_rows():
+    """The march of 2-D layers of up to 64 input channels goes by rows unless slices lie side by side (launch_conv_mfma)."""
+    met = set()
+    for case in small.ROWS:
+        for op, ki in ((FWD, case[3]), (DGRAD, case[4])):
+            family, (_, fold, _, _) = routes(op, [case])[0]
+            rows = family == "march" and fold == 1 and ki <= 64
+            assert rows or (op == DGRAD and (ki > 64 or fold > 1 or family == "gemm")), case
+            if rows:
+                met.add((op, ki))
+    assert met == {(op, ki) for op in (FWD, DGRAD) for ki in (32, 64)}
