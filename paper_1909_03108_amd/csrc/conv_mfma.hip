@@ -457,6 +457,7 @@ __global__ __launch_bounds__(kThreads, 1) void conv_mfma_kernel(ConvArgs a) {
     };
     if constexpr (PATCHES == kWhole3) march(std::integral_constant<Edge, kInside>{});
     else if constexpr (PATCHES == kRagged3) march(std::integral_constant<Edge, kDrops>{});
+    else if constexpr (MODE == kSingle) march(std::integral_constant<Edge, kBranches>{});       // slices side by side: 15 columns at most
     else if (h0 + PH <= bx.bh && w0 + PW <= bx.bw) march(std::integral_constant<Edge, kInside>{});
     else march(std::integral_constant<Edge, kBranches>{});
 }

@@ -525,7 +525,9 @@ __device__ __forceinline__ void run(const ConvArgs &a, char *lds, int logical, i
     // (kWhole3 with branches: short marches, see launch_conv_mfma.  Without that code the compiler arranges the march for whole
     // patches so that it takes 2 to 5 % longer, 64 -> 32 on 256^3 1420 -> 1470 us, 64 -> 64 on 128^3 in 2 x 2 x 1 tiles, masked, 380
     // -> 400.)
+    // (2-D in one launch: slices side by side, 15 columns at most.)
     if constexpr (PATCHES == kRagged3) march(std::integral_constant<Edge, kDrops>{});
+    else if constexpr (PATCHES == kAny2 && MODE == kSingle) march(std::integral_constant<Edge, kBranches>{});
     else if (h0 + PH <= bx.bh && w0 + PW <= bx.bw) march(std::integral_constant<Edge, kInside>{});
     else march(std::integral_constant<Edge, kBranches>{});
 }
