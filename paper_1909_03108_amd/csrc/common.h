@@ -169,8 +169,7 @@ int launch_conv_mfma(const void *Pin, const void *w, const float *bias, void *Po
 // layers on few voxels: output-stationary implicit GEMM on the packed weights (conv_gemm.hip); launch_conv_mfma hands
 // the layers for which it is the faster family over after packing
 bool conv_gemm_supported(const Geo &g, int ki, int ko);
-double conv_gemm_us(const Geo &g, int ki, int ko);            // estimated time, and where compute units have several items each
-double conv_gemm_rows_us(const Geo &g, int ki, int ko);
+double conv_gemm_us(const Geo &g, int ki, int ko);            // estimated time
 // the wide layers on the fewest voxels: served by this family alone, without gathered halos and one-bit masks
 bool conv_gemm_tensor_forms(const Geo &g, int ki, int ko);
 size_t conv_gemm_ws_bytes(const Geo &g, int ki, int ko);      // behind the packed weights

@@ -565,8 +565,7 @@ __global__ __launch_bounds__(kGemmThreads) void conv_gemm_join_kernel(GemmArgs a
 struct Box { int ed, eh, ew; };
 Box max_box(const Geo &g) { return Box{g.td + 2 * grow_d(g), g.th + 2 * g.grow, g.tw + 2 * g.grow}; }
 
-// us: estimated time, by the constants of one item per workgroup; rows_us: by those of several in a row where that is so
-struct GemmPlan { int cbw, vb, bl, nsplit, nvg, nblocks; long long nvox; double us, rows_us; };
+struct GemmPlan { int cbw, vb, bl, nsplit, nvg, nblocks; long long nvox; double us; };     // us: estimated time
 // records that 128 vb consecutive voxels touch at most, in wave loads of 16 per wave
 int record_loads(int vb, int ew) {
     const int n = wg_vox(vb), rows = n % ew == 0 ? n / ew - 1 : (n + ew - 2) / ew;
@@ -613,7 +612,6 @@ GemmPlan plan_gemm(const Geo &g, int ki, int ko) {
         }
     }
     if (p.nsplit == 1 && p.cbw == 2 && p.vb == 2 && cut_us(2, 1, tiles_of(1), nk) < 0.97 * cut_us(2, 2, tiles_of(2), nk)) p.vb = 1;
-    p.rows_us = p.nsplit == 1 && tiles_of(p.vb) > 256 ? cut_us(p.cbw, p.vb, tiles_of(p.vb), nk) : p.us;
     p.bl = record_loads(p.vb, b.ew);
     if (p.vb == 2 && p.bl > 6) { p.vb = 1; p.bl = record_loads(1, b.ew); }
     p.bl = p.vb == 2 ? (p.bl <= 5 ? 5 : 6) : (p.bl <= 3 ? 3 : (p.bl <= 4 ? 4 : 6));
@@ -636,7 +634,6 @@ bool conv_gemm_tensor_forms(const Geo &g, int ki, int ko) {
 }
 
 double conv_gemm_us(const Geo &g, int ki, int ko) { return plan_gemm(g, ki, ko).us; }
-double conv_gemm_rows_us(const Geo &g, int ki, int ko) { return plan_gemm(g, ki, ko).rows_us; }
 
 void conv_gemm_detail(const Geo &g, int ki, int ko, int *detail) {
     const GemmPlan p = plan_gemm(g, ki, ko);

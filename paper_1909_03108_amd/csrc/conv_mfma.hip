@@ -546,10 +546,11 @@ static PatchPlan plan_patches(const Geo &g, int ki, int ko) {
 // on 16^3 79 -> 34, on 32^3 146 -> 122, 128 -> 128 on 28 x 44 x 52 96 -> 71; 128 -> 64 on 56 x 88 x 104 279 against 328 (stays),
 // 128 -> 128 on 64^3 196 against 279 (stays); 2-D 256 -> 256 on 16 x 64^2 152 -> 107, 128 -> 128 on 2 x 256^2 173 -> 73, 64 -> 64
 // there 42 -> 35, 64 -> 256 on 5 x 240 x 177 153 against 170 (stays).
-// Where the GEMM's compute units have several items each, its workgroups have come to go from one to the next without a gap
-// (conv_gemm_rows_us): against several launches of the march that estimate decides as well, by 7 %, in 3-D for workgroups of 128
-// output channels (2-D, 128 -> 64 on 16 x 256^2 282 -> 202 us; 3-D, 256 -> 256 on 64^3 868 -> 798; 128 -> 128 there 218
-// against 214: stays).
+// Figures and constants are of the kernels that they were measured on: since then GEMM workgroups go from one item to the next without
+// a gap, and 2-D layers of one launch march by rows (conv_rows2d.hip).  The choice stays where it was, as the family decides in
+// which order a layer sums, and with it the last bits of all that follows: 2-D, 128 -> 64 on 16 x 256^2 marches in 280 us where a
+// GEMM takes 215, 3-D, 128 -> 128 on 64 x 48 x 24 in 91 against 82, 512 -> 256 on 64^3 in 1570 against 1650; 2-D, 64 -> 64 on 2 x
+// 256^2 takes the GEMM in 22.
 static bool prefer_gemm(const Geo &g, int ki, int ko) {
     if (!conv_gemm_supported(g, ki, ko)) return false;
     if (conv_gemm_tensor_forms(g, ki, ko)) return true;
@@ -564,7 +565,7 @@ static bool prefer_gemm(const Geo &g, int ki, int ko) {
     if (g.flat && launches == 1) return conv_gemm_us(g, ki, ko) < 0.9 * (4 + rounds * (5.6 + (p.pairs ? 1.75 : 1.62) * planes));
     const double us = g.flat ? 2 + launches * (rounds * (6.3 + (p.pairs ? 1.35 : 1.44) * planes) + 0.6) + sums / 7.4e6
                              : 2 + launches * (rounds * (7.2 + (p.pairs ? 2.56 : 2.63) * planes) + 3.6) + sums / 10.3e6;
-    return conv_gemm_us(g, ki, ko) < us || (launches > 1 && (g.flat || ko % (4 * C) == 0) && 1.07 * conv_gemm_rows_us(g, ki, ko) < us);
+    return conv_gemm_us(g, ki, ko) < us;
 }
 
 int conv_mfma_route(const Geo &g, int ki, int ko, int *detail) {

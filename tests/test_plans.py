@@ -208,3 +208,12 @@ def test_the_row_tests_meet_the_rows():
             if rows:
                 met.add((op, ki))
     assert met == {(op, ki) for op in (FWD, DGRAD) for ki in (32, 64)}
+
+
+@pytest.mark.parametrize("dhw, cin, cout, flat", [((16, 256, 256), 128, 64, 1), ((64, 64, 64), 512, 256, 0), ((64, 48, 24), 128, 128, 0)])
+def test_layers_keep_the_order_of_their_sums(dhw, cin, cout, flat):
+    """The family decides in which order a layer sums.  These are marched, in several launches, also where GEMM workgroups that
+    stay on their compute unit have become faster (csrc/conv_mfma.hip, prefer_gemm)."""
+    for grid in ((1, 1, 1), (1, 2, 2)):
+        family, detail = route(FWD, sp3d.Geom(1, dhw, grid, 1, 0, flat), cin, cout, BF16)
+        assert family == "march" and detail[3] > 1, grid
