@@ -276,7 +276,7 @@ __global__ __launch_bounds__(kThreads) void halo_kernel(const T *src, T *dst, Ha
 // What a convolution with SP_HALO_EXCHANGE does before its own launch: the first nhalo blocks exchange the margins of Pa, the
 // next nhalo those of Pb (if there is one: as many channels), the others pack weights.  The three have nothing to do with
 // each other, and each is little more than a launch where layers are small: 2-D inference on two slabs 1493 -> 1369 us, 48 of
-// 168 launches less; the four-level training step on 32^3 1006 -> 945, 26 of 151; on 16 slabs 16.35 -> 16.0 ms.
+// 168 launches less; the four-level training step on 32^3 1006 -> 945, 29 of 151; on 16 slabs 16.35 -> 16.0 ms.
 __global__ __launch_bounds__(kThreads) void exchange_and_pack_kernel(u32x4 *Pa, u32x4 *Pb, unsigned nhalo, HaloArgs a, PackArgs pack) {
     __shared__ __align__(16) convk::PackSquares square;
     static_assert(kThreads == 64 * convk::kPackWaves, "one block size");
