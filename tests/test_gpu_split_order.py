@@ -24,7 +24,7 @@ LAYERS = [(1, (8, 8, 8), 128, 128, 0, (2, 1, 3, 9)), (2, (1, 1, 5), 96, 192, 0, 
 @pytest.mark.parametrize("n, dhw, cin, cout, flat, cut", LAYERS, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_a_split_adds_its_share_of_the_steps_in_order(n, dhw, cin, cout, flat, cut):
     """A step is a kernel row times 32 input channels, chunks innermost; split s has the steps [s nk / S, (s + 1) nk / S), and the
-    splits' sums are added in order.  One product of a step is not zero: 2^40 in one step of each output channel, -2^40 in another,
+    splits' sums are added in order, the bias before the first split's first step.  One product of a step is not zero: 2^40 in one step of each output channel, -2^40 in another,
     1 in the others, so that what is added between the two, and only that, is lost: every cut of the steps has its own integers."""
     g = sp3d.Geom(n, dhw, (1, 1, 1), flat=flat)
     kind, detail = route(sp3d.SP_OP_FWD, g, cin, cout, BF16)
@@ -50,9 +50,10 @@ def test_a_split_adds_its_share_of_the_steps_in_order(n, dhw, cin, cout, flat, c
         dd = np.arange(D) + (0 if flat else kd - 1)
         hh = np.arange(H) + kh - 1
         inside[r] = ((dd >= 0) & (dd < D))[:, None] & ((hh >= 0) & (hh < H))[None, :]
+    bias = rng.integers(0, 8, cout).astype(np.float32)
     want = np.zeros((D, H, cout), np.float32)
     for s in range(splits):
-        part = np.zeros((D, H, cout), np.float32)
+        part = np.zeros((D, H, cout), np.float32) + (bias if s == 0 else 0)
         for k in range(s * nk // splits, (s + 1) * nk // splits):
             part += inside[k // nci][..., None] * p[:, k]
         want += part
@@ -61,7 +62,7 @@ def test_a_split_adds_its_share_of_the_steps_in_order(n, dhw, cin, cout, flat, c
     sp3d.sp_partition(x, P, g, cin, BF16)
     wd = torch.from_numpy(w if not flat else w[0]).to(torch.bfloat16).cuda()
     ws = sp3d.alloc_ws(sp3d.sp_workspace_bytes(sp3d.SP_OP_FWD, g, cin, cout, BF16))
-    sp3d.conv3d_fwd(P, wd, None, Py, g, cin, cout, BF16, 0, ws)
+    sp3d.conv3d_fwd(P, wd, torch.from_numpy(bias).cuda(), Py, g, cin, cout, BF16, 0, ws)
     y = torch.empty((n,) + dhw + (cout,), dtype=torch.bfloat16, device="cuda")
     sp3d.sp_unpartition(Py, y, g, cout, BF16)
     wrong = (y != want[None, :, :, None, :]).sum().item()
